@@ -196,15 +196,46 @@ void pack_weights(const HostModel &h, int pr, Image &im) {
   }
   if (pr == DP_FP32) {
     std::vector<size_t> &f = im.f32;
-    f.push_back(pk.addf(transpose(h.W2, E1, E2)));
-    f.push_back(pk.addf(tof(h.W2)));
-    f.push_back(pk.addf(transpose(h.W3, E2, M)));
-    f.push_back(pk.addf(tof(h.W3)));
+    // 16x16x4 fragments of the [M][M] products W[out][k]: tile t holds the outputs
+    // 16 t + row (t < 6) or 96 + row / 4; its pieces of 64 lanes x 4 values k = 16 kb + 4 (lane / 16) + s,
+    // row lane % 16, then 64 values k = 96 + lane / 16
+    auto frag100 = [](auto W) {
+      std::vector<float> v(7 * 1600);
+      for (int t = 0; t < 7; ++t)
+        for (int l = 0; l < 64; ++l) {
+          const int out = t < 6 ? 16 * t + l % 16 : 96 + l % 16 / 4;
+          for (int kb = 0; kb < 6; ++kb)
+            for (int e = 0; e < 4; ++e) v[1600 * t + 256 * kb + 4 * l + e] = (float)W(out, 16 * kb + 4 * (l / 16) + e);
+          v[1600 * t + 1536 + l] = (float)W(out, 96 + l / 16);
+        }
+      return v;
+    };
+    // ... and of the embedding's, features in groups of 25 (slot r of lane group q = feature
+    // 4 r + q of the group): NO output groups of two tiles, NI input groups of two pieces
+    auto frag25 = [](int NO, int NI, auto W) {
+      std::vector<float> v((size_t)NO * 2 * NI * 2 * 256, 0.f);
+      for (int og = 0; og < NO; ++og)
+        for (int u = 0; u < 2; ++u)
+          for (int ig = 0; ig < NI; ++ig)
+            for (int p = 0; p < 2; ++p)
+              for (int l = 0; l < 64; ++l)
+                for (int e = 0; e < 4; ++e) {
+                  const int ro = 4 * u + l % 4, fo = 4 * ro + l % 16 / 4;  // tile row 4 q + i is slot 4 u + i
+                  const int ri = 4 * p + e, fi = 4 * ri + l / 16;
+                  if (ro < 7 && fo < 25 && ri < 7 && fi < 25)
+                    v[(((size_t)og * 2 + u) * NI * 2 + 2 * ig + p) * 256 + 4 * l + e] = (float)W(25 * og + fo, 25 * ig + fi);
+                }
+      return v;
+    };
+    f.push_back(pk.addf(frag25(2, 1, [&](int c, int k) { return h.W2[(size_t)k * E2 + c]; })));
+    f.push_back(pk.addf(frag25(1, 2, [&](int c, int k) { return h.W2[(size_t)c * E2 + k]; })));
+    f.push_back(pk.addf(frag25(4, 2, [&](int c, int k) { return h.W3[(size_t)k * M + c]; })));
+    f.push_back(pk.addf(frag25(2, 4, [&](int c, int k) { return h.W3[(size_t)c * M + k]; })));
     for (int a = 0; a < NATTN; ++a) {
-      f.push_back(pk.addf(transpose(QK[a], M, M)));
-      f.push_back(pk.addf(tof(QK[a])));
-      f.push_back(pk.addf(transpose(VO[a], M, M)));
-      f.push_back(pk.addf(tof(VO[a])));
+      f.push_back(pk.addf(frag100([&](int c, int k) { return QK[a][(size_t)k * M + c]; })));
+      f.push_back(pk.addf(frag100([&](int c, int k) { return QK[a][(size_t)c * M + k]; })));
+      f.push_back(pk.addf(frag100([&](int c, int k) { return VO[a][(size_t)k * M + c]; })));
+      f.push_back(pk.addf(frag100([&](int c, int k) { return VO[a][(size_t)c * M + k]; })));
     }
     for (int k = 0; k < h.nheads; ++k) {
       f.push_back(pk.addf(transpose(h.F1[k], ND, FH)));
@@ -696,7 +727,7 @@ int enqueue_step(dp_model *m, Workspace &ws, const StepArgs &a, hipStream_t st, 
                            st));
     launch_prologue(ws, a.nsys, n, a.lists == LISTS_SKIN_REUSE ? 0 : a.ncells + 1, true, st);
   } else {
-    launch_prologue(ws, a.nsys, 0, 0, false, st);  // a later chunk: only the backward's atom lists restart
+    launch_prologue(ws, a.nsys, 0, 0, false, st);  // a later chunk: only the descriptor's atom lists restart
   }
   if (pm) mark(pm, 0, st);
   switch (a.lists) {
@@ -727,7 +758,7 @@ int enqueue_step(dp_model *m, Workspace &ws, const StepArgs &a, hipStream_t st, 
   if (m->prec == DP_BF16)
     launch_descriptor_fwd_b16(m->wf, m->wp, ws, a.X, a.types, n, cb, ce, rc, rcs, eps, st);
   else
-    launch_descriptor_fwd<float>(m->wf, ws, a.X, a.types, n, cb, ce, rc, rcs, eps, st);
+    launch_descriptor_fwd(m->wf, ws, a.X, a.types, n, cb, ce, rc, rcs, eps, st);
   if (pm) mark(pm, 2, st);
   if (m->prec == DP_BF16)
     launch_fitting_b16(m->wf, m->wp, ws, a.types, cb, ce, bwd, st);
@@ -742,7 +773,7 @@ int enqueue_step(dp_model *m, Workspace &ws, const StepArgs &a, hipStream_t st, 
     if (m->prec == DP_BF16)
       launch_descriptor_bwd_b16(m->wf, m->wp, ws, a.X, a.types, n, cb, ce, rc, rcs, eps, st);
     else
-      launch_descriptor_bwd<float>(m->wf, ws, a.X, a.types, n, cb, ce, rc, rcs, eps, st);
+      launch_descriptor_bwd(m->wf, ws, a.X, a.types, n, cb, ce, rc, rcs, eps, st);
     if (pm) mark(pm, 5, st);
     if (a.last_chunk) {
       double *F = a.forces;
@@ -1345,7 +1376,7 @@ int dp_backward_device(dp_model *m, const double *d_grad_energy, double *d_grad_
   // net with its backward
   if (m->prec == DP_FP32) {
     launch_fitting<float>(m->wf, ws, m->fwd_types, 0, n, true, st);
-    launch_descriptor_bwd<float>(m->wf, ws, m->fwd_coords, m->fwd_types, n, 0, n, rc, rcs, eps, st);
+    launch_descriptor_bwd(m->wf, ws, m->fwd_coords, m->fwd_types, n, 0, n, rc, rcs, eps, st);
   } else {
     launch_fitting_b16(m->wf, m->wp, ws, m->fwd_types, 0, n, true, st);
     launch_descriptor_bwd_b16(m->wf, m->wp, ws, m->fwd_coords, m->fwd_types, n, 0, n, rc, rcs, eps, st);

@@ -1,6 +1,6 @@
-// Per-atom descriptor kernels on gfx950: environment matrix, type-embedded
-// embedding net, two gated self-attention layers over the atom's neighbours,
-// and the descriptor contraction (forward), plus the hand-written backward
+// Per-atom descriptor kernels of the float32 path on gfx950: environment matrix,
+// type-embedded embedding net, two gated self-attention layers over the atom's
+// neighbours and the descriptor contraction (forward), and the hand-written backward
 // that turns dE/dD into g_ij = dE_i/dDelta_ij.
 //
 // Model (paper, Section II: embedding net over an atom and its neighbours,
@@ -17,603 +17,915 @@
 // (A V) WO = (A G)(WV WO), so each layer needs the two 100x100 products only;
 // they are formed once at model load.
 //
-// Layout: one workgroup (8 waves) per atom; tokens padded to NP = 16 ceil(n/16)
-// (<= 128).  The atom's [NP][100] representation lives in LDS; each attention
-// layer is processed in blocks of 16 query rows that all 8 waves share, so the
-// NP x NP score matrix never exists as a whole.  All cross-wave sums go through
-// per-wave partial arrays added in a fixed order: results do not depend on
-// scheduling.
+// Bound: the float32 MFMA rate (157 TFLOP/s).  Per 16-neighbour block and layer the
+// forward issues 668 and the backward 1,389 MFMAs 16x16x4 of 32 cycles at 96 neighbours.
+//
+// Layout: one workgroup per atom, one wave per block of 16 neighbours (tokens).  A wave
+// keeps everything that belongs to its tokens in registers, transposed (features or keys
+// along the accumulator rows, its 16 tokens along the columns): lane (q = lane / 16,
+// c = lane % 16) holds features 16 t + 4 q + i of token c.  In that form the accumulator
+// of one product is, register by register, the B operand of the next (k step i of tile t
+// takes k = 16 t + 4 q + i), so U, S, softmax, H, Y, LayerNorm and their gradients follow
+// one another without a trip through LDS; softmax and LayerNorm reduce over registers and
+// two lane exchanges.  Only the keys' rows G are shared: [token][100] float32 in LDS, a
+// stride for which both the 16-byte row reads and the reads along tokens spread over all
+// banks.  Weights come from L2 in fragment order, one output tile ahead.
+//
+// Two instances: atoms with up to 6 blocks (96 neighbours, nine in ten in water) run
+// with 6 waves, 77 KB of LDS and at most 168 registers, so that two atoms share a CU and
+// every SIMD has three waves; the others run with 8 waves on a second stream.
+#include <algorithm>
+
 #include "dp_env.h"
 
 namespace dp {
 namespace {
 
-// Embedding net for the 16 rows of block jb: writes h1 -> h1b, h2 -> h2b, G rows -> Gout.
-template <typename T>
-__device__ void embed_block(const Weights<T> &w, const Env &e, int ti, int jb, float *h1b, float *h2b,
-                            float *Gout) {
-  for (int q = threadIdx.x; q < 16 * E1; q += NTHREADS) {
-    const int r = q / E1, c = q % E1, j = jb * 16 + r;
-    h1b[r * LDM + c] = tanhf(e.s[j] * w.w1s[c] + w.Bt[(ti * NTYPES + e.tj[j]) * E1 + c]);
-  }
-  __syncthreads();
-  const int wv = wave_id();
-  if (wv < 4) {  // 16 x 50 -> four 16-column tiles
-    const int c0 = wv * 16;
-    f4 acc = {0, 0, 0, 0};
-    Mma<T>::tile(acc, [&](int r, int k) { return h1b[r * LDM + k]; },
-                 [&](int c, int k) { return (c0 + c < E2) ? ldw(w.W2T, (c0 + c) * E1 + k) : 0.f; }, E1);
-    const int col = c0 + acc_col();
-    if (col < E2)
-      for (int i = 0; i < 4; ++i) {
-        const int r = acc_row(i);
-        h2b[r * LDM + col] = tanhf(acc[i] + w.b2[col]) + h1b[r * LDM + (col % E1)];
-      }
-  }
-  __syncthreads();
-  if (wv < 7) {  // 16 x 100 -> seven tiles
-    const int c0 = wv * 16;
-    f4 acc = {0, 0, 0, 0};
-    Mma<T>::tile(acc, [&](int r, int k) { return h2b[r * LDM + k]; },
-                 [&](int c, int k) { return (c0 + c < M) ? ldw(w.W3T, (c0 + c) * E2 + k) : 0.f; }, E2);
-    const int col = c0 + acc_col();
-    if (col < M)
-      for (int i = 0; i < 4; ++i) {
-        const int r = acc_row(i);
-        Gout[(jb * 16 + r) * LDM + col] = tanhf(acc[i] + w.b3[col]) + h2b[r * LDM + (col % E2)];
-      }
-  }
-  __syncthreads();
+constexpr int LDG = M;    // row stride (floats) of G in LDS: 100
+constexpr int LDX = 68;   // row stride of a wave's transposition scratch [16 tokens][64]
+constexpr int LDW = 20;   // ... of a 16 x 16 tile in it
+constexpr int NB_SMALL = 6;  // blocks up to which an atom runs on the first instance
+static_assert(M == 100 && E1 == 25 && E2 == 50, "the fragment layouts below are written for these widths");
+
+// A vector over the 100 features of a lane's token: x[t][i] = feature 16 t + 4 q + i for
+// t < 6, x[6][0] = feature 96 + q (x[6][1..3] are never read as features).
+typedef f4 F100[7];
+
+__device__ __forceinline__ f4 mfma(float a, float b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+__device__ __forceinline__ f4 ldf4(const float *p) { return *reinterpret_cast<const f4 *>(p); }
+// The lane index through an empty asm statement: the compiler then forms lane-derived
+// addresses where they are used instead of keeping them all (and spilling) for the whole
+// kernel.
+__device__ __forceinline__ int lane() {
+  int l = lane_id();
+  asm volatile("" : "+v"(l));
+  return l;
+}
+// Keeps a tile's loads from being scheduled across other tiles' products.
+__device__ __forceinline__ void tile_barrier() { __builtin_amdgcn_sched_barrier(0); }
+__device__ __forceinline__ float sumq(float v) {  // over the four lane groups
+  v += __shfl_xor(v, 16);
+  v += __shfl_xor(v, 32);
+  return v;
+}
+// Orders a wave's own LDS traffic between its lanes.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Shared part of a layer for one 16-row block: U block, scores, weights E = exp(S - m)/Z
-// (into Eb, may be null), attention block A (into Ab) and H = A G (into Hb).
-template <typename T>
-__device__ void attn_block_front(const Weights<T> &w, int layer, const Env &e, const float *Gin, int jb, int n,
-                                 int NP, float *Ub, float *Eb, float *Ab, float *Hb, float *red) {
-  const int wv = wave_id();
-  const int nb = NP / 16;
-  // (a) U block = G_blk Wqk
-  if (wv < 7) {
-    const int c0 = wv * 16;
-    f4 acc = {0, 0, 0, 0};
-    const T *WqkT = w.WqkT[layer];
-    Mma<T>::tile(acc, [&](int r, int k) { return Gin[(jb * 16 + r) * LDM + k]; },
-                 [&](int c, int k) { return (c0 + c < M) ? ldw(WqkT, (c0 + c) * M + k) : 0.f; }, M);
-    const int col = c0 + acc_col();
-    if (col < M)
-      for (int i = 0; i < 4; ++i) Ub[acc_row(i) * LDM + col] = acc[i];
-  }
-  __syncthreads();
-  // (b) scores S = U G^T for this block; wave wv owns column tile wv
-  f4 sacc = {0, 0, 0, 0};
-  const int k = wv * 16 + acc_col();
-  const bool has = wv < nb;
-  if (has)
-    Mma<T>::tile(sacc, [&](int r, int kk) { return Ub[r * LDM + kk]; },
-                 [&](int c, int kk) { return Gin[(wv * 16 + c) * LDM + kk]; }, M);
-  const bool kval = has && k < n;
-  for (int i = 0; i < 4; ++i) {
-    const float m = max16(kval ? sacc[i] : -INFINITY);
-    if ((lane_id() & 15) == 0) red[(wv * 16 + acc_row(i)) * 8 + 0] = m;
-  }
-  __syncthreads();
-  float ex[4], esum[4];
-  for (int i = 0; i < 4; ++i) {
-    const int r = acc_row(i);
-    float m = -INFINITY;
-    for (int q = 0; q < NW; ++q) m = fmaxf(m, red[(q * 16 + r) * 8 + 0]);
-    if (m == -INFINITY) m = 0.f;
-    ex[i] = kval ? expf(sacc[i] - m) : 0.f;
-    esum[i] = sum16(kval ? e.sw[k] * ex[i] : 0.f);
-    if ((lane_id() & 15) == 0) red[(wv * 16 + r) * 8 + 1] = esum[i];
-  }
-  __syncthreads();
-  if (has)
-    for (int i = 0; i < 4; ++i) {
-      const int r = acc_row(i), j = jb * 16 + r;
-      float Z = 0.f;
-      for (int q = 0; q < NW; ++q) Z += red[(q * 16 + r) * 8 + 1];
-      const float E = Z > 0.f ? ex[i] / Z : 0.f;
-      if (Eb) Eb[r * LDN + k] = E;
-      const float gate = e.rh[3 * j] * e.rh[3 * k] + e.rh[3 * j + 1] * e.rh[3 * k + 1] + e.rh[3 * j + 2] * e.rh[3 * k + 2];
-      Ab[r * LDN + k] = e.sw[k] * E * gate;
+// acc += W x for a 100 x 100 matrix W[out][k] in fragment order: tile t (outputs
+// 16 t + row for t < 6; 96 + row / 4 for t = 6) at 1600 t, its k = 16 kb + 4 q + s at
+// + 256 kb + 4 lane + s, its k = 96 + q at + 1536 + lane.  The next tile's operands are
+// loaded while the current one's 25 products run.
+__device__ __forceinline__ void wmul(F100 &acc, const float *__restrict__ w, const F100 &x) {
+  const int l = lane();
+  f4 a[6];
+  float at;
+  const float *p = w + 4 * l;
+#pragma unroll
+  for (int kb = 0; kb < 6; ++kb) a[kb] = ldf4(p + 256 * kb);
+  at = w[1536 + l];
+#pragma unroll
+  for (int t = 0; t < 7; ++t) {
+    f4 b[6];
+    float bt = 0.f;
+    if (t < 6) {
+#pragma unroll
+      for (int kb = 0; kb < 6; ++kb) b[kb] = ldf4(p + 1600 * (t + 1) + 256 * kb);
+      bt = w[1600 * (t + 1) + 1536 + l];
     }
-  __syncthreads();
-  // (c) H = A G
-  if (wv < 7) {
-    const int c0 = wv * 16;
-    f4 acc = {0, 0, 0, 0};
-    Mma<T>::tile(acc, [&](int r, int kk) { return Ab[r * LDN + kk]; },
-                 [&](int c, int kk) { return (c0 + c < M) ? Gin[kk * LDM + c0 + c] : 0.f; }, NP);
-    const int col = c0 + acc_col();
-    if (col < M)
-      for (int i = 0; i < 4; ++i) Hb[acc_row(i) * LDM + col] = acc[i];
+    tile_barrier();
+#pragma unroll
+    for (int kb = 0; kb < 6; ++kb)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) acc[t] = mfma(a[kb][s], x[kb][s], acc[t]);
+    acc[t] = mfma(at, x[6][0], acc[t]);
+    if (t < 6) {
+#pragma unroll
+      for (int kb = 0; kb < 6; ++kb) a[kb] = b[kb];
+      at = bt;
+    }
   }
-  __syncthreads();
 }
 
-// Y = H Wvo for the block held by wave wv (< 7), then the residual X = G_in + Y and its
-// per-row LayerNorm statistics.  Returns xh (normalised X) and isig per accumulator row.
-template <typename T>
-__device__ void attn_block_ln(const Weights<T> &w, int layer, const float *Hb, const float *Gin, int jb, float *red,
-                              float ln_eps, f4 &yh, float isig[4]) {
-  const int wv = wave_id();
-  const int col = wv * 16 + acc_col();
-  const bool cval = wv < 7 && col < M;
-  f4 y = {0, 0, 0, 0};
-  if (wv < 7) {
-    const int c0 = wv * 16;
-    const T *WvoT = w.WvoT[layer];
-    Mma<T>::tile(y, [&](int r, int k) { return Hb[r * LDM + k]; },
-                 [&](int c, int k) { return (c0 + c < M) ? ldw(WvoT, (c0 + c) * M + k) : 0.f; }, M);
+// s[kt] = G x over the keys of tile kt < nb: rows key 16 kt + 4 q + i, columns tokens.
+template <int NB>
+__device__ __forceinline__ void keys_dot(f4 (&s)[NB], const float *G, const F100 &x, int nb) {
+  const int l = lane(), q = l >> 4, c = l & 15;
+#pragma unroll
+  for (int kt = 0; kt < NB; ++kt) {
+    s[kt] = f4{0.f, 0.f, 0.f, 0.f};
+    if (kt < nb) {
+      tile_barrier();
+      const float *g = G + (16 * kt + c) * LDG;
+      f4 a[6];
+#pragma unroll
+      for (int kb = 0; kb < 6; ++kb) a[kb] = ldf4(g + 16 * kb + 4 * q);
+      const float at = g[96 + q];
+#pragma unroll
+      for (int kb = 0; kb < 6; ++kb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[kt] = mfma(a[kb][e], x[kb][e], s[kt]);
+      s[kt] = mfma(at, x[6][0], s[kt]);
+    }
   }
-  if (cval)
-    for (int i = 0; i < 4; ++i) y[i] += Gin[(jb * 16 + acc_row(i)) * LDM + col];
-  for (int i = 0; i < 4; ++i) {
-    const float p = sum16(cval ? y[i] : 0.f);
-    if ((lane_id() & 15) == 0) red[(wv * 16 + acc_row(i)) * 8 + 2] = p;
+}
+
+// acc = G^T y, y(kt)[i] the value of key 16 kt + 4 q + i, kt < nb.
+template <int NB, class Y>
+__device__ __forceinline__ void keys_sum(F100 &acc, const float *G, const Y &y, int nb) {
+  const int l = lane(), q = l >> 4, c = l & 15;
+#pragma unroll
+  for (int t = 0; t < 7; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int kt = 0; kt < NB; ++kt)
+    if (kt < nb) {
+      tile_barrier();
+      const f4 v = y(kt);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        tile_barrier();
+        const float *g = G + (16 * kt + 4 * q + s) * LDG;
+        float a[7];
+#pragma unroll
+        for (int t = 0; t < 6; ++t) a[t] = g[16 * t + c];
+        a[6] = g[96 + (c >> 2)];
+#pragma unroll
+        for (int t = 0; t < 7; ++t) acc[t] = mfma(a[t], v[s], acc[t]);
+      }
+    }
+}
+
+// A token's features from / to a row of G.
+__device__ __forceinline__ void get_row(F100 &x, const float *row) {
+  const int q = lane() >> 4;
+#pragma unroll
+  for (int t = 0; t < 6; ++t) x[t] = ldf4(row + 16 * t + 4 * q);
+  x[6] = f4{row[96 + q], 0.f, 0.f, 0.f};
+}
+__device__ __forceinline__ void put_row(float *row, const F100 &x) {
+  const int q = lane() >> 4;
+#pragma unroll
+  for (int t = 0; t < 6; ++t) *reinterpret_cast<f4 *>(row + 16 * t + 4 * q) = x[t];
+  row[96 + q] = x[6][0];
+}
+// A per-feature table (bias, gain) in the same arrangement.
+__device__ __forceinline__ void get_table(F100 &x, const float *__restrict__ p) { get_row(x, p); }
+
+// A block's features in global memory: 1600 floats, every access one contiguous piece.
+__device__ __forceinline__ void save_block(float *__restrict__ p, const F100 &x) {
+  const int l = lane();
+#pragma unroll
+  for (int t = 0; t < 6; ++t) *reinterpret_cast<f4 *>(p + 256 * t + 4 * l) = x[t];
+  p[1536 + l] = x[6][0];
+}
+__device__ __forceinline__ void load_block(F100 &x, const float *__restrict__ p) {
+  const int l = lane();
+#pragma unroll
+  for (int t = 0; t < 6; ++t) x[t] = ldf4(p + 256 * t + 4 * l);
+  x[6] = f4{p[1536 + l], 0.f, 0.f, 0.f};
+}
+
+// Sum over a token's 100 features of f(t, i) (t = 6: i = 0 only).
+template <class Fn> __device__ __forceinline__ float sum100(const Fn &f) {
+  float v = f(6, 0);
+#pragma unroll
+  for (int t = 0; t < 6; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v += f(t, i);
+  return sumq(v);
+}
+
+// 1 / sigma of a centred row d, and xh = d / sigma in place.
+__device__ __forceinline__ float normalise(F100 &d, float eps) {
+  const float var = sum100([&](int t, int i) { return d[t][i] * d[t][i]; }) * (1.f / M);
+  const float is = 1.f / sqrtf(var + eps);
+#pragma unroll
+  for (int t = 0; t < 7; ++t) d[t] *= is;
+  return is;
+}
+
+// The environment of one atom, padded to whole blocks; padded tokens (j >= n) have
+// s = sw = dsw = 0, r = 1, rhat = 0.
+template <int NB> struct EnvF {
+  float s[16 * NB], sw[16 * NB] __attribute__((aligned(16)));
+  float r[16 * NB];
+  float rh[3][16 * NB] __attribute__((aligned(16)));
+  int tj[16 * NB];
+};
+
+template <int NB>
+__device__ void build_envf(EnvF<NB> &e, int tid, const double *__restrict__ X, const int *__restrict__ types,
+                           const int *__restrict__ nlist, int i, int n, int natoms, const Grid &g, float rc, float rcs) {
+  for (int j = tid; j < 16 * NB; j += 64 * NB) {
+    float s = 0.f, sw = 0.f, r = 1.f, hx = 0.f, hy = 0.f, hz = 0.f;
+    int tj = 0;
+    if (j < n) {
+      int nj = nlist[(size_t)i * SEL + j];
+      if (nj < 0 || nj >= natoms) nj = i;  // never read outside the coordinate array
+      tj = clamp_type(types[nj]);
+      double d[3];
+      for (int a = 0; a < 3; ++a) {
+        double v = X[3 * nj + a] - X[3 * i + a];
+        if (g.periodic) v -= g.L[a] * rint(v * g.invL[a]);
+        d[a] = v;
+      }
+      const float dx = (float)d[0], dy = (float)d[1], dz = (float)d[2];
+      r = sqrtf(dx * dx + dy * dy + dz * dz);
+      const float u = (r - rcs) / (rc - rcs);
+      if (r < rcs) sw = 1.f;
+      else if (r < rc) sw = u * u * u * (-6.f * u * u + 15.f * u - 10.f) + 1.f;
+      s = sw / r;
+      hx = dx / r; hy = dy / r; hz = dz / r;
+    }
+    e.s[j] = s; e.sw[j] = sw; e.r[j] = r; e.tj[j] = tj;
+    e.rh[0][j] = hx; e.rh[1][j] = hy; e.rh[2][j] = hz;
   }
-  __syncthreads();
-  float mu[4];
-  for (int i = 0; i < 4; ++i) {
-    const int r = acc_row(i);
-    float sacc = 0.f;
-    for (int q = 0; q < NW; ++q) sacc += red[(q * 16 + r) * 8 + 2];
-    mu[i] = sacc / (float)M;
-    const float dv = cval ? y[i] - mu[i] : 0.f;
-    const float p = sum16(dv * dv);
-    if ((lane_id() & 15) == 0) red[(wv * 16 + r) * 8 + 3] = p;
+}
+
+// ------------------------------------------------------------ embedding net
+// Its widths 25, 50 = 2 x 25, 100 = 4 x 25 are kept as groups of 25 features, slot r of
+// lane group q holding feature 4 r + q of the group (r < 7; r = 6 only for q = 0, zero
+// elsewhere), so that the residuals [h, h] add registers of the same lane.  h1[r];
+// h2[g][r] with feature 25 g + 4 r + q; G[g][r] likewise for g < 4.  Weights in fragment
+// order: an output group's slots 0-3 and 4-7 are two tiles (row 4 q + i of tile u is slot
+// 4 u + i); a contraction group's 8 slots are two pieces of 4 k steps.
+typedef float S7[7];
+__device__ __forceinline__ bool slot_ok(int r) { return r < 6 || lane() < 16; }
+
+// out[og] += W in over NI input groups: W at ((og * 2 + u) * NI * 2 + 2 ig + piece) * 256.
+template <int NI, int NO>
+__device__ __forceinline__ void emul(S7 (&out)[NO], const float *__restrict__ w, const S7 (&in)[NI]) {
+  const int l = lane();
+#pragma unroll
+  for (int og = 0; og < NO; ++og)
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      f4 acc = {0.f, 0.f, 0.f, 0.f};
+      f4 a[2 * NI];
+#pragma unroll
+      for (int p = 0; p < 2 * NI; ++p) a[p] = ldf4(w + ((og * 2 + u) * NI * 2 + p) * 256 + 4 * l);
+      tile_barrier();
+#pragma unroll
+      for (int ig = 0; ig < NI; ++ig)
+#pragma unroll
+        for (int r = 0; r < 7; ++r) acc = mfma(a[2 * ig + r / 4][r % 4], in[ig][r], acc);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (4 * u + i < 7) out[og][4 * u + i] = acc[i];
+    }
+}
+
+// h1, t2 = h2 - [h1, h1] and t3 = G - [h2, h2] of the lane's token.
+__device__ __forceinline__ void embed(const Weights<float> &w, float s, int ti, int tj, S7 (&h1)[1], S7 (&t2)[2], S7 (&t3)[4]) {
+  const int q = lane() >> 4;
+  const float *bt = w.Bt + (ti * NTYPES + tj) * E1;
+#pragma unroll
+  for (int r = 0; r < 7; ++r) {
+    const int f = slot_ok(r) ? 4 * r + q : 0;
+    const float v = tanhf(s * w.w1s[f] + bt[f]);
+    h1[0][r] = slot_ok(r) ? v : 0.f;
   }
-  __syncthreads();
-  for (int i = 0; i < 4; ++i) {
-    const int r = acc_row(i);
-    float v = 0.f;
-    for (int q = 0; q < NW; ++q) v += red[(q * 16 + r) * 8 + 3];
-    isig[i] = 1.f / sqrtf(v / (float)M + ln_eps);
-    yh[i] = (y[i] - mu[i]) * isig[i];
+  emul<1, 2>(t2, w.W2T, h1);
+  S7 h2[2];
+#pragma unroll
+  for (int g = 0; g < 2; ++g)
+#pragma unroll
+    for (int r = 0; r < 7; ++r) {
+      const int f = slot_ok(r) ? 25 * g + 4 * r + q : 0;
+      const float v = tanhf(t2[g][r] + w.b2[f]);
+      t2[g][r] = slot_ok(r) ? v : 0.f;
+      h2[g][r] = t2[g][r] + h1[0][r];
+    }
+  emul<2, 4>(t3, w.W3T, h2);
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+#pragma unroll
+    for (int r = 0; r < 7; ++r) {
+      const int f = slot_ok(r) ? 25 * g + 4 * r + q : 0;
+      const float v = tanhf(t3[g][r] + w.b3[f]);
+      t3[g][r] = slot_ok(r) ? v : 0.f;
+    }
+}
+
+// The embedding's G into the token's row.
+__device__ __forceinline__ void put_embedding(float *row, const S7 (&h1)[1], const S7 (&t2)[2], const S7 (&t3)[4]) {
+  const int q = lane() >> 4;
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+#pragma unroll
+    for (int r = 0; r < 7; ++r)
+      if (slot_ok(r)) row[25 * g + 4 * r + q] = t3[g][r] + (t2[g & 1][r] + h1[0][r]);
+}
+
+// E = exp(S - max) / Z over the keys in place of the scores (0 past the list), with
+// Z = sum_k sw_k exp(S_k - max).
+template <int NB>
+__device__ __forceinline__ void softmax_keys(f4 (&s)[NB], const EnvF<NB> &e, int n, int nb) {
+  const int q = lane() >> 4;
+  float m = -INFINITY;
+#pragma unroll
+  for (int kt = 0; kt < NB; ++kt)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (16 * kt + 4 * q + i >= n) s[kt][i] = -INFINITY;
+      m = fmaxf(m, s[kt][i]);
+    }
+  m = fmaxf(m, __shfl_xor(m, 16));
+  m = fmaxf(m, __shfl_xor(m, 32));
+  if (m == -INFINITY) m = 0.f;
+  float z = 0.f;
+#pragma unroll
+  for (int kt = 0; kt < NB; ++kt) {
+    const f4 sw = ldf4(e.sw + 16 * kt + 4 * q);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      s[kt][i] = expf(s[kt][i] - m);
+      z += sw[i] * s[kt][i];
+    }
   }
+  z = sumq(z);
+  const float iz = z > 0.f ? 1.f / z : 0.f;
+#pragma unroll
+  for (int kt = 0; kt < NB; ++kt) s[kt] *= iz;
+}
+
+// rhat_k . h for the four keys of tile kt the lane holds.
+template <int NB>
+__device__ __forceinline__ f4 gate4(const EnvF<NB> &e, int kt, const float (&h)[3]) {
+  const int k = 16 * kt + 4 * (lane() >> 4);
+  return ldf4(e.rh[0] + k) * h[0] + ldf4(e.rh[1] + k) * h[1] + ldf4(e.rh[2] + k) * h[2];
 }
 
 // ======================================================================== forward
-struct SmemFwd {
-  float G[2][NPMAX * LDM];
-  float Ub[16 * LDM];
-  float Ab[16 * LDN];
-  float Hb[16 * LDM];
-  float red[NW * 16 * 8];
+template <int NB> struct SmemFwd {
+  float G[16 * NB * LDG] __attribute__((aligned(16)));
+  float part[NB][M * 4] __attribute__((aligned(16)));
   float T[M * 4];
-  Env e;
+  EnvF<NB> e;
 };
 
-template <typename T>
-__global__ void __launch_bounds__(NTHREADS)
-k_desc_fwd(Weights<T> w, const double *__restrict__ X, const int *__restrict__ types, int natoms, int c0,
-           const int *__restrict__ nlist, const int *__restrict__ nnei, const Grid *__restrict__ grids, const int *__restrict__ sys_of,
-           float rc, float rcs, float ln_eps, float *__restrict__ Gsave, float *__restrict__ Tsave,
-           float *__restrict__ D) {
-  __shared__ SmemFwd sm;
-  const int i = c0 + blockIdx.x;
-  const Grid g = grids[sys_of[i]];
-  const int n = min(max(nnei[i], 0), SEL);
-  const int NP = n > 0 ? ((n + 15) / 16) * 16 : 16;
-  const int nb = NP / 16;
-  const int ti = clamp_type(types[i]);
-  build_env(sm.e, X, types, nlist, i, n, natoms, g, rc, rcs);
-  __syncthreads();
-  for (int jb = 0; jb < nb; ++jb) embed_block(w, sm.e, ti, jb, sm.Ub, sm.Hb, sm.G[0]);
-  for (int layer = 0; layer < NATTN; ++layer) {
-    float *Gin = sm.G[layer & 1];
-    float *Gout = sm.G[(layer + 1) & 1];
-    float *gs = Gsave + ((size_t)i * NATTN + layer) * GSAVE_LAYER;
-    for (int q = threadIdx.x; q < NP * M; q += NTHREADS) gs[q] = Gin[(q / M) * LDM + q % M];
-    for (int jb = 0; jb < nb; ++jb) {
-      attn_block_front(w, layer, sm.e, Gin, jb, n, NP, sm.Ub, nullptr, sm.Ab, sm.Hb, sm.red);
-      f4 yh;
-      float isig[4];
-      attn_block_ln(w, layer, sm.Hb, Gin, jb, sm.red, ln_eps, yh, isig);
-      const int wv = wave_id();
-      const int col = wv * 16 + acc_col();
-      if (wv < 7 && col < M)
-        for (int ii = 0; ii < 4; ++ii) {
-          const int j = jb * 16 + acc_row(ii);
-          Gout[j * LDM + col] = w.gamma[layer][col] * yh[ii] + w.beta[layer][col];
-        }
-      __syncthreads();
+// The part of a workgroup's work a wave takes: NA atoms (entries blk NA .. of the
+// instance's list), NB waves each.  Past the end of the list nb = 0; steps is the largest
+// nb, so that the waves of both atoms pass the same barriers.
+template <int NB, int NA> struct Part {
+  int half, jb, tid, i, n, nb, steps;
+  __device__ __forceinline__ Part(int blk, const int *__restrict__ idx, int count, const int *__restrict__ nnei) {
+    const int wv = __builtin_amdgcn_readfirstlane(wave_id());
+    half = NA == 1 ? 0 : wv / NB;
+    jb = wv - half * NB;
+    tid = threadIdx.x - half * 64 * NB;
+    steps = 0;
+#pragma unroll
+    for (int a = 0; a < NA; ++a) {
+      const int k = idx[min(blk * NA + a, count - 1)];
+      const int nk = min(max(nnei[k], 0), SEL);
+      const int b = blk * NA + a < count ? min(nk > 0 ? (nk + 15) / 16 : 1, NB) : 0;
+      steps = max(steps, b);
+      if (a == half) {
+        i = k;
+        n = nk;
+        nb = b;
+      }
     }
   }
-  const float *Gf = sm.G[NATTN & 1];
-  for (int q = threadIdx.x; q < M * 4; q += NTHREADS) {
-    const int m = q >> 2, c = q & 3;
-    float acc = 0.f;
-    for (int j = 0; j < n; ++j) acc += Gf[j * LDM + m] * sm.e.Rt[4 * j + c];
-    acc *= 1.f / (float)SEL;
-    sm.T[q] = acc;
-    Tsave[(size_t)i * M * 4 + q] = acc;
+};
+
+template <int NB, int NA>
+__device__ __forceinline__ void desc_fwd(int blk, int count, SmemFwd<NB> *smem, Weights<float> w, const double *__restrict__ X, const int *__restrict__ types, int natoms, const int *__restrict__ idx,
+           const int *__restrict__ nlist, const int *__restrict__ nnei, const Grid *__restrict__ grids,
+           const int *__restrict__ sys_of, float rc, float rcs, float ln_eps, float *__restrict__ Gsave,
+           float *__restrict__ Tsave, float *__restrict__ D) {
+  const Part<NB, NA> pt(blk, idx, count, nnei);
+  SmemFwd<NB> &sm = smem[pt.half];
+  const int i = pt.i, n = pt.n, nb = pt.nb, jb = pt.jb, tid = pt.tid;
+  const Grid g = grids[sys_of[i]];
+  const int ti = clamp_type(types[i]);
+  const int l = lane(), q = l >> 4, c = l & 15;
+  const bool act = jb < nb;
+  build_envf(sm.e, tid, X, types, nlist, i, n, natoms, g, rc, rcs);
+  __syncthreads();
+  const int j = 16 * jb + c;  // the lane's token
+  float *row = sm.G + j * LDG;
+  if (act) {
+    S7 h1[1], t2[2], t3[4];
+    embed(w, sm.e.s[j], ti, sm.e.tj[j], h1, t2, t3);
+    put_embedding(row, h1, t2, t3);
   }
   __syncthreads();
-  for (int q = threadIdx.x; q < ND; q += NTHREADS) {
-    const int m = q / M2, a = q % M2;
+  const float hj[3] = {sm.e.rh[0][j], sm.e.rh[1][j], sm.e.rh[2][j]};
+#pragma unroll 1
+  for (int layer = 0; layer < NATTN; ++layer) {
+    F100 y = {};
+    if (act) {
+      F100 x, u = {};
+      get_row(x, row);
+      wmul(u, w.WqkT[layer], x);  // U
+      f4 s[NB];
+      keys_dot<NB>(s, sm.G, u, nb);  // S = U G^T
+      softmax_keys<NB>(s, sm.e, n, nb);
+      // H = A G with A = sw E gate
+      keys_sum<NB>(x, sm.G, [&](int kt) { return s[kt] * gate4(sm.e, kt, hj) * ldf4(sm.e.sw + 16 * kt + 4 * q); }, nb);
+      wmul(y, w.WvoT[layer], x);     // Y, summed by itself and then added: starting from G would round at G's size
+      get_row(x, row);
+#pragma unroll
+      for (int t = 0; t < 7; ++t) y[t] += x[t];
+      // LayerNorm; the centred rows are what the backward reads
+      const float mu = sum100([&](int t, int k) { return y[t][k]; }) * (1.f / M);
+#pragma unroll
+      for (int t = 0; t < 7; ++t) y[t] -= mu;
+      save_block(Gsave + ((size_t)i * NATTN + layer) * GSAVE_LAYER + 1600 * jb, y);
+      normalise(y, ln_eps);
+      F100 ga, be;
+      get_table(ga, w.gamma[layer]);
+      get_table(be, w.beta[layer]);
+#pragma unroll
+      for (int t = 0; t < 7; ++t) y[t] = ga[t] * y[t] + be[t];
+    }
+    __syncthreads();  // every wave is done with the layer's input
+    if (act) put_row(row, y);
+    __syncthreads();
+  }
+  // T = G^T Rt / sel: each wave's 16 tokens on MFMA (T^T = Rt^T G, rows c < 4 of the 16
+  // used, step s taking token 4 s + q), then the waves' parts in order
+  if (act) {
+    f4 acc[7];
+#pragma unroll
+    for (int t = 0; t < 7; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int k = 16 * jb + 4 * s + q;
+      const float sk = sm.e.s[k];
+      const float rt = c == 0 ? sk : (c < 4 ? sk * sm.e.rh[c - 1][k] : 0.f);
+      const float *gk = sm.G + k * LDG;
+#pragma unroll
+      for (int t = 0; t < 7; ++t) acc[t] = mfma(rt, gk[t < 6 ? 16 * t + c : 96 + (c & 3)], acc[t]);
+    }
+    if (q == 0)
+#pragma unroll
+      for (int t = 0; t < 7; ++t)
+        if (t < 6 || c < 4) *reinterpret_cast<f4 *>(sm.part[jb] + 4 * (16 * t + c)) = acc[t];
+  }
+  __syncthreads();
+  for (int k = tid; k < M * 4; k += 64 * NB) {
+    float acc = 0.f;
+    for (int v = 0; v < nb; ++v) acc += sm.part[v][k];
+    acc *= 1.f / (float)SEL;
+    sm.T[k] = acc;
+    if (nb) Tsave[(size_t)i * M * 4 + k] = acc;
+  }
+  __syncthreads();
+  for (int k = tid; k < (nb ? ND : 0); k += 64 * NB) {
+    const int m = k / M2, a = k % M2;
     const float *tm = sm.T + 4 * m, *ta = sm.T + 4 * a;
-    D[(size_t)i * ND + q] = tm[0] * ta[0] + tm[1] * ta[1] + tm[2] * ta[2] + tm[3] * ta[3];
+    D[(size_t)i * ND + k] = tm[0] * ta[0] + tm[1] * ta[1] + tm[2] * ta[2] + tm[3] * ta[3];
+  }
+}
+
+// One workgroup per NA atoms of its instance's list; the 8-wave instance loops over its list
+// with at most one workgroup per CU.
+template <int NB, int NA>
+__global__ void __launch_bounds__(64 * NB * NA) __attribute__((amdgpu_waves_per_eu(NB == NB_SMALL ? 3 : 2)))
+k_desc_fwd(Weights<float> w, const double *__restrict__ X, const int *__restrict__ types, int natoms,
+           const int *__restrict__ idx, const int *__restrict__ cnt, const int *__restrict__ nlist,
+           const int *__restrict__ nnei, const Grid *__restrict__ grids, const int *__restrict__ sys_of, float rc, float rcs,
+           float ln_eps, float *__restrict__ Gsave, float *__restrict__ Tsave, float *__restrict__ D) {
+  __shared__ SmemFwd<NB> smem[NA];
+  const int count = *cnt;
+  if constexpr (NB == NB_SMALL) {  // without the loop, which would keep its invariants in registers
+    const int b = blockIdx.x;
+    if (b * NA < count)
+      desc_fwd<NB, NA>(b, count, smem, w, X, types, natoms, idx, nlist, nnei, grids, sys_of, rc, rcs, ln_eps, Gsave, Tsave, D);
+  } else {
+    for (int b = blockIdx.x; b * NA < count; b += gridDim.x) {
+      desc_fwd<NB, NA>(b, count, smem, w, X, types, natoms, idx, nlist, nnei, grids, sys_of, rc, rcs, ln_eps, Gsave, Tsave, D);
+      __syncthreads();
+    }
   }
 }
 
 // ======================================================================== backward
-struct SmemBwd {
-  float Gin[NPMAX * LDM];
-  float dG[NPMAX * LDM];
-  float Ub[16 * LDM];
-  float Eb[16 * LDN];
-  float Ab[16 * LDN];
-  float Hb[16 * LDM];
-  float dHb[16 * LDM];
-  float red[NW * 16 * 8];
-  float T[M * 4];
-  float dT[M * 4];
-  float dswa[NPMAX];
-  float drh[NPMAX * 3];
-  float dRt[NPMAX * 4];
-  Env e;
+template <int NB> struct SmemBwd {
+  float G[16 * NB * LDG] __attribute__((aligned(16)));      // a layer's input, then dE/dG
+  float scr[NB][16 * LDX] __attribute__((aligned(16)));     // per-wave transposition scratch
+  float drhw[NB][16 * NB * 3];                              // each wave's column sums of dC rhat
+  float drh[16 * NB * 3], dswa[16 * NB];
+  float dRt[16 * NB * 4] __attribute__((aligned(16)));
+  float dT[M * 4] __attribute__((aligned(16)));
+  EnvF<NB> e;
 };
 
-template <typename T>
-__global__ void __launch_bounds__(NTHREADS)
-k_desc_bwd(Weights<T> w, const double *__restrict__ X, const int *__restrict__ types, int natoms, int c0,
-           const int *__restrict__ nlist, const int *__restrict__ nnei, const Grid *__restrict__ grids, const int *__restrict__ sys_of,
-           float rc, float rcs, float ln_eps, const float *__restrict__ Gsave, const float *__restrict__ Tsave,
-           const float *__restrict__ dD, float4 *__restrict__ gout) {
-  __shared__ SmemBwd sm;
-  const int i = c0 + blockIdx.x;
+// A wave's 16 x 100 block x as the A operand of products that contract over its tokens:
+// o[t][s] = feature 16 t + c (t < 6) or 96 + c / 4 of token 4 q + s.
+__device__ __forceinline__ void transpose_block(f4 (&o)[7], const F100 &x, float *scr) {
+  const int l = lane(), q = l >> 4, c = l & 15;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    wave_sync();
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      if (4 * h + t < 6) *reinterpret_cast<f4 *>(scr + c * LDX + 16 * t + 4 * q) = x[4 * h + t];
+      if (4 * h + t == 6) scr[c * LDX + 16 * t + q] = x[6][0];
+    }
+    wave_sync();
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        if (4 * h + t < 6) o[4 * h + t][s] = scr[(4 * q + s) * LDX + 16 * t + c];
+        if (4 * h + t == 6) o[6][s] = scr[(4 * q + s) * LDX + 16 * t + (c >> 2)];
+      }
+  }
+  wave_sync();
+}
+
+// A key tile y (rows keys, columns tokens) as the B operand contracting over tokens:
+// o[s] = y of token 4 q + s, key c.  scr: 16 x LDW floats.
+__device__ __forceinline__ f4 transpose_tile(const f4 &y, float *scr) {
+  const int l = lane(), q = l >> 4, c = l & 15;
+  *reinterpret_cast<f4 *>(scr + c * LDW + 4 * q) = y;
+  wave_sync();
+  f4 o;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) o[s] = scr[(4 * q + s) * LDW + c];
+  return o;
+}
+
+// Backward of one layer, its input rows in sm.G.  go: the gradient of the layer's output
+// for the wave's tokens; d: the layer's saved centred rows.  On return sm.G holds the
+// gradient of the layer's input and every thread has passed a barrier.
+//   Row part (per token j): U, S, E recomputed; dX through the LayerNorm, dH = Wvo dX,
+//   dA = G dH, then per key P = sw E, dP = dA gate, rho = sum P dP, W = E (dP - rho),
+//   dS = sw W, dU = G^T dS, and dG_j = dX + Wqk dU.
+//   Column part (per key k): dG_k += sw_k sum_j (E gate)_jk dH_j + W_jk U_j and
+//   dsw_k += sum_j W_jk.  In step p the wave of block j adds its tokens' share to key block
+//   (j + p) mod nb; a barrier ends each step, so each sum has a fixed order.
+template <int NB>
+__device__ __forceinline__ void layer_bwd(const Weights<float> &w, int layer, SmemBwd<NB> &sm, F100 &go,
+                                          const float *__restrict__ saved, int jb, int tid, int n, int nb, int steps,
+                                          float ln_eps) {
+  const int l = lane(), q = l >> 4, c = l & 15;
+  const int j = 16 * jb + c;
+  float *row = sm.G + j * LDG;
+  float *scr = sm.scr[jb];
+  const bool act = jb < nb;
+  F100 u = {}, dh = {}, dx;
+  f4 E[NB], W[NB];
+  const float hj[3] = {sm.e.rh[0][j], sm.e.rh[1][j], sm.e.rh[2][j]};
+  if (act) {
+    {
+      F100 x;
+      get_row(x, row);
+      wmul(u, w.WqkT[layer], x);
+    }
+    keys_dot<NB>(E, sm.G, u, nb);
+    softmax_keys<NB>(E, sm.e, n, nb);
+    {  // LayerNorm backward: dX = (dxh - mean(dxh) - xh mean(dxh xh)) / sigma, dxh = gamma dG_out
+      F100 xh, ga;
+      load_block(xh, saved + 1600 * jb);
+      const float is = normalise(xh, ln_eps);
+      get_table(ga, w.gamma[layer]);
+#pragma unroll
+      for (int t = 0; t < 7; ++t) dx[t] = ga[t] * go[t];
+      const float s0 = sum100([&](int t, int k) { return dx[t][k]; }) * (1.f / M);
+      const float s1 = sum100([&](int t, int k) { return dx[t][k] * xh[t][k]; }) * (1.f / M);
+#pragma unroll
+      for (int t = 0; t < 7; ++t) dx[t] = (dx[t] - s0 - xh[t] * s1) * is;
+    }
+    wmul(dh, w.Wvo[layer], dx);
+    keys_dot<NB>(W, sm.G, dh, nb);  // dA
+    float rho = 0.f, hx = 0.f, hy = 0.f, hz = 0.f;
+    // columns of dC rhat: sum_j rhat_j (dA E)_jk, A operand rhat of token 4 q + s in rows a < 3
+    float rj[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) rj[s] = c < 3 ? sm.e.rh[c][16 * jb + 4 * q + s] : 0.f;
+#pragma unroll
+    for (int kt = 0; kt < NB; ++kt)
+      if (kt < nb) {
+        tile_barrier();
+        const int k = 16 * kt + 4 * q;
+        const f4 sw = ldf4(sm.e.sw + k), rx = ldf4(sm.e.rh[0] + k), ry = ldf4(sm.e.rh[1] + k), rz = ldf4(sm.e.rh[2] + k);
+        const f4 gt = rx * hj[0] + ry * hj[1] + rz * hj[2];
+        const f4 cc = W[kt] * E[kt];
+        const f4 dC = sw * cc, dP = W[kt] * gt, pr = sw * E[kt] * dP;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          rho += pr[i];
+          hx += dC[i] * rx[i];
+          hy += dC[i] * ry[i];
+          hz += dC[i] * rz[i];
+        }
+        W[kt] = dP;
+        wave_sync();
+        const f4 ct = transpose_tile(cc, scr);
+        f4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < 4; ++s) acc = mfma(rj[s], ct[s], acc);
+        if (q == 0) {
+          const float swk = sm.e.sw[16 * kt + c];
+          float *o = sm.drhw[jb] + 3 * (16 * kt + c);
+          o[0] = swk * acc[0]; o[1] = swk * acc[1]; o[2] = swk * acc[2];
+        }
+      }
+    rho = sumq(rho);
+    hx = sumq(hx); hy = sumq(hy); hz = sumq(hz);
+    if (q == 0) {
+      sm.drh[3 * j] += hx; sm.drh[3 * j + 1] += hy; sm.drh[3 * j + 2] += hz;
+    }
+    F100 du;
+    keys_sum<NB>(du, sm.G, [&](int kt) {
+      W[kt] = E[kt] * (W[kt] - rho);
+      return ldf4(sm.e.sw + 16 * kt + 4 * q) * W[kt];  // dS
+    }, nb);
+    F100 r = {};
+    wmul(r, w.Wqk[layer], du);
+#pragma unroll
+    for (int t = 0; t < 7; ++t) dx[t] += r[t];
+  }
+  __syncthreads();  // the layer's input is no longer needed
+  f4 ut[7], ht[7];
+  if (act) {
+    put_row(row, dx);
+    transpose_block(ut, u, scr);
+    transpose_block(ht, dh, scr);
+    // rows 4 q' + 1 of tile 6 collect sum_j W_jk
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      if ((c & 3) == 1) {
+        ut[6][s] = 1.f;
+        ht[6][s] = 0.f;
+      }
+    }
+  }
+#pragma unroll 1
+  for (int p = 0; p < steps; ++p) {
+    __syncthreads();
+    if (act && p < nb) {
+      int kb = jb + p;
+      if (kb >= nb) kb -= nb;
+      wave_sync();
+#pragma unroll
+      for (int kt = 0; kt < NB; ++kt)
+        if (kt == kb) {
+          *reinterpret_cast<f4 *>(scr + c * LDW + 4 * q) = E[kt] * gate4(sm.e, kt, hj);
+          *reinterpret_cast<f4 *>(scr + 16 * LDW + c * LDW + 4 * q) = W[kt];
+        }
+      wave_sync();
+      f4 ya, yw;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        ya[s] = scr[(4 * q + s) * LDW + c];
+        yw[s] = scr[16 * LDW + (4 * q + s) * LDW + c];
+      }
+      F100 acc = {};
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int t = 0; t < 7; ++t) acc[t] = mfma(ht[t][s], ya[s], acc[t]);
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int t = 0; t < 7; ++t) acc[t] = mfma(ut[t][s], yw[s], acc[t]);
+      const int k = 16 * kb + c;
+      const float swk = sm.e.sw[k];
+      float *gk = sm.G + k * LDG;
+#pragma unroll
+      for (int t = 0; t < 6; ++t) {
+        f4 *o = reinterpret_cast<f4 *>(gk + 16 * t + 4 * q);
+        *o = *o + swk * acc[t];
+      }
+      gk[96 + q] += swk * acc[6][0];
+      if (q == 0) sm.dswa[k] += acc[6][1];
+    }
+  }
+  __syncthreads();
+  for (int k = tid; k < 16 * nb * 3; k += 64 * NB) {
+    float v = sm.drh[k];
+    for (int u2 = 0; u2 < nb; ++u2) v += sm.drhw[u2][k];
+    sm.drh[k] = v;
+  }
+}
+
+template <int NB, int NA>
+__device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB> *smem, Weights<float> w, const double *__restrict__ X, const int *__restrict__ types, int natoms, const int *__restrict__ idx,
+           const int *__restrict__ nlist, const int *__restrict__ nnei, const Grid *__restrict__ grids,
+           const int *__restrict__ sys_of, float rc, float rcs, float ln_eps, const float *__restrict__ Gsave,
+           const float *__restrict__ Tsave, const float *__restrict__ dD, float4 *__restrict__ gout) {
+  const Part<NB, NA> pt(blk, idx, count, nnei);
+  SmemBwd<NB> &sm = smem[pt.half];
+  const int i = pt.i, n = pt.n, nb = pt.nb, jb = pt.jb, tid = pt.tid;
   const Grid g = grids[sys_of[i]];
-  const int n = min(max(nnei[i], 0), SEL);
-  const int NP = n > 0 ? ((n + 15) / 16) * 16 : 16;
-  const int nb = NP / 16;
   const int ti = clamp_type(types[i]);
-  const int wv = wave_id();
-  build_env(sm.e, X, types, nlist, i, n, natoms, g, rc, rcs);
-  for (int q = threadIdx.x; q < NPMAX; q += NTHREADS) {
-    sm.dswa[q] = 0.f;
-    for (int a = 0; a < 3; ++a) sm.drh[3 * q + a] = 0.f;
-    for (int a = 0; a < 4; ++a) sm.dRt[4 * q + a] = 0.f;
+  const int l = lane(), q = l >> 4, c = l & 15;
+  const bool act = jb < nb;
+  const float *gs = Gsave + (size_t)i * NATTN * GSAVE_LAYER;
+  build_envf(sm.e, tid, X, types, nlist, i, n, natoms, g, rc, rcs);
+  for (int k = tid; k < 16 * NB; k += 64 * NB) {
+    sm.dswa[k] = 0.f;
+    for (int a = 0; a < 3; ++a) sm.drh[3 * k + a] = 0.f;
   }
-  for (int q = threadIdx.x; q < M * 4; q += NTHREADS) sm.T[q] = Tsave[(size_t)i * M * 4 + q];
+  // dT from dE/dD (D = T T_<16^T): dT_m = sum_a dD_ma T_a + [m < 16] sum_m' dD_m'm T_m'; G is
+  // free until the layer input is put there
+  float *T = sm.G, *dDi = T + M * 4, *part = dDi + ND;
+  static_assert(M * 4 + ND + 64 * NB <= 16 * NB * LDG, "dT staging fits in G");
+  for (int k = tid; k < M; k += 64 * NB)
+    *reinterpret_cast<f4 *>(T + 4 * k) = ldf4(Tsave + ((size_t)i * M + k) * 4);
+  for (int k = tid; k < ND / 4; k += 64 * NB)
+    *reinterpret_cast<f4 *>(dDi + 4 * k) = ldf4(dD + (size_t)i * ND + 4 * k);
   __syncthreads();
-  // dT from dD:  D_ma = T_m . T_a  =>  dT_m += sum_a dD_ma T_a ;  dT_a += sum_m dD_ma T_m (a < 16)
-  const float *dDi = dD + (size_t)i * ND;
-  for (int q = threadIdx.x; q < M * 4; q += NTHREADS) {
-    const int m = q >> 2, c = q & 3;
+  for (int k = tid; k < M * 4; k += 64 * NB) {
+    const int m = k >> 2, a4 = k & 3;
     float acc = 0.f;
-    for (int a = 0; a < M2; ++a) acc += dDi[m * M2 + a] * sm.T[4 * a + c];
-    if (m < M2)
-      for (int mm = 0; mm < M; ++mm) acc += dDi[mm * M2 + m] * sm.T[4 * mm + c];
-    sm.dT[q] = acc;
+    for (int a = 0; a < M2; ++a) acc += dDi[m * M2 + a] * T[4 * a + a4];
+    sm.dT[k] = acc;
+  }
+  {
+    constexpr int CH = (M + NB - 1) / NB;
+    const int k = tid & 63, ch = tid >> 6, m = k >> 2, a4 = k & 3;
+    float acc = 0.f;
+    for (int mm = ch * CH; mm < min(M, (ch + 1) * CH); ++mm) acc += dDi[mm * M2 + m] * T[4 * mm + a4];
+    part[tid] = acc;
   }
   __syncthreads();
-  const float inv_sel = 1.f / (float)SEL;
-
-  for (int layer = NATTN - 1; layer >= 0; --layer) {
-    const float *gs = Gsave + ((size_t)i * NATTN + layer) * GSAVE_LAYER;
-    for (int q = threadIdx.x; q < NP * M; q += NTHREADS) sm.Gin[(q / M) * LDM + q % M] = gs[q];
-    __syncthreads();
-    f4 colacc[7];
-    for (int t = 0; t < 7; ++t) colacc[t] = f4{0, 0, 0, 0};
-    const bool top = layer == NATTN - 1;
-    for (int jb = 0; jb < nb; ++jb) {
-      attn_block_front(w, layer, sm.e, sm.Gin, jb, n, NP, sm.Ub, sm.Eb, sm.Ab, sm.Hb, sm.red);
-      f4 yh;
-      float isig[4];
-      attn_block_ln(w, layer, sm.Hb, sm.Gin, jb, sm.red, ln_eps, yh, isig);
-      // (d) LayerNorm backward; for the top layer the incoming gradient is
-      // dG = Rt dT^T / sel and the layer output also feeds dRt = G_out dT / sel.
-      // The residual runs through the LayerNorm: dG_in starts as dX and dY = dX.
-      const int col = wv * 16 + acc_col();
-      const bool cval = wv < 7 && col < M;
-      float dyh[4];
-      float prt[4][4];
-      for (int ii = 0; ii < 4; ++ii) {
-        const int r = acc_row(ii), j = jb * 16 + r;
-        float go = 0.f;
-        if (cval) {
-          if (top) {
-            go = (sm.e.Rt[4 * j] * sm.dT[4 * col] + sm.e.Rt[4 * j + 1] * sm.dT[4 * col + 1] +
-                  sm.e.Rt[4 * j + 2] * sm.dT[4 * col + 2] + sm.e.Rt[4 * j + 3] * sm.dT[4 * col + 3]) * inv_sel;
-            const float gout_v = w.gamma[layer][col] * yh[ii] + w.beta[layer][col];
-            for (int c = 0; c < 4; ++c) prt[ii][c] = gout_v * sm.dT[4 * col + c] * inv_sel;
-          } else {
-            go = sm.dG[j * LDM + col];
-            for (int c = 0; c < 4; ++c) prt[ii][c] = 0.f;
-          }
-        } else {
-          for (int c = 0; c < 4; ++c) prt[ii][c] = 0.f;
-        }
-        dyh[ii] = cval ? go * w.gamma[layer][col] : 0.f;
-        const float p0 = sum16(dyh[ii]);
-        const float p1 = sum16(dyh[ii] * (cval ? yh[ii] : 0.f));
-        if ((lane_id() & 15) == 0) {
-          sm.red[(wv * 16 + r) * 8 + 4] = p0;
-          sm.red[(wv * 16 + r) * 8 + 5] = p1;
-        }
-        if (top)
-          for (int c = 0; c < 4; ++c) prt[ii][c] = sum16(prt[ii][c]);
-      }
-      __syncthreads();
-      for (int ii = 0; ii < 4; ++ii) {
-        const int r = acc_row(ii);
-        float s0 = 0.f, s1 = 0.f;
-        for (int q = 0; q < NW; ++q) {
-          s0 += sm.red[(q * 16 + r) * 8 + 4];
-          s1 += sm.red[(q * 16 + r) * 8 + 5];
-        }
-        const float dX = (dyh[ii] - s0 / (float)M - (cval ? yh[ii] : 0.f) * (s1 / (float)M)) * isig[ii];
-        if (cval) {
-          sm.Hb[r * LDM + col] = dX;
-          sm.dG[(jb * 16 + r) * LDM + col] = dX;
-        }
-      }
-      // dRt row sums for the top layer: 4 values per row, reduced in two rounds of 2
-      if (top) {
-        for (int half = 0; half < 2; ++half) {
-          __syncthreads();
-          for (int ii = 0; ii < 4; ++ii)
-            if ((lane_id() & 15) == 0) {
-              const int r = acc_row(ii);
-              sm.red[(wv * 16 + r) * 8 + 6] = prt[ii][2 * half];
-              sm.red[(wv * 16 + r) * 8 + 7] = prt[ii][2 * half + 1];
-            }
-          __syncthreads();
-          if ((int)threadIdx.x < 16) {
-            const int r = threadIdx.x, j = jb * 16 + r;
-            float a0 = 0.f, a1 = 0.f;
-            for (int q = 0; q < NW; ++q) {
-              a0 += sm.red[(q * 16 + r) * 8 + 6];
-              a1 += sm.red[(q * 16 + r) * 8 + 7];
-            }
-            sm.dRt[4 * j + 2 * half] += a0;
-            sm.dRt[4 * j + 2 * half + 1] += a1;
-          }
-        }
-      }
-      __syncthreads();
-      // (e) dH = dY Wvo^T
-      if (wv < 7) {
-        const int c0 = wv * 16;
-        f4 acc = {0, 0, 0, 0};
-        const T *Wvo = w.Wvo[layer];
-        Mma<T>::tile(acc, [&](int r, int k) { return sm.Hb[r * LDM + k]; },
-                     [&](int c, int k) { return (c0 + c < M) ? ldw(Wvo, (c0 + c) * M + k) : 0.f; }, M);
-        const int cc = c0 + acc_col();
-        if (cc < M)
-          for (int ii = 0; ii < 4; ++ii) sm.dHb[acc_row(ii) * LDM + cc] = acc[ii];
-      }
-      __syncthreads();
-      // (f) dA = dH G^T, then gate, weighted-softmax backward; wave wv owns column tile wv
-      {
-        const bool has = wv < nb;
-        const int k = wv * 16 + acc_col();
-        f4 dA = {0, 0, 0, 0};
-        if (has)
-          Mma<T>::tile(dA, [&](int r, int kk) { return sm.dHb[r * LDM + kk]; },
-                       [&](int c, int kk) { return sm.Gin[(wv * 16 + c) * LDM + kk]; }, M);
-        const bool kval = has && k < n;
-        float dP[4], P[4], dC[4];
-        for (int ii = 0; ii < 4; ++ii) {
-          const int r = acc_row(ii), j = jb * 16 + r;
-          const bool v = kval && j < n;
-          const float E = v ? sm.Eb[r * LDN + k] : 0.f;
-          const float gate = sm.e.rh[3 * j] * sm.e.rh[3 * k] + sm.e.rh[3 * j + 1] * sm.e.rh[3 * k + 1] +
-                             sm.e.rh[3 * j + 2] * sm.e.rh[3 * k + 2];
-          P[ii] = v ? sm.e.sw[k] * E : 0.f;
-          dP[ii] = v ? dA[ii] * gate : 0.f;
-          dC[ii] = v ? dA[ii] * P[ii] : 0.f;
-          const float rp = sum16(P[ii] * dP[ii]);
-          const float hx = sum16(dC[ii] * sm.e.rh[3 * k]);
-          const float hy = sum16(dC[ii] * sm.e.rh[3 * k + 1]);
-          const float hz = sum16(dC[ii] * sm.e.rh[3 * k + 2]);
-          if ((lane_id() & 15) == 0) {
-            sm.red[(wv * 16 + r) * 8 + 0] = rp;
-            sm.red[(wv * 16 + r) * 8 + 1] = hx;
-            sm.red[(wv * 16 + r) * 8 + 2] = hy;
-            sm.red[(wv * 16 + r) * 8 + 3] = hz;
-          }
-        }
-        __syncthreads();
-        float wsum = 0.f, cx = 0.f, cy = 0.f, cz = 0.f;
-        for (int ii = 0; ii < 4; ++ii) {
-          const int r = acc_row(ii), j = jb * 16 + r;
-          float rho = 0.f;
-          for (int q = 0; q < NW; ++q) rho += sm.red[(q * 16 + r) * 8 + 0];
-          const bool v = kval && j < n;
-          const float E = v ? sm.Eb[r * LDN + k] : 0.f;
-          const float W = v ? E * (dP[ii] - rho) : 0.f;
-          if (has) sm.Eb[r * LDN + k] = v ? sm.e.sw[k] * W : 0.f;  // dS (the 1/sqrt(d) lives in Wqk)
-          wsum += W;
-          cx += dC[ii] * sm.e.rh[3 * j];
-          cy += dC[ii] * sm.e.rh[3 * j + 1];
-          cz += dC[ii] * sm.e.rh[3 * j + 2];
-        }
-        wsum = sum_cols4(wsum);
-        cx = sum_cols4(cx);
-        cy = sum_cols4(cy);
-        cz = sum_cols4(cz);
-        if (has && lane_id() < 16) {
-          sm.dswa[k] += wsum;
-          sm.drh[3 * k] += cx;
-          sm.drh[3 * k + 1] += cy;
-          sm.drh[3 * k + 2] += cz;
-        }
-        __syncthreads();
-        if ((int)threadIdx.x < 16) {
-          const int r = threadIdx.x, j = jb * 16 + r;
-          float hx = 0.f, hy = 0.f, hz = 0.f;
-          for (int q = 0; q < NW; ++q) {
-            hx += sm.red[(q * 16 + r) * 8 + 1];
-            hy += sm.red[(q * 16 + r) * 8 + 2];
-            hz += sm.red[(q * 16 + r) * 8 + 3];
-          }
-          sm.drh[3 * j] += hx;
-          sm.drh[3 * j + 1] += hy;
-          sm.drh[3 * j + 2] += hz;
-        }
-      }
-      __syncthreads();
-      // (g) dU = dS G
-      if (wv < 7) {
-        const int c0 = wv * 16;
-        f4 acc = {0, 0, 0, 0};
-        Mma<T>::tile(acc, [&](int r, int kk) { return sm.Eb[r * LDN + kk]; },
-                     [&](int c, int kk) { return (c0 + c < M) ? sm.Gin[kk * LDM + c0 + c] : 0.f; }, NP);
-        const int cc = c0 + acc_col();
-        if (cc < M)
-          for (int ii = 0; ii < 4; ++ii) sm.Hb[acc_row(ii) * LDM + cc] = acc[ii];
-      }
-      __syncthreads();
-      // (h) rows of this block: dG += dU Wqk^T ; (i) columns owned by this wave:
-      // dG[k] += sum_j A_jk dH_j + dS_jk U_j, accumulated in registers until the layer ends
-      if (wv < 7) {
-        const int c0 = wv * 16;
-        f4 acc = {0, 0, 0, 0};
-        const T *Wqk = w.Wqk[layer];
-        Mma<T>::tile(acc, [&](int r, int kk) { return sm.Hb[r * LDM + kk]; },
-                     [&](int c, int kk) { return (c0 + c < M) ? ldw(Wqk, (c0 + c) * M + kk) : 0.f; }, M);
-        const int cc = c0 + acc_col();
-        if (cc < M)
-          for (int ii = 0; ii < 4; ++ii) sm.dG[(jb * 16 + acc_row(ii)) * LDM + cc] += acc[ii];
-      }
-      if (wv < nb) {
-        const int k0 = wv * 16;
-        for (int t = 0; t < 7; ++t) {
-          const int m0 = t * 16;
-          Mma<T>::tile(colacc[t], [&](int rr, int kk) { return sm.Ab[kk * LDN + k0 + rr]; },
-                       [&](int c, int kk) { return (m0 + c < M) ? sm.dHb[kk * LDM + m0 + c] : 0.f; }, 16);
-          Mma<T>::tile(colacc[t], [&](int rr, int kk) { return sm.Eb[kk * LDN + k0 + rr]; },
-                       [&](int c, int kk) { return (m0 + c < M) ? sm.Ub[kk * LDM + m0 + c] : 0.f; }, 16);
-        }
-      }
-      __syncthreads();
-    }
-    if (wv < nb) {
-      for (int t = 0; t < 7; ++t) {
-        const int cc = t * 16 + acc_col();
-        if (cc < M)
-          for (int ii = 0; ii < 4; ++ii) sm.dG[(wv * 16 + acc_row(ii)) * LDM + cc] += colacc[t][ii];
-      }
-    }
-    __syncthreads();
+  if (tid < 64) {
+    float acc = sm.dT[tid];
+    for (int ch = 0; ch < NB; ++ch) acc += part[64 * ch + tid];
+    sm.dT[tid] = acc;
   }
-
-  // ---- embedding and environment backward, per block of 16 rows
-  float *h1b = sm.Ub;   // h1            [16][E1]
-  float *t2b = sm.Ab;   // tanh of layer 2, then dpre2
-  float *h2b = sm.Hb;   // h2
-  float *p3b = sm.dHb;  // dpre3
-  float *rsb = sm.Eb;   // dG halves sum, then dh2
-  for (int jb = 0; jb < nb; ++jb) {
-    for (int q = threadIdx.x; q < 16 * E1; q += NTHREADS) {
-      const int r = q / E1, c = q % E1, j = jb * 16 + r;
-      h1b[r * LDM + c] = tanhf(sm.e.s[j] * w.w1s[c] + w.Bt[(ti * NTYPES + sm.e.tj[j]) * E1 + c]);
-    }
-    __syncthreads();
-    if (wv < 4) {
-      const int c0 = wv * 16;
-      f4 acc = {0, 0, 0, 0};
-      Mma<T>::tile(acc, [&](int r, int k) { return h1b[r * LDM + k]; },
-                   [&](int c, int k) { return (c0 + c < E2) ? ldw(w.W2T, (c0 + c) * E1 + k) : 0.f; }, E1);
-      const int col = c0 + acc_col();
-      if (col < E2)
-        for (int ii = 0; ii < 4; ++ii) {
-          const int r = acc_row(ii), j = jb * 16 + r;
-          const float t2 = tanhf(acc[ii] + w.b2[col]);
-          t2b[r * LDN + col] = t2;
-          h2b[r * LDM + col] = t2 + h1b[r * LDM + (col % E1)];
-          rsb[r * LDN + col] = sm.dG[j * LDM + col] + sm.dG[j * LDM + col + E2];
-        }
-    }
-    __syncthreads();
-    if (wv < 7) {
-      const int c0 = wv * 16;
-      f4 acc = {0, 0, 0, 0};
-      Mma<T>::tile(acc, [&](int r, int k) { return h2b[r * LDM + k]; },
-                   [&](int c, int k) { return (c0 + c < M) ? ldw(w.W3T, (c0 + c) * E2 + k) : 0.f; }, E2);
-      const int col = c0 + acc_col();
-      if (col < M)
-        for (int ii = 0; ii < 4; ++ii) {
-          const int r = acc_row(ii), j = jb * 16 + r;
-          const float t3 = tanhf(acc[ii] + w.b3[col]);
-          p3b[r * LDM + col] = sm.dG[j * LDM + col] * (1.f - t3 * t3);
-        }
-    }
-    __syncthreads();
-    // dh2 = dpre3 W3^T + (dG[:, :50] + dG[:, 50:]);  dpre2 = dh2 (1 - t2^2)
-    if (wv < 4) {
-      const int c0 = wv * 16;
-      f4 acc = {0, 0, 0, 0};
-      Mma<T>::tile(acc, [&](int r, int k) { return p3b[r * LDM + k]; },
-                   [&](int c, int k) { return (c0 + c < E2) ? ldw(w.W3, (c0 + c) * M + k) : 0.f; }, M);
-      const int col = c0 + acc_col();
-      if (col < E2)
-        for (int ii = 0; ii < 4; ++ii) {
-          const int r = acc_row(ii);
-          const float dh2 = acc[ii] + rsb[r * LDN + col];
-          rsb[r * LDN + col] = dh2;
-          const float t2 = t2b[r * LDN + col];
-          t2b[r * LDN + col] = dh2 * (1.f - t2 * t2);
-        }
-    }
-    __syncthreads();
-    // dh1 = dpre2 W2^T + (dh2[:, :25] + dh2[:, 25:]);  ds_emb = sum_c dh1 (1 - h1^2) w1s
-    if (wv < 2) {
-      const int c0 = wv * 16;
-      f4 acc = {0, 0, 0, 0};
-      Mma<T>::tile(acc, [&](int r, int k) { return t2b[r * LDN + k]; },
-                   [&](int c, int k) { return (c0 + c < E1) ? ldw(w.W2, (c0 + c) * E2 + k) : 0.f; }, E2);
-      const int col = c0 + acc_col();
-      for (int ii = 0; ii < 4; ++ii) {
-        const int r = acc_row(ii);
-        float v = 0.f;
-        if (col < E1) {
-          const float dh1 = acc[ii] + rsb[r * LDN + col] + rsb[r * LDN + col + E1];
-          const float h1 = h1b[r * LDM + col];
-          v = dh1 * (1.f - h1 * h1) * w.w1s[col];
-        }
-        const float p = sum16(v);
-        if ((lane_id() & 15) == 0) sm.red[(wv * 16 + r) * 8 + 0] = p;
+  __syncthreads();
+  const int j = 16 * jb + c;
+  float *row = sm.G + j * LDG;
+  F100 go = {};
+  if (act) {
+    F100 x, ga, be;
+    // the top layer's input: layer 0's output
+    load_block(x, gs + 1600 * jb);
+    normalise(x, ln_eps);
+    get_table(ga, w.gamma[0]);
+    get_table(be, w.beta[0]);
+#pragma unroll
+    for (int t = 0; t < 7; ++t) x[t] = ga[t] * x[t] + be[t];
+    put_row(row, x);
+    // dG = Rt dT^T / sel for its output, and dRt = G dT / sel
+    load_block(x, gs + GSAVE_LAYER + 1600 * jb);
+    normalise(x, ln_eps);
+    get_table(ga, w.gamma[1]);
+    get_table(be, w.beta[1]);
+    const float inv_sel = 1.f / (float)SEL;
+    const float sj = sm.e.s[j];
+    const float rt1 = sj * sm.e.rh[0][j], rt2 = sj * sm.e.rh[1][j], rt3 = sj * sm.e.rh[2][j];
+    f4 p = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 7; ++t)
+#pragma unroll
+      for (int k = 0; k < (t < 6 ? 4 : 1); ++k) {
+        const f4 d = ldf4(sm.dT + 4 * (t < 6 ? 16 * t + 4 * q + k : 96 + q));
+        go[t][k] = (sj * d[0] + rt1 * d[1] + rt2 * d[2] + rt3 * d[3]) * inv_sel;
+        p += (ga[t][k] * x[t][k] + be[t][k]) * d;
       }
+#pragma unroll
+    for (int a = 0; a < 4; ++a) p[a] = sumq(p[a]) * inv_sel;
+    if (q == 0) *reinterpret_cast<f4 *>(sm.dRt + 4 * j) = p;
+  }
+  __syncthreads();
+  layer_bwd<NB>(w, 1, sm, go, gs + GSAVE_LAYER, jb, tid, n, nb, pt.steps, ln_eps);
+  if (act) get_row(go, row);
+  __syncthreads();
+  if (act) {
+    S7 h1[1], t2[2], t3[4];
+    embed(w, sm.e.s[j], ti, sm.e.tj[j], h1, t2, t3);
+    put_embedding(row, h1, t2, t3);
+  }
+  __syncthreads();
+  layer_bwd<NB>(w, 0, sm, go, gs, jb, tid, n, nb, pt.steps, ln_eps);
+  __syncthreads();
+  // embedding backward and the pair gradients of the wave's tokens
+  if (act) {
+    S7 h1[1], t2[2], t3[4];
+    embed(w, sm.e.s[j], ti, sm.e.tj[j], h1, t2, t3);
+    S7 dh2[2], d[4];
+#pragma unroll
+    for (int g4 = 0; g4 < 4; ++g4)
+#pragma unroll
+      for (int r = 0; r < 7; ++r) {
+        const float v = slot_ok(r) ? row[25 * g4 + 4 * r + q] : 0.f;
+        d[g4][r] = v;
+        t3[g4][r] = v * (1.f - t3[g4][r] * t3[g4][r]);  // dpre3
+      }
+    emul<4, 2>(dh2, w.W3, t3);
+#pragma unroll
+    for (int g2 = 0; g2 < 2; ++g2)
+#pragma unroll
+      for (int r = 0; r < 7; ++r) {
+        dh2[g2][r] += d[g2][r] + d[g2 + 2][r];
+        t2[g2][r] = dh2[g2][r] * (1.f - t2[g2][r] * t2[g2][r]);  // dpre2
+      }
+    S7 dh1[1];
+    emul<2, 1>(dh1, w.W2, t2);
+    float ds = 0.f;
+#pragma unroll
+    for (int r = 0; r < 7; ++r) {
+      const float v = dh1[0][r] + dh2[0][r] + dh2[1][r];
+      if (slot_ok(r)) ds += v * (1.f - h1[0][r] * h1[0][r]) * w.w1s[4 * r + q];
     }
-    __syncthreads();
-    if ((int)threadIdx.x < 16) {
-      const int r = threadIdx.x, j = jb * 16 + r;
+    ds = sumq(ds);
+    if (q == 0 && j < SEL) {
       float4 out = make_float4(0.f, 0.f, 0.f, 0.f);
       if (j < n) {
-        const float ds_emb = sm.red[(0 * 16 + r) * 8] + sm.red[(1 * 16 + r) * 8];
-        out = pair_gradient(sm.e, j, ds_emb, sm.dRt + 4 * j, sm.drh + 3 * j, sm.dswa[j]);
+        const float h[3] = {sm.e.rh[0][j], sm.e.rh[1][j], sm.e.rh[2][j]};
+        out = pair_gradient(sm.e.s[j], sm.e.sw[j], sm.e.r[j], h, ds, sm.dRt + 4 * j, sm.drh + 3 * j, sm.dswa[j], rc, rcs);
       }
-      if (j < SEL) gout[(size_t)i * SEL + j] = out;
+      gout[(size_t)i * SEL + j] = out;
     }
-    __syncthreads();
   }
-  for (int j = NP + threadIdx.x; j < SEL; j += NTHREADS) gout[(size_t)i * SEL + j] = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int k = nb ? 16 * nb + tid : SEL; k < SEL; k += 64 * NB) gout[(size_t)i * SEL + k] = make_float4(0.f, 0.f, 0.f, 0.f);
+}
+
+// One workgroup per NA atoms of its instance's list; the 8-wave instance loops over its list
+// with at most one workgroup per CU.
+template <int NB, int NA>
+__global__ void __launch_bounds__(64 * NB * NA) __attribute__((amdgpu_waves_per_eu(NB == NB_SMALL ? 3 : 2)))
+k_desc_bwd(Weights<float> w, const double *__restrict__ X, const int *__restrict__ types, int natoms,
+           const int *__restrict__ idx, const int *__restrict__ cnt, const int *__restrict__ nlist,
+           const int *__restrict__ nnei, const Grid *__restrict__ grids, const int *__restrict__ sys_of, float rc, float rcs,
+           float ln_eps, const float *__restrict__ Gsave, const float *__restrict__ Tsave, const float *__restrict__ dD, float4 *__restrict__ gout) {
+  __shared__ SmemBwd<NB> smem[NA];
+  const int count = *cnt;
+  if constexpr (NB == NB_SMALL) {  // without the loop, which would keep its invariants in registers
+    const int b = blockIdx.x;
+    if (b * NA < count)
+      desc_bwd<NB, NA>(b, count, smem, w, X, types, natoms, idx, nlist, nnei, grids, sys_of, rc, rcs, ln_eps, Gsave, Tsave, dD, gout);
+  } else {
+    for (int b = blockIdx.x; b * NA < count; b += gridDim.x) {
+      desc_bwd<NB, NA>(b, count, smem, w, X, types, natoms, idx, nlist, nnei, grids, sys_of, rc, rcs, ln_eps, Gsave, Tsave, dD, gout);
+      __syncthreads();
+    }
+  }
 }
 
 }  // namespace
 
-template <typename T>
-void launch_descriptor_fwd(const Weights<T> &w, const Workspace &ws, const double *coords, const int *types, int n,
-                           int c0, int c1, float rc, float rcs, float ln_eps, hipStream_t st) {
-  hipLaunchKernelGGL(k_desc_fwd<T>, dim3(c1 - c0), dim3(NTHREADS), 0, st, w, coords, types, n, c0, ws.nlist, ws.nnei, ws.grids,
-                     ws.sys_of, rc, rcs, ln_eps, ws.Gsave, ws.Tsave, ws.D);
+// Two atoms share a workgroup where there is more than one atom per CU (256): the waves of
+// a workgroup go to the SIMDs in turn, so that 12 waves put three on each, while a second
+// workgroup of 6 waves does not fit beside a first (two SIMDs would hold four waves of 168
+// registers; 9,999 atoms that way: forward 2.73 ms, backward 6.9 ms, against 2.10 and
+// 4.85 ms in pairs).  Fewer atoms run one to a CU.
+constexpr int PAIR_FROM = 257;
+constexpr int NCU = 256;
+
+// Lists the centres c0 .. c1-1 for the two instances, one addition per wave and instance
+// (one per atom, in the neighbour search, cost 30 us at 3,000 atoms).  The order only
+// changes scheduling.
+__global__ void __launch_bounds__(256) k_class_lists(const int *__restrict__ nnei, int c0, int c1, int *__restrict__ idx,
+                                                     int *__restrict__ cnt, int cap) {
+  const int i = c0 + blockIdx.x * 256 + threadIdx.x;
+  const int l = lane_id();
+  const bool small = i < c1 && nnei[i] <= 16 * NB_SMALL;
+  for (int cls = 0; cls < 2; ++cls) {
+    const unsigned long long mask = __ballot(i < c1 && small == (cls == 0));
+    if (!mask) continue;
+    const int first = __ffsll(mask) - 1;
+    int base = 0;
+    if (l == first) base = atomicAdd(cnt + cls, __popcll(mask));
+    base = __shfl(base, first);
+    const int pos = base + __popcll(mask & ((1ull << l) - 1ull));
+    if ((mask >> l & 1ull) && pos < cap) idx[(size_t)cls * cap + pos] = i;
+  }
 }
 
-template <typename T>
-void launch_descriptor_bwd(const Weights<T> &w, const Workspace &ws, const double *coords, const int *types, int n,
-                           int c0, int c1, float rc, float rcs, float ln_eps, hipStream_t st) {
-  hipLaunchKernelGGL(k_desc_bwd<T>, dim3(c1 - c0), dim3(NTHREADS), 0, st, w, coords, types, n, c0, ws.nlist, ws.nnei, ws.grids,
-                     ws.sys_of, rc, rcs, ln_eps, ws.Gsave, ws.Tsave, ws.D, ws.g);
+// launch(kernel, workgroups, threads, list, stream) for the instances that may have atoms.
+template <class Small, class Pair, class Large, class Launch>
+void launch_instances(const Workspace &ws, int ncen, Small small, Pair pair, Large large, hipStream_t st,
+                      const Launch &launch) {
+  (void)hipEventRecord(ws.fork_ev, st);
+  (void)hipStreamWaitEvent(ws.side, ws.fork_ev, 0);
+  launch(large, std::min(ncen, NCU), 64 * 8, 1, ws.side);
+  if (ncen >= PAIR_FROM) launch(pair, (ncen + 1) / 2, 64 * 2 * NB_SMALL, 0, st);
+  else launch(small, ncen, 64 * NB_SMALL, 0, st);
+  (void)hipEventRecord(ws.join_ev, ws.side);
+  (void)hipStreamWaitEvent(st, ws.join_ev, 0);
 }
 
-template void launch_descriptor_fwd<float>(const Weights<float> &, const Workspace &, const double *, const int *,
-                                           int, int, int, float, float, float, hipStream_t);
-template void launch_descriptor_bwd<float>(const Weights<float> &, const Workspace &, const double *, const int *,
-                                           int, int, int, float, float, float, hipStream_t);
+void launch_descriptor_fwd(const Weights<float> &w, const Workspace &ws, const double *coords, const int *types, int n,
+                           int c0, int c1, float rc, float rcs, float ln_eps, hipStream_t st) {
+  hipLaunchKernelGGL(k_class_lists, dim3((c1 - c0 + 255) / 256), dim3(256), 0, st, ws.nnei, c0, c1, ws.bidx, ws.bcnt,
+                     (int)ws.cap);
+  launch_instances(ws, c1 - c0, k_desc_fwd<NB_SMALL, 1>, k_desc_fwd<NB_SMALL, 2>, k_desc_fwd<8, 1>, st,
+                   [&](auto kernel, int groups, int threads, int list, hipStream_t s) {
+    hipLaunchKernelGGL(kernel, dim3(groups), dim3(threads), 0, s, w, coords, types, n, ws.bidx + list * ws.cap,
+                       ws.bcnt + list, ws.nlist, ws.nnei, ws.grids, ws.sys_of, rc, rcs, ln_eps, ws.Gsave, ws.Tsave, ws.D);
+  });
+}
+
+void launch_descriptor_bwd(const Weights<float> &w, const Workspace &ws, const double *coords, const int *types, int n,
+                           int c0, int c1, float rc, float rcs, float ln_eps, hipStream_t st) {
+  launch_instances(ws, c1 - c0, k_desc_bwd<NB_SMALL, 1>, k_desc_bwd<NB_SMALL, 2>, k_desc_bwd<8, 1>, st,
+                   [&](auto kernel, int groups, int threads, int list, hipStream_t s) {
+    hipLaunchKernelGGL(kernel, dim3(groups), dim3(threads), 0, s, w, coords, types, n, ws.bidx + list * ws.cap,
+                       ws.bcnt + list, ws.nlist, ws.nnei, ws.grids, ws.sys_of, rc, rcs, ln_eps, ws.Gsave, ws.Tsave, ws.D, ws.g);
+  });
+}
 
 }  // namespace dp

@@ -68,26 +68,6 @@ __device__ inline void build_envb(EnvB &e, const double *__restrict__ X, const i
   }
 }
 
-// g = dE_i/dDelta_ij of token j from the gradients reaching s (ds_emb, through Rt),
-// rhat (drh, through Rt and the gate) and sw (dswa, through the softmax weights); the
-// switch derivative is formed here from r.
-__device__ __forceinline__ float4 pair_gradient_b(const EnvB &e, int j, float ds_emb, const float *dRt,
-                                                  const float *drh, float dswa, float rc, float rcs) {
-  const float s = e.s[j], sw = e.sw[j], rr = e.r[j];
-  const float hx = e.rh[3 * j], hy = e.rh[3 * j + 1], hz = e.rh[3 * j + 2];
-  const float u = (rr - rcs) / (rc - rcs);
-  const float dsw = (rr >= rcs && rr < rc) ? -30.f * u * u * (1.f - u) * (1.f - u) / (rc - rcs) : 0.f;
-  const float ds = ds_emb + dRt[0] + dRt[1] * hx + dRt[2] * hy + dRt[3] * hz;
-  const float gx = drh[0] + s * dRt[1];
-  const float gy = drh[1] + s * dRt[2];
-  const float gz = drh[2] + s * dRt[3];
-  const float dswt = dswa + ds / rr;
-  const float dr = -ds * sw / (rr * rr) + dswt * dsw;
-  const float proj = gx * hx + gy * hy + gz * hz;
-  return make_float4((gx - proj * hx) / rr + dr * hx, (gy - proj * hy) / rr + dr * hy, (gz - proj * hz) / rr + dr * hz,
-                     0.f);
-}
-
 #ifdef DP_BF16_OPAQUE_LANE
 __device__ __forceinline__ int lane() {
   int l = lane_id();

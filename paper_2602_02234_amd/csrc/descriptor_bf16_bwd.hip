@@ -574,7 +574,9 @@ k_desc_bwd_b16(Tables w, WeightsB16 wp, const double *__restrict__ X, const int 
       const int j = jb * 16 + 4 * q + ii;
       if (cl == ii && j < SEL) {
         float4 out = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (j < n) out = pair_gradient_b(sm.e, j, dse[ii], sm.dRt + 4 * j, sm.drh + 3 * j, sm.dswa[j], rc, rcs);
+        if (j < n)
+          out = pair_gradient(sm.e.s[j], sm.e.sw[j], sm.e.r[j], sm.e.rh + 3 * j, dse[ii], sm.dRt + 4 * j, sm.drh + 3 * j,
+                              sm.dswa[j], rc, rcs);
         gout[(size_t)i * SEL + j] = out;
       }
     }

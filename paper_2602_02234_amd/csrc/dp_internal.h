@@ -61,13 +61,15 @@ struct Tables {
   const double *ebias[MAXH];  // [NTYPES]
 };
 
-// GEMM operands of the float32 path, T = float, row-major as named.
+// GEMM operands of the float32 path, T = float.  The descriptor's are in the MFMA fragment
+// order its kernels read (see wmul and emul there), named by the matrix whose rows are the
+// outputs; the fitting net's are row-major.
 template <typename T> struct Weights : Tables {
-  const T *W2T;       // [E2][E1]
+  const T *W2T;       // [E2][E1], groups of 25
   const T *W2;        // [E1][E2]
   const T *W3T;       // [M][E2]
   const T *W3;        // [E2][M]
-  const T *WqkT[NATTN];  // [M][M]  (WQ WK^T / sqrt(d))^T
+  const T *WqkT[NATTN];  // [M][M]  (WQ WK^T / sqrt(d))^T, 7 tiles of 1600 values
   const T *Wqk[NATTN];   // [M][M]
   const T *WvoT[NATTN];  // [M][M]  (WV WO)^T
   const T *Wvo[NATTN];   // [M][M]
@@ -126,7 +128,7 @@ struct Workspace {
   int *nnei = nullptr;        // [cap]
   float *Gsave = nullptr;     // [cap][NATTN][GSAVE_LAYER]  inputs of each attention layer
   float *Tsave = nullptr;     // [cap][M][4]
-  int *bidx = nullptr;        // [2][cap]  atoms of each backward kernel instance (bf16 path)
+  int *bidx = nullptr;        // [2][cap]  atoms of each descriptor kernel instance
   int *bcnt = nullptr;        // [2]
   int *done = nullptr;        // [2 cap_sys + 1]  completion counters (the cell pass's workgroup counter
                               // at [2 cap_sys]); cleared at the start of each step
@@ -140,7 +142,7 @@ struct Workspace {
   unsigned *flags = nullptr;  // [4] status words: flags, overflow count, rev misses, spare
   unsigned *flags_host = nullptr;  // pinned mirror
   double *gE = nullptr;       // [1] scale of the backward pass
-  hipStream_t side = nullptr;  // second stream of the bf16 backward (its instances run side by side)
+  hipStream_t side = nullptr;  // second stream: the two descriptor instances run side by side
   hipEvent_t fork_ev = nullptr, join_ev = nullptr;
   uint64_t gen = 0;           // bumped on every (re)allocation: graphs captured before it are stale
 };
@@ -251,8 +253,7 @@ void launch_skin_check(const Workspace &ws, const double *coords, const int *typ
 void launch_skin_ref(const Workspace &ws, const double *coords, int n, hipStream_t st);
 // The per-centre launchers run over the centre atoms c0 .. c1-1, reading the coordinates
 // and types of all n atoms as neighbours.
-template <typename T>
-void launch_descriptor_fwd(const Weights<T> &w, const Workspace &ws, const double *coords, const int *types,
+void launch_descriptor_fwd(const Weights<float> &w, const Workspace &ws, const double *coords, const int *types,
                            int n, int c0, int c1, float rc, float rcs, float ln_eps, hipStream_t st);
 // The fitting net over the first n atoms (E_i, and dE/dD over D when backward).
 template <typename T>
@@ -266,8 +267,7 @@ void launch_descriptor_bwd_b16(const Tables &w, const WeightsB16 &wp, const Work
                                float rcs, float ln_eps, hipStream_t st);
 void launch_fitting_b16(const Tables &w, const WeightsB16 &wp, const Workspace &ws, const int *types, int c0,
                         int c1, bool backward, hipStream_t st);
-template <typename T>
-void launch_descriptor_bwd(const Weights<T> &w, const Workspace &ws, const double *coords, const int *types,
+void launch_descriptor_bwd(const Weights<float> &w, const Workspace &ws, const double *coords, const int *types,
                            int n, int c0, int c1, float rc, float rcs, float ln_eps, hipStream_t st);
 // Forces of all n atoms and the per-atom virial partials.  skin_rows: the step reused skin
 // lists (one-sided pairs are then found through the skin rows, else through the cell list
