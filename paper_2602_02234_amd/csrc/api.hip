@@ -125,14 +125,6 @@ struct Packer {
 };
 
 std::vector<float> tof(const std::vector<double> &v) { return std::vector<float>(v.begin(), v.end()); }
-// [rows][cols] -> [cols][rows]
-std::vector<float> transpose(const std::vector<double> &v, int rows, int cols) {
-  std::vector<float> o((size_t)rows * cols);
-  for (int r = 0; r < rows; ++r)
-    for (int c = 0; c < cols; ++c) o[(size_t)c * rows + r] = (float)v[(size_t)r * cols + c];
-  return o;
-}
-
 // Offsets of the pieces of the weight image, in the order the binders take them.
 struct Image {
   Packer pk;
@@ -237,13 +229,26 @@ void pack_weights(const HostModel &h, int pr, Image &im) {
       f.push_back(pk.addf(frag100([&](int c, int k) { return VO[a][(size_t)k * M + c]; })));
       f.push_back(pk.addf(frag100([&](int c, int k) { return VO[a][(size_t)c * M + k]; })));
     }
+    // the fitting net's: output tile t, k step s of 16: lane l holds output 16 t + l % 16, four
+    // k from 16 s + 4 (l / 16) on; transposed: W is [K][R], else [R][K]
+    auto frag16 = [](const std::vector<double> &W, int R, int K, bool transposed) {
+      std::vector<float> v((size_t)R * K);
+      for (int t = 0; t < R / 16; ++t)
+        for (int s = 0; s < K / 16; ++s)
+          for (int l = 0; l < 64; ++l)
+            for (int e = 0; e < 4; ++e) {
+              const int o = 16 * t + l % 16, k = 16 * s + 4 * (l / 16) + e;
+              v[(((size_t)t * (K / 16) + s) * 64 + l) * 4 + e] = (float)(transposed ? W[(size_t)k * R + o] : W[(size_t)o * K + k]);
+            }
+      return v;
+    };
     for (int k = 0; k < h.nheads; ++k) {
-      f.push_back(pk.addf(transpose(h.F1[k], ND, FH)));
-      f.push_back(pk.addf(tof(h.F1[k])));
-      f.push_back(pk.addf(transpose(h.F2[k], FH, FH)));
-      f.push_back(pk.addf(tof(h.F2[k])));
-      f.push_back(pk.addf(transpose(h.F3[k], FH, FH)));
-      f.push_back(pk.addf(tof(h.F3[k])));
+      f.push_back(pk.addf(frag16(h.F1[k], FH, ND, true)));
+      f.push_back(pk.addf(frag16(h.F1[k], ND, FH, false)));
+      f.push_back(pk.addf(frag16(h.F2[k], FH, FH, true)));
+      f.push_back(pk.addf(frag16(h.F2[k], FH, FH, false)));
+      f.push_back(pk.addf(frag16(h.F3[k], FH, FH, true)));
+      f.push_back(pk.addf(frag16(h.F3[k], FH, FH, false)));
     }
     return;
   }
@@ -445,7 +450,7 @@ int build_weights(dp_model *m, const HostModel &h) {
 
 void free_ws(Workspace &ws) {
   void *ps[] = {ws.cell_of, ws.cell_count, ws.cell_start, ws.cell_cursor, ws.cell_atoms, ws.nlist, ws.nnei, ws.done,
-                ws.Gsave, ws.Tsave, ws.D, ws.Ei, ws.Eh, ws.Ehsys, ws.g, ws.vpart, ws.red, ws.grids, ws.sys_off, ws.sys_of, ws.slist,
+                ws.Gsave, ws.Tsave, ws.fit, ws.Ei, ws.Eh, ws.Ehsys, ws.g, ws.vpart, ws.red, ws.grids, ws.sys_off, ws.sys_of, ws.slist,
                 ws.snnei, ws.xref, ws.flags, ws.gE, ws.bidx, ws.bcnt};
   for (void *p : ps)
     if (p) (void)hipFree(p);
@@ -463,7 +468,7 @@ size_t ws_bytes_per_atom(int prec) {
   size_t b = 4 * sizeof(int)                              // cell_of, cell_atoms, nnei, sys_of
              + (size_t)SEL * sizeof(int)                  // nlist
              + (size_t)M * 4 * sizeof(float)              // Tsave
-             + (size_t)ND * sizeof(float)                 // D
+             + (size_t)ND * sizeof(float)                 // fit
              + (1 + MAXH) * sizeof(double)                // Ei, Eh
              + (size_t)SEL * sizeof(float4)               // g
              + 9 * sizeof(double)                         // vpart
@@ -508,12 +513,12 @@ int ensure_ws(Workspace &ws, int prec, int64_t n, int nsys, bool skin, bool list
   }
   if (n > ws.cap) {
     const int64_t cap = std::max<int64_t>(n, ws.cap + ws.cap / 4);
-    void *ps[] = {ws.cell_of, ws.cell_atoms, ws.nlist, ws.nnei, ws.Gsave, ws.Tsave, ws.D, ws.Ei, ws.Eh, ws.g,
+    void *ps[] = {ws.cell_of, ws.cell_atoms, ws.nlist, ws.nnei, ws.Gsave, ws.Tsave, ws.fit, ws.Ei, ws.Eh, ws.g,
                   ws.vpart, ws.sys_of, ws.slist, ws.snnei, ws.xref, ws.bidx};
     for (void *p : ps)
       if (p) (void)hipFree(p);
     ws.cell_of = ws.cell_atoms = ws.nlist = ws.nnei = ws.sys_of = ws.slist = ws.snnei = ws.bidx = nullptr;
-    ws.Gsave = ws.Tsave = ws.D = nullptr;
+    ws.Gsave = ws.Tsave = ws.fit = nullptr;
     ws.Ei = ws.Eh = ws.vpart = ws.xref = nullptr;
     ws.g = nullptr;
     ws.cap = 0;
@@ -526,8 +531,8 @@ int ensure_ws(Workspace &ws, int prec, int64_t n, int nsys, bool skin, bool list
       HIP_TRY(hipMalloc(&ws.Gsave, cap * (size_t)NATTN * GSAVE_LAYER * sizeof(float)));
       HIP_TRY(hipMalloc(&ws.Tsave, cap * (size_t)M * 4 * sizeof(float)));
       HIP_TRY(hipMalloc(&ws.bidx, 2 * cap * sizeof(int)));
-      HIP_TRY(hipMalloc(&ws.D, (cap + 16) * (size_t)ND * sizeof(float)));  // 16 spare rows for batched readers
-      HIP_TRY(hipMemset(ws.D, 0, (cap + 16) * (size_t)ND * sizeof(float)));
+      HIP_TRY(hipMalloc(&ws.fit, (cap + 16) * (size_t)ND * sizeof(float)));  // 16 spare rows for batched readers
+      HIP_TRY(hipMemset(ws.fit, 0, (cap + 16) * (size_t)ND * sizeof(float)));
       HIP_TRY(hipMalloc(&ws.Eh, cap * MAXH * sizeof(double)));
     }
     HIP_TRY(hipMalloc(&ws.Ei, cap * sizeof(double)));
@@ -588,7 +593,7 @@ size_t carve_ws(Workspace &ws, unsigned char *base, int64_t cap) {
   take(ws.Gsave, c * NATTN * GSAVE_LAYER * sizeof(float));
   take(ws.Tsave, c * M * 4 * sizeof(float));
   take(ws.bidx, 2 * c * sizeof(int));
-  take(ws.D, (c + 16) * ND * sizeof(float));
+  take(ws.fit, c * ND * sizeof(float));
   take(ws.Ei, c * sizeof(double));
   take(ws.Eh, c * MAXH * sizeof(double));
   take(ws.Ehsys, MAXH * sizeof(double));
@@ -763,7 +768,7 @@ int enqueue_step(dp_model *m, Workspace &ws, const StepArgs &a, hipStream_t st, 
   if (m->prec == DP_BF16)
     launch_fitting_b16(m->wf, m->wp, ws, a.types, cb, ce, bwd, st);
   else
-    launch_fitting<float>(m->wf, ws, a.types, cb, ce, bwd, st);
+    launch_fitting(m->wf, ws, a.types, cb, ce, bwd, st);
   if (pm) mark(pm, 3, st);
   // energies over the centre atoms (every atom, or the first nc of one system with ghosts)
   const int *eoff = nc < n ? ws.sys_off + 2 : ws.sys_off;
@@ -777,7 +782,7 @@ int enqueue_step(dp_model *m, Workspace &ws, const StepArgs &a, hipStream_t st, 
     if (pm) mark(pm, 5, st);
     if (a.last_chunk) {
       double *F = a.forces;
-      if (!F) F = (double *)ws.D;  // forces not requested: park them in the (now free) descriptor buffer
+      if (!F) F = (double *)ws.fit;  // forces not requested: park them in the (now free) fitting rows
       launch_forces(ws, a.X, n, nullptr, F, a.lists == LISTS_SKIN_REUSE, nc < n, st);
       launch_reduce(ws, eoff, a.nsys, a.energy, a.atom_energy, a.virial, m->wf.nheads, st);
     }
@@ -1375,7 +1380,7 @@ int dp_backward_device(dp_model *m, const double *d_grad_energy, double *d_grad_
   // the energy-only pass left D, the lists and the grid in place; rerun the fitting
   // net with its backward
   if (m->prec == DP_FP32) {
-    launch_fitting<float>(m->wf, ws, m->fwd_types, 0, n, true, st);
+    launch_fitting(m->wf, ws, m->fwd_types, 0, n, true, st);
     launch_descriptor_bwd(m->wf, ws, m->fwd_coords, m->fwd_types, n, 0, n, rc, rcs, eps, st);
   } else {
     launch_fitting_b16(m->wf, m->wp, ws, m->fwd_types, 0, n, true, st);

@@ -363,7 +363,6 @@ __device__ __forceinline__ f4 gate4(const EnvF<NB> &e, int kt, const float (&h)[
 template <int NB> struct SmemFwd {
   float G[16 * NB * LDG] __attribute__((aligned(16)));
   float part[NB][M * 4] __attribute__((aligned(16)));
-  float T[M * 4];
   EnvF<NB> e;
 };
 
@@ -397,7 +396,7 @@ template <int NB, int NA>
 __device__ __forceinline__ void desc_fwd(int blk, int count, SmemFwd<NB> *smem, Weights<float> w, const double *__restrict__ X, const int *__restrict__ types, int natoms, const int *__restrict__ idx,
            const int *__restrict__ nlist, const int *__restrict__ nnei, const Grid *__restrict__ grids,
            const int *__restrict__ sys_of, float rc, float rcs, float ln_eps, float *__restrict__ Gsave,
-           float *__restrict__ Tsave, float *__restrict__ D) {
+           float *__restrict__ Tsave) {
   const Part<NB, NA> pt(blk, idx, count, nnei);
   SmemFwd<NB> &sm = smem[pt.half];
   const int i = pt.i, n = pt.n, nb = pt.nb, jb = pt.jb, tid = pt.tid;
@@ -469,18 +468,10 @@ __device__ __forceinline__ void desc_fwd(int blk, int count, SmemFwd<NB> *smem, 
         if (t < 6 || c < 4) *reinterpret_cast<f4 *>(sm.part[jb] + 4 * (16 * t + c)) = acc[t];
   }
   __syncthreads();
-  for (int k = tid; k < M * 4; k += 64 * NB) {
+  for (int k = tid; k < (nb ? M * 4 : 0); k += 64 * NB) {
     float acc = 0.f;
     for (int v = 0; v < nb; ++v) acc += sm.part[v][k];
-    acc *= 1.f / (float)SEL;
-    sm.T[k] = acc;
-    if (nb) Tsave[(size_t)i * M * 4 + k] = acc;
-  }
-  __syncthreads();
-  for (int k = tid; k < (nb ? ND : 0); k += 64 * NB) {
-    const int m = k / M2, a = k % M2;
-    const float *tm = sm.T + 4 * m, *ta = sm.T + 4 * a;
-    D[(size_t)i * ND + k] = tm[0] * ta[0] + tm[1] * ta[1] + tm[2] * ta[2] + tm[3] * ta[3];
+    Tsave[(size_t)i * M * 4 + k] = acc * (1.f / (float)SEL);
   }
 }
 
@@ -491,16 +482,16 @@ __global__ void __launch_bounds__(64 * NB * NA) __attribute__((amdgpu_waves_per_
 k_desc_fwd(Weights<float> w, const double *__restrict__ X, const int *__restrict__ types, int natoms,
            const int *__restrict__ idx, const int *__restrict__ cnt, const int *__restrict__ nlist,
            const int *__restrict__ nnei, const Grid *__restrict__ grids, const int *__restrict__ sys_of, float rc, float rcs,
-           float ln_eps, float *__restrict__ Gsave, float *__restrict__ Tsave, float *__restrict__ D) {
+           float ln_eps, float *__restrict__ Gsave, float *__restrict__ Tsave) {
   __shared__ SmemFwd<NB> smem[NA];
   const int count = *cnt;
   if constexpr (NB == NB_SMALL) {  // without the loop, which would keep its invariants in registers
     const int b = blockIdx.x;
     if (b * NA < count)
-      desc_fwd<NB, NA>(b, count, smem, w, X, types, natoms, idx, nlist, nnei, grids, sys_of, rc, rcs, ln_eps, Gsave, Tsave, D);
+      desc_fwd<NB, NA>(b, count, smem, w, X, types, natoms, idx, nlist, nnei, grids, sys_of, rc, rcs, ln_eps, Gsave, Tsave);
   } else {
     for (int b = blockIdx.x; b * NA < count; b += gridDim.x) {
-      desc_fwd<NB, NA>(b, count, smem, w, X, types, natoms, idx, nlist, nnei, grids, sys_of, rc, rcs, ln_eps, Gsave, Tsave, D);
+      desc_fwd<NB, NA>(b, count, smem, w, X, types, natoms, idx, nlist, nnei, grids, sys_of, rc, rcs, ln_eps, Gsave, Tsave);
       __syncthreads();
     }
   }
@@ -712,7 +703,7 @@ template <int NB, int NA>
 __device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB> *smem, Weights<float> w, const double *__restrict__ X, const int *__restrict__ types, int natoms, const int *__restrict__ idx,
            const int *__restrict__ nlist, const int *__restrict__ nnei, const Grid *__restrict__ grids,
            const int *__restrict__ sys_of, float rc, float rcs, float ln_eps, const float *__restrict__ Gsave,
-           const float *__restrict__ Tsave, const float *__restrict__ dD, float4 *__restrict__ gout) {
+           const float *__restrict__ fit, float4 *__restrict__ gout) {
   const Part<NB, NA> pt(blk, idx, count, nnei);
   SmemBwd<NB> &sm = smem[pt.half];
   const int i = pt.i, n = pt.n, nb = pt.nb, jb = pt.jb, tid = pt.tid;
@@ -726,33 +717,12 @@ __device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB> *smem, 
     sm.dswa[k] = 0.f;
     for (int a = 0; a < 3; ++a) sm.drh[3 * k + a] = 0.f;
   }
-  // dT from dE/dD (D = T T_<16^T): dT_m = sum_a dD_ma T_a + [m < 16] sum_m' dD_m'm T_m'; G is
-  // free until the layer input is put there
-  float *T = sm.G, *dDi = T + M * 4, *part = dDi + ND;
-  static_assert(M * 4 + ND + 64 * NB <= 16 * NB * LDG, "dT staging fits in G");
-  for (int k = tid; k < M; k += 64 * NB)
-    *reinterpret_cast<f4 *>(T + 4 * k) = ldf4(Tsave + ((size_t)i * M + k) * 4);
-  for (int k = tid; k < ND / 4; k += 64 * NB)
-    *reinterpret_cast<f4 *>(dDi + 4 * k) = ldf4(dD + (size_t)i * ND + 4 * k);
-  __syncthreads();
+  const float *dTi = fit + (size_t)i * ND;
   for (int k = tid; k < M * 4; k += 64 * NB) {
-    const int m = k >> 2, a4 = k & 3;
-    float acc = 0.f;
-    for (int a = 0; a < M2; ++a) acc += dDi[m * M2 + a] * T[4 * a + a4];
-    sm.dT[k] = acc;
-  }
-  {
-    constexpr int CH = (M + NB - 1) / NB;
-    const int k = tid & 63, ch = tid >> 6, m = k >> 2, a4 = k & 3;
-    float acc = 0.f;
-    for (int mm = ch * CH; mm < min(M, (ch + 1) * CH); ++mm) acc += dDi[mm * M2 + m] * T[4 * mm + a4];
-    part[tid] = acc;
-  }
-  __syncthreads();
-  if (tid < 64) {
-    float acc = sm.dT[tid];
-    for (int ch = 0; ch < NB; ++ch) acc += part[64 * ch + tid];
-    sm.dT[tid] = acc;
+    float v = dTi[FIT_DT + k];
+    if (k < 4 * M2)
+      for (int p = 0; p < FIT_NPART; ++p) v += dTi[FIT_PART + 4 * M2 * p + k];
+    sm.dT[k] = v;
   }
   __syncthreads();
   const int j = 16 * jb + c;
@@ -850,16 +820,16 @@ __global__ void __launch_bounds__(64 * NB * NA) __attribute__((amdgpu_waves_per_
 k_desc_bwd(Weights<float> w, const double *__restrict__ X, const int *__restrict__ types, int natoms,
            const int *__restrict__ idx, const int *__restrict__ cnt, const int *__restrict__ nlist,
            const int *__restrict__ nnei, const Grid *__restrict__ grids, const int *__restrict__ sys_of, float rc, float rcs,
-           float ln_eps, const float *__restrict__ Gsave, const float *__restrict__ Tsave, const float *__restrict__ dD, float4 *__restrict__ gout) {
+           float ln_eps, const float *__restrict__ Gsave, const float *__restrict__ fit, float4 *__restrict__ gout) {
   __shared__ SmemBwd<NB> smem[NA];
   const int count = *cnt;
   if constexpr (NB == NB_SMALL) {  // without the loop, which would keep its invariants in registers
     const int b = blockIdx.x;
     if (b * NA < count)
-      desc_bwd<NB, NA>(b, count, smem, w, X, types, natoms, idx, nlist, nnei, grids, sys_of, rc, rcs, ln_eps, Gsave, Tsave, dD, gout);
+      desc_bwd<NB, NA>(b, count, smem, w, X, types, natoms, idx, nlist, nnei, grids, sys_of, rc, rcs, ln_eps, Gsave, fit, gout);
   } else {
     for (int b = blockIdx.x; b * NA < count; b += gridDim.x) {
-      desc_bwd<NB, NA>(b, count, smem, w, X, types, natoms, idx, nlist, nnei, grids, sys_of, rc, rcs, ln_eps, Gsave, Tsave, dD, gout);
+      desc_bwd<NB, NA>(b, count, smem, w, X, types, natoms, idx, nlist, nnei, grids, sys_of, rc, rcs, ln_eps, Gsave, fit, gout);
       __syncthreads();
     }
   }
@@ -915,7 +885,7 @@ void launch_descriptor_fwd(const Weights<float> &w, const Workspace &ws, const d
   launch_instances(ws, c1 - c0, k_desc_fwd<NB_SMALL, 1>, k_desc_fwd<NB_SMALL, 2>, k_desc_fwd<8, 1>, st,
                    [&](auto kernel, int groups, int threads, int list, hipStream_t s) {
     hipLaunchKernelGGL(kernel, dim3(groups), dim3(threads), 0, s, w, coords, types, n, ws.bidx + list * ws.cap,
-                       ws.bcnt + list, ws.nlist, ws.nnei, ws.grids, ws.sys_of, rc, rcs, ln_eps, ws.Gsave, ws.Tsave, ws.D);
+                       ws.bcnt + list, ws.nlist, ws.nnei, ws.grids, ws.sys_of, rc, rcs, ln_eps, ws.Gsave, ws.Tsave);
   });
 }
 
@@ -924,7 +894,7 @@ void launch_descriptor_bwd(const Weights<float> &w, const Workspace &ws, const d
   launch_instances(ws, c1 - c0, k_desc_bwd<NB_SMALL, 1>, k_desc_bwd<NB_SMALL, 2>, k_desc_bwd<8, 1>, st,
                    [&](auto kernel, int groups, int threads, int list, hipStream_t s) {
     hipLaunchKernelGGL(kernel, dim3(groups), dim3(threads), 0, s, w, coords, types, n, ws.bidx + list * ws.cap,
-                       ws.bcnt + list, ws.nlist, ws.nnei, ws.grids, ws.sys_of, rc, rcs, ln_eps, ws.Gsave, ws.Tsave, ws.D, ws.g);
+                       ws.bcnt + list, ws.nlist, ws.nnei, ws.grids, ws.sys_of, rc, rcs, ln_eps, ws.Gsave, ws.fit, ws.g);
   });
 }
 

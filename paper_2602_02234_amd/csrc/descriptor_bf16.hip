@@ -1,7 +1,6 @@
 // Forward descriptor kernel of the bfloat16 path: one workgroup (8 waves) per atom.
 // Environment, type-embedded embedding net (its weights staged in LDS), two attention
-// layers (their weights read from L2 in MFMA fragment order), T = G^T Rt / sel and
-// D = T T_<16^T; the input rows of each attention layer are saved for the backward.
+// layers (their weights read from L2 in MFMA fragment order), T = G^T Rt / sel; the input rows of each attention layer are saved for the backward.
 #include "descriptor_bf16.h"
 
 namespace dp {
@@ -19,7 +18,7 @@ __global__ void __launch_bounds__(NWF * 64)
 k_desc_fwd_b16(Tables w, WeightsB16 wp, const double *__restrict__ X, const int *__restrict__ types, int natoms, int c0,
                const int *__restrict__ nlist, const int *__restrict__ nnei, const Grid *__restrict__ grids, const int *__restrict__ sys_of,
                float rc, float rcs, float ln_eps, float *__restrict__ Gsave, float *__restrict__ Tsave,
-               float *__restrict__ D, int *__restrict__ bidx, int *__restrict__ bcnt, int cap) {
+               int *__restrict__ bidx, int *__restrict__ bcnt, int cap) {
   __shared__ SmemF16 sm;
   const int i = c0 + blockIdx.x;
   const Grid g = grids[sys_of[i]];
@@ -83,19 +82,10 @@ k_desc_fwd_b16(Tables w, WeightsB16 wp, const double *__restrict__ X, const int 
       }
   }
   __syncthreads();
-  float *T = (float *)sm.GbT;
   for (int x = threadIdx.x; x < M * 4; x += NWF * 64) {
     float acc = 0.f;
     for (int v = 0; v < nb; ++v) acc += ((float *)sm.stg[v])[x];
-    acc *= 1.f / (float)SEL;
-    T[x] = acc;
-    Tsave[(size_t)i * M * 4 + x] = acc;
-  }
-  __syncthreads();
-  for (int x = threadIdx.x; x < ND; x += NWF * 64) {
-    const int m = x / M2, a = x % M2;
-    const float *tm = T + 4 * m, *ta = T + 4 * a;
-    D[(size_t)i * ND + x] = tm[0] * ta[0] + tm[1] * ta[1] + tm[2] * ta[2] + tm[3] * ta[3];
+    Tsave[(size_t)i * M * 4 + x] = acc * (1.f / (float)SEL);
   }
 }
 
@@ -105,7 +95,7 @@ void launch_descriptor_fwd_b16(const Tables &w, const WeightsB16 &wp, const Work
                                const double *coords, const int *types, int n, int c0, int c1,
                                float rc, float rcs, float ln_eps, hipStream_t st) {
   hipLaunchKernelGGL(k_desc_fwd_b16, dim3(c1 - c0), dim3(NWF * 64), 0, st, w, wp, coords, types, n, c0, ws.nlist, ws.nnei, ws.grids,
-                     ws.sys_of, rc, rcs, ln_eps, ws.Gsave, ws.Tsave, ws.D, ws.bidx, ws.bcnt, (int)ws.cap);
+                     ws.sys_of, rc, rcs, ln_eps, ws.Gsave, ws.Tsave, ws.bidx, ws.bcnt, (int)ws.cap);
 }
 
 }  // namespace dp

@@ -1,5 +1,5 @@
 // Backward descriptor kernels of the bfloat16 path: g_ij = dE_i / dDelta_ij from
-// dE/dD, one workgroup per atom.  Each layer's forward is recomputed from its saved
+// dE/dT, one workgroup per atom.  Each layer's forward is recomputed from its saved
 // fp32 input rows; the terms of dG that couple a token to every query row (A^T dH and
 // dS^T U) are gathered in a second, column pass in which wave w recomputes the score
 // and score-gradient tiles of its own token blocks against every query block from U
@@ -386,7 +386,7 @@ __global__ void __launch_bounds__(NW * 64)
 k_desc_bwd_b16(Tables w, WeightsB16 wp, const double *__restrict__ X, const int *__restrict__ types, int natoms,
                const int *__restrict__ nlist, const int *__restrict__ nnei, const Grid *__restrict__ grids,
                const int *__restrict__ sys_of, float rc, float rcs, float ln_eps, const float *__restrict__ Gsave,
-               const float *__restrict__ Tsave, const float *__restrict__ dD, float4 *__restrict__ gout,
+               const float *__restrict__ fit, float4 *__restrict__ gout,
                const int *__restrict__ idx, const int *__restrict__ count) {
   __shared__ SmemB16<NW> sm;
   if ((int)blockIdx.x >= *count) return;
@@ -398,49 +398,25 @@ k_desc_bwd_b16(Tables w, WeightsB16 wp, const double *__restrict__ X, const int 
   const int ti = clamp_type(types[i]);
   const int wv = wave_id(), l = lane(), q = l >> 4, cl = l & 15;
   // the top layer's saved input rows of the wave's blocks, loaded first so that their
-  // latency overlaps the environment and dT work
+  // latency overlaps the environment work
   const float *gs0 = Gsave + (size_t)i * NATTN * GSAVE_LAYER;
   const float *gs1 = gs0 + GSAVE_LAYER;
   f4 gin[BPW][7];
 #pragma unroll
   for (int b = 0; b < BPW; ++b)
     if (wv + NW * b < nb) load_rows(gs1, gin[b], wv + NW * b, n);
-  // dT = dE/dT from dE/dD (D = T T<^T): dT[m] = sum_a dD[m][a] T[a] + [m < M2] sum_m' dD[m'][m] T[m'];
-  // staging is free until the first layer: T [100][4], dE/dD [1600], partial sums [NW * 64]
-  float *T = (float *)sm.stg[0];
-  float *dDi = T + M * 4;
-  float *part = dDi + ND;
-  static_assert((M * 4 + ND + NW * 64) * sizeof(float) <= sizeof(sm.stg), "dT staging must fit in stg");
-  for (int x = threadIdx.x; x < M; x += NW * 64)
-    *(float4 *)(T + 4 * x) = *(const float4 *)(Tsave + ((size_t)i * M + x) * 4);
-  for (int x = threadIdx.x; x < ND / 4; x += NW * 64)
-    *(float4 *)(dDi + 4 * x) = *(const float4 *)(dD + (size_t)i * ND + 4 * x);
+  const float *dTi = fit + (size_t)i * ND;
+  for (int x = threadIdx.x; x < M * 4; x += NW * 64) {
+    float v = dTi[FIT_DT + x];
+    if (x < 4 * M2)
+      for (int p = 0; p < FIT_NPART; ++p) v += dTi[FIT_PART + 4 * M2 * p + x];
+    sm.dT[x] = v;
+  }
   build_envb(sm.e, X, types, nlist, i, n, natoms, g, rc, rcs);
   for (int x = threadIdx.x; x < NPMAX; x += NW * 64) {
     sm.dswa[x] = 0.f;
     for (int a = 0; a < 3; ++a) sm.drh[3 * x + a] = 0.f;
     for (int a = 0; a < 4; ++a) sm.dRt[4 * x + a] = 0.f;
-  }
-  __syncthreads();
-  for (int x = threadIdx.x; x < M * 4; x += NW * 64) {
-    const int m = x >> 2, c = x & 3;
-    float acc = 0.f;
-    for (int a = 0; a < M2; ++a) acc += dDi[m * M2 + a] * T[4 * a + c];
-    sm.dT[x] = acc;
-  }
-  {
-    // the second sum of the 64 entries m < M2 in NW chunks of m', one (chunk, entry) per thread
-    constexpr int CH = (M + NW - 1) / NW;
-    const int e = threadIdx.x & 63, ch = threadIdx.x >> 6, m = e >> 2, c = e & 3;
-    float acc = 0.f;
-    for (int mm2 = ch * CH; mm2 < min(M, (ch + 1) * CH); ++mm2) acc += dDi[mm2 * M2 + m] * T[4 * mm2 + c];
-    part[threadIdx.x] = acc;
-  }
-  __syncthreads();
-  if (threadIdx.x < 64) {
-    float acc = sm.dT[threadIdx.x];
-    for (int ch = 0; ch < NW; ++ch) acc += part[64 * ch + threadIdx.x];
-    sm.dT[threadIdx.x] = acc;
   }
   put_layer_input<NW, BPW>(sm, gin, nb);
   __syncthreads();
@@ -597,10 +573,10 @@ void launch_descriptor_bwd_b16(const Tables &w, const WeightsB16 &wp, const Work
   (void)hipEventRecord(ws.fork_ev, st);
   (void)hipStreamWaitEvent(ws.side, ws.fork_ev, 0);
   hipLaunchKernelGGL((k_desc_bwd_b16<4, 2>), dim3(ncen), dim3(4 * 64), 0, ws.side, w, wp, coords, types, n, ws.nlist,
-                     ws.nnei, ws.grids, ws.sys_of, rc, rcs, ln_eps, ws.Gsave, ws.Tsave, ws.D, ws.g, ws.bidx + ws.cap,
+                     ws.nnei, ws.grids, ws.sys_of, rc, rcs, ln_eps, ws.Gsave, ws.fit, ws.g, ws.bidx + ws.cap,
                      ws.bcnt + 1);
   hipLaunchKernelGGL((k_desc_bwd_b16<7, 1>), dim3(ncen), dim3(7 * 64), 0, st, w, wp, coords, types, n, ws.nlist, ws.nnei,
-                     ws.grids, ws.sys_of, rc, rcs, ln_eps, ws.Gsave, ws.Tsave, ws.D, ws.g, ws.bidx, ws.bcnt);
+                     ws.grids, ws.sys_of, rc, rcs, ln_eps, ws.Gsave, ws.fit, ws.g, ws.bidx, ws.bcnt);
   (void)hipEventRecord(ws.join_ev, ws.side);
   (void)hipStreamWaitEvent(st, ws.join_ev, 0);
 }

@@ -17,6 +17,9 @@ constexpr int DATTN = 128;   // attention width (enters through the fused 100x10
 constexpr int M2 = 16;       // axis neurons
 constexpr int ND = M * M2;   // descriptor length 1600
 constexpr int FH = 240;      // fitting width
+// An atom's row of Workspace::fit as the descriptor backward reads it: dE/dT [M][4] at
+// FIT_DT, to which FIT_NPART partial sums [16][4] from FIT_PART on are added.
+constexpr int FIT_DT = 960, FIT_PART = 1360, FIT_NPART = 3;
 constexpr int SEL = 120;     // neighbour capacity
 constexpr int NPMAX = 128;   // tokens per atom after padding to a multiple of 16
 constexpr int GSAVE_LAYER = NPMAX * M;  // floats per atom and layer of the saved layer inputs

@@ -63,7 +63,8 @@ struct Tables {
 
 // GEMM operands of the float32 path, T = float.  The descriptor's are in the MFMA fragment
 // order its kernels read (see wmul and emul there), named by the matrix whose rows are the
-// outputs; the fitting net's are row-major.
+// outputs; the fitting net's likewise (fragment (t, s) of a matrix with S k steps of 16 at
+// ((t S + s) 64 + lane) 4).
 template <typename T> struct Weights : Tables {
   const T *W2T;       // [E2][E1], groups of 25
   const T *W2;        // [E1][E2]
@@ -132,7 +133,7 @@ struct Workspace {
   int *bcnt = nullptr;        // [2]
   int *done = nullptr;        // [2 cap_sys + 1]  completion counters (the cell pass's workgroup counter
                               // at [2 cap_sys]); cleared at the start of each step
-  float *D = nullptr;         // [cap][ND]  descriptor, then dE/dD
+  float *fit = nullptr;       // [cap][ND]  the fitting net's row of each atom (hidden activations, dE/dT)
   double *Ei = nullptr;       // [cap] atomic energies (the weighted head combination)
   double *Eh = nullptr;       // [cap][MAXH]  atomic energy of each fitting head (models with several)
   double *Ehsys = nullptr;    // [cap_sys][MAXH]  each head's energy per system
@@ -255,9 +256,8 @@ void launch_skin_ref(const Workspace &ws, const double *coords, int n, hipStream
 // and types of all n atoms as neighbours.
 void launch_descriptor_fwd(const Weights<float> &w, const Workspace &ws, const double *coords, const int *types,
                            int n, int c0, int c1, float rc, float rcs, float ln_eps, hipStream_t st);
-// The fitting net over the first n atoms (E_i, and dE/dD over D when backward).
-template <typename T>
-void launch_fitting(const Weights<T> &w, const Workspace &ws, const int *types, int c0, int c1, bool backward,
+// The fitting net over the atoms c0 .. c1-1 from ws.Tsave (E_i, and dE/dT into ws.fit when backward).
+void launch_fitting(const Weights<float> &w, const Workspace &ws, const int *types, int c0, int c1, bool backward,
                     hipStream_t st);
 void launch_descriptor_fwd_b16(const Tables &w, const WeightsB16 &wp, const Workspace &ws,
                                const double *coords, const int *types, int n, int c0, int c1, float rc,
