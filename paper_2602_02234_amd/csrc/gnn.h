@@ -25,7 +25,15 @@ constexpr int NLAYER = 3;
 constexpr int FWID = 128;  // fitting width
 constexpr int ASEL = 48;   // largest angle-neighbour count a model may set
 
-// Device weights, float32, row-major [in][out] as in the model file.
+// A weight matrix in the MFMA fragment order of the layer kernels (see gnn.hip), in the
+// precision of the model's products.
+struct Frag {
+  const float *f32 = nullptr;
+  const bf16_t *b16 = nullptr;
+};
+
+// Device weights: float32, row-major [in][out] as in the model file (the T-named copies
+// transposed), and the fragment-ordered operands.
 struct Weights {
   const float *TN;                // [NTYPES][64]
   const float *We0, *be0;         // [64]
@@ -35,6 +43,15 @@ struct Weights {
   const float *Wee[NLAYER], *bee[NLAYER];  // [192][64], [64]
   const float *Wnn[NLAYER], *bnn[NLAYER];  // [128][64], [64]
   const float *G1, *d1, *G2, *d2, *G3;     // [64][128], [128], [128][128], [128], [128]
+  const float *G1T, *G2T;         // [128][64], [128][128]
+  const float *WnnT[NLAYER];      // [64][128]
+  const float *WeeT[NLAYER];      // [64][64]  of Wee[0:64]
+  Frag A[NLAYER], Mg[NLAYER];     // a -> Waa[0:32] (32 outputs), a' -> Wea[0:32] (64)
+  Frag Xt[NLAYER], Yt[NLAYER];    // dz_m -> Wea[0:32]^T (32 outputs of 64), dz_a -> Waa[0:32]^T
+  Frag E[NLAYER];                 // [n_j, e] -> Wee[64:192] (64 outputs of 128)
+  Frag N[NLAYER], D[NLAYER];      // dz_e -> Wee[64:128]^T and Wee[128:192]^T
+  const float *PQ[NLAYER];        // e[:32] -> [Waa[32:64], Waa[64:96], Wea[32:64]] (128 outputs of 32), float32
+  const float *PS[NLAYER];        // edge sums -> dE/de[:32] (32 outputs of 128), float32
   const double *G3d;              // [128]  last layer in float64 (energy sum)
   double d3;
 };

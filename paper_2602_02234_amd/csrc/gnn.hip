@@ -1,25 +1,36 @@
-// GNN-variant descriptor kernels for gfx950: one workgroup (four waves) per centre atom
-// and one launch per message-passing layer, forward and backward (a layer's edge update
-// reads the neighbours' node features of the layer before, so layers meet at launch
-// boundaries).  Every product of a feature tile with a weight matrix runs on MFMA
-// (16 angles or 16 edges per tile, f32 or bf16 operands, f32 accumulation); feature
-// tiles are staged in per-wave LDS slabs and the angle weights of a layer stay in each
-// wave's registers for all its tiles.  Features are stored in float32.
+// GNN-variant descriptor kernels for gfx950: one workgroup per centre atom and one launch
+// per message-passing layer, forward and backward (a layer's edge update reads the
+// neighbours' node features of the layer before, so layers meet at launch boundaries).
+//
+// Every product of a feature tile with a weight matrix runs on MFMA (f32 or bf16 operands,
+// f32 accumulation) transposed: weights as A operand, features along the accumulator rows,
+// 16 angles or 16 edges along the columns.  Lane (q = lane / 16, c = lane % 16) then holds
+// features 16 t + 4 q + i of angle or edge c, which is at once the layout of the float4
+// rows in memory and the B operand of the next product (k step i of tile t is feature
+// 16 t + 4 q + i), so a tile goes from memory through all its products and back without
+// passing through LDS.  Weights come in that fragment order; the angle weights of a layer
+// stay in each wave's registers.  Features are stored in float32.
 //
 // Forward, layer l, centre i:
-//   angles  each wave owns angle rows p (p = wave, wave + 4, ...) and walks q in tiles
-//           of 16: a' = a + tanh([a, e_ip, e_iq] Waa + b), then the message tile
-//           tanh([a', e_iq] Wea + b) weighted by sw_a(r_ip) sw_a(r_iq) / asel and summed
-//           over q in a fixed order into m_ip;
-//   edges   tiles of 16 edges: e' = e + tanh([n_i, n_j, e] Wee + b) + m;
+//   per angle-list edge x, once: PQ[x] = the terms that its edge features add to the angle
+//           products (with the biases);
+//   angles  a wave owns rows p (p = wave, wave + NW, ...) and walks q in tiles of 16:
+//           a' = a + tanh([a, e_ip, e_iq] Waa + b), and m_ip += sw_a(r_ip) sw_a(r_iq) / asel
+//           tanh([a', e_iq] Wea + b);
+//   edges   tiles of 16: e' = e + tanh([n_i, n_j, e] Wee + b) + m;
 //   node    n' = n + tanh([n, sum_j sw_e e' / sel] Wnn + b); after the last layer the
 //           fitting net, E_i in float64, and dE/dn_i.
-// Backward, layer l (reverse of the above, activations recomputed from the stored layer
-// inputs): dE/dn_i is gathered from the edges (j, i) of the neighbours in list order
-// (binary search of i in N(j)); per-angle terms that belong to edge (i, q) are summed
-// per wave in LDS and the wave sums added in wave order, so every sum has a fixed order
-// and the result is deterministic.  Layer 0 turns the accumulated gradients of s, sw_e,
-// sw_a and rhat into g_ij = dE/dDelta_ij for the shared force gather.
+// Backward, layer l (activations recomputed from the stored layer inputs): dE/dn_i is
+// gathered from the edges (j, i) of the neighbours in list order.  A wave owns columns q
+// and walks p: the gradients that meet at edge q, which enter through two weight products,
+// are summed in registers and multiplied by the weights once per edge instead of once per
+// angle; those of edge p go to a per-wave LDS array, and the waves' arrays are added in
+// wave order, so every sum has a fixed order.  Layer 0 turns the accumulated gradients of
+// s, sw_e, sw_a and rhat into g_ij = dE/dDelta_ij for the shared force gather.
+//
+// Bound: at the 9,999-atom box a forward layer moves 1.7 GB of angle rows (0.33 ms at the
+// copy rate) and has 0.42 ms of float32 MFMA work, a backward layer 3.4 GB (0.66 ms) and
+// 0.8 ms.
 #include "dp_env.h"
 #include "gnn.h"
 
@@ -27,102 +38,106 @@ namespace dp {
 namespace gnn {
 namespace {
 
-constexpr int NWG = 4;          // waves per workgroup
-constexpr int NT = NWG * 64;
-constexpr int LDE = 68;         // row stride of [edge][64] LDS arrays
-constexpr int LDF = 196;        // forward slab row stride (192 columns used)
-constexpr int LDB = 164;        // backward slab row stride (160 columns used)
-constexpr int QLD = 36;         // per-edge angle accumulators: 32 features, sw_a, rhat
+constexpr int LPQ = 132;  // row stride of the per-edge terms [angle-list edge][128]
+constexpr int LMS = 68;   // ... of [angle-list edge][64]
+constexpr int LSZ = 100;  // backward: per-edge terms of edge q [96], later the sums over its angles [96 + 4]
+constexpr int LPP = 36;   // backward: sums of edge p [32 features, sw_a, rhat], and its terms [32]
 
 __device__ __forceinline__ bool failed(const unsigned *flags) { return (flags[0] & FLAG_ERRORS) != 0u; }
-
-// Ordering of LDS traffic between the lanes of one wave (per-wave slabs).
+__device__ __forceinline__ f4 ldf4(const float *p) { return *reinterpret_cast<const f4 *>(p); }
+__device__ __forceinline__ void stf4(float *p, f4 v) { *reinterpret_cast<f4 *>(p) = v; }
+// Sum over the four lane groups (the lanes of one column).
+__device__ __forceinline__ float sumq(float v) {
+  v += __shfl_xor(v, 16);
+  v += __shfl_xor(v, 32);
+  return v;
+}
+__device__ __forceinline__ f4 sum16(f4 v) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = dp::sum16(v[i]);
+  return v;
+}
+// Ordering of LDS traffic between the lanes of one wave.
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
+// Keeps the loads of one tile from being scheduled across another's products.
+__device__ __forceinline__ void tile_barrier() { __builtin_amdgcn_sched_barrier(0); }
 
-// Sum over all 64 lanes, the same in every lane.
-__device__ __forceinline__ float wave_sum64(float v) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  return v;
-}
-
-// Weight fragments held in registers for one 16-column tile of a product X W (X: 16
-// rows in an LDS slab, W: K x 16).  The k order inside each MFMA step is permuted
-// (the sum does not depend on it) so that a lane's A operands for consecutive steps
-// are adjacent in LDS and come in 128-bit reads: f32, steps s = 0..3 of block kb use
-// k = 16 kb + 4 (lane / 16) + s; bf16, block kb uses k = 32 kb + 8 (lane / 16) + e.
-// y(c, k) gives W[k][c]; col(k0) maps the first k of a block to its slab column
-// (operands may come from several column ranges, each a multiple of 32 wide).
-template <typename T, int K> struct Frag;
-
-template <int K> struct Frag<float, K> {
-  float v[K / 4];
-  template <class Y> __device__ __forceinline__ void load(const Y &y) {
-    const int c = lane_id() & 15, kq = lane_id() >> 4;
+// B operand over 16 NK features (tiles x[t], features 16 t + 4 q + i), and an A operand tile
+// of 16 outputs over the same contraction from fragment order: float32, tile t at
+// ((t NK + kb) 64 + lane) 4; bf16, two tiles of features per step, at ((t NK/2 + kp) 64 +
+// lane) 8, the first four values from tile 2 kp, the others from tile 2 kp + 1.
+template <typename T, int NK> struct X;
+template <typename T, int NK> struct W;
+template <int NK> struct X<float, NK> {
+  f4 v[NK];
+  __device__ __forceinline__ explicit X(const f4 (&x)[NK]) {
 #pragma unroll
-    for (int kb = 0; kb < K / 16; ++kb)
-#pragma unroll
-      for (int s = 0; s < 4; ++s) v[kb * 4 + s] = y(c, kb * 16 + 4 * kq + s);
-  }
-  template <class C> __device__ __forceinline__ void mma(f4 &acc, const float *row, const C &col) const {
-    const int kq = lane_id() >> 4;
-#pragma unroll
-    for (int kb = 0; kb < K / 16; ++kb) {
-      const float4 a = *reinterpret_cast<const float4 *>(row + col(kb * 16) + 4 * kq);
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, v[kb * 4 + 0], acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, v[kb * 4 + 1], acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, v[kb * 4 + 2], acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, v[kb * 4 + 3], acc, 0, 0, 0);
-    }
+    for (int k = 0; k < NK; ++k) v[k] = x[k];
   }
 };
-
-template <int K> struct Frag<bf16_t, K> {
-  bf8 v[K / 32];
-  template <class Y> __device__ __forceinline__ void load(const Y &y) {
-    const int c = lane_id() & 15, kq = lane_id() >> 4;
+template <int NK> struct W<float, NK> {
+  f4 v[NK];
+  __device__ __forceinline__ void load(const float *__restrict__ p, int t) {
 #pragma unroll
-    for (int kb = 0; kb < K / 32; ++kb)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[kb][e] = (__bf16)y(c, kb * 32 + 8 * kq + e);
+    for (int k = 0; k < NK; ++k) v[k] = ldf4(p + ((t * NK + k) * 64 + lane_id()) * 4);
   }
-  template <class C> __device__ __forceinline__ void mma(f4 &acc, const float *row, const C &col) const {
-    const int kq = lane_id() >> 4;
+  __device__ __forceinline__ f4 operator()(const X<float, NK> &x, f4 acc) const {
 #pragma unroll
-    for (int kb = 0; kb < K / 32; ++kb) {
-      const float *q = row + col(kb * 32) + 8 * kq;
-      const float4 a0 = *reinterpret_cast<const float4 *>(q);
-      const float4 a1 = *reinterpret_cast<const float4 *>(q + 4);
-      bf8 a;
-      a[0] = (__bf16)a0.x; a[1] = (__bf16)a0.y; a[2] = (__bf16)a0.z; a[3] = (__bf16)a0.w;
-      a[4] = (__bf16)a1.x; a[5] = (__bf16)a1.y; a[6] = (__bf16)a1.z; a[7] = (__bf16)a1.w;
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, v[kb], acc, 0, 0, 0);
-    }
+    for (int k = 0; k < NK; ++k)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(v[k][s], x.v[k][s], acc, 0, 0, 0);
+    return acc;
   }
 };
+template <int NK> struct X<bf16_t, NK> {
+  bf8 v[NK / 2];
+  __device__ __forceinline__ explicit X(const f4 (&x)[NK]) {
+#pragma unroll
+    for (int k = 0; k < NK / 2; ++k)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[k][e] = (__bf16)x[2 * k + e / 4][e % 4];
+  }
+};
+template <int NK> struct W<bf16_t, NK> {
+  bf8 v[NK / 2];
+  __device__ __forceinline__ void load(const bf16_t *__restrict__ p, int t) {
+#pragma unroll
+    for (int k = 0; k < NK / 2; ++k) v[k] = *reinterpret_cast<const bf8 *>(p + ((t * (NK / 2) + k) * 64 + lane_id()) * 8);
+  }
+  __device__ __forceinline__ f4 operator()(const X<bf16_t, NK> &x, f4 acc) const {
+#pragma unroll
+    for (int k = 0; k < NK / 2; ++k) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v[k], x.v[k], acc, 0, 0, 0);
+    return acc;
+  }
+};
+template <typename T> __device__ __forceinline__ const T *frag(const Frag &f);
+template <> __device__ __forceinline__ const float *frag<float>(const Frag &f) { return f.f32; }
+template <> __device__ __forceinline__ const bf16_t *frag<bf16_t>(const Frag &f) { return f.b16; }
 
 // tanh of the layers' hot loops, from the hardware exponential and reciprocal:
 // tanh|x| = (1 - t) / (1 + t), t = exp(-2|x|); absolute error a few 1e-8, below the
 // float32 rounding of the products it follows (measured forces unchanged against tanhf).
-template <typename T> __device__ __forceinline__ float act(float x) {
+__device__ __forceinline__ float act(float x) {
   const float t = __expf(-2.f * fabsf(x));
   return copysignf((1.f - t) * __builtin_amdgcn_rcpf(1.f + t), x);
 }
-
-// Compiler barrier: weight fragments loaded after it are not hoisted out of the loop
-// around it (they would then all be live at once).
-__device__ __forceinline__ void opaque() { asm volatile("" ::: "memory"); }
-
-struct Ident {
-  __device__ __forceinline__ int operator()(int k) const { return k; }
-};
-struct Shift {  // operands at slab columns from `s` on
-  int s;
-  __device__ __forceinline__ int operator()(int k) const { return s + k; }
-};
+__device__ __forceinline__ f4 act(f4 v) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = act(v[i]);
+  return v;
+}
+// Initial features tanh(x w + b) of a lane's four features.
+__device__ __forceinline__ f4 init4(float x, const float *__restrict__ w, const float *__restrict__ b) {
+  const f4 wv = ldf4(w), bv = ldf4(b);
+  f4 v;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = tanhf(x * wv[i] + bv[i]);
+  return v;
+}
 
 struct GEnv {
   float r[SEL], swe[SEL], dswe[SEL], swa[SEL], dswa[SEL], s[SEL];
@@ -143,7 +158,7 @@ __device__ __forceinline__ float quintic(float r, float rc, float rcs, float &ds
 
 // Geometry of centre i's edges and its angle list (the first asel neighbours, in list
 // order, closer than rca; the test is made in float64 on the minimum-image vector).
-__device__ void build_genv(GEnv &e, const double *__restrict__ X, const int *__restrict__ types,
+template <int NT> __device__ void build_genv(GEnv &e, const double *__restrict__ X, const int *__restrict__ types,
                            const int *__restrict__ nlist, const int *__restrict__ nnei, int i, int n,
                            const Grid &g, const Geo &geo) {
   const int nn = min(max(nnei[i], 0), SEL);
@@ -201,28 +216,57 @@ __device__ __forceinline__ size_t erow(const Buffers &b, int l, int i, int j) {
   return (((size_t)l * b.cap + i) * SEL + j) * EDIM;
 }
 
+// out[c] = sum_k x[k] Wm[k][c] for threads c < C (x in LDS, Wm row-major): the rows split
+// over the workgroup, the parts (in `part`, one float per thread) added in order.  Starts
+// with a barrier.
+template <int NW, int K, int C>
+__device__ __forceinline__ float matvec(const float *__restrict__ Wm, const float *x, float *part) {
+  constexpr int SEG = NW * 64 / C, PER = K / SEG;
+  static_assert(K % SEG == 0 && SEG >= 1, "whole segments");
+  const int c = threadIdx.x % C, sg = threadIdx.x / C;
+  __syncthreads();
+  float v = 0.f;
+#pragma unroll 16
+  for (int k = 0; k < PER; ++k) v += x[sg * PER + k] * Wm[(sg * PER + k) * C + c];
+  part[threadIdx.x] = v;
+  __syncthreads();
+  float r = 0.f;
+  if ((int)threadIdx.x < C)
+#pragma unroll
+    for (int s = 0; s < SEG; ++s) r += part[s * C + c];
+  return r;
+}
+
 // ------------------------------------------------------------------ angle offsets
-__global__ void __launch_bounds__(256) k_angle_count(const double *__restrict__ X, const int *__restrict__ nlist,
+// One wave per atom.
+__global__ void __launch_bounds__(256) k_angle_count(const double *__restrict__ Xc, const int *__restrict__ nlist,
                                                      const int *__restrict__ nnei, const Grid *__restrict__ grids,
                                                      int n, Geo geo, int64_t *__restrict__ aoff) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
+  const int i = blockIdx.x * 4 + wave_id(), l = lane_id();
   if (i >= n) return;
   const Grid g = grids[0];
   const int nn = min(max(nnei[i], 0), SEL);
   int nc = 0;
-  for (int j = 0; j < nn && nc < geo.asel; ++j) {
-    int nj = nlist[(size_t)i * SEL + j];
-    if (nj < 0 || nj >= n) continue;
-    double d[3];
-    for (int a = 0; a < 3; ++a) {
-      double v = X[3 * nj + a] - X[3 * i + a];
-      if (g.periodic) v -= g.L[a] * rint(v * g.invL[a]);
-      d[a] = v;
+  for (int j0 = 0; j0 < nn; j0 += 64) {
+    const int j = j0 + l;
+    bool close = false;
+    if (j < nn) {
+      const int nj = nlist[(size_t)i * SEL + j];
+      if (nj >= 0 && nj < n) {
+        double d[3];
+        for (int a = 0; a < 3; ++a) {
+          double v = Xc[3 * nj + a] - Xc[3 * i + a];
+          if (g.periodic) v -= g.L[a] * rint(v * g.invL[a]);
+          d[a] = v;
+        }
+        close = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]) < (double)geo.rca;
+      }
     }
-    nc += sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]) < (double)geo.rca;
+    nc += __popcll(__ballot(close));
   }
-  aoff[i + 1] = (int64_t)nc * (nc - 1);
-  if (i == 0) aoff[0] = 0;
+  nc = min(nc, geo.asel);
+  if (l == 0) aoff[i + 1] = (int64_t)nc * (nc - 1);
+  if (i == 0 && l == 0) aoff[0] = 0;
 }
 
 // Inclusive prefix of aoff[1 .. n] in one workgroup: each thread sums a contiguous run,
@@ -242,22 +286,23 @@ __global__ void __launch_bounds__(1024) k_angle_scan(int64_t *__restrict__ aoff,
     const int64_t cnt = aoff[k];
     s += cnt;
     se += min(max(nnei[k - 1], 0), SEL);
-    int nc = 0;
-    while ((int64_t)nc * (nc - 1) < cnt) ++nc;  // cnt = nc (nc - 1), nc <= 48 (atoms with angles)
-    sc += nc;
+    // cnt = nc (nc - 1) with nc <= 48 (0 for no angles)
+    sc += cnt > 0 ? (int)(0.5f + sqrtf((float)cnt + 0.25f)) : 0;
   }
   part[t] = s;
   epart[t] = se;
   cpart[t] = sc;
   __syncthreads();
-  if (t == 0) {
-    int64_t tot = 0, totc = 0;
-    for (int k = 0; k < 1024; ++k) {
-      tot += epart[k];
-      totc += cpart[k];
+  for (int off = 512; off > 0; off >>= 1) {
+    if (t < off) {
+      epart[t] += epart[t + off];
+      cpart[t] += cpart[t + off];
     }
-    etot[0] = tot;
-    etot[1] = totc;
+    __syncthreads();
+  }
+  if (t == 0) {
+    etot[0] = epart[0];
+    etot[1] = cpart[0];
   }
   for (int off = 1; off < 1024; off <<= 1) {
     const int64_t v = t >= off ? part[t - off] : 0;
@@ -272,758 +317,564 @@ __global__ void __launch_bounds__(1024) k_angle_scan(int64_t *__restrict__ aoff,
   }
 }
 
-// The terms an angle's products take from its two edges depend on the edge alone:
-// PQ[x] = [e_x[:32] Waa[32:64], e_x[:32] Waa[64:96], e_x[:32] Wea[32:64]] for every
-// angle-list edge x (rows of E at stride lde, first 32 columns), computed once per
-// layer instead of once per angle.  Each thread owns one of the 128 columns and holds
-// its 32 weights in registers.  Ends synchronised.
-constexpr int PQW = 2 * ADIM + EDIM;  // 128
-__device__ void edge_terms(const float *__restrict__ Waa, const float *__restrict__ Wea, const float *E, int lde,
-                           const int *cl, int nc, float *PQ) {
-  const int c = threadIdx.x & (PQW - 1);
-  float wc[ADIM];
+// The layer's input features e_ij of edge slot j, features 16 t + 4 q .. + 3.
+__device__ __forceinline__ f4 edge_in(const Weights &w, const Buffers &b, const GEnv &e, int l, int i, int j, int f) {
+  return l == 0 ? init4(e.s[j], w.We0 + f, w.be0 + f) : ldf4(b.ef + erow(b, l - 1, i, j) + f);
+}
+// ... and n of the neighbour of slot j.
+__device__ __forceinline__ f4 node_in(const Weights &w, const Buffers &b, const GEnv &e, int l, int j, int f) {
+  return l == 0 ? ldf4(w.TN + e.tj[j] * NDIM + f) : ldf4(b.nf + ((size_t)(l - 1) * b.cap + e.jn[j]) * NDIM + f);
+}
+
+// The terms an angle's products take from its two edges depend on the edge alone; for every
+// angle-list edge x, in float32: [e_x[:32] Waa[32:64] (edge p's), e_x[:32] Waa[64:96] + baa,
+// e_x[:32] Wea[32:64] + bea], 128 columns, given to put(x, column, four values).
+template <int NW, class Put>
+__device__ __forceinline__ void edge_terms(const Weights &w, const Buffers &b, const GEnv &e, int l, int i, const Put &put) {
+  const int q = lane_id() >> 4, c = lane_id() & 15;
+  for (int x0 = 0; x0 < e.nc; x0 += 16) {
+    const int x = x0 + c;
+    const bool ok = x < e.nc;
+    f4 ev[2];
 #pragma unroll
-  for (int k = 0; k < ADIM; ++k)
-    wc[k] = c < ADIM ? Waa[(ADIM + k) * ADIM + c]
-                     : (c < 2 * ADIM ? Waa[(2 * ADIM + k) * ADIM + c - ADIM] : Wea[(ADIM + k) * EDIM + c - 2 * ADIM]);
-  for (int x = threadIdx.x >> 7; x < nc; x += NT / PQW) {
-    const float *ex = E + (lde > 0 ? cl[x] * lde : x * ADIM);
-    float v = 0.f;
-#pragma unroll
-    for (int k = 0; k < ADIM; ++k) v += ex[k] * wc[k];
-    PQ[x * PQW + c] = v;
+    for (int t = 0; t < 2; ++t) ev[t] = ok ? edge_in(w, b, e, l, i, e.cl[x], 16 * t + 4 * q) : f4{0.f, 0.f, 0.f, 0.f};
+    const X<float, 2> xo(ev);
+    for (int ot = wave_id(); ot < 8; ot += NW) {
+      W<float, 2> wt;
+      wt.load(w.PQ[l], ot);
+      const int col = 16 * ot + 4 * q;
+      const f4 bias = ot < 2 ? f4{0.f, 0.f, 0.f, 0.f} : (ot < 4 ? ldf4(w.baa[l] + col - 32) : ldf4(w.bea[l] + col - 64));
+      const f4 v = wt(xo, f4{0.f, 0.f, 0.f, 0.f}) + bias;
+      if (ok) put(x, col, v);
+    }
   }
-  __syncthreads();
 }
 
 // ------------------------------------------------------------------ forward
-struct SmemF {
+template <int NW> struct SmemF {
   GEnv env;
-  float El[SEL * LDE] __attribute__((aligned(16)));  // e of the layer's input
-  float Msg[ASEL * EDIM];                            // m_ip
-  float PQ[ASEL * PQW];                              // per-edge terms of the angle products
-  float slab[NWG][16 * LDF] __attribute__((aligned(16)));  // per-wave operand tiles
-  float ni[NDIM] __attribute__((aligned(16))), xs[2 * NDIM], aggw[NWG][NDIM], nbias[EDIM];
+  float PQ[ASEL * LPQ] __attribute__((aligned(16)));   // per-edge terms of the angle products
+  float Msg[ASEL * LMS] __attribute__((aligned(16)));  // m_ip
+  float nbias[EDIM] __attribute__((aligned(16))), aggw[NW][EDIM] __attribute__((aligned(16)));
+  float ni[NDIM], xs[2 * NDIM], part[NW * 64];
   float y1[FWID], t2[FWID], dp[FWID];
 };
 
-// Stages 16 rows x 32 S floats into a slab: segment s (columns 32 s .. 32 s + 31) of
-// row r is src(s, r, c4), c4 = 0..7 the float4 within the segment (zero for rows past
-// the end).  Each lane moves two rows of one float4 column per segment; the reads of G
-// segments are issued before their writes, so their latencies overlap.  s is a
-// compile-time constant in every call of src (the loops are unrolled).
-template <int S, int G, class Src>
-__device__ __forceinline__ void stage(float *sl, int ld, const Src &src) {
-  const int c4 = lane_id() & 7, r0 = lane_id() >> 3;
-#pragma unroll
-  for (int g0 = 0; g0 < S; g0 += G) {
-    float4 v[G][2];
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-        if (g0 + g < S) v[g][h] = src(g0 + g, r0 + 8 * h, c4);
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-        if (g0 + g < S) *reinterpret_cast<float4 *>(sl + (r0 + 8 * h) * ld + 32 * (g0 + g) + 4 * c4) = v[g][h];
-  }
-}
-
-__device__ __forceinline__ float4 ld4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
-
-template <typename T>
-__global__ void __launch_bounds__(NT) k_layer_fwd(Weights w, Buffers b, const double *__restrict__ X,
-                                                  const int *__restrict__ types, const int *__restrict__ nlist,
-                                                  const int *__restrict__ nnei, const Grid *__restrict__ grids,
-                                                  int n, int layer, Geo geo, double *__restrict__ Ei,
-                                                  const unsigned *__restrict__ flags) {
-  __shared__ SmemF sm;
+template <typename T, int NW>
+__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 4 ? 3 : 2)))
+k_layer_fwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__restrict__ types,
+            const int *__restrict__ nlist, const int *__restrict__ nnei, const Grid *__restrict__ grids, int n, int layer,
+            Geo geo, double *__restrict__ Ei, const unsigned *__restrict__ flags) {
+  __shared__ SmemF<NW> sm;
   const int i = blockIdx.x;
   if (i >= n || failed(flags)) return;
-  const int tid = threadIdx.x, wv = wave_id(), ln = lane_id();
+  const int tid = threadIdx.x, wv = wave_id(), ln = lane_id(), q = ln >> 4, c = ln & 15;
   const int l = layer;
-  const float *Waa = w.Waa[l], *baa = w.baa[l], *Wea = w.Wea[l], *bea = w.bea[l];
-  const float *Wee = w.Wee[l], *bee = w.bee[l], *Wnn = w.Wnn[l], *bnn = w.bnn[l];
-  // the angle rows' parts of this layer's angle weights (the first 32 inputs), held by
-  // every wave for all its tiles
-  Frag<T, ADIM> fa[2];
-  Frag<T, ADIM> fm[4];
-#pragma unroll
-  for (int ct = 0; ct < 2; ++ct) fa[ct].load([&](int c, int k) { return Waa[k * ADIM + ct * 16 + c]; });
-#pragma unroll
-  for (int ct = 0; ct < 4; ++ct) fm[ct].load([&](int c, int k) { return Wea[k * EDIM + ct * 16 + c]; });
-  build_genv(sm.env, X, types, nlist, nnei, i, n, grids[0], geo);
+  build_genv<NW * 64>(sm.env, Xc, types, nlist, nnei, i, n, grids[0], geo);
   const GEnv &e = sm.env;
   const int nn = e.nn, nc = e.nc;
-
-  if (l == 0) {
-    for (int k = tid; k < nn * EDIM; k += NT) {
-      const int j = k >> 6, c = k & 63;
-      sm.El[j * LDE + c] = tanhf(e.s[j] * w.We0[c] + w.be0[c]);
-    }
-  } else {  // the input edges, all reads issued before the writes
-    constexpr int NI = (SEL * EDIM / 4 + NT - 1) / NT;
-    float4 v[NI];
-#pragma unroll
-    for (int it = 0; it < NI; ++it) {
-      const int k = tid + NT * it, j = k >> 4;
-      if (j < nn) v[it] = ld4(b.ef + erow(b, l - 1, i, j) + 4 * (k & 15));
-    }
-#pragma unroll
-    for (int it = 0; it < NI; ++it) {
-      const int k = tid + NT * it, j = k >> 4;
-      if (j < nn) *reinterpret_cast<float4 *>(sm.El + j * LDE + 4 * (k & 15)) = v[it];
-    }
-  }
   if (tid < NDIM)
     sm.ni[tid] = l == 0 ? w.TN[clamp_type(types[i]) * NDIM + tid] : b.nf[((size_t)(l - 1) * b.cap + i) * NDIM + tid];
-  __syncthreads();
-  if (tid < EDIM) {  // the centre's part of every edge update: bee + n_i Wee[0:64]
-    float v = bee[tid];
-    for (int k = 0; k < NDIM; ++k) v += sm.ni[k] * Wee[k * EDIM + tid];
-    sm.nbias[tid] = v;
+  edge_terms<NW>(w, b, e, l, i, [&](int x, int col, f4 v) { stf4(sm.PQ + x * LPQ + col, v); });
+  {  // the centre's part of every edge update: bee + n_i Wee[0:64]
+    const float v = matvec<NW, NDIM, EDIM>(w.Wee[l], sm.ni, sm.part);
+    if (tid < EDIM) sm.nbias[tid] = v + w.bee[l][tid];
   }
-  edge_terms(Waa, Wea, sm.El, LDE, e.cl, nc, sm.PQ);
+  __syncthreads();
 
-  float *sl = sm.slab[wv];
-  const float *rowA = sl + (ln & 15) * LDF;
+  // ---------------- angles and messages
   const int na = nc - 1;  // angles per row p
   const int64_t abase = b.aoff[i];
-  // ---------------- angles and messages
-  // A wave takes rows p = wv, wv + NWG, ... and the angles of each in pairs of tiles of
-  // 16 (t0 .. t0 + 15 at slab columns 0 .. 31, t0 + 16 .. t0 + 31 at columns 32 .. 63),
-  // whose product chains are independent and interleave; for l > 0 the input a of its
-  // next pair is read while the current pair is processed.
-  const int sc4 = ln & 7, sr0 = ln >> 3;  // the lane's float4 column and first row in a staged tile
-  auto pair_in = [&](int p, int t0, float4 (&v)[4]) {
-    const float *ap = b.af + ((size_t)(l - 1) * b.acap + abase + (int64_t)p * na) * ADIM;
+  {
+    W<T, 2> wa[2], wm[4];
 #pragma unroll
-    for (int h = 0; h < 4; ++h) {
-      const int t = t0 + 16 * (h >> 1) + sr0 + 8 * (h & 1);
-      v[h] = t < na ? ld4(ap + (size_t)t * ADIM + 4 * sc4) : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-  };
-  const Shift second{ADIM};
-  float4 nxt[4];
-  if (l > 0 && wv < nc && na > 0) pair_in(wv, 0, nxt);
-  for (int p = wv; p < nc; p += NWG) {
-    float mr[4] = {0.f, 0.f, 0.f, 0.f};
-    const int jp = e.cl[p];
-    for (int t0 = 0; t0 < na; t0 += 32) {
-      // a of the pair's 32 angles; the edge terms come from PQ
-      if (l > 0) {
-        const float4 cur[4] = {nxt[0], nxt[1], nxt[2], nxt[3]};
-        const int pn = t0 + 32 < na ? p : p + NWG, tn = t0 + 32 < na ? t0 + 32 : 0;
-        if (pn < nc) pair_in(pn, tn, nxt);
+    for (int t = 0; t < 2; ++t) wa[t].load(frag<T>(w.A[l]), t);
 #pragma unroll
-        for (int h = 0; h < 4; ++h)
-          *reinterpret_cast<float4 *>(sl + (sr0 + 8 * (h & 1)) * LDF + ADIM * (h >> 1) + 4 * sc4) = cur[h];
-      } else stage<2, 2>(sl, LDF, [&](int sg, int r, int c4) -> float4 {
-        const int t = t0 + 16 * sg + r;
-        if (t >= na) return make_float4(0.f, 0.f, 0.f, 0.f);
-        const float cs = cosang(e, jp, e.cl[t + (t >= p)]);
-        float4 v;
-        v.x = tanhf(cs * w.Wa0[4 * c4] + w.ba0[4 * c4]);
-        v.y = tanhf(cs * w.Wa0[4 * c4 + 1] + w.ba0[4 * c4 + 1]);
-        v.z = tanhf(cs * w.Wa0[4 * c4 + 2] + w.ba0[4 * c4 + 2]);
-        v.w = tanhf(cs * w.Wa0[4 * c4 + 3] + w.ba0[4 * c4 + 3]);
-        return v;
-      });
-      wave_sync();
-      int qrow[2][4];
+    for (int t = 0; t < 4; ++t) wm[t].load(frag<T>(w.Mg[l]), t);
+    const auto rows_in = [&](int p, int t0, f4 (&v)[2]) {  // a of angle t0 + c of row p (layers > 0)
+      const int t = t0 + c;
+      const float *ap = b.af + ((size_t)(l - 1) * b.acap + abase + (int64_t)p * na + t) * ADIM + 4 * q;
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
+      for (int k = 0; k < 2; ++k) v[k] = t < na ? ldf4(ap + 16 * k) : f4{0.f, 0.f, 0.f, 0.f};
+    };
+    f4 nxt[2];
+    if (l > 0 && wv < nc && na > 0) rows_in(wv, 0, nxt);
+    for (int p = wv; p < nc; p += NW) {
+      const int jp = e.cl[p];
+      const float swp = e.swa[jp] * geo.inv_asel;
+      f4 bp[2], m[4] = {};
 #pragma unroll
-        for (int ii = 0; ii < 4; ++ii) {
-          const int t = t0 + 16 * h + acc_row(ii);
-          qrow[h][ii] = t < na ? t + (t >= p) : p;  // rows past the end read a valid row, and are not used
+      for (int k = 0; k < 2; ++k) bp[k] = ldf4(sm.PQ + p * LPQ + 16 * k + 4 * q);
+      for (int t0 = 0; t0 < na; t0 += 16) {
+        const int t = t0 + c;
+        const bool ok = t < na;
+        const int qr = ok ? t + (t >= p) : p;  // columns past the end read a valid row, unused
+        f4 a[2];
+        if (l > 0) {
+          a[0] = nxt[0];
+          a[1] = nxt[1];
+          const bool more = t0 + 16 < na;  // the next tile's rows are read while this one is processed
+          const int pn = more ? p : p + NW;
+          if (pn < nc) rows_in(pn, more ? t0 + 16 : 0, nxt);
+        } else {
+          const float cs = cosang(e, jp, e.cl[qr]);
+#pragma unroll
+          for (int k = 0; k < 2; ++k) a[k] = init4(cs, w.Wa0 + 16 * k + 4 * q, w.ba0 + 16 * k + 4 * q);
         }
-      f4 aa[2][2] = {};
+        const float *pq = sm.PQ + qr * LPQ + 4 * q;
+        {
+          const X<T, 2> x(a);
 #pragma unroll
-      for (int ct = 0; ct < 2; ++ct) {
-        fa[ct].mma(aa[0][ct], rowA, Ident());
-        fa[ct].mma(aa[1][ct], rowA, second);
-      }
-      wave_sync();
+          for (int k = 0; k < 2; ++k) a[k] += act(wa[k](x, f4{0.f, 0.f, 0.f, 0.f}) + bp[k] + ldf4(pq + 32 + 16 * k));
+        }
+        if (ok) {
+          float *ao = b.af + ((size_t)l * b.acap + abase + (int64_t)p * na + t) * ADIM + 4 * q;
+          stf4(ao, a[0]);
+          stf4(ao + 16, a[1]);
+        }
+        const X<T, 2> x(a);
+        const float wr = ok ? swp * e.swa[e.cl[qr]] : 0.f;
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int ct = 0; ct < 2; ++ct)
-#pragma unroll
-          for (int ii = 0; ii < 4; ++ii) {
-            const int r = acc_row(ii), c = ct * 16 + acc_col(), t = t0 + 16 * h + r;
-            const float z = aa[h][ct][ii] + baa[c] + sm.PQ[p * PQW + c] + sm.PQ[qrow[h][ii] * PQW + ADIM + c];
-            const float a1 = sl[r * LDF + ADIM * h + c] + act<T>(z);
-            sl[r * LDF + ADIM * h + c] = a1;
-            if (t < na) b.af[((size_t)l * b.acap + abase + (int64_t)p * na + t) * ADIM + c] = a1;
-          }
-      wave_sync();
-      f4 am[2][4] = {};
-#pragma unroll
-      for (int ct = 0; ct < 4; ++ct) {
-        fm[ct].mma(am[0][ct], rowA, Ident());
-        fm[ct].mma(am[1][ct], rowA, second);
+        for (int k = 0; k < 4; ++k) m[k] += wr * act(wm[k](x, f4{0.f, 0.f, 0.f, 0.f}) + ldf4(pq + 64 + 16 * k));
       }
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int ii = 0; ii < 4; ++ii) {
-          const int t = t0 + 16 * h + acc_row(ii);
-          const float wr = t < na ? e.swa[jp] * e.swa[e.cl[qrow[h][ii]]] * geo.inv_asel : 0.f;
-#pragma unroll
-          for (int ct = 0; ct < 4; ++ct) {
-            const int c = ct * 16 + acc_col();
-            mr[ct] += wr * act<T>(am[h][ct][ii] + bea[c] + sm.PQ[qrow[h][ii] * PQW + 2 * ADIM + c]);
-          }
-        }
-      wave_sync();
-    }
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct) {
-      const float v = sum_cols4(mr[ct]);
-      if (ln < 16) sm.Msg[p * EDIM + ct * 16 + ln] = v;
+      for (int k = 0; k < 4; ++k) {
+        const f4 v = sum16(m[k]);
+        if (c == 0) stf4(sm.Msg + p * LMS + 16 * k + 4 * q, v);
+      }
     }
   }
   __syncthreads();
 
   // ---------------- edges
-  float aw[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int j0 = wv * 16; j0 < nn; j0 += NWG * 16) {
-    // [n_i, n_j, e_ij]
-    stage<4, 2>(sl, LDF, [&](int sg, int r, int c4) -> float4 {  // [n_j, e_ij]; n_i enters through nbias
-      const int j = j0 + r;
-      if (j >= nn) return make_float4(0.f, 0.f, 0.f, 0.f);
-      const int c = 32 * (sg & 1) + 4 * c4;
-      if (sg < 2)
-        return l == 0 ? ld4(w.TN + e.tj[j] * NDIM + c) : ld4(b.nf + ((size_t)(l - 1) * b.cap + e.jn[j]) * NDIM + c);
-      return ld4(sm.El + j * LDE + c);
-    });
-    wave_sync();
-    f4 ae[4] = {};
+  f4 aw[4] = {};
+  for (int j0 = wv * 16; j0 < nn; j0 += NW * 16) {
+    const bool ok = j0 + c < nn;
+    const int j = ok ? j0 + c : 0;
+    f4 x[8];  // [n_j, e_ij]; n_i enters through nbias
 #pragma unroll
-    for (int ct = 0; ct < 4; ++ct) {
-      opaque();  // load each column tile's weights here, not once for all tiles
-      Frag<T, 128> f;
-      f.load([&](int c, int k) { return Wee[(NDIM + k) * EDIM + ct * 16 + c]; });
-      f.mma(ae[ct], rowA, Ident());
+    for (int k = 0; k < 4; ++k) x[k] = node_in(w, b, e, l, j, 16 * k + 4 * q);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[4 + k] = edge_in(w, b, e, l, i, j, 16 * k + 4 * q);
+    const X<T, 8> xo(x);
+    const int cp = ok ? e.cpos[j] : -1;
+    const float swj = ok ? e.swe[j] : 0.f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      tile_barrier();
+      W<T, 8> wt;
+      wt.load(frag<T>(w.E[l]), k);
+      f4 v = x[4 + k] + act(wt(xo, f4{0.f, 0.f, 0.f, 0.f}) + ldf4(sm.nbias + 16 * k + 4 * q));
+      if (cp >= 0) v += ldf4(sm.Msg + cp * LMS + 16 * k + 4 * q);
+      if (ok) stf4(b.ef + erow(b, l, i, j) + 16 * k + 4 * q, v);
+      aw[k] += swj * v;
     }
-#pragma unroll
-    for (int ii = 0; ii < 4; ++ii) {
-      const int j = j0 + acc_row(ii);
-      if (j < nn) {
-        const int cp = e.cpos[j];
-#pragma unroll
-        for (int ct = 0; ct < 4; ++ct) {
-          const int c = ct * 16 + acc_col();
-          const float e1 =
-              sm.El[j * LDE + c] + act<T>(ae[ct][ii] + sm.nbias[c]) + (cp >= 0 ? sm.Msg[cp * EDIM + c] : 0.f);
-          b.ef[erow(b, l, i, j) + c] = e1;
-          aw[ct] += e.swe[j] * e1;
-        }
-      }
-    }
-    wave_sync();
   }
 #pragma unroll
-  for (int ct = 0; ct < 4; ++ct) {
-    const float v = sum_cols4(aw[ct]);
-    if (ln < 16) sm.aggw[wv][ct * 16 + ln] = v;
+  for (int k = 0; k < 4; ++k) {
+    const f4 v = sum16(aw[k]);
+    if (c == 0) stf4(sm.aggw[wv] + 16 * k + 4 * q, v);
   }
   __syncthreads();
 
   // ---------------- node
   if (tid < NDIM) {
+    float v = 0.f;
+    for (int u = 0; u < NW; ++u) v += sm.aggw[u][tid];
     sm.xs[tid] = sm.ni[tid];
-    sm.xs[NDIM + tid] = (sm.aggw[0][tid] + sm.aggw[1][tid] + sm.aggw[2][tid] + sm.aggw[3][tid]) * geo.inv_sel;
+    sm.xs[NDIM + tid] = v * geo.inv_sel;
   }
-  __syncthreads();
+  const float z = matvec<NW, 2 * NDIM, NDIM>(w.Wnn[l], sm.xs, sm.part);
   float n1 = 0.f;
   if (tid < NDIM) {
-    float z = bnn[tid];
-    for (int k = 0; k < 2 * NDIM; ++k) z += sm.xs[k] * Wnn[k * NDIM + tid];
-    n1 = sm.ni[tid] + tanhf(z);
+    n1 = sm.ni[tid] + tanhf(z + w.bnn[l][tid]);
     if (l < NLAYER - 1) b.nf[((size_t)l * b.cap + i) * NDIM + tid] = n1;
   }
   if (l < NLAYER - 1) return;
 
   // ---------------- fitting net, E_i and dE/dn_i
-  __syncthreads();
-  if (tid < NDIM) sm.ni[tid] = n1;
-  __syncthreads();
+  if (tid < NDIM) sm.xs[tid] = n1;
+  const float z1 = matvec<NW, NDIM, FWID>(w.G1, sm.xs, sm.part);
+  if (tid < FWID) sm.y1[tid] = tanhf(z1 + w.d1[tid]);
+  const float z2 = matvec<NW, FWID, FWID>(w.G2, sm.y1, sm.part);
   if (tid < FWID) {
-    float z = w.d1[tid];
-    for (int k = 0; k < NDIM; ++k) z += sm.ni[k] * w.G1[k * FWID + tid];
-    sm.y1[tid] = tanhf(z);
-  }
-  __syncthreads();
-  if (tid < FWID) {
-    float z = w.d2[tid];
-    for (int k = 0; k < FWID; ++k) z += sm.y1[k] * w.G2[k * FWID + tid];
-    const float t2 = tanhf(z);
+    const float t2 = tanhf(z2 + w.d2[tid]);
     sm.t2[tid] = t2;
     sm.dp[tid] = w.G3[tid] * (1.f - t2 * t2);
   }
-  __syncthreads();
-  if (tid == 0) {
-    double E = w.d3;
-    for (int k = 0; k < FWID; ++k) E += (double)(sm.t2[k] + sm.y1[k]) * w.G3d[k];
-    Ei[i] = E;
+  const float z3 = matvec<NW, FWID, FWID>(w.G2T, sm.dp, sm.part);  // its first barrier: t2 is complete
+  if (wv == 0) {
+    double E = (double)(sm.t2[ln] + sm.y1[ln]) * w.G3d[ln] + (double)(sm.t2[ln + 64] + sm.y1[ln + 64]) * w.G3d[ln + 64];
+    for (int off = 32; off > 0; off >>= 1) E += __shfl_xor(E, off);
+    if (ln == 0) Ei[i] = w.d3 + E;
   }
   float dp1 = 0.f;
-  if (tid < FWID) {
-    float dy1 = w.G3[tid];
-    for (int k = 0; k < FWID; ++k) dy1 += sm.dp[k] * w.G2[tid * FWID + k];
-    dp1 = dy1 * (1.f - sm.y1[tid] * sm.y1[tid]);
-  }
+  if (tid < FWID) dp1 = (z3 + w.G3[tid]) * (1.f - sm.y1[tid] * sm.y1[tid]);
   __syncthreads();
   if (tid < FWID) sm.dp[tid] = dp1;
-  __syncthreads();
-  if (tid < NDIM) {
-    float dn = 0.f;
-    for (int k = 0; k < FWID; ++k) dn += sm.dp[k] * w.G1[tid * FWID + k];
-    b.dnl[(size_t)i * NDIM + tid] = dn;
-  }
+  const float dn = matvec<NW, FWID, NDIM>(w.G1T, sm.dp, sm.part);
+  if (tid < NDIM) b.dnl[(size_t)i * NDIM + tid] = dn;
 }
 
 // ------------------------------------------------------------------ backward
-struct SmemB {
+template <int NW> struct SmemB {
   GEnv env;
-  float DEl[SEL * EDIM];      // dE/de of this layer's input edges
-  float DM[ASEL * EDIM];      // dE/dm_ip
-  float Ec[ASEL * ADIM] __attribute__((aligned(16)));  // e[:32] of the angle-list edges
-  float slab[NWG][16 * LDB] __attribute__((aligned(16)));
-  float Qacc[NWG][ASEL * QLD];  // per-wave sums of the terms of edge q
-  float Pacc[ASEL * QLD];       // terms of edge p from its own angle row
-  float PQ[ASEL * PQW];         // per-edge terms of the angle products
-  float dn[NDIM], ni[NDIM] __attribute__((aligned(16))), xs[2 * NDIM], dagg[NDIM], dnsum[NWG][NDIM], zz[NDIM],
-      nbias[EDIM];
-  int slot[SEL];
+  float P[NW][ASEL * LPP] __attribute__((aligned(16)));  // per-wave sums of the terms of edge p
+  float SZ[ASEL * LSZ] __attribute__((aligned(16)));     // terms of edge q; once its wave is done with q, sums over its angles
+  float PP[ASEL * LPP] __attribute__((aligned(16)));     // terms of edge p
+  float DM[ASEL * LMS] __attribute__((aligned(16)));     // dE/dm_ip
+  float nbias[EDIM] __attribute__((aligned(16))), dagg[NDIM] __attribute__((aligned(16)));
+  float dnsum[NW][NDIM] __attribute__((aligned(16)));
+  float dn[NDIM], ni[NDIM], xs[2 * NDIM], zz[NDIM], part[NW * 64], ds[SEL];
 };
 
-template <typename T>
-__global__ void __launch_bounds__(NT) k_layer_bwd(Weights w, Buffers b, const double *__restrict__ X,
-                                                  const int *__restrict__ types, const int *__restrict__ nlist,
-                                                  const int *__restrict__ nnei, const Grid *__restrict__ grids,
-                                                  int n, int layer, Geo geo, float4 *__restrict__ gout,
-                                                  const unsigned *__restrict__ flags) {
-  __shared__ SmemB sm;
+template <typename T, int NW>
+__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2)))
+k_layer_bwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__restrict__ types,
+            const int *__restrict__ nlist, const int *__restrict__ nnei, const Grid *__restrict__ grids, int n, int layer,
+            Geo geo, float4 *__restrict__ gout, const unsigned *__restrict__ flags) {
+  __shared__ SmemB<NW> sm;
   const int i = blockIdx.x;
   if (i >= n || failed(flags)) return;
-  const int tid = threadIdx.x, wv = wave_id(), ln = lane_id();
-  build_genv(sm.env, X, types, nlist, nnei, i, n, grids[0], geo);
+  const int tid = threadIdx.x, wv = wave_id(), ln = lane_id(), q = ln >> 4, c = ln & 15;
+  build_genv<NW * 64>(sm.env, Xc, types, nlist, nnei, i, n, grids[0], geo);
   const GEnv &e = sm.env;
   const int nn = e.nn, nc = e.nc, l = layer;
-  const float *Waa = w.Waa[l], *baa = w.baa[l], *Wea = w.Wea[l], *bea = w.bea[l];
-  const float *Wee = w.Wee[l], *bee = w.bee[l], *Wnn = w.Wnn[l], *bnn = w.bnn[l];
   const bool top = l == NLAYER - 1;
+  const f4 zero = {0.f, 0.f, 0.f, 0.f};
 
-  // ---------------- dE/dn_i after this layer: own part + the neighbours' edge parts
-  if (!top)
-    for (int j = tid; j < nn; j += NT) sm.slot[j] = b.slot[(size_t)i * SEL + j];
-  for (int k = tid; k < nc * ADIM; k += NT) {
-    const int p = k >> 5, c = k & 31, j = e.cl[p];
-    sm.Ec[k] = l == 0 ? tanhf(e.s[j] * w.We0[c] + w.be0[c]) : b.ef[erow(b, l - 1, i, j) + c];
-  }
   if (tid < NDIM)
     sm.ni[tid] = l == 0 ? w.TN[clamp_type(types[i]) * NDIM + tid] : b.nf[((size_t)(l - 1) * b.cap + i) * NDIM + tid];
-  __syncthreads();
+  edge_terms<NW>(w, b, e, l, i, [&](int x, int col, f4 v) {
+    if (col < ADIM) stf4(sm.PP + x * LPP + col, v);
+    else stf4(sm.SZ + x * LSZ + col - ADIM, v);
+  });
+  for (int k = tid; k < NW * nc * LPP; k += NW * 64) sm.P[k / (nc * LPP)][k % (nc * LPP)] = 0.f;
+  // ---------------- dE/dn_i after this layer: own part + the neighbours' edge parts; each wave
+  // sums the rows j = wave, wave + NW, ... in list order (the neighbours' parts, and agg from
+  // the stored output edges), the waves combine in order
+  float dnw = 0.f, aggw = 0.f;
   {
-    // each wave sums the rows j = wave, wave + 4, ... in list order (the neighbours' edge
-    // parts of dE/dn_i, and agg from the stored output edges); waves combine in order
-    float dn = 0.f, agg = 0.f;
     const float *src = b.dnj + (size_t)((l + 1) & 1) * b.cap * SEL * EDIM;
 #pragma unroll 8
-    for (int j = wv; j < nn; j += NWG) {
+    for (int j = wv; j < nn; j += NW) {
       if (!top) {  // branch-free in j (a missing slot reads row 0 and adds 0), so the loads overlap
-        const int sj = sm.slot[j];
+        const int sj = b.slot[(size_t)i * SEL + j];
         const float x = src[((size_t)e.jn[j] * SEL + max(sj, 0)) * EDIM + ln];
-        dn += sj >= 0 ? x : 0.f;
+        dnw += sj >= 0 ? x : 0.f;
       }
-      agg += e.swe[j] * b.ef[erow(b, l, i, j) + ln];
+      aggw += e.swe[j] * b.ef[erow(b, l, i, j) + ln];
     }
-    sm.dnsum[wv][ln] = dn;
-    sm.Pacc[wv * EDIM + ln] = agg;
   }
+  sm.dnsum[wv][ln] = dnw;
   __syncthreads();
   if (tid < NDIM) {
-    float dn = b.dnl[(size_t)i * NDIM + tid], agg = 0.f;
-    for (int u = 0; u < NWG; ++u) {
-      dn += sm.dnsum[u][tid];
-      agg += sm.Pacc[u * EDIM + tid];
-    }
+    float dn = b.dnl[(size_t)i * NDIM + tid];
+    for (int u = 0; u < NW; ++u) dn += sm.dnsum[u][tid];
     sm.dn[tid] = dn;
+  }
+  __syncthreads();
+  sm.dnsum[wv][ln] = aggw;
+  __syncthreads();
+  if (tid < NDIM) {
+    float agg = 0.f;
+    for (int u = 0; u < NW; ++u) agg += sm.dnsum[u][tid];
     sm.xs[tid] = sm.ni[tid];
     sm.xs[NDIM + tid] = agg * geo.inv_sel;
   }
-  __syncthreads();
   // ---------------- node backward (and the centre's part of every edge update)
-  if (tid < EDIM) {
-    float v = bee[tid];
-    for (int k = 0; k < NDIM; ++k) v += sm.ni[k] * Wee[k * EDIM + tid];
-    sm.nbias[tid] = v;
-  }
-  if (tid < NDIM) {
-    float z = bnn[tid];
-    for (int k = 0; k < 2 * NDIM; ++k) z += sm.xs[k] * Wnn[k * NDIM + tid];
-    const float t = tanhf(z);
-    sm.zz[tid] = sm.dn[tid] * (1.f - t * t);
-  }
-  __syncthreads();
-  if (tid < NDIM) {
-    float dni = sm.dn[tid], dg = 0.f;
-    for (int k = 0; k < NDIM; ++k) {
-      dni += sm.zz[k] * Wnn[tid * NDIM + k];
-      dg += sm.zz[k] * Wnn[(NDIM + tid) * NDIM + k];
+  {
+    const float v = matvec<NW, NDIM, EDIM>(w.Wee[l], sm.ni, sm.part);
+    if (tid < EDIM) sm.nbias[tid] = v + w.bee[l][tid];
+    const float z = matvec<NW, 2 * NDIM, NDIM>(w.Wnn[l], sm.xs, sm.part);
+    if (tid < NDIM) {
+      const float t = tanhf(z + w.bnn[l][tid]);
+      sm.zz[tid] = sm.dn[tid] * (1.f - t * t);
     }
-    sm.dn[tid] = dni;  // now dE/dn_i of this layer's input, without the edge terms
-    sm.dagg[tid] = dg * geo.inv_sel;
+    const float d = matvec<NW, NDIM, 2 * NDIM>(w.WnnT[l], sm.zz, sm.part);
+    if (tid < NDIM) sm.dn[tid] += d;  // now dE/dn_i of this layer's input, without the edge terms
+    else if (tid < 2 * NDIM) sm.dagg[tid - NDIM] = d * geo.inv_sel;
   }
   __syncthreads();
 
-  float *sl = sm.slab[wv];
-  const float *rowA = sl + (ln & 15) * LDB;
   // ---------------- edges
-  float dns[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int j0 = wv * 16; j0 < nn; j0 += NWG * 16) {
-    stage<4, 2>(sl, LDB, [&](int sg, int r, int c4) -> float4 {  // [n_j, e_ij]; n_i enters through nbias
-      const int j = j0 + r;
-      if (j >= nn) return make_float4(0.f, 0.f, 0.f, 0.f);
-      const int c = 32 * (sg & 1) + 4 * c4;
-      if (sg < 2)
-        return l == 0 ? ld4(w.TN + e.tj[j] * NDIM + c) : ld4(b.nf + ((size_t)(l - 1) * b.cap + e.jn[j]) * NDIM + c);
-      if (l > 0) return ld4(b.ef + erow(b, l - 1, i, j) + c);
-      float4 v;
-      v.x = tanhf(e.s[j] * w.We0[c] + w.be0[c]);
-      v.y = tanhf(e.s[j] * w.We0[c + 1] + w.be0[c + 1]);
-      v.z = tanhf(e.s[j] * w.We0[c + 2] + w.be0[c + 2]);
-      v.w = tanhf(e.s[j] * w.We0[c + 3] + w.be0[c + 3]);
-      return v;
-    });
-    float pde[4][4], pef[4][4];  // dE/de and e of the layer's output, read ahead of their use
+  f4 dns[4] = {};
+  for (int j0 = wv * 16; j0 < nn; j0 += NW * 16) {
+    const bool ok = j0 + c < nn;
+    const int j = ok ? j0 + c : 0;
+    f4 ein[4], de1[4], dz[4];
+    float rs = 0.f;
+    {
+      f4 x[8];
 #pragma unroll
-    for (int ii = 0; ii < 4; ++ii) {
-      const int j = j0 + acc_row(ii);
+      for (int k = 0; k < 4; ++k) x[k] = node_in(w, b, e, l, j, 16 * k + 4 * q);
 #pragma unroll
-      for (int ct = 0; ct < 4; ++ct) {
-        const int c = ct * 16 + acc_col();
-        pde[ct][ii] = (!top && j < nn) ? b.de[((size_t)i * SEL + j) * EDIM + c] : 0.f;
-        pef[ct][ii] = j < nn ? b.ef[erow(b, l, i, j) + c] : 0.f;
+      for (int k = 0; k < 4; ++k) x[4 + k] = edge_in(w, b, e, l, i, j, 16 * k + 4 * q);
+      f4 eo[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        ein[k] = x[4 + k];
+        eo[k] = ldf4(b.ef + erow(b, l, i, j) + 16 * k + 4 * q);
+        de1[k] = top ? zero : ldf4(b.de + ((size_t)i * SEL + j) * EDIM + 16 * k + 4 * q);
+      }
+      const X<T, 8> xo(x);
+      const float swj = e.swe[j];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        tile_barrier();
+        W<T, 8> wt;
+        wt.load(frag<T>(w.E[l]), k);
+        const f4 te = act(wt(xo, zero) + ldf4(sm.nbias + 16 * k + 4 * q));
+        const f4 dg = ldf4(sm.dagg + 16 * k + 4 * q);
+        const f4 pr = eo[k] * dg;
+        rs += (pr[0] + pr[1]) + (pr[2] + pr[3]);
+        de1[k] = ok ? de1[k] + swj * dg : zero;
+        dz[k] = de1[k] * (1.f - te * te);
+        dns[k] += dz[k];
       }
     }
-    wave_sync();
-    f4 ae[4] = {};
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct) {
-      if constexpr (sizeof(T) == 2) {
-        opaque();  // load each column tile's weights here, not once for all tiles
-        Frag<T, 128> f;
-        f.load([&](int c, int k) { return Wee[(NDIM + k) * EDIM + ct * 16 + c]; });
-        f.mma(ae[ct], rowA, Ident());
-      } else {  // float32 operands: 32 more registers per lane would spill; read W as it goes
-        Mma<T>::tile(ae[ct], [&](int r, int k) { return sl[r * LDB + k]; },
-                     [&](int c, int k) { return Wee[(NDIM + k) * EDIM + ct * 16 + c]; }, 128);
-      }
+    rs = sumq(rs);
+    if (ok && q == 0) {
+      float *g = b.gs + ((size_t)i * SEL + j) * 2;
+      g[0] = top ? rs : g[0] + rs;
     }
-    wave_sync();
-    float de1[4][4], rs[4];
-#pragma unroll
-    for (int ii = 0; ii < 4; ++ii) {
-      const int r = acc_row(ii), j = j0 + r;
-      const bool ok = j < nn;
-      rs[ii] = 0.f;
-#pragma unroll
-      for (int ct = 0; ct < 4; ++ct) {
-        const int c = ct * 16 + acc_col();
-        float d = 0.f, dz = 0.f;
-        if (ok) {
-          d = pde[ct][ii] + e.swe[j] * sm.dagg[c];
-          rs[ii] += pef[ct][ii] * sm.dagg[c];
-          const float t = act<T>(ae[ct][ii] + sm.nbias[c]);
-          dz = d * (1.f - t * t);
-        }
-        de1[ct][ii] = d;
-        sl[r * LDB + c] = dz;  // dz_e over the n_j columns (the products that read them are done)
-        dns[ct] += dz;
-      }
-      rs[ii] = sum16(rs[ii]);
-    }
-#pragma unroll
-    for (int ii = 0; ii < 4; ++ii) {
-      const int j = j0 + acc_row(ii);
-      if (j < nn && acc_col() == 0) {
-        float *g = b.gs + ((size_t)i * SEL + j) * 2;
-        g[0] = top ? rs[ii] : g[0] + rs[ii];
-      }
-    }
-    wave_sync();
+    const X<T, 4> xz(dz);
     if (l > 0) {  // edge (i, j)'s part of dE/dn_j
-      float *dst = b.dnj + (size_t)(l & 1) * b.cap * SEL * EDIM;
-      f4 an[4] = {};
+      float *dst = b.dnj + (size_t)(l & 1) * b.cap * SEL * EDIM + ((size_t)i * SEL + j) * EDIM + 4 * q;
 #pragma unroll
-        for (int ct = 0; ct < 4; ++ct) {
-        opaque();
-        Frag<T, 64> f;
-        f.load([&](int c, int k) { return Wee[(NDIM + ct * 16 + c) * EDIM + k]; });
-        f.mma(an[ct], rowA, Ident());
-      }
-#pragma unroll
-      for (int ii = 0; ii < 4; ++ii) {
-        const int j = j0 + acc_row(ii);
-        if (j < nn)
-#pragma unroll
-          for (int ct = 0; ct < 4; ++ct) dst[((size_t)i * SEL + j) * EDIM + ct * 16 + acc_col()] = an[ct][ii];
+      for (int k = 0; k < 4; ++k) {
+        tile_barrier();
+        W<T, 4> wt;
+        wt.load(frag<T>(w.N[l]), k);
+        const f4 v = wt(xz, zero);
+        if (ok) stf4(dst + 16 * k, v);
       }
     }
-    f4 ad[4] = {};
+    const int cp = ok ? e.cpos[j] : -1;
+    float ds = 0.f;
 #pragma unroll
-    for (int ct = 0; ct < 4; ++ct) {
-      opaque();
-      Frag<T, 64> f;
-      f.load([&](int c, int k) { return Wee[(2 * NDIM + ct * 16 + c) * EDIM + k]; });
-      f.mma(ad[ct], rowA, Ident());
-    }
-#pragma unroll
-    for (int ii = 0; ii < 4; ++ii) {
-      const int j = j0 + acc_row(ii);
-      if (j < nn) {
-        const int cp = e.cpos[j];
-#pragma unroll
-        for (int ct = 0; ct < 4; ++ct) {
-          const int c = ct * 16 + acc_col();
-          sm.DEl[j * EDIM + c] = de1[ct][ii] + ad[ct][ii];
-          if (cp >= 0) sm.DM[cp * EDIM + c] = de1[ct][ii];
-        }
+    for (int k = 0; k < 4; ++k) {
+      tile_barrier();
+      W<T, 4> wt;
+      wt.load(frag<T>(w.D[l]), k);
+      const f4 v = de1[k] + wt(xz, zero);  // dE/de of the layer's input; the angle terms are added below
+      const int f = 16 * k + 4 * q;
+      if (cp >= 0) stf4(sm.DM + cp * LMS + f, de1[k]);
+      if (l > 0) {
+        if (ok) stf4(b.de + ((size_t)i * SEL + j) * EDIM + f, v);
+      } else {
+        const f4 g = v * (1.f - ein[k] * ein[k]) * ldf4(w.We0 + f);
+        ds += (g[0] + g[1]) + (g[2] + g[3]);
       }
     }
-    wave_sync();
+    if (l == 0) {
+      ds = sumq(ds);
+      if (ok && q == 0) sm.ds[j] = ds;
+    }
   }
 #pragma unroll
-  for (int ct = 0; ct < 4; ++ct) {
-    const float v = sum_cols4(dns[ct]);
-    if (ln < 16) sm.dnsum[wv][ct * 16 + ln] = v;
+  for (int k = 0; k < 4; ++k) {
+    const f4 v = sum16(dns[k]);
+    if (c == 0) stf4(sm.dnsum[wv] + 16 * k + 4 * q, v);
   }
-  float *Q = sm.Qacc[wv];
-  for (int k = ln; k < ASEL * QLD; k += 64) Q[k] = 0.f;
   __syncthreads();
 
   // ---------------- angles
-  // this layer's angle weights in registers: forward recomputation (Wea, Waa) and the
-  // transposed products (Wea^T, Waa^T, and [Wea; Waa]^T for the terms of edge q)
-  // ([Wea; Waa]^T stays in registers only for bf16 operands: as float32 it would not fit
-  // beside the rest and is reloaded for each tile)
-  constexpr bool FV_RESIDENT = sizeof(T) == 2;
-  auto wv_q = [&](int ct) {
-    return [=](int c, int k) {
-      return k < 64 ? Wea[(32 + ct * 16 + c) * EDIM + k] : Waa[(64 + ct * 16 + c) * ADIM + k - 64];
-    };
-  };
-  Frag<T, ADIM> fm[4], fa[2];  // the angle rows' parts (first 32 inputs) of Wea, Waa
-  Frag<T, 64> fx[2];
-  Frag<T, 96> fv[FV_RESIDENT ? 2 : 1];
-  Frag<T, 32> fy[2];
-#pragma unroll
-  for (int ct = 0; ct < 4; ++ct) fm[ct].load([&](int c, int k) { return Wea[k * EDIM + ct * 16 + c]; });
-#pragma unroll
-  for (int ct = 0; ct < 2; ++ct) {
-    fa[ct].load([&](int c, int k) { return Waa[k * ADIM + ct * 16 + c]; });
-    fx[ct].load([&](int c, int k) { return Wea[(ct * 16 + c) * EDIM + k]; });
-    fy[ct].load([&](int c, int k) { return Waa[(ct * 16 + c) * ADIM + k]; });
-    if constexpr (FV_RESIDENT) fv[ct].load(wv_q(ct));
-  }
-  edge_terms(Waa, Wea, sm.Ec, 0, e.cl, nc, sm.PQ);
   const int na = nc - 1;
   const int64_t abase = b.aoff[i];
-  for (int p = wv; p < nc; p += NWG) {
-    const int jp = e.cl[p];
-    float S[2] = {0.f, 0.f};      // column sums of dz_a
-    float sp = 0.f, hp[3] = {0.f, 0.f, 0.f};  // dE/dsw_a(r_ip), dE/drhat_ip from this row
-    const float *a1p = b.af + ((size_t)l * b.acap + abase + (int64_t)p * na) * ADIM;
-    const float *a0p = b.af + ((size_t)(l > 0 ? l - 1 : 0) * b.acap + abase + (int64_t)p * na) * ADIM;
-    for (int t0 = 0; t0 < na; t0 += 16) {
-      // [a', a] of the tile's 16 angles; the edge terms come from PQ
-      stage<2, 2>(sl, LDB, [&](int sg, int r, int c4) -> float4 {
-        const int t = t0 + r;
-        if (t >= na) return make_float4(0.f, 0.f, 0.f, 0.f);
-        if (sg == 0) return ld4(a1p + (size_t)t * ADIM + 4 * c4);
-        if (l > 0) return ld4(a0p + (size_t)t * ADIM + 4 * c4);
-        const float cs = cosang(e, jp, e.cl[t + (t >= p)]);
-        const int c = 4 * c4;
-        float4 v;
-        v.x = tanhf(cs * w.Wa0[c] + w.ba0[c]);
-        v.y = tanhf(cs * w.Wa0[c + 1] + w.ba0[c + 1]);
-        v.z = tanhf(cs * w.Wa0[c + 2] + w.ba0[c + 2]);
-        v.w = tanhf(cs * w.Wa0[c + 3] + w.ba0[c + 3]);
-        return v;
-      });
-      float dap[2][4];  // dE/da of the layer's output, read ahead of its use
+  {
+    W<T, 2> wm[4], wa[2], wy[2];  // recomputation, and the transposed products
+    W<T, 4> wx[2];
 #pragma unroll
-      for (int ii = 0; ii < 4; ++ii) {
-        const int t = t0 + acc_row(ii);
+    for (int k = 0; k < 4; ++k) wm[k].load(frag<T>(w.Mg[l]), k);
 #pragma unroll
-        for (int ct = 0; ct < 2; ++ct)
-          dap[ct][ii] = (!top && t < na) ? b.da[(size_t)(abase + (int64_t)p * na + t) * ADIM + ct * 16 + acc_col()] : 0.f;
-      }
-      wave_sync();
-      f4 am[4] = {}, aa[2] = {};
+    for (int k = 0; k < 2; ++k) {
+      wa[k].load(frag<T>(w.A[l]), k);
+      wx[k].load(frag<T>(w.Xt[l]), k);
+      wy[k].load(frag<T>(w.Yt[l]), k);
+    }
+    float *P = sm.P[wv];
+    for (int qq = wv; qq < nc; qq += NW) {
+      const int jq = e.cl[qq];
+      const float swq = e.swa[jq] * geo.inv_asel;
+      const float rq[3] = {e.rh[3 * jq], e.rh[3 * jq + 1], e.rh[3 * jq + 2]};
+      float *row = sm.SZ + qq * LSZ;
+      f4 ba[2], bm[4], za[2] = {}, zm[4] = {};
 #pragma unroll
-      for (int ct = 0; ct < 4; ++ct) fm[ct].mma(am[ct], rowA, Ident());  // a' (columns 0..31)
+      for (int k = 0; k < 2; ++k) ba[k] = ldf4(row + 16 * k + 4 * q);
 #pragma unroll
-      for (int ct = 0; ct < 2; ++ct) fa[ct].mma(aa[ct], rowA, [](int k) { return ADIM + k; });  // a (32..63)
-      float dwa[4], ta[2][4];
-      int qv[4];
+      for (int k = 0; k < 4; ++k) bm[k] = ldf4(row + ADIM + 16 * k + 4 * q);
+      float sq = 0.f, hq[3] = {0.f, 0.f, 0.f};  // dE/dsw_a(r_iq), dE/drhat_iq
+      for (int t0 = 0; t0 < na; t0 += 16) {
+        const int t = t0 + c;
+        const bool ok = t < na;
+        const int p = ok ? t + (t >= qq) : 0;  // columns past the end read a valid row, unused
+        const int jp = e.cl[p];
+        const int64_t idx = ok ? abase + (int64_t)p * na + qq - (qq > p) : abase;
+        f4 a1[2], a0[2], da[2];
 #pragma unroll
-      for (int ii = 0; ii < 4; ++ii) {
-        const int r = acc_row(ii), t = t0 + r;
-        qv[ii] = t < na ? t + (t >= p) : -1;
-        const int qr = qv[ii] >= 0 ? qv[ii] : p;  // rows past the end read a valid row, unused
-        const float wr = qv[ii] >= 0 ? e.swa[jp] * e.swa[e.cl[qv[ii]]] * geo.inv_asel : 0.f;
-        float d = 0.f;
+        for (int k = 0; k < 2; ++k) a1[k] = ldf4(b.af + ((size_t)l * b.acap + idx) * ADIM + 16 * k + 4 * q);
+        if (l > 0) {
 #pragma unroll
-        for (int ct = 0; ct < 4; ++ct) {
-          const int c = ct * 16 + acc_col();
-          const float tm = act<T>(am[ct][ii] + bea[c] + sm.PQ[qr * PQW + 2 * ADIM + c]);
-          const float dm = qv[ii] >= 0 ? sm.DM[p * EDIM + c] : 0.f;
-          d += dm * tm;
-          sl[r * LDB + 64 + c] = wr * dm * (1.f - tm * tm);  // dz_m
-        }
-        dwa[ii] = sum16(d);
-#pragma unroll
-        for (int ct = 0; ct < 2; ++ct) {
-          const int c = ct * 16 + acc_col();
-          ta[ct][ii] = act<T>(aa[ct][ii] + baa[c] + sm.PQ[p * PQW + c] + sm.PQ[qr * PQW + ADIM + c]);
-        }
-      }
-      wave_sync();
-      f4 ax[2] = {};
-#pragma unroll
-      for (int ct = 0; ct < 2; ++ct) fx[ct].mma(ax[ct], rowA, [](int k) { return 64 + k; });
-      float da1[2][4];
-#pragma unroll
-      for (int ii = 0; ii < 4; ++ii) {
-        const int r = acc_row(ii);
-#pragma unroll
-        for (int ct = 0; ct < 2; ++ct) {
-          const int c = ct * 16 + acc_col();
-          float d = 0.f;
-          if (qv[ii] >= 0) d = dap[ct][ii] + ax[ct][ii];
-          da1[ct][ii] = d;
-          const float dz = d * (1.f - ta[ct][ii] * ta[ct][ii]);
-          sl[r * LDB + 128 + c] = dz;  // dz_a
-          S[ct] += dz;
-        }
-      }
-      wave_sync();
-      f4 ay[2] = {}, av[2] = {};
-#pragma unroll
-      for (int ct = 0; ct < 2; ++ct) {
-        fy[ct].mma(ay[ct], rowA, [](int k) { return 128 + k; });
-        if constexpr (FV_RESIDENT) {
-          fv[ct].mma(av[ct], rowA, [](int k) { return 64 + k; });
+          for (int k = 0; k < 2; ++k) a0[k] = ldf4(b.af + ((size_t)(l - 1) * b.acap + idx) * ADIM + 16 * k + 4 * q);
         } else {
-          opaque();
-          Frag<T, 96> f;
-          f.load(wv_q(ct));
-          f.mma(av[ct], rowA, [](int k) { return 64 + k; });
-        }
-      }
-      float dc[4];
+          const float cs = cosang(e, jp, jq);
 #pragma unroll
-      for (int ii = 0; ii < 4; ++ii) {
-        const int r = acc_row(ii);
+          for (int k = 0; k < 2; ++k) a0[k] = init4(cs, w.Wa0 + 16 * k + 4 * q, w.ba0 + 16 * k + 4 * q);
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) da[k] = top ? zero : ldf4(b.da + (size_t)idx * ADIM + 16 * k + 4 * q);
+        // the message: dE/dw and dz_m = w dE/dm (1 - tanh^2)
+        const float wr = ok ? e.swa[jp] * swq : 0.f;
         float d = 0.f;
+        f4 dz[4];
+        {
+          const X<T, 2> x(a1);
 #pragma unroll
-        for (int ct = 0; ct < 2; ++ct) {
-          const int c = ct * 16 + acc_col();
-          const float dal = da1[ct][ii] + ay[ct][ii];
-          if (qv[ii] >= 0) {
-            if (l > 0) b.da[(size_t)(abase + (int64_t)p * na + t0 + r) * ADIM + c] = dal;
-            Q[qv[ii] * QLD + c] += av[ct][ii];
-          }
-          if (l == 0) {
-            const float a0 = sl[r * LDB + ADIM + c];
-            d += dal * (1.f - a0 * a0) * w.Wa0[c];
+          for (int k = 0; k < 4; ++k) {
+            const f4 tm = act(wm[k](x, zero) + bm[k]);
+            const f4 dm = ldf4(sm.DM + p * LMS + 16 * k + 4 * q);
+            const f4 g = dm * tm;
+            d += (g[0] + g[1]) + (g[2] + g[3]);
+            dz[k] = wr * dm * (1.f - tm * tm);
+            zm[k] += dz[k];
           }
         }
-        dc[ii] = l == 0 ? sum16(d) : 0.f;
-      }
-      if (acc_col() == 0)
+        d = ok ? sumq(d) : 0.f;
+        // the angle update: dE/da' and dz_a
+        f4 ta[2];
+        {
+          const X<T, 2> x(a0);
 #pragma unroll
-        for (int ii = 0; ii < 4; ++ii) {
-          const int q = qv[ii];
-          if (q < 0) continue;
-          const int jq = e.cl[q];
-          Q[q * QLD + 32] += dwa[ii] * e.swa[jp] * geo.inv_asel;
-          sp += dwa[ii] * e.swa[jq] * geo.inv_asel;
+          for (int k = 0; k < 2; ++k) ta[k] = act(wa[k](x, zero) + ba[k] + ldf4(sm.PP + p * LPP + 16 * k + 4 * q));
+        }
+        f4 za1[2];
+        {
+          const X<T, 4> x(dz);
+#pragma unroll
+          for (int k = 0; k < 2; ++k) {
+            da[k] = ok ? wx[k](x, zero) + da[k] : zero;
+            za1[k] = da[k] * (1.f - ta[k] * ta[k]);
+            za[k] += za1[k];
+          }
+        }
+        {
+          const X<T, 2> x(za1);
+#pragma unroll
+          for (int k = 0; k < 2; ++k) da[k] += wy[k](x, zero);
+        }
+        float dc = 0.f;
+        if (l == 0) {
+#pragma unroll
+          for (int k = 0; k < 2; ++k) {
+            const f4 g = da[k] * (1.f - a0[k] * a0[k]) * ldf4(w.Wa0 + 16 * k + 4 * q);
+            dc += (g[0] + g[1]) + (g[2] + g[3]);
+          }
+          dc = sumq(dc);
+        }
+        if (ok) {
+          float *pp = P + p * LPP;
+#pragma unroll
+          for (int k = 0; k < 2; ++k) {
+            if (l > 0) stf4(b.da + (size_t)idx * ADIM + 16 * k + 4 * q, da[k]);
+            stf4(pp + 16 * k + 4 * q, ldf4(pp + 16 * k + 4 * q) + za1[k]);
+          }
+          const float sp = e.swa[jp] * geo.inv_asel;
+          sq += d * sp;
           if (l == 0)
-            for (int a = 0; a < 3; ++a) {
-              Q[q * QLD + 33 + a] += dc[ii] * e.rh[3 * jp + a];
-              hp[a] += dc[ii] * e.rh[3 * jq + a];
-            }
+            for (int a = 0; a < 3; ++a) hq[a] += dc * e.rh[3 * jp + a];
+          if (q == 0) {
+            f4 s = ldf4(pp + ADIM);
+            s[0] += d * swq;
+            if (l == 0)
+              for (int a = 0; a < 3; ++a) s[1 + a] += dc * rq[a];
+            stf4(pp + ADIM, s);
+          }
         }
+      }
+      // the sums over the angles of edge q, in place of its terms
+#pragma unroll
+      for (int k = 0; k < 2; ++k) za[k] = sum16(za[k]);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) zm[k] = sum16(zm[k]);
+      const f4 sh = sum16(f4{sq, hq[0], hq[1], hq[2]});
       wave_sync();
+      if (c == 0) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) stf4(row + 16 * k + 4 * q, za[k]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) stf4(row + ADIM + 16 * k + 4 * q, zm[k]);
+        if (q == 0) stf4(row + ADIM + EDIM, sh);
+      }
     }
-    // row p: its own edge's terms
-    S[0] = sum_cols4(S[0]);
-    S[1] = sum_cols4(S[1]);
-    sp = wave_sum64(sp);
-    for (int a = 0; a < 3; ++a) hp[a] = wave_sum64(hp[a]);
-    if (ln < 16) {
-      sl[ln] = S[0];
-      sl[16 + ln] = S[1];
-    }
-    wave_sync();
-    if (ln < ADIM) {
-      float v = 0.f;
-      for (int k = 0; k < ADIM; ++k) v += sl[k] * Waa[(ADIM + ln) * ADIM + k];
-      sm.Pacc[p * QLD + ln] = v;
-    }
-    if (ln == 0) {
-      sm.Pacc[p * QLD + 32] = sp;
-      for (int a = 0; a < 3; ++a) sm.Pacc[p * QLD + 33 + a] = hp[a];
-    }
-    wave_sync();
   }
   __syncthreads();
 
-  // ---------------- the angle terms of each angle-list edge, in wave order
-  for (int k = tid; k < nc * QLD; k += NT) {
-    const int q = k / QLD, c = k % QLD;
-    float v = sm.Pacc[k];
-    for (int u = 0; u < NWG; ++u) v += sm.Qacc[u][k];
-    if (c < ADIM) sm.DEl[e.cl[q] * EDIM + c] += v;
-    else sm.Pacc[k] = v;  // sw_a and rhat terms, complete
+  // ---------------- the angle terms of each angle-list edge: the waves' sums of edge p in wave
+  // order (sw_a and rhat complete with edge q's), then the weights once per edge
+  for (int k = tid; k < nc * LPP; k += NW * 64) {
+    const int x = k / LPP, f = k % LPP;
+    float v = sm.P[0][k];
+    for (int u = 1; u < NW; ++u) v += sm.P[u][k];
+    if (f >= ADIM) v += sm.SZ[x * LSZ + ADIM + EDIM + f - ADIM];
+    sm.P[0][k] = v;
   }
   if (tid < NDIM) {
     float s = 0.f;
-    for (int u = 0; u < NWG; ++u) s += sm.dnsum[u][tid];
+    for (int u = 0; u < NW; ++u) s += sm.dnsum[u][tid];
     sm.zz[tid] = s;
   }
   __syncthreads();
-  for (int j = tid; j < nn; j += NT) {
+  for (int x0 = 0; x0 < nc; x0 += 16) {
+    const bool ok = x0 + c < nc;
+    const int x = ok ? x0 + c : 0;
+    const int j = e.cl[x];
+    if (x0 / 16 % NW != wv) continue;
+    f4 v[8];  // [sum of dz_a over row p, over column q, sum of dz_m over column q]
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      v[k] = ldf4(sm.P[0] + x * LPP + 16 * k + 4 * q);
+      v[2 + k] = ldf4(sm.SZ + x * LSZ + 16 * k + 4 * q);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[4 + k] = ldf4(sm.SZ + x * LSZ + ADIM + 16 * k + 4 * q);
+    const X<float, 8> xo(v);
+    float ds = 0.f;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      W<float, 8> wt;
+      wt.load(w.PS[l], k);
+      const f4 d = wt(xo, zero);
+      const int f = 16 * k + 4 * q;
+      if (l > 0) {
+        float *o = b.de + ((size_t)i * SEL + j) * EDIM + f;
+        if (ok) stf4(o, ldf4(o) + d);
+      } else {
+        const f4 e0 = edge_in(w, b, e, 0, i, j, f);
+        const f4 g = d * (1.f - e0 * e0) * ldf4(w.We0 + f);
+        ds += (g[0] + g[1]) + (g[2] + g[3]);
+      }
+    }
+    if (l == 0) {
+      ds = sumq(ds);
+      if (ok && q == 0) sm.ds[j] += ds;
+    }
+  }
+  for (int j = tid; j < nn; j += NW * 64) {
     const int cp = e.cpos[j];
     float *g = b.gs + ((size_t)i * SEL + j) * 2;
-    const float dsa = cp >= 0 ? sm.Pacc[cp * QLD + 32] : 0.f;
+    const float dsa = cp >= 0 ? sm.P[0][cp * LPP + ADIM] : 0.f;
     g[1] = top ? dsa : g[1] + dsa;
   }
   if (l > 0) {
-    for (int k = tid; k < nn * EDIM; k += NT) b.de[(size_t)i * SEL * EDIM + k] = sm.DEl[k];
-    if (tid < NDIM) {
-      float v = sm.dn[tid];
-      for (int k = 0; k < NDIM; ++k) v += sm.zz[k] * Wee[tid * EDIM + k];
-      b.dnl[(size_t)i * NDIM + tid] = v;
-    }
+    const float v = matvec<NW, NDIM, NDIM>(w.WeeT[l], sm.zz, sm.part);
+    if (tid < NDIM) b.dnl[(size_t)i * NDIM + tid] = sm.dn[tid] + v;
     return;
   }
   __syncthreads();
   // ---------------- layer 0: g_ij = dE/dDelta_ij
-  for (int j = tid; j < nn; j += NT) {
-    float ds = 0.f;
-    for (int c = 0; c < EDIM; ++c) {
-      const float e0 = tanhf(e.s[j] * w.We0[c] + w.be0[c]);
-      ds += sm.DEl[j * EDIM + c] * (1.f - e0 * e0) * w.We0[c];
-    }
+  for (int j = tid; j < nn; j += NW * 64) {
+    const float ds = sm.ds[j];
     const float *g2 = b.gs + ((size_t)i * SEL + j) * 2;
     const int cp = e.cpos[j];
     const float rr = e.r[j], sw = e.swe[j];
@@ -1031,9 +882,9 @@ __global__ void __launch_bounds__(NT) k_layer_bwd(Weights w, Buffers b, const do
     const float hx = e.rh[3 * j], hy = e.rh[3 * j + 1], hz = e.rh[3 * j + 2];
     float gx = 0.f, gy = 0.f, gz = 0.f;
     if (cp >= 0) {
-      gx = sm.Pacc[cp * QLD + 33];
-      gy = sm.Pacc[cp * QLD + 34];
-      gz = sm.Pacc[cp * QLD + 35];
+      gx = sm.P[0][cp * LPP + ADIM + 1];
+      gy = sm.P[0][cp * LPP + ADIM + 2];
+      gz = sm.P[0][cp * LPP + ADIM + 3];
     }
     const float proj = gx * hx + gy * hy + gz * hz;
     gout[(size_t)i * SEL + j] = make_float4((gx - proj * hx) / rr + dr * hx, (gy - proj * hy) / rr + dr * hy,
@@ -1041,27 +892,39 @@ __global__ void __launch_bounds__(NT) k_layer_bwd(Weights w, Buffers b, const do
   }
 }
 
+// Up to this many atoms every CU holds at most one workgroup of four waves on each SIMD
+// pair; eight waves per atom then shorten the step.
+constexpr int WIDE_UP_TO = 512;
+
 }  // namespace
 
 void launch_angle_offsets(const Buffers &b, const Workspace &ws, const double *coords, int n, const Geo &geo,
                           hipStream_t st) {
-  hipLaunchKernelGGL(k_angle_count, dim3((n + 255) / 256), dim3(256), 0, st, coords, ws.nlist, ws.nnei, ws.grids, n,
-                     geo, b.aoff);
+  hipLaunchKernelGGL(k_angle_count, dim3((n + 3) / 4), dim3(256), 0, st, coords, ws.nlist, ws.nnei, ws.grids, n, geo,
+                     b.aoff);
   hipLaunchKernelGGL(k_angle_scan, dim3(1), dim3(1024), 0, st, b.aoff, ws.nnei, n, b.aoff + b.cap + 1);
 }
 
 template <typename T>
 void launch_layer_fwd(const Weights &w, const Buffers &b, const Workspace &ws, const double *coords,
                       const int *types, int n, int layer, const Geo &geo, double *Ei, hipStream_t st) {
-  hipLaunchKernelGGL(k_layer_fwd<T>, dim3(n), dim3(NT), 0, st, w, b, coords, types, ws.nlist, ws.nnei, ws.grids, n,
-                     layer, geo, Ei, ws.flags);
+  const auto go = [&](auto kernel, int nw) {
+    hipLaunchKernelGGL(kernel, dim3(n), dim3(nw * 64), 0, st, w, b, coords, types, ws.nlist, ws.nnei, ws.grids, n, layer,
+                       geo, Ei, ws.flags);
+  };
+  if (n <= WIDE_UP_TO) go(k_layer_fwd<T, 8>, 8);
+  else go(k_layer_fwd<T, 4>, 4);
 }
 
 template <typename T>
 void launch_layer_bwd(const Weights &w, const Buffers &b, const Workspace &ws, const double *coords,
                       const int *types, int n, int layer, const Geo &geo, hipStream_t st) {
-  hipLaunchKernelGGL(k_layer_bwd<T>, dim3(n), dim3(NT), 0, st, w, b, coords, types, ws.nlist, ws.nnei, ws.grids, n,
-                     layer, geo, ws.g, ws.flags);
+  const auto go = [&](auto kernel, int nw) {
+    hipLaunchKernelGGL(kernel, dim3(n), dim3(nw * 64), 0, st, w, b, coords, types, ws.nlist, ws.nnei, ws.grids, n, layer,
+                       geo, ws.g, ws.flags);
+  };
+  if (n <= WIDE_UP_TO) go(k_layer_bwd<T, 8>, 8);
+  else go(k_layer_bwd<T, 4>, 4);
 }
 
 template void launch_layer_fwd<float>(const Weights &, const Buffers &, const Workspace &, const double *,

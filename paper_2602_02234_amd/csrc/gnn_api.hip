@@ -5,6 +5,7 @@
 #include <cmath>
 #include <cstring>
 #include <fstream>
+#include <map>
 #include <string>
 #include <vector>
 
@@ -111,7 +112,7 @@ int load_weights(dp_gnn *m, const char *path) {
   std::vector<size_t> offs;
   size_t off = 128;
   double d3 = 0.0;
-  std::vector<double> G3;
+  std::map<std::string, std::vector<double>> src;
   for (auto &a : gnn_arrays(m->ntypes)) {
     if (off + 8 * a.second > raw.size()) {
       set_error("GNN model file: truncated at " + a.first);
@@ -126,7 +127,7 @@ int load_weights(dp_gnn *m, const char *path) {
         return DP_ERR_MODEL_FILE;
       }
     if (a.first == "d3") d3 = v[0];
-    if (a.first == "G3") G3 = v;
+    src[a.first] = v;
     const size_t o = (img.size() + 255) & ~size_t(255);
     img.resize(o + 4 * v.size());
     for (size_t k = 0; k < v.size(); ++k) {
@@ -141,7 +142,67 @@ int load_weights(dp_gnn *m, const char *path) {
   }
   const size_t og = (img.size() + 255) & ~size_t(255);
   img.resize(og + 8 * FWID);
-  std::memcpy(img.data() + og, G3.data(), 8 * FWID);
+  std::memcpy(img.data() + og, src["G3"].data(), 8 * FWID);
+  // transposed copies and MFMA fragments (their order: gnn.hip, X and W)
+  auto put = [&](const void *p, size_t bytes) {
+    const size_t o = (img.size() + 255) & ~size_t(255);
+    img.resize(o + bytes);
+    std::memcpy(img.data() + o, p, bytes);
+    offs.push_back(o);
+  };
+  auto transposed = [&](const std::vector<double> &v, int rows, int cols) {  // of the first `rows` rows
+    std::vector<float> t((size_t)rows * cols);
+    for (int r = 0; r < rows; ++r)
+      for (int c = 0; c < cols; ++c) t[(size_t)c * rows + r] = (float)v[(size_t)r * cols + c];
+    put(t.data(), 4 * t.size());
+  };
+  auto frag32 = [&](int outs, int K, auto W) {
+    std::vector<float> v((size_t)outs * K);
+    for (int t = 0; t < outs / 16; ++t)
+      for (int k = 0; k < K / 16; ++k)
+        for (int ln = 0; ln < 64; ++ln)
+          for (int s = 0; s < 4; ++s)
+            v[((size_t)(t * (K / 16) + k) * 64 + ln) * 4 + s] = (float)W(16 * t + ln % 16, 16 * k + 4 * (ln / 16) + s);
+    put(v.data(), 4 * v.size());
+  };
+  auto frag16 = [&](int outs, int K, auto W) {
+    std::vector<uint16_t> v((size_t)outs * K);
+    for (int t = 0; t < outs / 16; ++t)
+      for (int k = 0; k < K / 32; ++k)
+        for (int ln = 0; ln < 64; ++ln)
+          for (int s = 0; s < 8; ++s) {  // round to nearest even (the weights are finite)
+            const float x = (float)W(16 * t + ln % 16, 32 * k + 16 * (s / 4) + 4 * (ln / 16) + s % 4);
+            uint32_t u;
+            std::memcpy(&u, &x, 4);
+            v[((size_t)(t * (K / 32) + k) * 64 + ln) * 8 + s] = (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
+          }
+    put(v.data(), 2 * v.size());
+  };
+  auto frag = [&](int outs, int K, auto W) {
+    if (m->prec == DP_BF16) frag16(outs, K, W);
+    else frag32(outs, K, W);
+  };
+  transposed(src["G1"], NDIM, FWID);
+  transposed(src["G2"], FWID, FWID);
+  for (int l = 0; l < NLAYER; ++l) {
+    const std::string s = std::to_string(l);
+    const std::vector<double> &aa = src["Waa" + s], &ea = src["Wea" + s], &ee = src["Wee" + s];
+    transposed(src["Wnn" + s], 2 * NDIM, NDIM);
+    transposed(ee, NDIM, EDIM);
+    frag(ADIM, ADIM, [&](int o, int k) { return aa[k * ADIM + o]; });
+    frag(EDIM, ADIM, [&](int o, int k) { return ea[k * EDIM + o]; });
+    frag(ADIM, EDIM, [&](int o, int k) { return ea[o * EDIM + k]; });
+    frag(ADIM, ADIM, [&](int o, int k) { return aa[o * ADIM + k]; });
+    frag(EDIM, 2 * EDIM, [&](int o, int k) { return ee[(NDIM + k) * EDIM + o]; });
+    frag(EDIM, EDIM, [&](int o, int k) { return ee[(NDIM + o) * EDIM + k]; });
+    frag(EDIM, EDIM, [&](int o, int k) { return ee[(2 * NDIM + o) * EDIM + k]; });
+    frag32(128, ADIM, [&](int o, int k) {
+      return o < 32 ? aa[(ADIM + k) * ADIM + o] : (o < 64 ? aa[(2 * ADIM + k) * ADIM + o - 32] : ea[(ADIM + k) * EDIM + o - 64]);
+    });
+    frag32(ADIM, 128, [&](int o, int k) {
+      return k < 32 ? aa[(ADIM + o) * ADIM + k] : (k < 64 ? aa[(2 * ADIM + o) * ADIM + k - 32] : ea[(ADIM + o) * EDIM + k - 64]);
+    });
+  }
   G_TRY(hipMalloc(&m->wbuf, img.size()));
   G_TRY(hipMemcpy(m->wbuf, img.data(), img.size(), hipMemcpyHostToDevice));
   const unsigned char *base = (const unsigned char *)m->wbuf;
@@ -156,6 +217,17 @@ int load_weights(dp_gnn *m, const char *path) {
   w.G1 = nxt(); w.d1 = nxt(); w.G2 = nxt(); w.d2 = nxt(); w.G3 = nxt();
   (void)nxt();  // d3 goes by value
   w.G3d = (const double *)(base + og);
+  w.G1T = nxt(); w.G2T = nxt();
+  for (int l = 0; l < NLAYER; ++l) {
+    auto fr = [&](gnn::Frag &f) {
+      const void *p = base + offs[k++];
+      if (m->prec == DP_BF16) f.b16 = (const bf16_t *)p;
+      else f.f32 = (const float *)p;
+    };
+    w.WnnT[l] = nxt(); w.WeeT[l] = nxt();
+    fr(w.A[l]); fr(w.Mg[l]); fr(w.Xt[l]); fr(w.Yt[l]); fr(w.E[l]); fr(w.N[l]); fr(w.D[l]);
+    w.PQ[l] = nxt(); w.PS[l] = nxt();
+  }
   w.d3 = d3;
   return DP_OK;
 }
