@@ -118,12 +118,35 @@ template <typename T> __device__ __forceinline__ const T *frag(const Frag &f);
 template <> __device__ __forceinline__ const float *frag<float>(const Frag &f) { return f.f32; }
 template <> __device__ __forceinline__ const bf16_t *frag<bf16_t>(const Frag &f) { return f.b16; }
 
+// The four 16-output tiles of a product over the NK feature tiles x, one after the other:
+// use(k, acc) with acc = W_k x + init(k).  The contraction goes in pieces of 64 features, and
+// the next piece's weights are loaded while the current one is used.
+template <typename T, int NK, class Init, class Use>
+__device__ __forceinline__ void tiles(const T *__restrict__ p, const f4 (&x)[NK], const Init &init, const Use &use) {
+  constexpr int H = NK / 4;  // pieces; fragment order makes piece h of tile k the tile k H + h of 64
+  W<T, 4> cur;
+  cur.load(p, 0);
+  f4 acc;
+#pragma unroll
+  for (int s = 0; s < 4 * H; ++s) {
+    W<T, 4> nxt = cur;
+    if (s + 1 < 4 * H) nxt.load(p, s + 1);
+    tile_barrier();
+    const f4 xs[4] = {x[4 * (s % H)], x[4 * (s % H) + 1], x[4 * (s % H) + 2], x[4 * (s % H) + 3]};
+    if (s % H == 0) acc = init(s / H);
+    acc = cur(X<T, 4>(xs), acc);
+    if (s % H == H - 1) use(s / H, acc);
+    tile_barrier();
+    cur = nxt;
+  }
+}
+
 // tanh of the layers' hot loops, from the hardware exponential and reciprocal:
-// tanh|x| = (1 - t) / (1 + t), t = exp(-2|x|); absolute error a few 1e-8, below the
-// float32 rounding of the products it follows (measured forces unchanged against tanhf).
+// tanh x = 1 - 2 / (1 + exp(2 x)); absolute error about 1e-7, the float32 rounding of the
+// sums it enters.
 __device__ __forceinline__ float act(float x) {
-  const float t = __expf(-2.f * fabsf(x));
-  return copysignf((1.f - t) * __builtin_amdgcn_rcpf(1.f + t), x);
+  const float t = __builtin_amdgcn_exp2f(x * 2.885390081777927f);  // exp(2 x)
+  return fmaf(-2.f, __builtin_amdgcn_rcpf(1.f + t), 1.f);
 }
 __device__ __forceinline__ f4 act(f4 v) {
 #pragma unroll
@@ -344,7 +367,7 @@ __device__ __forceinline__ void edge_terms(const Weights &w, const Buffers &b, c
       wt.load(w.PQ[l], ot);
       const int col = 16 * ot + 4 * q;
       const f4 bias = ot < 2 ? f4{0.f, 0.f, 0.f, 0.f} : (ot < 4 ? ldf4(w.baa[l] + col - 32) : ldf4(w.bea[l] + col - 64));
-      const f4 v = wt(xo, f4{0.f, 0.f, 0.f, 0.f}) + bias;
+      const f4 v = wt(xo, bias);
       if (ok) put(x, col, v);
     }
   }
@@ -425,7 +448,7 @@ k_layer_fwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__re
         {
           const X<T, 2> x(a);
 #pragma unroll
-          for (int k = 0; k < 2; ++k) a[k] += act(wa[k](x, f4{0.f, 0.f, 0.f, 0.f}) + bp[k] + ldf4(pq + 32 + 16 * k));
+          for (int k = 0; k < 2; ++k) a[k] += act(wa[k](x, bp[k] + ldf4(pq + 32 + 16 * k)));
         }
         if (ok) {
           float *ao = b.af + ((size_t)l * b.acap + abase + (int64_t)p * na + t) * ADIM + 4 * q;
@@ -435,7 +458,7 @@ k_layer_fwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__re
         const X<T, 2> x(a);
         const float wr = ok ? swp * e.swa[e.cl[qr]] : 0.f;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) m[k] += wr * act(wm[k](x, f4{0.f, 0.f, 0.f, 0.f}) + ldf4(pq + 64 + 16 * k));
+        for (int k = 0; k < 4; ++k) m[k] += wr * act(wm[k](x, ldf4(pq + 64 + 16 * k)));
       }
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
@@ -462,9 +485,9 @@ k_layer_fwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__re
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       tile_barrier();
-      W<T, 8> wt;
+      W<T, 8> wt;  // not loaded ahead: more registers would spill at three waves per SIMD (float32 1.23 -> 1.34 ms)
       wt.load(frag<T>(w.E[l]), k);
-      f4 v = x[4 + k] + act(wt(xo, f4{0.f, 0.f, 0.f, 0.f}) + ldf4(sm.nbias + 16 * k + 4 * q));
+      f4 v = x[4 + k] + act(wt(xo, ldf4(sm.nbias + 16 * k + 4 * q)));
       if (cp >= 0) v += ldf4(sm.Msg + cp * LMS + 16 * k + 4 * q);
       if (ok) stf4(b.ef + erow(b, l, i, j) + 16 * k + 4 * q, v);
       aw[k] += swj * v;
@@ -524,8 +547,12 @@ template <int NW> struct SmemB {
   float PP[ASEL * LPP] __attribute__((aligned(16)));     // terms of edge p
   float DM[ASEL * LMS] __attribute__((aligned(16)));     // dE/dm_ip
   float nbias[EDIM] __attribute__((aligned(16))), dagg[NDIM] __attribute__((aligned(16)));
-  float dnsum[NW][NDIM] __attribute__((aligned(16)));
-  float dn[NDIM], ni[NDIM], xs[2 * NDIM], zz[NDIM], part[NW * 64], ds[SEL];
+  float dnsum[NW][NDIM] __attribute__((aligned(16))), aggw[NW][NDIM] __attribute__((aligned(16)));
+  union {  // the reverse slots are read before the edges, ds written by them
+    int slot[SEL];
+    float ds[SEL];
+  };
+  float dn[NDIM], ni[NDIM], xs[2 * NDIM], zz[NDIM], part[NW * 64];
 };
 
 template <typename T, int NW>
@@ -550,35 +577,53 @@ k_layer_bwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__re
     else stf4(sm.SZ + x * LSZ + col - ADIM, v);
   });
   for (int k = tid; k < NW * nc * LPP; k += NW * 64) sm.P[k / (nc * LPP)][k % (nc * LPP)] = 0.f;
-  // ---------------- dE/dn_i after this layer: own part + the neighbours' edge parts; each wave
-  // sums the rows j = wave, wave + NW, ... in list order (the neighbours' parts, and agg from
-  // the stored output edges), the waves combine in order
-  float dnw = 0.f, aggw = 0.f;
+  // ---------------- dE/dn_i after this layer: own part + the neighbours' edge parts, and agg
+  // from the stored output edges.  Sixteen lanes read a row; the 4 NW row groups walk the
+  // list in turn, four rows in flight each, and are added in order.
+  for (int j = tid; j < nn; j += NW * 64) sm.slot[j] = top ? -1 : b.slot[(size_t)i * SEL + j];
+  __syncthreads();
   {
+    constexpr int G = 4 * NW, R = (SEL + G - 1) / G;
     const float *src = b.dnj + (size_t)((l + 1) & 1) * b.cap * SEL * EDIM;
-#pragma unroll 8
-    for (int j = wv; j < nn; j += NW) {
-      if (!top) {  // branch-free in j (a missing slot reads row 0 and adds 0), so the loads overlap
-        const int sj = b.slot[(size_t)i * SEL + j];
-        const float x = src[((size_t)e.jn[j] * SEL + max(sj, 0)) * EDIM + ln];
-        dnw += sj >= 0 ? x : 0.f;
+    const int g0 = tid >> 4;
+    f4 dn = zero, agg = zero;
+#pragma unroll
+    for (int r0 = 0; r0 < R; r0 += 4) {
+      f4 vd[4], ve[4];
+      float sw[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int j = g0 + G * (r0 + r);
+        const bool ok = j < nn;
+        const int sj = ok ? sm.slot[j] : -1;
+        sw[r] = ok ? e.swe[j] : 0.f;
+        vd[r] = sj >= 0 ? ldf4(src + ((size_t)e.jn[j] * SEL + sj) * EDIM + 4 * c) : zero;
+        ve[r] = ok ? ldf4(b.ef + erow(b, l, i, j) + 4 * c) : zero;
       }
-      aggw += e.swe[j] * b.ef[erow(b, l, i, j) + ln];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        dn += vd[r];
+        agg += sw[r] * ve[r];
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      dn[k] = sumq(dn[k]);
+      agg[k] = sumq(agg[k]);
+    }
+    if (q == 0) {
+      stf4(sm.dnsum[wv] + 4 * c, dn);
+      stf4(sm.aggw[wv] + 4 * c, agg);
     }
   }
-  sm.dnsum[wv][ln] = dnw;
   __syncthreads();
   if (tid < NDIM) {
-    float dn = b.dnl[(size_t)i * NDIM + tid];
-    for (int u = 0; u < NW; ++u) dn += sm.dnsum[u][tid];
+    float dn = b.dnl[(size_t)i * NDIM + tid], agg = 0.f;
+    for (int u = 0; u < NW; ++u) {
+      dn += sm.dnsum[u][tid];
+      agg += sm.aggw[u][tid];
+    }
     sm.dn[tid] = dn;
-  }
-  __syncthreads();
-  sm.dnsum[wv][ln] = aggw;
-  __syncthreads();
-  if (tid < NDIM) {
-    float agg = 0.f;
-    for (int u = 0; u < NW; ++u) agg += sm.dnsum[u][tid];
     sm.xs[tid] = sm.ni[tid];
     sm.xs[NDIM + tid] = agg * geo.inv_sel;
   }
@@ -617,47 +662,32 @@ k_layer_bwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__re
         eo[k] = ldf4(b.ef + erow(b, l, i, j) + 16 * k + 4 * q);
         de1[k] = top ? zero : ldf4(b.de + ((size_t)i * SEL + j) * EDIM + 16 * k + 4 * q);
       }
-      const X<T, 8> xo(x);
       const float swj = e.swe[j];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        tile_barrier();
-        W<T, 8> wt;
-        wt.load(frag<T>(w.E[l]), k);
-        const f4 te = act(wt(xo, zero) + ldf4(sm.nbias + 16 * k + 4 * q));
+      tiles<T, 8>(frag<T>(w.E[l]), x, [&](int k) { return ldf4(sm.nbias + 16 * k + 4 * q); }, [&](int k, f4 z) {
+        const f4 te = act(z);
         const f4 dg = ldf4(sm.dagg + 16 * k + 4 * q);
         const f4 pr = eo[k] * dg;
         rs += (pr[0] + pr[1]) + (pr[2] + pr[3]);
         de1[k] = ok ? de1[k] + swj * dg : zero;
         dz[k] = de1[k] * (1.f - te * te);
         dns[k] += dz[k];
-      }
+      });
     }
     rs = sumq(rs);
     if (ok && q == 0) {
       float *g = b.gs + ((size_t)i * SEL + j) * 2;
       g[0] = top ? rs : g[0] + rs;
     }
-    const X<T, 4> xz(dz);
     if (l > 0) {  // edge (i, j)'s part of dE/dn_j
       float *dst = b.dnj + (size_t)(l & 1) * b.cap * SEL * EDIM + ((size_t)i * SEL + j) * EDIM + 4 * q;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        tile_barrier();
-        W<T, 4> wt;
-        wt.load(frag<T>(w.N[l]), k);
-        const f4 v = wt(xz, zero);
+      tiles<T, 4>(frag<T>(w.N[l]), dz, [&](int) { return zero; }, [&](int k, f4 v) {
         if (ok) stf4(dst + 16 * k, v);
-      }
+      });
     }
     const int cp = ok ? e.cpos[j] : -1;
     float ds = 0.f;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      tile_barrier();
-      W<T, 4> wt;
-      wt.load(frag<T>(w.D[l]), k);
-      const f4 v = de1[k] + wt(xz, zero);  // dE/de of the layer's input; the angle terms are added below
+    tiles<T, 4>(frag<T>(w.D[l]), dz, [&](int) { return zero; }, [&](int k, f4 d) {
+      const f4 v = de1[k] + d;  // dE/de of the layer's input; the angle terms are added below
       const int f = 16 * k + 4 * q;
       if (cp >= 0) stf4(sm.DM + cp * LMS + f, de1[k]);
       if (l > 0) {
@@ -666,7 +696,7 @@ k_layer_bwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__re
         const f4 g = v * (1.f - ein[k] * ein[k]) * ldf4(w.We0 + f);
         ds += (g[0] + g[1]) + (g[2] + g[3]);
       }
-    }
+    });
     if (l == 0) {
       ds = sumq(ds);
       if (ok && q == 0) sm.ds[j] = ds;
@@ -694,36 +724,45 @@ k_layer_bwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__re
       wy[k].load(frag<T>(w.Yt[l]), k);
     }
     float *P = sm.P[wv];
+    // the rows of angle (p, qq) at column t0 + c of edge qq's walk; past the end the atom's first
+    const auto angle = [&](int qq, int t0) -> int64_t {
+      const int t = t0 + c, p = t + (t >= qq);
+      return t < na ? abase + (int64_t)p * na + qq - (qq > p) : abase;
+    };
+    const auto rows = [&](const float *src, int64_t idx, f4 (&v)[2]) {
+#pragma unroll
+      for (int k = 0; k < 2; ++k) v[k] = ldf4(src + (size_t)idx * ADIM + 16 * k + 4 * q);
+    };
+    const float *a1s = b.af + (size_t)l * b.acap * ADIM, *a0s = b.af + (size_t)max(l - 1, 0) * b.acap * ADIM;
+    f4 a1[2], a0[2];
+    if (wv < nc && na > 0) {
+      const int64_t idx = angle(wv, 0);
+      rows(a1s, idx, a1);
+      if (l > 0) rows(a0s, idx, a0);
+    }
     for (int qq = wv; qq < nc; qq += NW) {
       const int jq = e.cl[qq];
       const float swq = e.swa[jq] * geo.inv_asel;
       const float rq[3] = {e.rh[3 * jq], e.rh[3 * jq + 1], e.rh[3 * jq + 2]};
       float *row = sm.SZ + qq * LSZ;
-      f4 ba[2], bm[4], za[2] = {}, zm[4] = {};
-#pragma unroll
-      for (int k = 0; k < 2; ++k) ba[k] = ldf4(row + 16 * k + 4 * q);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) bm[k] = ldf4(row + ADIM + 16 * k + 4 * q);
+      f4 za[2] = {}, zm[4] = {};
       float sq = 0.f, hq[3] = {0.f, 0.f, 0.f};  // dE/dsw_a(r_iq), dE/drhat_iq
       for (int t0 = 0; t0 < na; t0 += 16) {
         const int t = t0 + c;
         const bool ok = t < na;
         const int p = ok ? t + (t >= qq) : 0;  // columns past the end read a valid row, unused
         const int jp = e.cl[p];
-        const int64_t idx = ok ? abase + (int64_t)p * na + qq - (qq > p) : abase;
-        f4 a1[2], a0[2], da[2];
-#pragma unroll
-        for (int k = 0; k < 2; ++k) a1[k] = ldf4(b.af + ((size_t)l * b.acap + idx) * ADIM + 16 * k + 4 * q);
-        if (l > 0) {
-#pragma unroll
-          for (int k = 0; k < 2; ++k) a0[k] = ldf4(b.af + ((size_t)(l - 1) * b.acap + idx) * ADIM + 16 * k + 4 * q);
-        } else {
+        const int64_t idx = angle(qq, t0);
+        // the next tile's rows of a' and a are read as soon as this one has used its own
+        const bool same = t0 + 16 < na, more = same || qq + NW < nc;
+        const int64_t nidx = more ? angle(same ? qq : qq + NW, same ? t0 + 16 : 0) : abase;
+        f4 da[2] = {zero, zero};
+        if (!top) rows(b.da, idx, da);  // needed after most of the tile's products only
+        if (l == 0) {
           const float cs = cosang(e, jp, jq);
 #pragma unroll
           for (int k = 0; k < 2; ++k) a0[k] = init4(cs, w.Wa0 + 16 * k + 4 * q, w.ba0 + 16 * k + 4 * q);
         }
-#pragma unroll
-        for (int k = 0; k < 2; ++k) da[k] = top ? zero : ldf4(b.da + (size_t)idx * ADIM + 16 * k + 4 * q);
         // the message: dE/dw and dz_m = w dE/dm (1 - tanh^2)
         const float wr = ok ? e.swa[jp] * swq : 0.f;
         float d = 0.f;
@@ -732,7 +771,7 @@ k_layer_bwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__re
           const X<T, 2> x(a1);
 #pragma unroll
           for (int k = 0; k < 4; ++k) {
-            const f4 tm = act(wm[k](x, zero) + bm[k]);
+            const f4 tm = act(wm[k](x, ldf4(row + ADIM + 16 * k + 4 * q)));
             const f4 dm = ldf4(sm.DM + p * LMS + 16 * k + 4 * q);
             const f4 g = dm * tm;
             d += (g[0] + g[1]) + (g[2] + g[3]);
@@ -740,20 +779,26 @@ k_layer_bwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__re
             zm[k] += dz[k];
           }
         }
-        d = ok ? sumq(d) : 0.f;
+        rows(a1s, nidx, a1);
+        tile_barrier();
+        d = sumq(d);
+        d = ok ? d : 0.f;
         // the angle update: dE/da' and dz_a
         f4 ta[2];
         {
           const X<T, 2> x(a0);
 #pragma unroll
-          for (int k = 0; k < 2; ++k) ta[k] = act(wa[k](x, zero) + ba[k] + ldf4(sm.PP + p * LPP + 16 * k + 4 * q));
+          for (int k = 0; k < 2; ++k) ta[k] = act(wa[k](x, ldf4(row + 16 * k + 4 * q) + ldf4(sm.PP + p * LPP + 16 * k + 4 * q)));
         }
+        if (l > 0) rows(a0s, nidx, a0);
+        tile_barrier();
         f4 za1[2];
         {
           const X<T, 4> x(dz);
 #pragma unroll
           for (int k = 0; k < 2; ++k) {
-            da[k] = ok ? wx[k](x, zero) + da[k] : zero;
+            const f4 v = wx[k](x, da[k]);  // outside the selection: matrix instructions ignore the lane mask
+            da[k] = ok ? v : zero;
             za1[k] = da[k] * (1.f - ta[k] * ta[k]);
             za[k] += za1[k];
           }
@@ -761,7 +806,7 @@ k_layer_bwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__re
         {
           const X<T, 2> x(za1);
 #pragma unroll
-          for (int k = 0; k < 2; ++k) da[k] += wy[k](x, zero);
+          for (int k = 0; k < 2; ++k) da[k] = wy[k](x, da[k]);
         }
         float dc = 0.f;
         if (l == 0) {
