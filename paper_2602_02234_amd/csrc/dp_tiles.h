@@ -1,0 +1,157 @@
+// Shared parts of the message-passing kernels (gnn.hip, repformer.hip): MFMA products in the
+// transposed form -- weights as A operand, features along the accumulator rows, 16 angles,
+// edges or tokens along the columns -- in which lane (q = lane / 16, c = lane % 16) holds
+// features 16 t + 4 q + i of column c, the layout of float4 rows in memory, of an
+// accumulator and of the next product's B operand alike.
+#pragma once
+#include "dp_internal.h"
+
+namespace dp {
+namespace {
+
+__device__ __forceinline__ bool failed(const unsigned *flags) { return (flags[0] & FLAG_ERRORS) != 0u; }
+__device__ __forceinline__ f4 ldf4(const float *p) { return *reinterpret_cast<const f4 *>(p); }
+__device__ __forceinline__ void stf4(float *p, f4 v) { *reinterpret_cast<f4 *>(p) = v; }
+// Sum over the four lane groups (the lanes of one column).
+__device__ __forceinline__ float sumq(float v) {
+  v += __shfl_xor(v, 16);
+  v += __shfl_xor(v, 32);
+  return v;
+}
+__device__ __forceinline__ f4 sum16(f4 v) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = dp::sum16(v[i]);
+  return v;
+}
+// Ordering of LDS traffic between the lanes of one wave.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+// The lane index through an empty asm statement: inside a loop over atoms the compiler then
+// forms lane-derived addresses where they are used instead of keeping (and spilling) them all.
+__device__ __forceinline__ int lane() {
+  int l = lane_id();
+  asm volatile("" : "+v"(l));
+  return l;
+}
+// Keeps the loads of one tile from being scheduled across another's products.
+__device__ __forceinline__ void tile_barrier() { __builtin_amdgcn_sched_barrier(0); }
+
+// B operand over 16 NK features (tiles x[t], features 16 t + 4 q + i), and an A operand tile
+// of 16 outputs over the same contraction from fragment order: float32, tile t at
+// ((t NK + kb) 64 + lane) 4; bf16, two tiles of features per step, at ((t NK/2 + kp) 64 +
+// lane) 8, the first four values from tile 2 kp, the others from tile 2 kp + 1.
+template <typename T, int NK> struct X;
+template <typename T, int NK> struct W;
+template <int NK> struct X<float, NK> {
+  f4 v[NK];
+  __device__ __forceinline__ explicit X(const f4 (&x)[NK]) {
+#pragma unroll
+    for (int k = 0; k < NK; ++k) v[k] = x[k];
+  }
+};
+template <int NK> struct W<float, NK> {
+  f4 v[NK];
+  __device__ __forceinline__ void load(const float *__restrict__ p, int t) {
+#pragma unroll
+    for (int k = 0; k < NK; ++k) v[k] = ldf4(p + ((t * NK + k) * 64 + lane_id()) * 4);
+  }
+  __device__ __forceinline__ f4 operator()(const X<float, NK> &x, f4 acc) const {
+#pragma unroll
+    for (int k = 0; k < NK; ++k)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(v[k][s], x.v[k][s], acc, 0, 0, 0);
+    return acc;
+  }
+};
+template <int NK> struct X<bf16_t, NK> {
+  bf8 v[NK / 2];
+  __device__ __forceinline__ explicit X(const f4 (&x)[NK]) {
+#pragma unroll
+    for (int k = 0; k < NK / 2; ++k)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[k][e] = (__bf16)x[2 * k + e / 4][e % 4];
+  }
+};
+template <int NK> struct W<bf16_t, NK> {
+  bf8 v[NK / 2];
+  __device__ __forceinline__ void load(const bf16_t *__restrict__ p, int t) {
+#pragma unroll
+    for (int k = 0; k < NK / 2; ++k) v[k] = *reinterpret_cast<const bf8 *>(p + ((t * (NK / 2) + k) * 64 + lane_id()) * 8);
+  }
+  __device__ __forceinline__ f4 operator()(const X<bf16_t, NK> &x, f4 acc) const {
+#pragma unroll
+    for (int k = 0; k < NK / 2; ++k) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v[k], x.v[k], acc, 0, 0, 0);
+    return acc;
+  }
+};
+// The four 16-output tiles of a product over the NK feature tiles x, one after the other:
+// use(k, acc) with acc = W_k x + init(k).  The contraction goes in pieces of 64 features, and
+// the next piece's weights are loaded while the current one is used.
+template <typename T, int NK, class Init, class Use>
+__device__ __forceinline__ void tiles(const T *__restrict__ p, const f4 (&x)[NK], const Init &init, const Use &use) {
+  constexpr int H = NK / 4;  // pieces; fragment order makes piece h of tile k the tile k H + h of 64
+  W<T, 4> cur;
+  cur.load(p, 0);
+  f4 acc;
+#pragma unroll
+  for (int s = 0; s < 4 * H; ++s) {
+    W<T, 4> nxt = cur;
+    if (s + 1 < 4 * H) nxt.load(p, s + 1);
+    tile_barrier();
+    const f4 xs[4] = {x[4 * (s % H)], x[4 * (s % H) + 1], x[4 * (s % H) + 2], x[4 * (s % H) + 3]};
+    if (s % H == 0) acc = init(s / H);
+    acc = cur(X<T, 4>(xs), acc);
+    if (s % H == H - 1) use(s / H, acc);
+    tile_barrier();
+    cur = nxt;
+  }
+}
+
+// tanh of the layers' hot loops, from the hardware exponential and reciprocal:
+// tanh x = 1 - 2 / (1 + exp(2 x)); absolute error about 1e-7, the float32 rounding of the
+// sums it enters.
+__device__ __forceinline__ float act(float x) {
+  const float t = __builtin_amdgcn_exp2f(x * 2.885390081777927f);  // exp(2 x)
+  return fmaf(-2.f, __builtin_amdgcn_rcpf(1.f + t), 1.f);
+}
+__device__ __forceinline__ f4 act(f4 v) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = act(v[i]);
+  return v;
+}
+// Initial features tanh(x w + b) of a lane's four features.
+__device__ __forceinline__ f4 init4(float x, const float *__restrict__ w, const float *__restrict__ b) {
+  const f4 wv = ldf4(w), bv = ldf4(b);
+  f4 v;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = tanhf(x * wv[i] + bv[i]);
+  return v;
+}
+
+// out[c] = sum_k x[k] Wm[k][c] for threads c < C of a group of NT threads (tid within it; x in
+// LDS, Wm row-major): the rows split over the group, the parts (in `part`, one float per
+// thread) added in order.  Starts with a workgroup barrier, which every thread passes.
+template <int NT, int K, int C>
+__device__ __forceinline__ float matvec(const float *__restrict__ Wm, const float *x, float *part, int tid) {
+  constexpr int SEG = NT / C, PER = (K + SEG - 1) / SEG;
+  static_assert(SEG >= 1, "at least one thread per output");
+  const int c = tid % C, sg = tid / C;
+  __syncthreads();
+  float v = 0.f;
+  if (sg < SEG)
+#pragma unroll 16
+    for (int k = sg * PER; k < min(K, (sg + 1) * PER); ++k) v += x[k] * Wm[k * C + c];
+  part[tid] = v;
+  __syncthreads();
+  float r = 0.f;
+  if (tid < C)
+#pragma unroll
+    for (int s = 0; s < SEG; ++s) r += part[s * C + c];
+  return r;
+}
+
+}  // namespace
+}  // namespace dp

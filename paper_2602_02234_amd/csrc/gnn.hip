@@ -32,6 +32,7 @@
 // copy rate) and has 0.42 ms of float32 MFMA work, a backward layer 3.4 GB (0.66 ms) and
 // 0.8 ms.
 #include "dp_env.h"
+#include "dp_tiles.h"
 #include "gnn.h"
 
 namespace dp {
@@ -43,124 +44,9 @@ constexpr int LMS = 68;   // ... of [angle-list edge][64]
 constexpr int LSZ = 100;  // backward: per-edge terms of edge q [96], later the sums over its angles [96 + 4]
 constexpr int LPP = 36;   // backward: sums of edge p [32 features, sw_a, rhat], and its terms [32]
 
-__device__ __forceinline__ bool failed(const unsigned *flags) { return (flags[0] & FLAG_ERRORS) != 0u; }
-__device__ __forceinline__ f4 ldf4(const float *p) { return *reinterpret_cast<const f4 *>(p); }
-__device__ __forceinline__ void stf4(float *p, f4 v) { *reinterpret_cast<f4 *>(p) = v; }
-// Sum over the four lane groups (the lanes of one column).
-__device__ __forceinline__ float sumq(float v) {
-  v += __shfl_xor(v, 16);
-  v += __shfl_xor(v, 32);
-  return v;
-}
-__device__ __forceinline__ f4 sum16(f4 v) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) v[i] = dp::sum16(v[i]);
-  return v;
-}
-// Ordering of LDS traffic between the lanes of one wave.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-// Keeps the loads of one tile from being scheduled across another's products.
-__device__ __forceinline__ void tile_barrier() { __builtin_amdgcn_sched_barrier(0); }
-
-// B operand over 16 NK features (tiles x[t], features 16 t + 4 q + i), and an A operand tile
-// of 16 outputs over the same contraction from fragment order: float32, tile t at
-// ((t NK + kb) 64 + lane) 4; bf16, two tiles of features per step, at ((t NK/2 + kp) 64 +
-// lane) 8, the first four values from tile 2 kp, the others from tile 2 kp + 1.
-template <typename T, int NK> struct X;
-template <typename T, int NK> struct W;
-template <int NK> struct X<float, NK> {
-  f4 v[NK];
-  __device__ __forceinline__ explicit X(const f4 (&x)[NK]) {
-#pragma unroll
-    for (int k = 0; k < NK; ++k) v[k] = x[k];
-  }
-};
-template <int NK> struct W<float, NK> {
-  f4 v[NK];
-  __device__ __forceinline__ void load(const float *__restrict__ p, int t) {
-#pragma unroll
-    for (int k = 0; k < NK; ++k) v[k] = ldf4(p + ((t * NK + k) * 64 + lane_id()) * 4);
-  }
-  __device__ __forceinline__ f4 operator()(const X<float, NK> &x, f4 acc) const {
-#pragma unroll
-    for (int k = 0; k < NK; ++k)
-#pragma unroll
-      for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(v[k][s], x.v[k][s], acc, 0, 0, 0);
-    return acc;
-  }
-};
-template <int NK> struct X<bf16_t, NK> {
-  bf8 v[NK / 2];
-  __device__ __forceinline__ explicit X(const f4 (&x)[NK]) {
-#pragma unroll
-    for (int k = 0; k < NK / 2; ++k)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[k][e] = (__bf16)x[2 * k + e / 4][e % 4];
-  }
-};
-template <int NK> struct W<bf16_t, NK> {
-  bf8 v[NK / 2];
-  __device__ __forceinline__ void load(const bf16_t *__restrict__ p, int t) {
-#pragma unroll
-    for (int k = 0; k < NK / 2; ++k) v[k] = *reinterpret_cast<const bf8 *>(p + ((t * (NK / 2) + k) * 64 + lane_id()) * 8);
-  }
-  __device__ __forceinline__ f4 operator()(const X<bf16_t, NK> &x, f4 acc) const {
-#pragma unroll
-    for (int k = 0; k < NK / 2; ++k) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v[k], x.v[k], acc, 0, 0, 0);
-    return acc;
-  }
-};
 template <typename T> __device__ __forceinline__ const T *frag(const Frag &f);
 template <> __device__ __forceinline__ const float *frag<float>(const Frag &f) { return f.f32; }
 template <> __device__ __forceinline__ const bf16_t *frag<bf16_t>(const Frag &f) { return f.b16; }
-
-// The four 16-output tiles of a product over the NK feature tiles x, one after the other:
-// use(k, acc) with acc = W_k x + init(k).  The contraction goes in pieces of 64 features, and
-// the next piece's weights are loaded while the current one is used.
-template <typename T, int NK, class Init, class Use>
-__device__ __forceinline__ void tiles(const T *__restrict__ p, const f4 (&x)[NK], const Init &init, const Use &use) {
-  constexpr int H = NK / 4;  // pieces; fragment order makes piece h of tile k the tile k H + h of 64
-  W<T, 4> cur;
-  cur.load(p, 0);
-  f4 acc;
-#pragma unroll
-  for (int s = 0; s < 4 * H; ++s) {
-    W<T, 4> nxt = cur;
-    if (s + 1 < 4 * H) nxt.load(p, s + 1);
-    tile_barrier();
-    const f4 xs[4] = {x[4 * (s % H)], x[4 * (s % H) + 1], x[4 * (s % H) + 2], x[4 * (s % H) + 3]};
-    if (s % H == 0) acc = init(s / H);
-    acc = cur(X<T, 4>(xs), acc);
-    if (s % H == H - 1) use(s / H, acc);
-    tile_barrier();
-    cur = nxt;
-  }
-}
-
-// tanh of the layers' hot loops, from the hardware exponential and reciprocal:
-// tanh x = 1 - 2 / (1 + exp(2 x)); absolute error about 1e-7, the float32 rounding of the
-// sums it enters.
-__device__ __forceinline__ float act(float x) {
-  const float t = __builtin_amdgcn_exp2f(x * 2.885390081777927f);  // exp(2 x)
-  return fmaf(-2.f, __builtin_amdgcn_rcpf(1.f + t), 1.f);
-}
-__device__ __forceinline__ f4 act(f4 v) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) v[i] = act(v[i]);
-  return v;
-}
-// Initial features tanh(x w + b) of a lane's four features.
-__device__ __forceinline__ f4 init4(float x, const float *__restrict__ w, const float *__restrict__ b) {
-  const f4 wv = ldf4(w), bv = ldf4(b);
-  f4 v;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) v[i] = tanhf(x * wv[i] + bv[i]);
-  return v;
-}
 
 struct GEnv {
   float r[SEL], swe[SEL], dswe[SEL], swa[SEL], dswa[SEL], s[SEL];
@@ -237,27 +123,6 @@ __device__ __forceinline__ float cosang(const GEnv &e, int jp, int jq) {
 
 __device__ __forceinline__ size_t erow(const Buffers &b, int l, int i, int j) {
   return (((size_t)l * b.cap + i) * SEL + j) * EDIM;
-}
-
-// out[c] = sum_k x[k] Wm[k][c] for threads c < C (x in LDS, Wm row-major): the rows split
-// over the workgroup, the parts (in `part`, one float per thread) added in order.  Starts
-// with a barrier.
-template <int NW, int K, int C>
-__device__ __forceinline__ float matvec(const float *__restrict__ Wm, const float *x, float *part) {
-  constexpr int SEG = NW * 64 / C, PER = K / SEG;
-  static_assert(K % SEG == 0 && SEG >= 1, "whole segments");
-  const int c = threadIdx.x % C, sg = threadIdx.x / C;
-  __syncthreads();
-  float v = 0.f;
-#pragma unroll 16
-  for (int k = 0; k < PER; ++k) v += x[sg * PER + k] * Wm[(sg * PER + k) * C + c];
-  part[threadIdx.x] = v;
-  __syncthreads();
-  float r = 0.f;
-  if ((int)threadIdx.x < C)
-#pragma unroll
-    for (int s = 0; s < SEG; ++s) r += part[s * C + c];
-  return r;
 }
 
 // ------------------------------------------------------------------ angle offsets
@@ -400,7 +265,7 @@ k_layer_fwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__re
     sm.ni[tid] = l == 0 ? w.TN[clamp_type(types[i]) * NDIM + tid] : b.nf[((size_t)(l - 1) * b.cap + i) * NDIM + tid];
   edge_terms<NW>(w, b, e, l, i, [&](int x, int col, f4 v) { stf4(sm.PQ + x * LPQ + col, v); });
   {  // the centre's part of every edge update: bee + n_i Wee[0:64]
-    const float v = matvec<NW, NDIM, EDIM>(w.Wee[l], sm.ni, sm.part);
+    const float v = matvec<NW * 64, NDIM, EDIM>(w.Wee[l], sm.ni, sm.part, threadIdx.x);
     if (tid < EDIM) sm.nbias[tid] = v + w.bee[l][tid];
   }
   __syncthreads();
@@ -507,7 +372,7 @@ k_layer_fwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__re
     sm.xs[tid] = sm.ni[tid];
     sm.xs[NDIM + tid] = v * geo.inv_sel;
   }
-  const float z = matvec<NW, 2 * NDIM, NDIM>(w.Wnn[l], sm.xs, sm.part);
+  const float z = matvec<NW * 64, 2 * NDIM, NDIM>(w.Wnn[l], sm.xs, sm.part, threadIdx.x);
   float n1 = 0.f;
   if (tid < NDIM) {
     n1 = sm.ni[tid] + tanhf(z + w.bnn[l][tid]);
@@ -517,15 +382,15 @@ k_layer_fwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__re
 
   // ---------------- fitting net, E_i and dE/dn_i
   if (tid < NDIM) sm.xs[tid] = n1;
-  const float z1 = matvec<NW, NDIM, FWID>(w.G1, sm.xs, sm.part);
+  const float z1 = matvec<NW * 64, NDIM, FWID>(w.G1, sm.xs, sm.part, threadIdx.x);
   if (tid < FWID) sm.y1[tid] = tanhf(z1 + w.d1[tid]);
-  const float z2 = matvec<NW, FWID, FWID>(w.G2, sm.y1, sm.part);
+  const float z2 = matvec<NW * 64, FWID, FWID>(w.G2, sm.y1, sm.part, threadIdx.x);
   if (tid < FWID) {
     const float t2 = tanhf(z2 + w.d2[tid]);
     sm.t2[tid] = t2;
     sm.dp[tid] = w.G3[tid] * (1.f - t2 * t2);
   }
-  const float z3 = matvec<NW, FWID, FWID>(w.G2T, sm.dp, sm.part);  // its first barrier: t2 is complete
+  const float z3 = matvec<NW * 64, FWID, FWID>(w.G2T, sm.dp, sm.part, threadIdx.x);  // its first barrier: t2 is complete
   if (wv == 0) {
     double E = (double)(sm.t2[ln] + sm.y1[ln]) * w.G3d[ln] + (double)(sm.t2[ln + 64] + sm.y1[ln + 64]) * w.G3d[ln + 64];
     for (int off = 32; off > 0; off >>= 1) E += __shfl_xor(E, off);
@@ -535,7 +400,7 @@ k_layer_fwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__re
   if (tid < FWID) dp1 = (z3 + w.G3[tid]) * (1.f - sm.y1[tid] * sm.y1[tid]);
   __syncthreads();
   if (tid < FWID) sm.dp[tid] = dp1;
-  const float dn = matvec<NW, FWID, NDIM>(w.G1T, sm.dp, sm.part);
+  const float dn = matvec<NW * 64, FWID, NDIM>(w.G1T, sm.dp, sm.part, threadIdx.x);
   if (tid < NDIM) b.dnl[(size_t)i * NDIM + tid] = dn;
 }
 
@@ -629,14 +494,14 @@ k_layer_bwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__re
   }
   // ---------------- node backward (and the centre's part of every edge update)
   {
-    const float v = matvec<NW, NDIM, EDIM>(w.Wee[l], sm.ni, sm.part);
+    const float v = matvec<NW * 64, NDIM, EDIM>(w.Wee[l], sm.ni, sm.part, threadIdx.x);
     if (tid < EDIM) sm.nbias[tid] = v + w.bee[l][tid];
-    const float z = matvec<NW, 2 * NDIM, NDIM>(w.Wnn[l], sm.xs, sm.part);
+    const float z = matvec<NW * 64, 2 * NDIM, NDIM>(w.Wnn[l], sm.xs, sm.part, threadIdx.x);
     if (tid < NDIM) {
       const float t = tanhf(z + w.bnn[l][tid]);
       sm.zz[tid] = sm.dn[tid] * (1.f - t * t);
     }
-    const float d = matvec<NW, NDIM, 2 * NDIM>(w.WnnT[l], sm.zz, sm.part);
+    const float d = matvec<NW * 64, NDIM, 2 * NDIM>(w.WnnT[l], sm.zz, sm.part, threadIdx.x);
     if (tid < NDIM) sm.dn[tid] += d;  // now dE/dn_i of this layer's input, without the edge terms
     else if (tid < 2 * NDIM) sm.dagg[tid - NDIM] = d * geo.inv_sel;
   }
@@ -912,7 +777,7 @@ k_layer_bwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__re
     g[1] = top ? dsa : g[1] + dsa;
   }
   if (l > 0) {
-    const float v = matvec<NW, NDIM, NDIM>(w.WeeT[l], sm.zz, sm.part);
+    const float v = matvec<NW * 64, NDIM, NDIM>(w.WeeT[l], sm.zz, sm.part, threadIdx.x);
     if (tid < NDIM) b.dnl[(size_t)i * NDIM + tid] = sm.dn[tid] + v;
     return;
   }

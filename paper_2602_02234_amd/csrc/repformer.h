@@ -25,12 +25,18 @@ constexpr int XD = G1D + G2D * NAX + G2D;  // node-update input width, 224
 constexpr int FWID = 128;
 constexpr int GSN = 8;                  // per-edge gradient slots: ds, dsw, drhat (3), pad
 
-struct Weights {  // float32, row-major [in][out] as in the model file
+// Device weights: float32, row-major [in][out] as in the model file (the T-named copies
+// transposed), and the products' operands in MFMA fragment order (dp_tiles.h).
+struct Weights {
   const float *TN;                      // [NTYPES][64]
   const float *Wp0, *bp0;               // [32]
-  const float *Wa[NLAYER], *ba[NLAYER];  // [96][32], [32]
-  const float *Wq[NLAYER], *Wk[NLAYER], *Wv[NLAYER];  // [32][32]
+  const float *ba[NLAYER];               // [32]
   const float *W1[NLAYER], *b1[NLAYER];  // [224][64], [64]
+  const float *G1T, *G2T;                // [128][64], [128][128]
+  const float *Pa[NLAYER];               // [g2, g1_j] -> Wa (32 outputs of 96)
+  const float *Pqkv[NLAYER];             // g2a -> [Q, K, V] (96 outputs of 32)
+  const float *Pqkvt[NLAYER];            // [dQ, dK, dV] -> dE/dg2a (32 outputs of 96)
+  const float *Pat[NLAYER];              // dz -> dE/d[g2, g1_j] (96 outputs of 32)
   const float *G1, *d1, *G2, *d2, *G3;   // fitting
   const double *G3d;
   double d3;
@@ -41,11 +47,14 @@ struct Buffers {
   int64_t cap = 0;
   float *g1f = nullptr;  // [2][cap][64]       g1 after layers 1, 2
   float *g2f = nullptr;  // [3][cap][SEL][32]  g2 after layers 1, 2, 3
+  float *tn = nullptr;   // [3][cap][64]       tanh of the node updates, for the backward pass
+  float *Tn = nullptr;   // [3][cap][32][4]    T of the node updates
   float *dg2 = nullptr;  // [cap][SEL][32]     dE/dg2 of the current layer's output, in place
   float *dnj = nullptr;  // [2][cap][SEL][64]  edge (i, j)'s part of dE/dg1_j, by layer parity
   float *dnl = nullptr;  // [cap][64]          atom i's own part of dE/dg1_i
   float *gs = nullptr;   // [cap][SEL][GSN]    dE/ds, dE/dsw, dE/drhat per edge over the layers
   int *slot = nullptr;   // [cap][SEL]         position of i in the list of its j-th neighbour, or -1
+  int *idx = nullptr;    // [2][cap]           atoms of each kernel instance (counts: Workspace::bcnt)
   int64_t *etot = nullptr;  // [1] edges of the step
 };
 
@@ -53,7 +62,7 @@ struct Geo {
   float rc, rcs, inv_sel;
 };
 
-// *b.etot = sum of the list lengths of the n atoms.
+// *b.etot = sum of the list lengths of the n atoms; also lists the atoms of the kernels' instances.
 void launch_edge_count(const Buffers &b, const Workspace &ws, int n, hipStream_t st);
 // Layer `layer` (0 .. 2) forward over all n atoms; the last layer also evaluates the
 // fitting net (E_i into Ei) and its gradient dE/dg1 (into dnl).  Layer `layer` backward

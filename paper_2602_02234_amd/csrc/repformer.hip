@@ -1,76 +1,89 @@
-// Repformer-style model kernels for gfx950: one workgroup (eight waves) per centre atom
-// and one launch per layer, forward and backward (a layer's pair update and convolution
-// read the neighbours' g1 of the layer before, so layers meet at launch boundaries).
-// The products run on MFMA (16x16x4 f32): the pair update and projections and the
-// backward's dE/d[g2, g1_j] over tiles of 16 edges, one tile per wave; the
-// neighbour-to-neighbour attention (every ordered pair of an atom's up to 120
-// neighbours, width 32) over tiles of 16 queries in the forward and the backward's row
-// pass (statistics, dQ, the row terms of the gate), and tiles of 16 keys in the column
-// pass (dK, dV, the key terms of the switch and gate, with the scores recomputed).
-// The contraction T = sum_j g2_j R_j^T and its gradient also run on MFMA; the node
-// update (input 224) and the convolution sums stay float32 VALU work.  Every sum has
-// one owner and a fixed order: results are deterministic.
-#include <cmath>
+// Repformer-style model kernels for gfx950: one launch per layer, forward and backward (a
+// layer's pair update and convolution read the neighbours' g1 of the layer before, so
+// layers meet at launch boundaries).
+//
+// A wave owns a block of 16 of the centre's neighbours (tokens) and keeps all that belongs to
+// them in registers, transposed (dp_tiles.h): the pair update, its query, the scores of its
+// tokens as queries against every key, softmax, the attention output, and their gradients.
+// Only what other waves read goes through LDS: the keys' rows K and V, and, in the backward,
+// the gradients that meet at a key.  The products run on MFMA (16x16x4 f32).
+//   forward   g2a = g2 + tanh([g2, g1_j] Wa + ba); Q, K, V; E = exp(S - max) / Z over the keys;
+//             g2 <- g2a + sum_k sw_k E gate V_k; T = sum_j g2_j R_j^T and the convolution sums;
+//             the node update; after the last layer the fitting net, E_i and dE/dg1_i.
+//   backward  the same recomputed but for the layer's output, which is stored; per token j
+//             dA = V dY, per key P = sw E, dP = dA gate, rho = sum P dP, W = E (dP - rho),
+//             dQ = K^T (sw W) / sqrt 32; per key k dV_k = sw_k sum_j E gate dY_j, dK_k = sw_k sum_j
+//             W Q_j / sqrt 32, dsw_k = sum_j W: the wave reads its column of the tiles of E gate
+//             and W, which the waves of all blocks leave in LDS.
+// Every sum has a fixed order: results are deterministic.
+//
+// Up to ONE_UP_TO atoms each has a workgroup of 8 waves; above, atoms of up to 6 blocks go two
+// to a workgroup of 12 waves, so that every SIMD has three (a second group of 6 waves is never
+// placed beside the first: each brings two waves to the same two SIMDs, and 168 registers
+// leave room for three), and atoms of 7 or 8 blocks take 8 of the 12.
+// Bound: matrix cores, then the latency of the stages between barriers.  At 96 neighbours
+// a forward layer has 1,250 MFMAs of 32 cycles per atom (0.16 ms at 9,999 atoms on 256 CUs), a
+// backward layer 2,900 (0.38 ms).  Measured at 9,999 atoms of chain density, per layer: 0.93 ->
+// 0.49 ms forward, 1.97 -> 0.89 ms backward, against kernels that staged every product's
+// operands in LDS and had one atom per CU; at 768 atoms 76 -> 53 and 157 -> 90 us.
+#include <algorithm>
 
 #include "dp_env.h"
+#include "dp_tiles.h"
 #include "repformer.h"
 
 namespace dp {
 namespace rep {
 namespace {
 
-constexpr int NWG = 8;
-constexpr int NT = NWG * 64;
-constexpr int LQ = G2D + 1;   // row stride of [edge][32] LDS arrays (odd: rows fall in different banks)
-constexpr int LQA = G2D + 4;  // row stride of the attention operands Q, K, V, dY (16-byte aligned rows)
-constexpr int LG = G1D + 1;   // row stride of [edge][64]
+constexpr int LK = G2D + 4;   // row stride of the keys' rows in LDS: row reads and reads along keys without conflicts
+constexpr int NB_SMALL = 6;   // blocks up to which two atoms share a workgroup of 12 waves
+constexpr int NB_MAX = 8;     // blocks of the longest list
+constexpr int ONE_UP_TO = 256;  // atoms up to which each has a workgroup (and a CU) of its own
+constexpr int NLONG = 256;    // workgroups of 12 waves that take the longer lists: one per CU
 
-__device__ __forceinline__ bool failed(const unsigned *flags) { return (flags[0] & FLAG_ERRORS) != 0u; }
+__device__ __forceinline__ f4 mfma(float a, float b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// tanh and exp of the hot loops from the hardware exponential and reciprocal
-// (absolute error a few 1e-8 for tanh; relative a few 1e-7 for the softmax weights).
-__device__ __forceinline__ float ftanh(float x) {
-  const float t = __expf(-2.f * fabsf(x));
-  return copysignf((1.f - t) * __builtin_amdgcn_rcpf(1.f + t), x);
-}
-
-constexpr int SELP = 16 * ((SEL + 15) / 16);  // SEL rounded up to whole tiles of 16
-
-// Environment of atom i.  sw and rh are padded to SELP entries (zero past the list) so
-// that four consecutive neighbours of a tile are read with 16-byte loads.
-struct EnvR {
-  float sw[SELP] __attribute__((aligned(16)));
-  float rh[SELP * 3] __attribute__((aligned(16)));
-  float r[SEL], dsw[SEL], s[SEL];
-  int jn[SEL], tj[SEL];
-  int nn;
+// The part of a workgroup's work a wave takes: NA atoms (entries blk NA .. of the list, or
+// atom blk without one), NB waves each.  Past the end of the list nb = 0; steps is the largest nb, so that
+// the waves of both atoms pass the same barriers.
+template <int NB, int NA> struct Part {
+  int half, jb, tid, i, n, nb, steps;
+  __device__ __forceinline__ Part(int blk, const int *__restrict__ idx, int count, const int *__restrict__ nnei) {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));  // as lane()
+    const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
+    half = NA == 1 ? 0 : wv / NB;
+    jb = wv - half * NB;
+    tid = t - half * 64 * NB;
+    steps = 0;
+#pragma unroll
+    for (int a = 0; a < NA; ++a) {
+      const int k = idx ? idx[min(blk * NA + a, count - 1)] : blk;
+      const int nk = min(max(nnei[k], 0), SEL);
+      const int b = blk * NA + a < count ? min(nk > 0 ? (nk + 15) / 16 : 1, NB) : 0;
+      steps = max(steps, b);
+      if (a == half) {
+        i = k;
+        n = nk;
+        nb = b;
+      }
+    }
+  }
 };
 
-// rh of the neighbours k0 .. k0 + 3 (k0 a multiple of 4): h[3 ii + a] = rhat_{k0 + ii}[a].
-__device__ __forceinline__ void rh_quad(const EnvR &e, int k0, float (&h)[12]) {
-  const float4 a = *reinterpret_cast<const float4 *>(e.rh + 3 * k0);
-  const float4 b = *reinterpret_cast<const float4 *>(e.rh + 3 * k0 + 4);
-  const float4 c = *reinterpret_cast<const float4 *>(e.rh + 3 * k0 + 8);
-  h[0] = a.x; h[1] = a.y; h[2] = a.z; h[3] = a.w;
-  h[4] = b.x; h[5] = b.y; h[6] = b.z; h[7] = b.w;
-  h[8] = c.x; h[9] = c.y; h[10] = c.z; h[11] = c.w;
-}
-__device__ __forceinline__ void quad(const float *p, float (&v)[4]) {
-  const float4 a = *reinterpret_cast<const float4 *>(p);
-  v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-}
+// Environment of one atom, padded to whole blocks (s = sw = dsw = 0, r = 1, rhat = 0 past the list).
+template <int NB> struct EnvN {
+  float sw[16 * NB] __attribute__((aligned(16)));
+  float rh[3][16 * NB] __attribute__((aligned(16)));
+  float r[16 * NB], dsw[16 * NB], s[16 * NB];
+  int jn[16 * NB], tj[16 * NB];
+};
 
-__device__ void build_env_r(EnvR &e, const double *__restrict__ X, const int *__restrict__ types,
-                            const int *__restrict__ nlist, const int *__restrict__ nnei, int i, int n, const Grid &g,
-                            const Geo &geo) {
-  const int nn = min(max(nnei[i], 0), SEL);
-  for (int j = threadIdx.x; j < SELP; j += NT) {
+template <int NB>
+__device__ void build_envn(EnvN<NB> &e, int tid, const double *__restrict__ X, const int *__restrict__ types,
+                           const int *__restrict__ nlist, int i, int nn, int n, const Grid &g, const Geo &geo) {
+  for (int j = tid; j < 16 * NB; j += 64 * NB) {
     float r = 1.f, sw = 0.f, dsw = 0.f, hx = 0.f, hy = 0.f, hz = 0.f;
     int nj = i, tj = 0;
     if (j < nn) {
@@ -94,895 +107,738 @@ __device__ void build_env_r(EnvR &e, const double *__restrict__ X, const int *__
       }
       hx = dx / r; hy = dy / r; hz = dz / r;
     }
-    e.sw[j] = sw;
-    e.rh[3 * j] = hx; e.rh[3 * j + 1] = hy; e.rh[3 * j + 2] = hz;
-    if (j < SEL) {
-      e.r[j] = r; e.dsw[j] = dsw; e.s[j] = sw / r;
-      e.jn[j] = nj; e.tj[j] = tj;
-    }
+    e.sw[j] = sw; e.dsw[j] = dsw; e.r[j] = r; e.s[j] = sw / r;
+    e.rh[0][j] = hx; e.rh[1][j] = hy; e.rh[2][j] = hz;
+    e.jn[j] = nj; e.tj[j] = tj;
   }
-  if (threadIdx.x == 0) e.nn = nn;
-  __syncthreads();
 }
-
-__device__ __forceinline__ float Rcomp(const EnvR &e, int j, int a) { return a == 0 ? e.s[j] : e.s[j] * e.rh[3 * j + a - 1]; }
 
 __device__ __forceinline__ size_t erow2(const Buffers &b, int l, int i, int j) {
   return (((size_t)l * b.cap + i) * SEL + j) * G2D;
 }
 
-__device__ __forceinline__ float4 ld4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
-__device__ __forceinline__ void st4(float *p, float4 v) {  // LDS rows have odd strides: four scalar stores
-  p[0] = v.x; p[1] = v.y; p[2] = v.z; p[3] = v.w;
+// The layer's input of token j: x = [g2 (2 tiles), g1 of the neighbour (4 tiles)], zero past the list.
+template <int NB>
+__device__ __forceinline__ void token_in(const Weights &w, const Buffers &b, const EnvN<NB> &e, int l, int i, int j,
+                                         int nn, f4 (&x)[6]) {
+  const int q = lane() >> 4;
+  if (j < nn) {
+    const float *g1 = l == 0 ? w.TN + e.tj[j] * G1D : b.g1f + ((size_t)(l - 1) * b.cap + e.jn[j]) * G1D;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) x[2 + t] = ldf4(g1 + 16 * t + 4 * q);
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+      x[t] = l == 0 ? init4(e.s[j], w.Wp0 + 16 * t + 4 * q, w.bp0 + 16 * t + 4 * q) : ldf4(b.g2f + erow2(b, l - 1, i, j) + 16 * t + 4 * q);
+  } else {
+#pragma unroll
+    for (int t = 0; t < 6; ++t) x[t] = f4{0.f, 0.f, 0.f, 0.f};
+  }
 }
 
-// Rows of WIDTH floats (a multiple of 4) for j < nn, copied from global memory (row j
-// at src(j)) into LDS rows of stride ld in two steps, so that the reads of several
-// arrays can all be issued before the first write.
-template <int WIDTH> struct Rows {
-  static constexpr int Q = WIDTH / 4, NI = (SEL * Q + NT - 1) / NT;
-  float4 v[NI];
-  template <class S> __device__ __forceinline__ void issue(int nn, const S &src) {
+// out[t] = W_t x + bias (16 t + 4 q ..) for a product with NT output tiles.
+template <int NK, int NT>
+__device__ __forceinline__ void product(f4 (&out)[NT], const float *__restrict__ wf, const f4 (&x)[NK]) {
+  const X<float, NK> xo(x);
 #pragma unroll
-    for (int it = 0; it < NI; ++it) {
-      const int k = threadIdx.x + NT * it, j = k / Q;
-      if (j < nn) v[it] = ld4(src(j) + 4 * (k % Q));
+  for (int t = 0; t < NT; ++t) {
+    W<float, NK> wt;
+    wt.load(wf, t);
+    out[t] = wt(xo, out[t]);
+  }
+}
+
+// Pair update and projections of the lane's token: ta = tanh([g2, g1_j] Wa + ba), g2a = g2 + ta,
+// q its query; its key and value rows go to LDS.
+__device__ __forceinline__ void pair_and_qkv(const Weights &w, int l, const f4 (&x)[6], f4 (&ta)[2], f4 (&g2a)[2],
+                                             f4 (&qr)[2], float *Krow, float *Vrow) {
+  const int q = lane() >> 4;
+#pragma unroll
+  for (int t = 0; t < 2; ++t) ta[t] = ldf4(w.ba[l] + 16 * t + 4 * q);
+  product<6, 2>(ta, w.Pa[l], x);
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    ta[t] = act(ta[t]);
+    g2a[t] = x[t] + ta[t];
+  }
+  f4 qkv[6] = {};
+  product<2, 6>(qkv, w.Pqkv[l], g2a);
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    qr[t] = qkv[t];
+    stf4(Krow + 16 * t + 4 * q, qkv[2 + t]);
+    stf4(Vrow + 16 * t + 4 * q, qkv[4 + t]);
+  }
+}
+
+// s[kt] = (rows of R) x for key tile kt < nb: rows key 16 kt + 4 q + i, columns tokens.
+template <int NB>
+__device__ __forceinline__ void keys_dot(f4 (&s)[NB], const float *R, const f4 (&x)[2], int nb) {
+  const int q = lane() >> 4, c = lane() & 15;
+#pragma unroll
+  for (int kt = 0; kt < NB; ++kt) {
+    s[kt] = f4{0.f, 0.f, 0.f, 0.f};
+    if (kt < nb)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const f4 a = ldf4(R + (16 * kt + c) * LK + 16 * t + 4 * q);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[kt] = mfma(a[e], x[t][e], s[kt]);
+      }
+  }
+}
+// acc = R^T y, y(kt)[i] the value of key 16 kt + 4 q + i, kt < nb.
+template <int NB, class Y>
+__device__ __forceinline__ void keys_sum(f4 (&acc)[2], const float *R, const Y &y, int nb) {
+  const int q = lane() >> 4, c = lane() & 15;
+  acc[0] = acc[1] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int kt = 0; kt < NB; ++kt)
+    if (kt < nb) {
+      const f4 v = y(kt);
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) acc[t] = mfma(R[(16 * kt + 4 * q + s) * LK + 16 * t + c], v[s], acc[t]);
+    }
+}
+
+// E = exp((S - max) / sqrt 32) / Z over the keys in place of the scores (0 past the list), with
+// Z = sum_k sw_k exp(...).
+template <int NB>
+__device__ __forceinline__ void softmax_keys(f4 (&s)[NB], const EnvN<NB> &e, int n) {
+  const int q = lane() >> 4;
+  const float isq = 0.17677669529663687f;  // 1 / sqrt(32)
+  float m = -INFINITY;
+#pragma unroll
+  for (int kt = 0; kt < NB; ++kt)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      s[kt][i] = 16 * kt + 4 * q + i < n ? s[kt][i] * isq : -INFINITY;
+      m = fmaxf(m, s[kt][i]);
+    }
+  m = fmaxf(m, __shfl_xor(m, 16));
+  m = fmaxf(m, __shfl_xor(m, 32));
+  if (m == -INFINITY) m = 0.f;
+  float z = 0.f;
+#pragma unroll
+  for (int kt = 0; kt < NB; ++kt) {
+    const f4 sw = ldf4(e.sw + 16 * kt + 4 * q);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      s[kt][i] = __expf(s[kt][i] - m);
+      z += sw[i] * s[kt][i];
     }
   }
-  __device__ __forceinline__ void store(float *dst, int ld, int nn) const {
+  z = sumq(z);
+  const float iz = z > 0.f ? 1.f / z : 0.f;
 #pragma unroll
-    for (int it = 0; it < NI; ++it) {
-      const int k = threadIdx.x + NT * it, j = k / Q;
-      if (j < nn) st4(dst + j * ld + 4 * (k % Q), v[it]);
+  for (int kt = 0; kt < NB; ++kt) s[kt] *= iz;
+}
+
+// A block's rows x (16 tokens x 32 features) with the token along the lane group: o[t][s] =
+// feature 16 t + c of token 4 q + s.  scr: [16][LK].
+__device__ __forceinline__ void transpose_block(f4 (&o)[2], const f4 (&x)[2], float *scr) {
+  const int q = lane() >> 4, c = lane() & 15;
+  wave_sync();
+#pragma unroll
+  for (int t = 0; t < 2; ++t) stf4(scr + c * LK + 16 * t + 4 * q, x[t]);
+  wave_sync();
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int s = 0; s < 4; ++s) o[t][s] = scr[(4 * q + s) * LK + 16 * t + c];
+  wave_sync();
+}
+// 16 x 16 tile in LDS, element (token, key) swizzled so that neither access has a bank conflict:
+// put writes a lane's four keys of its token, get reads token 4 q + s of key c.
+__device__ __forceinline__ void put_tile(float *tile, f4 y) {
+  const int q = lane() >> 4, c = lane() & 15, h = c >> 2;
+  stf4(tile + 16 * (4 * h + ((c & 3) ^ h)) + 4 * (q ^ h), y);
+}
+__device__ __forceinline__ f4 get_tile(const float *tile) {
+  const int q = lane() >> 4, c = lane() & 15;
+  f4 o;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) o[s] = tile[16 * (4 * q + (s ^ q)) + (c ^ (4 * q))];
+  return o;
+}
+
+// The node update's W1 (224 x 64) in the registers of a workgroup of NW waves, a quarter-wave to a
+// row: row 4 (wave + NW r) + q, columns 4 c ..  One load serves every atom of the workgroup,
+// and W1 x and W1^T dz alike.
+template <int NW> struct NodeW {
+  static constexpr int R = (XD / 4 + NW - 1) / NW;
+  f4 w[R];
+  int wave;
+  __device__ __forceinline__ int row(int r) const { return 4 * (wave + NW * r) + (lane() >> 4); }
+  __device__ __forceinline__ NodeW(const float *__restrict__ W1, int wv) : wave(wv) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) w[r] = row(r) < XD ? ldf4(W1 + row(r) * G1D + 4 * (lane() & 15)) : f4{0.f, 0.f, 0.f, 0.f};
+  }
+  // The wave's part of sum_k x[k] W1[k][:], to part[64].
+  __device__ __forceinline__ void forward(const float *x, float *part) const {
+    f4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int r = 0; r < R; ++r) v += x[min(row(r), XD - 1)] * w[r];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = sumq(v[i]);
+    if (lane() < 16) stf4(part + 4 * lane(), v);
+  }
+  // dx[k] = sum_o W1[k][o] dz[o] for the wave's rows.
+  __device__ __forceinline__ void backward(const float *dz, float *dx) const {
+    const f4 z = ldf4(dz + 4 * (lane() & 15));
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const float v = dp::sum16(fmaf(w[r][0], z[0], w[r][1] * z[1]) + fmaf(w[r][2], z[2], w[r][3] * z[3]));
+      if ((lane() & 15) == 0 && row(r) < XD) dx[row(r)] = v;
     }
   }
 };
 
-struct NoRows {
-  __device__ void issue() {}
-  __device__ void store() {}
-};
-
-// Layer input of atom i's features: g1 of the neighbours (G1J), g2 of its edges (G2) and
-// its own g1 (g1i); `more` issues its own reads after these and stores after them.
-template <class More>
-__device__ __forceinline__ void load_inputs(const Weights &w, const Buffers &b, const EnvR &e, const int *types, int i,
-                                            int l, float *G1J, float *G2, float *g1i, More &more) {
-  const int nn = e.nn;
-  Rows<G1D> a;
-  Rows<G2D> c;
-  if (l == 0) {
-    a.issue(nn, [&](int j) { return w.TN + e.tj[j] * G1D; });
-  } else {
-    a.issue(nn, [&](int j) { return b.g1f + ((size_t)(l - 1) * b.cap + e.jn[j]) * G1D; });
-    c.issue(nn, [&](int j) { return b.g2f + erow2(b, l - 1, i, j); });
-  }
-  float gi = 0.f;
-  if (threadIdx.x < G1D)
-    gi = l == 0 ? w.TN[clamp_type(types[i]) * G1D + threadIdx.x]
-                : b.g1f[((size_t)(l - 1) * b.cap + i) * G1D + threadIdx.x];
-  more.issue();
-  a.store(G1J, LG, nn);
-  if (l == 0) {
-    for (int k = threadIdx.x; k < nn * G2D; k += NT) {
-      const int j = k >> 5, cc = k & 31;
-      G2[j * LQ + cc] = tanhf(e.s[j] * w.Wp0[cc] + w.bp0[cc]);
+// The wave's share of T^T = sum_j R_j g2_j^T (4 x 32) and of the convolution sums c = sum_j
+// sw_j g2_j * g1_j[:32]: 5 rows of 32 in part.  The A operand has R in rows a < 4 and ones in row 4.
+template <int NB>
+__device__ __forceinline__ void node_parts(const EnvN<NB> &e, int jb, const f4 (&g2)[2], const f4 (&g1)[2], float *scr,
+                                           float (*part)[G2D]) {
+  const int q = lane() >> 4, c = lane() & 15;
+  f4 gt[2], pt[2], p[2], acc[2] = {};
+  const float swj = e.sw[16 * jb + c];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) p[t] = swj * g2[t] * g1[t];
+  transpose_block(gt, g2, scr);
+  transpose_block(pt, p, scr);
+  const float one = c == 4 ? 1.f : 0.f;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const int j = 16 * jb + 4 * q + s;
+    const float r = c == 0 ? e.s[j] : (c < 4 ? e.s[j] * e.rh[c < 4 ? max(c - 1, 0) : 0][j] : 0.f);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      acc[t] = mfma(r, gt[t][s], acc[t]);
+      acc[t] = mfma(one, pt[t][s], acc[t]);
     }
-  } else {
-    c.store(G2, LQ, nn);
   }
-  if (threadIdx.x < G1D) g1i[threadIdx.x] = gi;
-  more.store();
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    if (q == 0)
+#pragma unroll
+      for (int a = 0; a < 4; ++a) part[a][16 * t + c] = acc[t][a];
+    if (q == 1) part[4][16 * t + c] = acc[t][0];
+  }
 }
 
-// Pair update and projections on MFMA (16x16x4 f32), one tile of 16 edges per wave:
-// G2A = G2 + tanh([G2, G1J] Wa + ba) (TA, the tanh term, written over G2 when
-// `keep_ta`), then Q, K, V = G2A Wq, Wk, Wv.  The weights are B operands held in
-// registers (lane l holds W[4 s + l / 16][16 ct + l % 16] for k step s); a wave reads
-// and writes only the rows of its own tiles.  Ends synchronised.
-__device__ void pair_and_qkv(const Weights &w, int l, int nn, float *G2, const float *G1J, float *G2A, float *Q,
-                             float *K, float *V, bool keep_ta) {
-  const int ln = lane_id(), wv = wave_id(), kq = ln >> 4, col = ln & 15;
-  const int nkt = (nn + 15) >> 4;
-  constexpr int KA = (G2D + G1D) / 4, KP = G2D / 4;  // k steps of the two products
-  float wa[KA][2], wq[KP][2], wk[KP][2], wvv[KP][2];
-#pragma unroll
-  for (int st = 0; st < KA; ++st)
-#pragma unroll
-    for (int ct = 0; ct < 2; ++ct) wa[st][ct] = w.Wa[l][(4 * st + kq) * G2D + 16 * ct + col];
-#pragma unroll
-  for (int st = 0; st < KP; ++st)
-#pragma unroll
-    for (int ct = 0; ct < 2; ++ct) {
-      wq[st][ct] = w.Wq[l][(4 * st + kq) * G2D + 16 * ct + col];
-      wk[st][ct] = w.Wk[l][(4 * st + kq) * G2D + 16 * ct + col];
-      wvv[st][ct] = w.Wv[l][(4 * st + kq) * G2D + 16 * ct + col];
-    }
-  const float bias[2] = {w.ba[l][col], w.ba[l][16 + col]};
-  for (int et = wv; et < nkt; et += NWG) {
-    const int ra = 16 * et + col;  // this lane's A-operand row
-    const bool aok = ra < nn;
-    f4 z[2] = {};
-#pragma unroll
-    for (int st = 0; st < KA; ++st) {
-      const int k = 4 * st + kq;
-      const float x = aok ? (k < G2D ? G2[ra * LQ + k] : G1J[ra * LG + k - G2D]) : 0.f;
-#pragma unroll
-      for (int ct = 0; ct < 2; ++ct) z[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, wa[st][ct], z[ct], 0, 0, 0);
-    }
-#pragma unroll
-    for (int ct = 0; ct < 2; ++ct)
-#pragma unroll
-      for (int ii = 0; ii < 4; ++ii) {
-        const int r = 16 * et + 4 * kq + ii, c = 16 * ct + col;
-        if (r < nn) {
-          const float ta = ftanh(z[ct][ii] + bias[ct]);
-          G2A[r * LQ + c] = G2[r * LQ + c] + ta;
-          if (keep_ta) G2[r * LQ + c] = ta;
-        }
-      }
-    wave_sync();
-    f4 q[2] = {}, k[2] = {}, v[2] = {};
-#pragma unroll
-    for (int st = 0; st < KP; ++st) {
-      const float x = aok ? G2A[ra * LQ + 4 * st + kq] : 0.f;
-#pragma unroll
-      for (int ct = 0; ct < 2; ++ct) {
-        q[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, wq[st][ct], q[ct], 0, 0, 0);
-        k[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, wk[st][ct], k[ct], 0, 0, 0);
-        v[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, wvv[st][ct], v[ct], 0, 0, 0);
-      }
-    }
-#pragma unroll
-    for (int ct = 0; ct < 2; ++ct)
-#pragma unroll
-      for (int ii = 0; ii < 4; ++ii) {
-        const int r = 16 * et + 4 * kq + ii, c = 16 * ct + col;
-        if (r < nn) {
-          Q[r * LQA + c] = q[ct][ii];
-          K[r * LQA + c] = k[ct][ii];
-          V[r * LQA + c] = v[ct][ii];
-        }
-      }
-  }
+// T[m][a] and the node-update input xs = [g1_i, D, c] with D = T T[:4]^T, from the waves' shares
+// (added in order).  Passes three barriers, the first before the shares are read.
+template <int NB>
+__device__ __forceinline__ void node_inputs(int tid, int nb, const float (*part)[5][G2D], const float *g1i, float inv_sel,
+                                            float *T, float *xs) {
   __syncthreads();
-}
-
-// One column of the node update's product z_c = b1_c + xs . W1[:, c], split over the
-// waves (wave u sums the XD / NWG consecutive inputs from u XD / NWG, in order) and
-// combined in wave order; the result is in zc[c] for c < 64.  Ends synchronised.
-__device__ void node_product(const float *W1, const float *b1, const float *xs, float (*part)[G1D], float *zc) {
-  const int c = threadIdx.x & 63, u = threadIdx.x >> 6;
-  constexpr int QW = XD / NWG;
-  float v = 0.f;
-#pragma unroll 8
-  for (int q = u * QW; q < (u + 1) * QW; ++q) v += xs[q] * W1[q * G1D + c];
-  part[u][c] = v;
-  __syncthreads();
-  if (threadIdx.x < G1D) {
-    float z = b1[c];
-    for (int uu = 0; uu < NWG; ++uu) z += part[uu][c];
-    zc[c] = z;
-  }
-  __syncthreads();
-}
-
-// T = sum_j g2_j R_j^T / sel (into T[32][4]), c = sum_j sw_j g2_j g1_j[:32] / sel, and the
-// node-update input xs = [g1i, D, c] with D = T T[:4]^T.  Waves 0 and 1 form T^T = R^T G2B
-// on MFMA (16x16x4 f32, four neighbours per step, rows a < 4 of the 16 used) over the
-// two halves of j; waves 2 .. 5 split the sums of c into eight ranges of j.  Partials go
-// to `part` (at least 512 floats) and are added in order.  Ends synchronised.
-__device__ void node_inputs(const EnvR &e, int nn, const float *G2B, const float *G1J, const float *g1i,
-                            float inv_sel, float *T, float *xs, float *part) {
-  static_assert(NWG >= 6, "node_inputs uses six waves");
-  constexpr int NSEG = 8;
-  const int t = threadIdx.x, wv = wave_id(), ln = lane_id();
-  if (wv < 2) {
-    const int kq = ln >> 4, col = ln & 15;
-    const int j0 = wv * nn / 2, j1 = (wv + 1) * nn / 2;
-    f4 acc[2] = {};
-    for (int jb = j0; jb < j1; jb += 4) {
-      const int j = jb + kq;
-      float ra = 0.f;  // A[a = col][j] = R_j[a]
-      if (j < j1 && col < 4) ra = col == 0 ? e.s[j] : e.s[j] * e.rh[3 * j + col - 1];
-#pragma unroll
-      for (int ct = 0; ct < 2; ++ct) {
-        const float g = j < j1 ? G2B[j * LQ + 16 * ct + col] : 0.f;
-        acc[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(ra, g, acc[ct], 0, 0, 0);
-      }
-    }
-    if (kq == 0)
-#pragma unroll
-      for (int ct = 0; ct < 2; ++ct)
-#pragma unroll
-        for (int ii = 0; ii < 4; ++ii) part[wv * 128 + (16 * ct + col) * 4 + ii] = acc[ct][ii];
-  } else if (wv < 6) {
-    const int u = t - 128, c = u % G2D, sg = u / G2D;
-    const int j0 = sg * nn / NSEG, j1 = (sg + 1) * nn / NSEG;
+  if (tid < 5 * G2D) {
+    const int a = tid / G2D, m = tid % G2D;
     float v = 0.f;
-    for (int j = j0; j < j1; ++j) v += e.sw[j] * G2B[j * LQ + c] * G1J[j * LG + c];
-    part[256 + u] = v;
+    for (int u = 0; u < nb; ++u) v += part[u][a][m];
+    if (a < 4) T[4 * m + a] = v * inv_sel;
+    else xs[G1D + G2D * NAX + m] = v * inv_sel;
+  } else if (tid >= 5 * G2D && tid < 5 * G2D + G1D) {
+    xs[tid - 5 * G2D] = g1i[tid - 5 * G2D];
   }
   __syncthreads();
-  if (t < G2D * 4) {
-    T[t] = (part[t] + part[128 + t]) * inv_sel;
-  } else if (t < G2D * 5) {
-    const int c = t - G2D * 4;
-    float v = part[256 + c];
-    for (int sg = 1; sg < NSEG; ++sg) v += part[256 + sg * G2D + c];
-    xs[G1D + G2D * NAX + c] = v * inv_sel;
-  } else if (t >= 256 && t < 256 + G1D) {
-    xs[t - 256] = g1i[t - 256];
-  }
-  __syncthreads();
-  if (t < G2D * NAX) {
-    const int c = t >> 2, bb = t & 3;  // D[c][b], flattened c * 4 + b
+  if (tid < G2D * NAX) {
+    const int c = tid >> 2, bb = tid & 3;  // D[c][b], flattened c * 4 + b
     float v = 0.f;
     for (int a = 0; a < 4; ++a) v += T[c * 4 + a] * T[bb * 4 + a];
-    xs[G1D + t] = v;
+    xs[G1D + tid] = v;
   }
   __syncthreads();
-}
-
-// The attention on MFMA (16x16x4 f32).  Score tiles are kept transposed, keys x
-// queries: lane l holds S^T[key 16 kt + 4 (l / 16) + i][query q0 + l % 16], so the
-// weights of a query are reduced over i, over the key tiles and across l / 16, and they
-// are already the B operand of Y^T = V^T A^T with the k order permuted as in the
-// products below (step s of a key tile takes key 16 kt + 4 (l / 16) + s).
-// acc += sum_{c < 32} A[r][c] B[col][c] with lane's A row (r = l % 16) at arow and B row
-// (col = l % 16) at brow, 16-byte aligned rows of 32 floats; nullptr reads as zeros.
-__device__ __forceinline__ void dot32_tile(f4 &acc, const float *arow, const float *brow) {
-  const int kq = lane_id() >> 4;
-#pragma unroll
-  for (int kb = 0; kb < 2; ++kb) {
-    const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-    const float4 a = arow ? ld4(arow + 16 * kb + 4 * kq) : z;
-    const float4 b = brow ? ld4(brow + 16 * kb + 4 * kq) : z;
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b.x, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b.y, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, b.z, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, b.w, acc, 0, 0, 0);
-  }
-}
-constexpr int NKT = (SEL + 15) / 16;  // key (or query) tiles of 16
-
-// A operand of out^T = W dX^T for a row-major [32][32] W (dE/dx = dE/dy W^T for y = x W):
-// lane l holds W[16 ot + l % 16][16 ct + 4 (l / 16) + ii], the k order of the rows of an
-// accumulator tile, so a dX^T tile from a product above is the B operand as it stands.
-__device__ __forceinline__ void load_wt(const float *W, float (&r)[2][2][4]) {
-  const int kq = lane_id() >> 4, col = lane_id() & 15;
-#pragma unroll
-  for (int ot = 0; ot < 2; ++ot)
-#pragma unroll
-    for (int ct = 0; ct < 2; ++ct)
-#pragma unroll
-      for (int ii = 0; ii < 4; ++ii) r[ot][ct][ii] = W[(16 * ot + col) * G2D + 16 * ct + 4 * kq + ii];
-}
-// out[ot] += W dX^T over the 32 features, x[ct][ii] = dX^T[16 ct + 4 (l / 16) + ii][l % 16].
-__device__ __forceinline__ void wt_product(f4 (&out)[2], const float (&r)[2][2][4], const f4 (&x)[2]) {
-#pragma unroll
-  for (int ot = 0; ot < 2; ++ot)
-#pragma unroll
-    for (int ct = 0; ct < 2; ++ct)
-#pragma unroll
-      for (int ii = 0; ii < 4; ++ii)
-        out[ot] = __builtin_amdgcn_mfma_f32_16x16x4f32(r[ot][ct][ii], x[ct][ii], out[ot], 0, 0, 0);
 }
 
 // ------------------------------------------------------------------ forward
-struct SmemF {
-  EnvR env;
-  float G1J[SEL * LG];
-  float G2[SEL * LQ];   // layer input, then the layer's output g2
-  float G2A[SEL * LQ];
-  float Q[SEL * LQA] __attribute__((aligned(16)));
-  float K[SEL * LQA] __attribute__((aligned(16)));
-  float V[SEL * LQA] __attribute__((aligned(16)));
-  float g1i[G1D], T[G2D * 4], xs[XD], part[NWG][G1D], zc[G1D];
+template <int NB> struct SmemF {
+  EnvN<NB> e;
+  float K[16 * NB * LK] __attribute__((aligned(16)));
+  float V[16 * NB * LK] __attribute__((aligned(16)));
+  float scr[NB][16 * LK] __attribute__((aligned(16)));
+  float part[NB][5][G2D];
+  float T[G2D * 4];
+  float zp[2 * NB_SMALL][G1D] __attribute__((aligned(16)));  // the waves' parts of the node update
+  float g1i[G1D], xs[XD], mv[64 * NB];
   float y1[FWID], t2[FWID], dp[FWID];
 };
 
-__global__ void __launch_bounds__(NT) k_rep_fwd(Weights w, Buffers b, const double *__restrict__ X,
-                                                const int *__restrict__ types, const int *__restrict__ nlist,
-                                                const int *__restrict__ nnei, const Grid *__restrict__ grids, int n,
-                                                int l, Geo geo, double *__restrict__ Ei,
-                                                const unsigned *__restrict__ flags) {
-  __shared__ SmemF sm;
-  const int i = blockIdx.x;
-  if (i >= n || failed(flags)) return;
-  const int tid = threadIdx.x, wv = wave_id(), ln = lane_id();
-  build_env_r(sm.env, X, types, nlist, nnei, i, n, grids[0], geo);
-  const EnvR &e = sm.env;
-  const int nn = e.nn;
-  NoRows none;
-  load_inputs(w, b, e, types, i, l, sm.G1J, sm.G2, sm.g1i, none);
+template <int NB, int NA>
+__device__ __forceinline__ void layer_fwd(int blk, int count, SmemF<NB> *smem, const Weights &w, const Buffers &b,
+                                          const double *__restrict__ Xc, const int *__restrict__ types,
+                                          const int *__restrict__ nlist, const int *__restrict__ nnei,
+                                          const Grid *__restrict__ grids, int natoms, int l, const Geo &geo,
+                                          const int *__restrict__ idx, double *__restrict__ Ei) {
+  const Part<NB, NA> pt(blk, idx, count, nnei);
+  SmemF<NB> &sm = smem[pt.half];
+  constexpr int NT = 64 * NB;
+  const int i = pt.i, nn = pt.n, nb = pt.nb, jb = pt.jb, tid = pt.tid;
+  const int ln = lane(), q = ln >> 4, c = ln & 15;
+  const bool act_ = jb < nb, live = nb > 0;
+  build_envn<NB>(sm.e, tid, Xc, types, nlist, i, nn, natoms, grids[0], geo);
+  if (tid < G1D)
+    sm.g1i[tid] = l == 0 ? w.TN[clamp_type(types[i]) * G1D + tid] : b.g1f[((size_t)(l - 1) * b.cap + i) * G1D + tid];
   __syncthreads();
-  pair_and_qkv(w, l, nn, sm.G2, sm.G1J, sm.G2A, sm.Q, sm.K, sm.V, false);
-
-  // attention, one tile of 16 queries per wave
-  const float isq = 1.f / sqrtf((float)G2D);
-  const int nkt = (nn + 15) >> 4;
-  const int kq = ln >> 4, col = ln & 15;
-  for (int qt = wv; qt < nkt; qt += NWG) {
-    const int qme = 16 * qt + col;  // this lane's query
-    const bool qok = qme < nn;
-    f4 st[NKT];
-#pragma unroll
-    for (int kt = 0; kt < NKT; ++kt) {
-      st[kt] = f4{0.f, 0.f, 0.f, 0.f};
-      if (kt < nkt) {
-        const int kr = 16 * kt + col;
-        dot32_tile(st[kt], kr < nn ? sm.K + kr * LQA : nullptr, qok ? sm.Q + qme * LQA : nullptr);
-      }
-    }
-    // weights of the lane's query over its keys: max, then sw_k exp(S - max) / sum, times the gate
-    float m = -INFINITY;
-#pragma unroll
-    for (int kt = 0; kt < NKT; ++kt)
-#pragma unroll
-      for (int ii = 0; ii < 4; ++ii) {
-        const int k = 16 * kt + 4 * kq + ii;
-        if (kt < nkt && k < nn) m = fmaxf(m, st[kt][ii] * isq);
-      }
-    m = fmaxf(m, __shfl_xor(m, 16));
-    m = fmaxf(m, __shfl_xor(m, 32));
-    float z = 0.f;
-#pragma unroll
-    for (int kt = 0; kt < NKT; ++kt) {
-      float swv[4];
-      quad(e.sw + 16 * kt + 4 * kq, swv);
-#pragma unroll
-      for (int ii = 0; ii < 4; ++ii) {
-        const int k = 16 * kt + 4 * kq + ii;
-        const float ex = (kt < nkt && k < nn) ? swv[ii] * __expf(st[kt][ii] * isq - m) : 0.f;
-        st[kt][ii] = ex;
-        z += ex;
-      }
-    }
-    z += __shfl_xor(z, 16);
-    z += __shfl_xor(z, 32);
-    const float iz = qok ? 1.f / z : 0.f;
-    const float hx = e.rh[3 * (qok ? qme : 0)], hy = e.rh[3 * (qok ? qme : 0) + 1], hz = e.rh[3 * (qok ? qme : 0) + 2];
-#pragma unroll
-    for (int kt = 0; kt < NKT; ++kt) {
-      float h[12];
-      rh_quad(e, 16 * kt + 4 * kq, h);
-#pragma unroll
-      for (int ii = 0; ii < 4; ++ii) st[kt][ii] *= iz * (hx * h[3 * ii] + hy * h[3 * ii + 1] + hz * h[3 * ii + 2]);
-    }
-    // Y^T[c][q] = sum_k V[k][c] A^T[k][q], two tiles of 16 features
-    f4 yt[2] = {};
-#pragma unroll
-    for (int kt = 0; kt < NKT; ++kt) {
-      if (kt >= nkt) break;
-#pragma unroll
-      for (int ss = 0; ss < 4; ++ss) {
-        const int k = 16 * kt + 4 * kq + ss;
-#pragma unroll
-        for (int ct = 0; ct < 2; ++ct) {
-          const float v = k < nn ? sm.V[k * LQA + 16 * ct + col] : 0.f;
-          yt[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(v, st[kt][ss], yt[ct], 0, 0, 0);
-        }
-      }
-    }
-    if (qok)
-#pragma unroll
-      for (int ct = 0; ct < 2; ++ct)
-#pragma unroll
-        for (int ii = 0; ii < 4; ++ii) {
-          const int c = 16 * ct + 4 * kq + ii;
-          const float g2b = sm.G2A[qme * LQ + c] + yt[ct][ii];
-          sm.G2[qme * LQ + c] = g2b;
-          b.g2f[erow2(b, l, i, qme) + c] = g2b;
-        }
+  const int j = 16 * jb + c;
+  f4 x[6], ta[2], g2a[2], qr[2];
+  if (act_) {
+    token_in<NB>(w, b, sm.e, l, i, j, nn, x);
+    pair_and_qkv(w, l, x, ta, g2a, qr, sm.K + j * LK, sm.V + j * LK);
   }
+  const NodeW<NA * NB> w1(w.W1[l], pt.half * NB + jb);
+  tile_barrier();
   __syncthreads();
-
-  node_inputs(e, nn, sm.G2, sm.G1J, sm.g1i, geo.inv_sel, sm.T, sm.xs, &sm.part[0][0]);
-  node_product(w.W1[l], w.b1[l], sm.xs, sm.part, sm.zc);
+  if (act_) {
+    f4 s[NB], y[2];
+    keys_dot<NB>(s, sm.K, qr, nb);
+    softmax_keys<NB>(s, sm.e, nn);
+    const float hx = sm.e.rh[0][j], hy = sm.e.rh[1][j], hz = sm.e.rh[2][j];
+    keys_sum<NB>(y, sm.V, [&](int kt) {
+      const int k = 16 * kt + 4 * q;
+      return s[kt] * ldf4(sm.e.sw + k) * (hx * ldf4(sm.e.rh[0] + k) + hy * ldf4(sm.e.rh[1] + k) + hz * ldf4(sm.e.rh[2] + k));
+    }, nb);
+    f4 g1[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      y[t] += g2a[t];
+      g1[t] = x[2 + t];
+      if (j < nn) stf4(b.g2f + erow2(b, l, i, j) + 16 * t + 4 * q, y[t]);
+    }
+    node_parts<NB>(sm.e, jb, y, g1, sm.scr[jb], sm.part[jb]);
+  }
+  node_inputs<NB>(tid, nb, sm.part, sm.g1i, geo.inv_sel, sm.T, sm.xs);
+#pragma unroll
+  for (int a = 0; a < NA; ++a) w1.forward(smem[a].xs, smem[a].zp[w1.wave]);
+  __syncthreads();
+  const size_t li = (size_t)l * b.cap + i;
   float g1n = 0.f;
   if (tid < G1D) {
-    g1n = sm.g1i[tid] + tanhf(sm.zc[tid]);
-    if (l < NLAYER - 1) b.g1f[((size_t)l * b.cap + i) * G1D + tid] = g1n;
+    float z = w.b1[l][tid];
+#pragma unroll
+    for (int u = 0; u < NA * NB; ++u) z += sm.zp[u][tid];
+    const float t = tanhf(z);
+    g1n = sm.g1i[tid] + t;
+    if (live) b.tn[li * G1D + tid] = t;
+    if (l < NLAYER - 1 && live) b.g1f[li * G1D + tid] = g1n;
   }
+  if (live && tid < 4 * G2D) b.Tn[li * (4 * G2D) + tid] = sm.T[tid];
   if (l < NLAYER - 1) return;
 
   // fitting net, E_i and dE/dg1_i
-  __syncthreads();
-  if (tid < G1D) sm.g1i[tid] = g1n;
-  __syncthreads();
+  if (tid < G1D) sm.xs[tid] = g1n;
+  const float z1 = matvec<NT, G1D, FWID>(w.G1, sm.xs, sm.mv, tid);
+  if (tid < FWID) sm.y1[tid] = tanhf(z1 + w.d1[tid]);
+  const float z2 = matvec<NT, FWID, FWID>(w.G2, sm.y1, sm.mv, tid);
   if (tid < FWID) {
-    float z = w.d1[tid];
-    for (int k = 0; k < G1D; ++k) z += sm.g1i[k] * w.G1[k * FWID + tid];
-    sm.y1[tid] = tanhf(z);
-  }
-  __syncthreads();
-  if (tid < FWID) {
-    float z = w.d2[tid];
-    for (int k = 0; k < FWID; ++k) z += sm.y1[k] * w.G2[k * FWID + tid];
-    const float t2 = tanhf(z);
+    const float t2 = tanhf(z2 + w.d2[tid]);
     sm.t2[tid] = t2;
     sm.dp[tid] = w.G3[tid] * (1.f - t2 * t2);
   }
-  __syncthreads();
-  if (tid == 0) {
-    double E = w.d3;
-    for (int k = 0; k < FWID; ++k) E += (double)(sm.t2[k] + sm.y1[k]) * w.G3d[k];
-    Ei[i] = E;
+  const float z3 = matvec<NT, FWID, FWID>(w.G2T, sm.dp, sm.mv, tid);  // its first barrier: t2 is complete
+  if (jb == 0) {
+    double E = (double)(sm.t2[ln] + sm.y1[ln]) * w.G3d[ln] + (double)(sm.t2[ln + 64] + sm.y1[ln + 64]) * w.G3d[ln + 64];
+    for (int off = 32; off > 0; off >>= 1) E += __shfl_xor(E, off);
+    if (ln == 0 && live) Ei[i] = w.d3 + E;
   }
   float dp1 = 0.f;
-  if (tid < FWID) {
-    float dy1 = w.G3[tid];
-    for (int k = 0; k < FWID; ++k) dy1 += sm.dp[k] * w.G2[tid * FWID + k];
-    dp1 = dy1 * (1.f - sm.y1[tid] * sm.y1[tid]);
-  }
+  if (tid < FWID) dp1 = (z3 + w.G3[tid]) * (1.f - sm.y1[tid] * sm.y1[tid]);
   __syncthreads();
   if (tid < FWID) sm.dp[tid] = dp1;
-  __syncthreads();
-  if (tid < G1D) {
-    float dn = 0.f;
-    for (int k = 0; k < FWID; ++k) dn += sm.dp[k] * w.G1[tid * FWID + k];
-    b.dnl[(size_t)i * G1D + tid] = dn;
-  }
+  const float dn = matvec<NT, FWID, G1D>(w.G1T, sm.dp, sm.mv, tid);
+  if (tid < G1D && live) b.dnl[(size_t)i * G1D + tid] = dn;
 }
 
 // ------------------------------------------------------------------ backward
-struct SmemB {
-  EnvR env;
-  float G1J[SEL * LG];
-  float G2[SEL * LQ];    // layer input g2, then the pair update's tanh term
-  float G2A[SEL * LQ];   // after the pair update; later dE/dg2a
-  float Q[SEL * LQA] __attribute__((aligned(16)));
-  float K[SEL * LQA] __attribute__((aligned(16)));
-  float V[SEL * LQA] __attribute__((aligned(16)));
-  float G2B[SEL * LQ];   // the layer's output g2
-  float DY[SEL * LQA] __attribute__((aligned(16)));  // dE/dg2 of the output; later the pair update's dz
-  float EG[SEL * GSN];   // per-edge dE/ds, dE/dsw, dE/drhat
-  float stat[3][SELP] __attribute__((aligned(16)));  // per query row: max score, 1 / normaliser, rho
-  float g1i[G1D], T[G2D * 4], xs[XD], dg1[G1D], dxn[XD], dT[G2D * 4], part[NWG][G1D], zc[G1D];
-  int slot[SEL];
+template <int NB> struct SmemB {
+  EnvN<NB> e;
+  float K[16 * NB * LK] __attribute__((aligned(16)));  // the keys' rows, then the queries'
+  float V[16 * NB * LK] __attribute__((aligned(16)));  // the values' rows, then those of dY
+  float tile[NB][NB][256] __attribute__((aligned(16)));  // E gate, then W: tokens' block, keys' block
+  float drhw[NB][16 * NB * 3];  // each wave's column sums of dC rhat
+  float T[G2D * 4];
+  float dT[G2D * 4] __attribute__((aligned(16)));
+  float dxn[XD] __attribute__((aligned(16)));
+  float dg1[G1D], zz[G1D] __attribute__((aligned(16)));
+  float rows[NB][G1D] __attribute__((aligned(16)));
+  int slot[16 * NB];
 };
 
-__global__ void __launch_bounds__(NT) k_rep_bwd(Weights w, Buffers b, const double *__restrict__ X,
-                                                const int *__restrict__ types, const int *__restrict__ nlist,
-                                                const int *__restrict__ nnei, const Grid *__restrict__ grids, int n,
-                                                int l, Geo geo, float4 *__restrict__ gout,
-                                                const unsigned *__restrict__ flags) {
-  __shared__ SmemB sm;
-  const int i = blockIdx.x;
-  if (i >= n || failed(flags)) return;
-  const int tid = threadIdx.x, wv = wave_id(), ln = lane_id();
-  const bool top = l == NLAYER - 1;
-  build_env_r(sm.env, X, types, nlist, nnei, i, n, grids[0], geo);
-  const EnvR &e = sm.env;
-  const int nn = e.nn;
-  // the layer's output g2, the output gradient and edge terms from the layer above and
-  // the reverse slots, read together with the layer input
-  struct More {
-    const Buffers &b;
-    SmemB &sm;
-    int i, l, nn;
-    bool top;
-    Rows<G2D> g2b, dy;
-    Rows<GSN> eg;
-    int sl;
-    __device__ void issue() {
-      g2b.issue(nn, [&](int j) { return b.g2f + erow2(b, l, i, j); });
-      if (!top) {
-        dy.issue(nn, [&](int j) { return b.dg2 + ((size_t)i * SEL + j) * G2D; });
-        eg.issue(nn, [&](int j) { return b.gs + ((size_t)i * SEL + j) * GSN; });
-        if ((int)threadIdx.x < nn) sl = b.slot[(size_t)i * SEL + threadIdx.x];
-      }
-    }
-    __device__ void store() {
-      g2b.store(sm.G2B, LQ, nn);
-      if (top) {
-        for (int k = threadIdx.x; k < nn * G2D; k += NT) sm.DY[(k >> 5) * LQA + (k & 31)] = 0.f;
-        for (int k = threadIdx.x; k < nn * GSN; k += NT) sm.EG[k] = 0.f;
-      } else {
-        dy.store(sm.DY, LQA, nn);
-        eg.store(sm.EG, GSN, nn);
-        if ((int)threadIdx.x < nn) sm.slot[threadIdx.x] = sl;
-      }
-    }
-  } more{b, sm, i, l, nn, top, {}, {}, {}, -1};
-  load_inputs(w, b, e, types, i, l, sm.G1J, sm.G2, sm.g1i, more);
-  __syncthreads();
-  {  // dE/dg1_i after this layer: own part + the neighbours' edge parts, rows by wave, waves in order
-    float v = 0.f;
-    if (!top) {
-      const float *src = b.dnj + (size_t)((l + 1) & 1) * b.cap * SEL * G1D;
-#pragma unroll 8
-      for (int j = wv; j < nn; j += NWG) {  // branch-free (a missing slot reads row 0 and adds 0), so the loads overlap
-        const int sj = sm.slot[j];
-        const float x = src[((size_t)e.jn[j] * SEL + max(sj, 0)) * G1D + ln];
-        v += sj >= 0 ? x : 0.f;
-      }
-    }
-    sm.part[wv][ln] = v;
-  }
-  __syncthreads();
+template <int NB, int NA>
+__device__ __forceinline__ void layer_bwd(int blk, int count, SmemB<NB> *smem, const Weights &w, const Buffers &b,
+                                          const double *__restrict__ Xc, const int *__restrict__ types,
+                                          const int *__restrict__ nlist, const int *__restrict__ nnei,
+                                          const Grid *__restrict__ grids, int natoms, int l, const Geo &geo,
+                                          const int *__restrict__ idx, float4 *__restrict__ gout) {
+  const Part<NB, NA> pt(blk, idx, count, nnei);
+  SmemB<NB> &sm = smem[pt.half];
+  constexpr int NT = 64 * NB;
+  const int i = pt.i, nn = pt.n, nb = pt.nb, jb = pt.jb, tid = pt.tid;
+  const int ln = lane(), q = ln >> 4, c = ln & 15;
+  const bool act_ = jb < nb, live = nb > 0, top = l == NLAYER - 1;
+  const f4 zero = {0.f, 0.f, 0.f, 0.f};
+  const float isq = 0.17677669529663687f;
+  build_envn<NB>(sm.e, tid, Xc, types, nlist, i, nn, natoms, grids[0], geo);
+  for (int k = tid; k < 16 * NB; k += NT) sm.slot[k] = !top && k < nn ? b.slot[(size_t)i * SEL + k] : -1;
+  const size_t li = (size_t)l * b.cap + i;
+  float tn = 0.f, dni = 0.f;
   if (tid < G1D) {
-    float v = b.dnl[(size_t)i * G1D + tid];
-    for (int u = 0; u < NWG; ++u) v += sm.part[u][tid];
-    sm.dg1[tid] = v;
+    tn = b.tn[li * G1D + tid];
+    dni = b.dnl[(size_t)i * G1D + tid];
   }
-  // recompute the layer's forward: pair update (tanh term kept in G2), projections, node input
-  pair_and_qkv(w, l, nn, sm.G2, sm.G1J, sm.G2A, sm.Q, sm.K, sm.V, true);
-  node_inputs(e, nn, sm.G2B, sm.G1J, sm.g1i, geo.inv_sel, sm.T, sm.xs, &sm.part[0][0]);
-  // node backward: dz = dg1 (1 - t^2), dxn = W1 dz
-  node_product(w.W1[l], w.b1[l], sm.xs, sm.part, sm.zc);
+  if (tid < 4 * G2D) sm.T[tid] = b.Tn[li * (4 * G2D) + tid];
+  __syncthreads();
+  const int j = 16 * jb + c;
+  const bool ok = act_ && j < nn;
+  // dE/dg1_i after this layer: the neighbours' edge parts, sixteen lanes a row, the row groups in
+  // turn through the list and added in order
+  constexpr int G = 4 * NB, R = 4;
+  f4 v[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int k = (tid >> 4) + G * r, sk = sm.slot[k];
+    v[r] = sk >= 0 ? ldf4(b.dnj + (size_t)((l + 1) & 1) * b.cap * SEL * G1D + ((size_t)sm.e.jn[k] * SEL + sk) * G1D + 4 * c) : zero;
+  }
+  // the layer's forward again: pair update, projections; its output is stored
+  f4 ta[2], qr[2], g1[2], g2b[2], dy[2];
+  if (act_) {
+    f4 x[6], g2a[2];
+    token_in<NB>(w, b, sm.e, l, i, j, nn, x);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      g2b[t] = ok ? ldf4(b.g2f + erow2(b, l, i, j) + 16 * t + 4 * q) : zero;
+      dy[t] = ok && !top ? ldf4(b.dg2 + ((size_t)i * SEL + j) * G2D + 16 * t + 4 * q) : zero;
+      g1[t] = x[2 + t];
+    }
+    pair_and_qkv(w, l, x, ta, g2a, qr, sm.K + j * LK, sm.V + j * LK);
+  }
+  {
+    f4 dn = v[0] + v[1] + v[2] + v[3];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) dn[k] = sumq(dn[k]);
+    if (q == 0) stf4(sm.rows[jb] + 4 * c, dn);
+  }
+  const NodeW<NA * NB> w1(w.W1[l], pt.half * NB + jb);
+  tile_barrier();
+  __syncthreads();
+  // node backward: dz = dg1 (1 - t^2), dxn = W1 dz, and meanwhile the tokens' softmax
   if (tid < G1D) {
-    const float t = tanhf(sm.zc[tid]);
-    sm.zc[tid] = sm.dg1[tid] * (1.f - t * t);
+#pragma unroll
+    for (int u = 0; u < NB; ++u) dni += sm.rows[u][tid];
+    sm.dg1[tid] = dni;
+    sm.zz[tid] = dni * (1.f - tn * tn);
+  }
+  f4 E[NB], Wg[NB], dq[2];
+  if (act_) {
+    keys_dot<NB>(E, sm.K, qr, nb);
+    softmax_keys<NB>(E, sm.e, nn);
   }
   __syncthreads();
-  if (tid < XD) {
-    float v = 0.f;
-#pragma unroll 16
-    for (int k = 0; k < G1D; ++k) v += sm.zc[k] * w.W1[l][tid * G1D + k];
-    sm.dxn[tid] = v;
-  }
+#pragma unroll
+  for (int a = 0; a < NA; ++a) w1.backward(smem[a].zz, smem[a].dxn);
   __syncthreads();
-  // dT from dD = dxn[64:192] (D[c][b] = sum_a T[c][a] T[b][a], b < 4), then / sel
+  // dT from dD = dxn[64:192] (D[c][b] = sum_a T[c][a] T[b][a], b < 4), then / sel; the sums over c
+  // of the b < 4 rows by the whole first wave
   if (tid < G2D * 4) {
-    const int c = tid >> 2, a = tid & 3;
-    float v = 0.f;
-    for (int bb = 0; bb < 4; ++bb) v += sm.dxn[G1D + c * 4 + bb] * sm.T[bb * 4 + a];
-    if (c < 4)
-      for (int m = 0; m < G2D; ++m) v += sm.dxn[G1D + m * 4 + c] * sm.T[m * 4 + a];
-    sm.dT[tid] = v * geo.inv_sel;
+    const int m = tid >> 2, a = tid & 3;
+    float d = 0.f;
+    for (int bb = 0; bb < 4; ++bb) d += sm.dxn[G1D + m * 4 + bb] * sm.T[bb * 4 + a];
+    if (jb == 0) {
+      float u = 0.f;
+#pragma unroll
+      for (int k = 0; k < G2D / 4; ++k) u += sm.dxn[G1D + (4 * k + q) * 4 + (c >> 2)] * sm.T[(4 * k + q) * 4 + a];
+      u = sumq(u);
+      if (tid < 16) d += u;
+    }
+    sm.dT[tid] = d * geo.inv_sel;
   }
   __syncthreads();
   const float *dc = sm.dxn + G1D + G2D * NAX;  // dE/dc (times sel: divided where used)
-  // dE/dg2 of the output from the contraction and the convolution; edge terms of R and sw.
-  // dR = G2B dT runs on MFMA, one tile of 16 edges per wave (B operand dT[c][a], columns
-  // a < 4 of the 16 used), into part[4 j + a].
-  {
-    const int kq = ln >> 4, col = ln & 15, net = (nn + 15) >> 4;
-    float bv[G2D / 4];
-#pragma unroll
-    for (int st = 0; st < G2D / 4; ++st) bv[st] = col < 4 ? sm.dT[(4 * st + kq) * 4 + col] : 0.f;
-    float *dRs = &sm.part[0][0];
-    for (int et = wv; et < net; et += NWG) {
-      const int ra = 16 * et + col;
-      f4 acc = {};
-#pragma unroll
-      for (int st = 0; st < G2D / 4; ++st) {
-        const float x = ra < nn ? sm.G2B[ra * LQ + 4 * st + kq] : 0.f;
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x, bv[st], acc, 0, 0, 0);
-      }
-      if (col < 4)
-#pragma unroll
-        for (int ii = 0; ii < 4; ++ii) {
-          const int j = 16 * et + 4 * kq + ii;
-          if (j < nn) dRs[4 * j + col] = acc[ii];
-        }
-    }
-  }
-  for (int o = tid; o < nn * G2D; o += NT) {
-    const int j = o >> 5, c = o & 31;
-    float v = sm.DY[j * LQA + c] + e.sw[j] * dc[c] * geo.inv_sel * sm.G1J[j * LG + c];
-    for (int a = 0; a < 4; ++a) v += sm.dT[c * 4 + a] * Rcomp(e, j, a);
-    sm.DY[j * LQA + c] = v;
-  }
-  __syncthreads();
-  for (int j = tid; j < nn; j += NT) {
-    const float *dR = &sm.part[0][0] + 4 * j;
+  // the token's gradients: dE/dg2 of the output, and of s, sw and rhat (eg)
+  float eg[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
+  const float hj[3] = {sm.e.rh[0][j], sm.e.rh[1][j], sm.e.rh[2][j]};
+  if (act_) {
+    const float sj = sm.e.s[j], swj = sm.e.sw[j];
+    f4 dR = zero;
     float dswc = 0.f;
-#pragma unroll 8
-    for (int c = 0; c < G2D; ++c) dswc += dc[c] * geo.inv_sel * sm.G2B[j * LQ + c] * sm.G1J[j * LG + c];
-    float *eg = sm.EG + j * GSN;
-    eg[0] += dR[0] + dR[1] * e.rh[3 * j] + dR[2] * e.rh[3 * j + 1] + dR[3] * e.rh[3 * j + 2];
-    eg[1] += dswc;
-    for (int a = 0; a < 3; ++a) eg[2 + a] += e.s[j] * dR[1 + a];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const f4 dcv = ldf4(dc + 16 * t + 4 * q) * geo.inv_sel;
+      dy[t] += swj * dcv * g1[t];
+      const f4 pc = dcv * g2b[t] * g1[t];
+      dswc += (pc[0] + pc[1]) + (pc[2] + pc[3]);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const f4 d = ldf4(sm.dT + 4 * (16 * t + 4 * q + k));
+        dy[t][k] += sj * (d[0] + d[1] * hj[0] + d[2] * hj[1] + d[3] * hj[2]);
+        dR += g2b[t][k] * d;
+      }
+    }
+    dswc = sumq(dswc);
+#pragma unroll
+    for (int a = 0; a < 4; ++a) dR[a] = sumq(dR[a]);
+    eg[0] = dR[0] + dR[1] * hj[0] + dR[2] * hj[1] + dR[3] * hj[2];
+    eg[1] = dswc;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) eg[2 + a] = sj * dR[1 + a];
+    // the tokens as queries
+    keys_dot<NB>(Wg, sm.V, dy, nb);  // dA
+    float rho = 0.f, h0 = 0.f, h1 = 0.f, h2 = 0.f, rj[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) rj[s] = c < 3 ? sm.e.rh[c][16 * jb + 4 * q + s] : 0.f;
+#pragma unroll
+    for (int kt = 0; kt < NB; ++kt)
+      if (kt < nb) {
+        tile_barrier();
+        const int k = 16 * kt + 4 * q;
+        const f4 sw = ldf4(sm.e.sw + k), rx = ldf4(sm.e.rh[0] + k), ry = ldf4(sm.e.rh[1] + k), rz = ldf4(sm.e.rh[2] + k);
+        const f4 cc = Wg[kt] * E[kt], dC = sw * cc, gate = rx * hj[0] + ry * hj[1] + rz * hj[2];
+        const f4 dP = Wg[kt] * gate, pr = sw * E[kt] * dP;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          rho += pr[s];
+          h0 += dC[s] * rx[s];
+          h1 += dC[s] * ry[s];
+          h2 += dC[s] * rz[s];
+        }
+        Wg[kt] = dP;
+        // columns of dC rhat: sum_j rhat_j (dA E)_jk
+        float *tile = sm.tile[jb][kt];
+        put_tile(tile, cc);
+        wave_sync();
+        const f4 ct = get_tile(tile);
+        wave_sync();
+        put_tile(tile, E[kt] * gate);
+        f4 acc = zero;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) acc = mfma(rj[s], ct[s], acc);
+        if (q == 0) {
+          const float swk = sm.e.sw[16 * kt + c];
+          float *o = sm.drhw[jb] + 3 * (16 * kt + c);
+          o[0] = swk * acc[0]; o[1] = swk * acc[1]; o[2] = swk * acc[2];
+        }
+      }
+    rho = sumq(rho);
+    eg[2] += sumq(h0);
+    eg[3] += sumq(h1);
+    eg[4] += sumq(h2);
+    keys_sum<NB>(dq, sm.K, [&](int kt) {
+      Wg[kt] = E[kt] * (Wg[kt] - rho);
+      return ldf4(sm.e.sw + 16 * kt + 4 * q) * Wg[kt] * isq;  // dS
+    }, nb);
   }
+  // the tokens as keys: the wave reads its column of tiles and the rows of every block
+  const auto column = [&](const float *rows, auto use, f4 (&acc)[2]) {
+    acc[0] = acc[1] = zero;
+#pragma unroll
+    for (int jt = 0; jt < NB; ++jt) {
+      if (jt >= nb) continue;
+      const f4 y = get_tile(sm.tile[jt][jb]);
+      use(y);
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) acc[t] = mfma(rows[(16 * jt + 4 * q + s) * LK + 16 * t + c], y[s], acc[t]);
+    }
+  };
+  f4 dk[2], dv[2];
+  float wsum = 0.f;
   __syncthreads();
-
-  // attention backward on MFMA.  Row pass: one tile of 16 queries per wave with the
-  // score tiles transposed as in the forward; the query's statistics (max, 1 / normaliser,
-  // rho), its terms of the gate gradient, dQ^T = K^T dS^T and the query rows of
-  // dE/dg2a = dY + dQ Wq^T.
-  const float isq = 1.f / sqrtf((float)G2D);
-  const int nkt = (nn + 15) >> 4;
-  const int kq = ln >> 4, col = ln & 15;
-  {
-    for (int qt = wv; qt < nkt; qt += NWG) {
-      const int qme = 16 * qt + col;
-      const bool qok = qme < nn;
-      float wq[2][2][4];  // issued first: their latency overlaps the score tiles
-      load_wt(w.Wq[l], wq);
-      f4 st[NKT], da[NKT];  // S^T and dA^T = V dY^T: [key 16 kt + 4 kq + ii][query qme]
+  if (act_)
 #pragma unroll
-      for (int kt = 0; kt < NKT; ++kt) {
-        st[kt] = f4{0.f, 0.f, 0.f, 0.f};
-        da[kt] = f4{0.f, 0.f, 0.f, 0.f};
-        if (kt < nkt) {
-          const int kr = 16 * kt + col;
-          dot32_tile(st[kt], kr < nn ? sm.K + kr * LQA : nullptr, qok ? sm.Q + qme * LQA : nullptr);
-          dot32_tile(da[kt], kr < nn ? sm.V + kr * LQA : nullptr, qok ? sm.DY + qme * LQA : nullptr);
-        }
-      }
-      float m = -INFINITY;
-#pragma unroll
-      for (int kt = 0; kt < NKT; ++kt)
-#pragma unroll
-        for (int ii = 0; ii < 4; ++ii) {
-          const int k = 16 * kt + 4 * kq + ii;
-          if (kt < nkt && k < nn) m = fmaxf(m, st[kt][ii] * isq);
-        }
-      m = fmaxf(m, __shfl_xor(m, 16));
-      m = fmaxf(m, __shfl_xor(m, 32));
-      float z = 0.f;
-#pragma unroll
-      for (int kt = 0; kt < NKT; ++kt) {
-        float swv[4];
-        quad(e.sw + 16 * kt + 4 * kq, swv);
-#pragma unroll
-        for (int ii = 0; ii < 4; ++ii) {
-          const int k = 16 * kt + 4 * kq + ii;
-          const float ex = (kt < nkt && k < nn) ? swv[ii] * __expf(st[kt][ii] * isq - m) : 0.f;
-          st[kt][ii] = ex;
-          z += ex;
-        }
-      }
-      z += __shfl_xor(z, 16);
-      z += __shfl_xor(z, 32);
-      const float iz = qok ? 1.f / z : 0.f;
-      const int qq = qok ? qme : 0;
-      const float hx = e.rh[3 * qq], hy = e.rh[3 * qq + 1], hz = e.rh[3 * qq + 2];
-      // P, dP = dA gate, rho = sum_k dP P and the row terms sum_k dA P rhat_k of the gate
-      float rho = 0.f, h0 = 0.f, h1 = 0.f, h2 = 0.f;
-#pragma unroll
-      for (int kt = 0; kt < NKT; ++kt) {
-        float h[12];
-        rh_quad(e, 16 * kt + 4 * kq, h);
-#pragma unroll
-        for (int ii = 0; ii < 4; ++ii) {
-          const float rx = h[3 * ii], ry = h[3 * ii + 1], rz = h[3 * ii + 2];
-          const float P = st[kt][ii] * iz, dA = da[kt][ii];
-          const float dP = dA * (hx * rx + hy * ry + hz * rz), dG = dA * P;
-          rho += dP * P;
-          h0 += dG * rx;
-          h1 += dG * ry;
-          h2 += dG * rz;
-          st[kt][ii] = P;
-          da[kt][ii] = dP;
-        }
-      }
-#pragma unroll
-      for (int o = 16; o < 64; o <<= 1) {
-        rho += __shfl_xor(rho, o);
-        h0 += __shfl_xor(h0, o);
-        h1 += __shfl_xor(h1, o);
-        h2 += __shfl_xor(h2, o);
-      }
-      if (qok && kq == 0) {
-        sm.stat[0][qme] = m;
-        sm.stat[1][qme] = iz;
-        sm.stat[2][qme] = rho;
-        sm.EG[qme * GSN + 2] += h0;
-        sm.EG[qme * GSN + 3] += h1;
-        sm.EG[qme * GSN + 4] += h2;
-      }
-      // dS^T = P (dP - rho) / sqrt(32); dQ^T[c][q] = sum_k K[k][c] dS^T[k][q]
-      f4 dq[2] = {};
-#pragma unroll
-      for (int kt = 0; kt < NKT; ++kt) {
-        if (kt >= nkt) break;
-#pragma unroll
-        for (int ss = 0; ss < 4; ++ss) {
-          const int k = 16 * kt + 4 * kq + ss;
-          const float ds = st[kt][ss] * (da[kt][ss] - rho) * isq;
-#pragma unroll
-          for (int ct = 0; ct < 2; ++ct) {
-            const float kv = k < nn ? sm.K[k * LQA + 16 * ct + col] : 0.f;
-            dq[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(kv, ds, dq[ct], 0, 0, 0);
-          }
-        }
-      }
-      f4 o[2] = {};
-      wt_product(o, wq, dq);
-      if (qok)
-#pragma unroll
-        for (int ot = 0; ot < 2; ++ot)
-#pragma unroll
-          for (int ii = 0; ii < 4; ++ii) {
-            const int c = 16 * ot + 4 * kq + ii;
-            sm.G2A[qme * LQ + c] = sm.DY[qme * LQA + c] + o[ot][ii];  // dE/dg2a, row terms
-          }
+    for (int t = 0; t < 2; ++t) {
+      stf4(sm.K + j * LK + 16 * t + 4 * q, qr[t]);
+      stf4(sm.V + j * LK + 16 * t + 4 * q, dy[t]);
     }
-  }
   __syncthreads();
-  // column pass: one tile of 16 keys per wave, streaming over the query tiles with the
-  // scores S[query][key] recomputed; the key terms of the switch and gate,
-  // dV^T = dY^T A, dK^T = Q^T dS and the key rows of dE/dg2a += dV Wv^T + dK Wk^T.
-  for (int kt = wv; kt < nkt; kt += NWG) {
-    const int kme = 16 * kt + col;
-    const bool kok = kme < nn;
-    const int kk = kok ? kme : 0;
-    float wk[2][2][4], wvv[2][2][4];  // issued first: their latency overlaps the query tiles
-    load_wt(w.Wk[l], wk);
-    load_wt(w.Wv[l], wvv);
-    const float kx = e.rh[3 * kk], ky = e.rh[3 * kk + 1], kz = e.rh[3 * kk + 2], swk = e.sw[kk];
-    float dsk = 0.f, h0 = 0.f, h1 = 0.f, h2 = 0.f;
-    f4 dv[2] = {}, dk[2] = {};
-    for (int jt = 0; jt < nkt; ++jt) {
-      f4 sc = {}, da = {};  // S and dA = dY V^T: [query 16 jt + 4 kq + ii][key kme]
-      const int jr = 16 * jt + col;
-      dot32_tile(sc, jr < nn ? sm.Q + jr * LQA : nullptr, kok ? sm.K + kme * LQA : nullptr);
-      dot32_tile(da, jr < nn ? sm.DY + jr * LQA : nullptr, kok ? sm.V + kme * LQA : nullptr);
-      float h[12], mx[4], iz[4], rh4[4];
-      rh_quad(e, 16 * jt + 4 * kq, h);
-      quad(sm.stat[0] + 16 * jt + 4 * kq, mx);
-      quad(sm.stat[1] + 16 * jt + 4 * kq, iz);
-      quad(sm.stat[2] + 16 * jt + 4 * kq, rh4);
-#pragma unroll
-      for (int ii = 0; ii < 4; ++ii) {
-        const int j = 16 * jt + 4 * kq + ii;
-        float A = 0.f, ds = 0.f;
-        if (kok && j < nn) {
-          const float exz = __expf(sc[ii] * isq - mx[ii]) * iz[ii];
-          const float rx = h[3 * ii], ry = h[3 * ii + 1], rz = h[3 * ii + 2];
-          const float P = swk * exz, g = rx * kx + ry * ky + rz * kz, dA = da[ii];
-          const float dP = dA * g, dG = dA * P, rho = rh4[ii];
-          A = P * g;
-          ds = P * (dP - rho) * isq;
-          dsk += exz * (dP - rho);
-          h0 += dG * rx;
-          h1 += dG * ry;
-          h2 += dG * rz;
-        }
-        sc[ii] = A;
-        da[ii] = ds;
-      }
-#pragma unroll
-      for (int ss = 0; ss < 4; ++ss) {
-        const int j = 16 * jt + 4 * kq + ss;
-#pragma unroll
-        for (int ct = 0; ct < 2; ++ct) {
-          const float dy = j < nn ? sm.DY[j * LQA + 16 * ct + col] : 0.f;
-          const float qv = j < nn ? sm.Q[j * LQA + 16 * ct + col] : 0.f;
-          dv[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(dy, sc[ss], dv[ct], 0, 0, 0);
-          dk[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(qv, da[ss], dk[ct], 0, 0, 0);
-        }
-      }
-    }
-#pragma unroll
-    for (int o = 16; o < 64; o <<= 1) {
-      dsk += __shfl_xor(dsk, o);
-      h0 += __shfl_xor(h0, o);
-      h1 += __shfl_xor(h1, o);
-      h2 += __shfl_xor(h2, o);
-    }
-    if (kok && kq == 0) {
-      sm.EG[kme * GSN + 1] += dsk;
-      sm.EG[kme * GSN + 2] += h0;
-      sm.EG[kme * GSN + 3] += h1;
-      sm.EG[kme * GSN + 4] += h2;
-    }
-    f4 o[2] = {};
-    wt_product(o, wvv, dv);
-    wt_product(o, wk, dk);
-    if (kok)
-#pragma unroll
-      for (int ot = 0; ot < 2; ++ot)
-#pragma unroll
-        for (int ii = 0; ii < 4; ++ii) {
-          const int c = 16 * ot + 4 * kq + ii;
-          sm.G2A[kme * LQ + c] += o[ot][ii];  // dE/dg2a, complete
-        }
-  }
+  if (act_) column(sm.V, [](f4) {}, dv);
   __syncthreads();
-  // pair update backward: dz = dE/dg2a (1 - ta^2) into DY
-  for (int o = tid; o < nn * G2D; o += NT) {
-    const int j = o >> 5, c = o & 31;
-    const float ta = sm.G2[j * LQ + c];
-    sm.DY[j * LQA + c] = sm.G2A[j * LQ + c] * (1.f - ta * ta);
-  }
+  if (act_)
+#pragma unroll
+    for (int kt = 0; kt < NB; ++kt)
+      if (kt < nb) put_tile(sm.tile[jb][kt], Wg[kt]);
   __syncthreads();
-  // dxa = dz Wa^T on MFMA, one tile of 16 edges per wave; k step s of block kb takes
-  // k = 16 kb + 4 (l / 16) + s, so a lane's four B values (Wa[16 qt + l % 16][k]) and A
-  // values (dz[row][k]) are each one 16-byte load.  Its first 32 columns go to dE/dg2 of
-  // the layer input, the other 64 (with the convolution's term) to the edge's part of
-  // dE/dg1_j
-  float *dnj = b.dnj + (size_t)(l & 1) * b.cap * SEL * G1D;
-  {
-    constexpr int QT = (G2D + G1D) / 16;
-    float4 wt[2][QT];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int qt = 0; qt < QT; ++qt) wt[kb][qt] = ld4(w.Wa[l] + (16 * qt + col) * G2D + 16 * kb + 4 * kq);
-    for (int et = wv; et < nkt; et += NWG) {
-      const int ra = 16 * et + col;
-      const bool aok = ra < nn;
-      f4 acc[QT] = {};
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb) {
-        const float4 x = aok ? ld4(sm.DY + ra * LQA + 16 * kb + 4 * kq) : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-        for (int qt = 0; qt < QT; ++qt) {
-          acc[qt] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.x, wt[kb][qt].x, acc[qt], 0, 0, 0);
-          acc[qt] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.y, wt[kb][qt].y, acc[qt], 0, 0, 0);
-          acc[qt] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.z, wt[kb][qt].z, acc[qt], 0, 0, 0);
-          acc[qt] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.w, wt[kb][qt].w, acc[qt], 0, 0, 0);
-        }
-      }
-#pragma unroll
-      for (int qt = 0; qt < QT; ++qt)
-#pragma unroll
-        for (int ii = 0; ii < 4; ++ii) {
-          const int j = 16 * et + 4 * kq + ii, q = 16 * qt + col;
-          if (j >= nn) continue;
-          float v = acc[qt][ii];
-          if (q < G2D) {
-            const float dg2in = sm.G2A[j * LQ + q] + v;
-            if (l > 0) b.dg2[((size_t)i * SEL + j) * G2D + q] = dg2in;
-            else sm.V[j * LQA + q] = dg2in;  // kept for the initial-feature gradient below
-          } else if (l > 0) {
-            const int c1 = q - G2D;
-            if (c1 < G2D) v += e.sw[j] * dc[c1] * geo.inv_sel * sm.G2B[j * LQ + c1];
-            dnj[((size_t)i * SEL + j) * G1D + c1] = v;
-          }
-        }
-    }
-  }
-  if (l > 0) {
-    if (tid < G1D) {
-      float v = sm.dg1[tid] + sm.dxn[tid];
-      b.dnl[(size_t)i * G1D + tid] = v;
-    }
-    for (int k = tid; k < nn * GSN; k += NT) b.gs[(size_t)i * SEL * GSN + k] = sm.EG[k];
+  if (!act_) {
+    if (l > 0 && live && tid < G1D) b.dnl[(size_t)i * G1D + tid] = sm.dg1[tid] + sm.dxn[tid];
     return;
   }
-  __syncthreads();
-  // layer 0: g2 = tanh(s Wp0 + bp0) adds to dE/ds; then g_ij = dE/dDelta_ij
-  for (int j = tid; j < nn; j += NT) {
-    float ds = sm.EG[j * GSN];
-    for (int c = 0; c < G2D; ++c) {
-      const float g0 = tanhf(e.s[j] * w.Wp0[c] + w.bp0[c]);
-      ds += sm.V[j * LQA + c] * (1.f - g0 * g0) * w.Wp0[c];
+  column(sm.K, [&](f4 y) { wsum += (y[0] + y[1]) + (y[2] + y[3]); }, dk);
+  // the token's key terms, then the projections and the pair update backward
+  eg[1] += sumq(wsum);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    float v = 0.f;
+    for (int u = 0; u < nb; ++u) v += sm.drhw[u][3 * j + a];
+    eg[2 + a] += v;
+  }
+  f4 dqkv[6], dg[2], dz[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    dqkv[t] = dq[t];
+    dqkv[2 + t] = sm.e.sw[j] * isq * dk[t];
+    dqkv[4 + t] = sm.e.sw[j] * dv[t];
+    dg[t] = zero;
+  }
+  product<6, 2>(dg, w.Pqkvt[l], dqkv);
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    dg[t] += dy[t];  // dE/dg2a
+    dz[t] = dg[t] * (1.f - ta[t] * ta[t]);
+  }
+  f4 dx[6] = {};
+  product<2, 6>(dx, w.Pat[l], dz);
+#pragma unroll
+  for (int t = 0; t < 2; ++t) dg[t] += dx[t];  // dE/dg2 of the layer's input
+  if (l > 0) {
+    if (ok) {
+      float *dst = b.dnj + (size_t)(l & 1) * b.cap * SEL * G1D + ((size_t)i * SEL + j) * G1D + 4 * q;
+      const float sc = sm.e.sw[j] * geo.inv_sel;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        stf4(b.dg2 + ((size_t)i * SEL + j) * G2D + 16 * t + 4 * q, dg[t]);
+        stf4(dst + 16 * t, dx[2 + t] + sc * ldf4(dc + 16 * t + 4 * q) * g2b[t]);
+        stf4(dst + 32 + 16 * t, dx[4 + t]);
+      }
+      if (q == 0) {
+        float *g = b.gs + ((size_t)i * SEL + j) * GSN;
+#pragma unroll
+        for (int a = 0; a < 5; ++a) g[a] = top ? eg[a] : g[a] + eg[a];
+      }
     }
-    const float rr = e.r[j], sw = e.sw[j];
-    const float dr = ds * (e.dsw[j] / rr - sw / (rr * rr)) + sm.EG[j * GSN + 1] * e.dsw[j];
-    const float hx = e.rh[3 * j], hy = e.rh[3 * j + 1], hz = e.rh[3 * j + 2];
-    const float gx = sm.EG[j * GSN + 2], gy = sm.EG[j * GSN + 3], gz = sm.EG[j * GSN + 4];
-    const float proj = gx * hx + gy * hy + gz * hz;
-    gout[(size_t)i * SEL + j] = make_float4((gx - proj * hx) / rr + dr * hx, (gy - proj * hy) / rr + dr * hy,
-                                            (gz - proj * hz) / rr + dr * hz, 0.f);
+    if (tid < G1D) b.dnl[(size_t)i * G1D + tid] = sm.dg1[tid] + sm.dxn[tid];
+    return;
+  }
+  // layer 0: g2 = tanh(s Wp0 + bp0) adds to dE/ds; then g_ij = dE/dDelta_ij
+  float ds = 0.f;
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const f4 g0 = init4(sm.e.s[j], w.Wp0 + 16 * t + 4 * q, w.bp0 + 16 * t + 4 * q);
+    const f4 g = dg[t] * (1.f - g0 * g0) * ldf4(w.Wp0 + 16 * t + 4 * q);
+    ds += (g[0] + g[1]) + (g[2] + g[3]);
+  }
+  ds = sumq(ds);
+  if (ok && q == 0) {
+    const float *g = b.gs + ((size_t)i * SEL + j) * GSN;
+#pragma unroll
+    for (int a = 0; a < 5; ++a) eg[a] += g[a];
+    ds += eg[0];
+    const float rr = sm.e.r[j], sw = sm.e.sw[j];
+    const float dr = ds * (sm.e.dsw[j] / rr - sw / (rr * rr)) + eg[1] * sm.e.dsw[j];
+    const float proj = eg[2] * hj[0] + eg[3] * hj[1] + eg[4] * hj[2];
+    gout[(size_t)i * SEL + j] = make_float4((eg[2] - proj * hj[0]) / rr + dr * hj[0], (eg[3] - proj * hj[1]) / rr + dr * hj[1],
+                                            (eg[4] - proj * hj[2]) / rr + dr * hj[2], 0.f);
   }
 }
 
-__global__ void __launch_bounds__(1024) k_edge_count(const int *__restrict__ nnei, int n, int64_t *__restrict__ etot) {
+// One atom per workgroup, any list length.
+__global__ void __launch_bounds__(64 * NB_MAX) __attribute__((amdgpu_waves_per_eu(2)))
+k_rep_fwd_one(Weights w, Buffers b, const double *__restrict__ Xc, const int *__restrict__ types,
+              const int *__restrict__ nlist, const int *__restrict__ nnei, const Grid *__restrict__ grids, int n, int l,
+              Geo geo, double *__restrict__ Ei, const unsigned *__restrict__ flags) {
+  __shared__ SmemF<NB_MAX> sm;
+  if (failed(flags)) return;
+  layer_fwd<NB_MAX, 1>(blockIdx.x, n, &sm, w, b, Xc, types, nlist, nnei, grids, n, l, geo, nullptr, Ei);
+}
+__global__ void __launch_bounds__(64 * NB_MAX) __attribute__((amdgpu_waves_per_eu(2)))
+k_rep_bwd_one(Weights w, Buffers b, const double *__restrict__ Xc, const int *__restrict__ types,
+              const int *__restrict__ nlist, const int *__restrict__ nnei, const Grid *__restrict__ grids, int n, int l,
+              Geo geo, float4 *__restrict__ gout, const unsigned *__restrict__ flags) {
+  __shared__ SmemB<NB_MAX> sm;
+  if (failed(flags)) return;
+  layer_bwd<NB_MAX, 1>(blockIdx.x, n, &sm, w, b, Xc, types, nlist, nnei, grids, n, l, geo, nullptr, gout);
+}
+// 12 waves: the first NLONG workgroups go through the long lists' atoms, eight waves each (the
+// others end at once), the rest take two atoms each.
+__global__ void __launch_bounds__(128 * NB_SMALL) __attribute__((amdgpu_waves_per_eu(3)))
+k_rep_fwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__restrict__ types, const int *__restrict__ nlist,
+          const int *__restrict__ nnei, const Grid *__restrict__ grids, int n, int l, Geo geo, const int *__restrict__ cnt,
+          double *__restrict__ Ei, const unsigned *__restrict__ flags) {
+  __shared__ union { SmemF<NB_SMALL> two[2]; SmemF<NB_MAX> one; } sm;
+  if (failed(flags)) return;
+  const int blk = blockIdx.x - NLONG;
+  if (blk >= 0) {
+    if (2 * blk < cnt[0]) layer_fwd<NB_SMALL, 2>(blk, cnt[0], sm.two, w, b, Xc, types, nlist, nnei, grids, n, l, geo, b.idx, Ei);
+    return;
+  }
+  if (threadIdx.x >= 64 * NB_MAX) return;
+  for (int k = blockIdx.x; k < cnt[1]; k += NLONG) {
+    layer_fwd<NB_MAX, 1>(k, cnt[1], &sm.one, w, b, Xc, types, nlist, nnei, grids, n, l, geo, b.idx + b.cap, Ei);
+    __syncthreads();
+  }
+}
+__global__ void __launch_bounds__(128 * NB_SMALL) __attribute__((amdgpu_waves_per_eu(3)))
+k_rep_bwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__restrict__ types, const int *__restrict__ nlist,
+          const int *__restrict__ nnei, const Grid *__restrict__ grids, int n, int l, Geo geo, const int *__restrict__ cnt,
+          float4 *__restrict__ gout, const unsigned *__restrict__ flags) {
+  __shared__ union { SmemB<NB_SMALL> two[2]; SmemB<NB_MAX> one; } sm;
+  if (failed(flags)) return;
+  const int blk = blockIdx.x - NLONG;
+  if (blk >= 0) {
+    if (2 * blk < cnt[0]) layer_bwd<NB_SMALL, 2>(blk, cnt[0], sm.two, w, b, Xc, types, nlist, nnei, grids, n, l, geo, b.idx, gout);
+    return;
+  }
+  if (threadIdx.x >= 64 * NB_MAX) return;
+  for (int k = blockIdx.x; k < cnt[1]; k += NLONG) {
+    layer_bwd<NB_MAX, 1>(k, cnt[1], &sm.one, w, b, Xc, types, nlist, nnei, grids, n, l, geo, b.idx + b.cap, gout);
+    __syncthreads();
+  }
+}
+
+// The edge count, and the atoms of the two instances (up to 96 neighbours, or more; the order
+// only changes scheduling).
+__global__ void __launch_bounds__(1024) k_edge_count(const int *__restrict__ nnei, int n, int64_t *__restrict__ etot,
+                                                     int *__restrict__ idx, int *__restrict__ cnt, int cap) {
   __shared__ int64_t part[1024];
+  const int l = lane();
   int64_t s = 0;
-  for (int k = threadIdx.x; k < n; k += 1024) s += min(max(nnei[k], 0), SEL);
+  for (int k0 = 0; k0 < n; k0 += 1024) {
+    const int k = k0 + threadIdx.x;
+    const int nk = k < n ? min(max(nnei[k], 0), SEL) : 0;
+    s += nk;
+    for (int cls = 0; cls < 2; ++cls) {
+      const unsigned long long mask = __ballot(k < n && (nk > 16 * NB_SMALL) == (cls == 1));
+      if (!mask) continue;
+      const int first = __ffsll(mask) - 1;
+      int base = 0;
+      if (l == first) base = atomicAdd(cnt + cls, __popcll(mask));
+      base = __shfl(base, first);
+      if (mask >> l & 1ull) idx[(size_t)cls * cap + base + __popcll(mask & ((1ull << l) - 1ull))] = k;
+    }
+  }
   part[threadIdx.x] = s;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int64_t t = 0;
-    for (int k = 0; k < 1024; ++k) t += part[k];
-    *etot = t;
+  for (int off = 512; off > 0; off >>= 1) {
+    if ((int)threadIdx.x < off) part[threadIdx.x] += part[threadIdx.x + off];
+    __syncthreads();
   }
+  if (threadIdx.x == 0) *etot = part[0];
 }
 
 }  // namespace
 
 void launch_edge_count(const Buffers &b, const Workspace &ws, int n, hipStream_t st) {
-  hipLaunchKernelGGL(k_edge_count, dim3(1), dim3(1024), 0, st, ws.nnei, n, b.etot);
+  hipLaunchKernelGGL(k_edge_count, dim3(1), dim3(1024), 0, st, ws.nnei, n, b.etot, b.idx, ws.bcnt, (int)b.cap);
 }
 
 void launch_layer_fwd(const Weights &w, const Buffers &b, const Workspace &ws, const double *coords,
                       const int *types, int n, int layer, const Geo &geo, double *Ei, hipStream_t st) {
-  hipLaunchKernelGGL(k_rep_fwd, dim3(n), dim3(NT), 0, st, w, b, coords, types, ws.nlist, ws.nnei, ws.grids, n, layer,
-                     geo, Ei, ws.flags);
+  if (n <= ONE_UP_TO)
+    hipLaunchKernelGGL(k_rep_fwd_one, dim3(n), dim3(64 * NB_MAX), 0, st, w, b, coords, types, ws.nlist, ws.nnei, ws.grids, n,
+                       layer, geo, Ei, ws.flags);
+  else
+    hipLaunchKernelGGL(k_rep_fwd, dim3(NLONG + (n + 1) / 2), dim3(128 * NB_SMALL), 0, st, w, b, coords, types, ws.nlist,
+                       ws.nnei, ws.grids, n, layer, geo, ws.bcnt, Ei, ws.flags);
 }
 
 void launch_layer_bwd(const Weights &w, const Buffers &b, const Workspace &ws, const double *coords,
                       const int *types, int n, int layer, const Geo &geo, hipStream_t st) {
-  hipLaunchKernelGGL(k_rep_bwd, dim3(n), dim3(NT), 0, st, w, b, coords, types, ws.nlist, ws.nnei, ws.grids, n, layer,
-                     geo, ws.g, ws.flags);
+  if (n <= ONE_UP_TO)
+    hipLaunchKernelGGL(k_rep_bwd_one, dim3(n), dim3(64 * NB_MAX), 0, st, w, b, coords, types, ws.nlist, ws.nnei, ws.grids, n,
+                       layer, geo, ws.g, ws.flags);
+  else
+    hipLaunchKernelGGL(k_rep_bwd, dim3(NLONG + (n + 1) / 2), dim3(128 * NB_SMALL), 0, st, w, b, coords, types, ws.nlist,
+                       ws.nnei, ws.grids, n, layer, geo, ws.bcnt, ws.g, ws.flags);
 }
 
 }  // namespace rep

@@ -5,6 +5,7 @@
 #include <cmath>
 #include <cstring>
 #include <fstream>
+#include <map>
 #include <string>
 #include <vector>
 
@@ -103,7 +104,7 @@ int load_weights(dp_rep *m, const char *path) {
   std::vector<size_t> offs;
   size_t off = 128;
   double d3 = 0.0;
-  std::vector<double> G3;
+  std::map<std::string, std::vector<double>> src;
   for (auto &a : rep_arrays(m->ntypes)) {
     if (off + 8 * a.second > raw.size()) {
       set_error("repformer model file: truncated at " + a.first);
@@ -118,7 +119,7 @@ int load_weights(dp_rep *m, const char *path) {
         return DP_ERR_MODEL_FILE;
       }
     if (a.first == "d3") d3 = v[0];
-    if (a.first == "G3") G3 = v;
+    src[a.first] = v;
     const size_t o = (img.size() + 255) & ~size_t(255);
     img.resize(o + 4 * v.size());
     for (size_t k = 0; k < v.size(); ++k) {
@@ -133,7 +134,40 @@ int load_weights(dp_rep *m, const char *path) {
   }
   const size_t og = (img.size() + 255) & ~size_t(255);
   img.resize(og + 8 * FWID);
-  std::memcpy(img.data() + og, G3.data(), 8 * FWID);
+  std::memcpy(img.data() + og, src["G3"].data(), 8 * FWID);
+  // transposed copies and MFMA fragments (their order: dp_tiles.h, W)
+  auto put = [&](const std::vector<float> &v) {
+    const size_t o = (img.size() + 255) & ~size_t(255);
+    img.resize(o + 4 * v.size());
+    std::memcpy(img.data() + o, v.data(), 4 * v.size());
+    offs.push_back(o);
+  };
+  auto transposed = [&](const std::vector<double> &v, int rows, int cols) {
+    std::vector<float> t((size_t)rows * cols);
+    for (int r = 0; r < rows; ++r)
+      for (int c = 0; c < cols; ++c) t[(size_t)c * rows + r] = (float)v[(size_t)r * cols + c];
+    put(t);
+  };
+  auto frag = [&](int outs, int K, auto W) {
+    std::vector<float> v((size_t)outs * K);
+    for (int t = 0; t < outs / 16; ++t)
+      for (int k = 0; k < K / 16; ++k)
+        for (int ln = 0; ln < 64; ++ln)
+          for (int s = 0; s < 4; ++s)
+            v[((size_t)(t * (K / 16) + k) * 64 + ln) * 4 + s] = (float)W(16 * t + ln % 16, 16 * k + 4 * (ln / 16) + s);
+    put(v);
+  };
+  transposed(src["G1"], G1D, FWID);
+  transposed(src["G2"], FWID, FWID);
+  for (int l = 0; l < NLAYER; ++l) {
+    const std::string s = std::to_string(l);
+    const std::vector<double> &wa = src["Wa" + s];
+    const std::vector<double> *p[3] = {&src["Wq" + s], &src["Wk" + s], &src["Wv" + s]};
+    frag(G2D, G2D + G1D, [&](int o, int k) { return wa[k * G2D + o]; });
+    frag(3 * G2D, G2D, [&](int o, int k) { return (*p[o / G2D])[k * G2D + o % G2D]; });
+    frag(G2D, 3 * G2D, [&](int o, int k) { return (*p[k / G2D])[o * G2D + k % G2D]; });
+    frag(G2D + G1D, G2D, [&](int o, int k) { return wa[o * G2D + k]; });
+  }
   R_TRY(hipMalloc(&m->wbuf, img.size()));
   R_TRY(hipMemcpy(m->wbuf, img.data(), img.size(), hipMemcpyHostToDevice));
   const unsigned char *base = (const unsigned char *)m->wbuf;
@@ -142,18 +176,24 @@ int load_weights(dp_rep *m, const char *path) {
   rep::Weights &w = m->w;
   w.TN = nxt(); w.Wp0 = nxt(); w.bp0 = nxt();
   for (int l = 0; l < NLAYER; ++l) {
-    w.Wa[l] = nxt(); w.ba[l] = nxt(); w.Wq[l] = nxt(); w.Wk[l] = nxt(); w.Wv[l] = nxt();
+    (void)nxt();  // Wa, and Wq, Wk, Wv below, are read in fragment order only
+    w.ba[l] = nxt();
+    k += 3;
     w.W1[l] = nxt(); w.b1[l] = nxt();
   }
   w.G1 = nxt(); w.d1 = nxt(); w.G2 = nxt(); w.d2 = nxt(); w.G3 = nxt();
   (void)nxt();  // d3 goes by value
   w.G3d = (const double *)(base + og);
+  w.G1T = nxt(); w.G2T = nxt();
+  for (int l = 0; l < NLAYER; ++l) {
+    w.Pa[l] = nxt(); w.Pqkv[l] = nxt(); w.Pqkvt[l] = nxt(); w.Pat[l] = nxt();
+  }
   w.d3 = d3;
   return DP_OK;
 }
 
 void free_buffers(rep::Buffers &b) {
-  void *ps[] = {b.g1f, b.g2f, b.dg2, b.dnj, b.dnl, b.gs, b.slot, b.etot};
+  void *ps[] = {b.g1f, b.g2f, b.dg2, b.dnj, b.dnl, b.gs, b.slot, b.idx, b.tn, b.Tn, b.etot};
   for (void *p : ps)
     if (p) (void)hipFree(p);
   b = rep::Buffers{};
@@ -163,20 +203,23 @@ int ensure_buffers(rep::Buffers &b, int64_t n) {
   if (!b.etot) R_TRY(hipMalloc(&b.etot, sizeof(int64_t)));
   if (n <= b.cap) return DP_OK;
   const int64_t cap = std::max<int64_t>(n, b.cap + b.cap / 4);
-  void *ps[] = {b.g1f, b.g2f, b.dg2, b.dnj, b.dnl, b.gs, b.slot};
+  void *ps[] = {b.g1f, b.g2f, b.dg2, b.dnj, b.dnl, b.gs, b.slot, b.idx, b.tn, b.Tn};
   for (void *p : ps)
     if (p) (void)hipFree(p);
-  b.g1f = b.g2f = b.dg2 = b.dnj = b.dnl = b.gs = nullptr;
-  b.slot = nullptr;
+  b.g1f = b.g2f = b.dg2 = b.dnj = b.dnl = b.gs = b.tn = b.Tn = nullptr;
+  b.slot = b.idx = nullptr;
   b.cap = 0;
   const size_t c = (size_t)cap, e = c * SEL;
   R_TRY(hipMalloc(&b.g1f, 2 * c * G1D * sizeof(float)));
   R_TRY(hipMalloc(&b.g2f, 3 * e * G2D * sizeof(float)));
+  R_TRY(hipMalloc(&b.tn, NLAYER * c * G1D * sizeof(float)));
+  R_TRY(hipMalloc(&b.Tn, NLAYER * c * 4 * G2D * sizeof(float)));
   R_TRY(hipMalloc(&b.dg2, e * G2D * sizeof(float)));
   R_TRY(hipMalloc(&b.dnj, 2 * e * G1D * sizeof(float)));
   R_TRY(hipMalloc(&b.dnl, c * G1D * sizeof(float)));
   R_TRY(hipMalloc(&b.gs, e * rep::GSN * sizeof(float)));
   R_TRY(hipMalloc(&b.slot, e * sizeof(int)));
+  R_TRY(hipMalloc(&b.idx, 2 * c * sizeof(int)));
   b.cap = cap;
   return DP_OK;
 }
