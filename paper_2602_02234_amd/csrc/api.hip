@@ -271,32 +271,47 @@ void pack_weights(const HostModel &h, int pr, Image &im) {
     }
     return pk.add(b.data(), b.size() * 2);
   };
-  auto W2 = [&](int a, int b) { return h.W2[(size_t)a * E2 + b]; };
-  auto W3 = [&](int a, int b) { return h.W3[(size_t)a * M + b]; };
-  op.push_back(hi_lo(mat(64, 32, [&](int c, int k) { return (c < E2 && k < E1) ? W2(k, c) : 0.0; }), 0));
-  op.push_back(hi_lo(mat(112, 64, [&](int c, int k) { return (c < M && k < E2) ? W3(k, c) : 0.0; }), 0));
-  op.push_back(hi_lo(mat(64, 112, [&](int c, int k) { return (c < E2 && k < M) ? W3(c, k) : 0.0; }), 0));
-  op.push_back(hi_lo(mat(32, 64, [&](int c, int k) { return (c < E1 && k < E2) ? W2(c, k) : 0.0; }), 0));
+  // the descriptor's, in the order of 16x16x32 fragments: lane l holds row l % 16 of the tile and
+  // eight k.  A [M][M] product W[out][k]: tile t (outputs 16 t + row; 96 + row / 4 for t = 6), step
+  // p < 3 at (7 p + t) 512 + 8 l with k = 32 p + 4 (l / 16) + e, 12 more from e = 4 on; k = 96 + l / 16
+  // of tile t at 10752 + 8 l + t
+  auto frag100 = [](auto W) {
+    std::vector<float> v(11264, 0.f);
+    for (int t = 0; t < 7; ++t)
+      for (int l = 0; l < 64; ++l) {
+        const int out = t < 6 ? 16 * t + l % 16 : 96 + l % 16 / 4;
+        for (int p = 0; p < 3; ++p)
+          for (int e = 0; e < 8; ++e)
+            v[(7 * p + t) * 512 + 8 * l + e] = (float)W(out, 32 * p + 4 * (l / 16) + (e < 4 ? e : e + 12));
+        v[10752 + 8 * l + t] = (float)W(out, 96 + l / 16);
+      }
+    return v;
+  };
+  // the embedding's, features in groups of 25 (slot r of lane group q = feature 4 r + q of the
+  // group): NO output groups of two tiles, NI input groups of one step
+  auto frag25 = [](int NO, int NI, auto W) {
+    std::vector<float> v((size_t)NO * 2 * NI * 512, 0.f);
+    for (int og = 0; og < NO; ++og)
+      for (int u = 0; u < 2; ++u)
+        for (int ig = 0; ig < NI; ++ig)
+          for (int l = 0; l < 64; ++l)
+            for (int e = 0; e < 7; ++e) {
+              const int ro = 4 * u + l % 4, fo = 4 * ro + l % 16 / 4;  // tile row 4 q + i is slot 4 u + i
+              const int fi = 4 * e + l / 16;
+              if (ro < 7 && fo < 25 && fi < 25)
+                v[(((size_t)og * 2 + u) * NI + ig) * 512 + 8 * l + e] = (float)W(25 * og + fo, 25 * ig + fi);
+            }
+    return v;
+  };
+  op.push_back(hi_lo(frag25(2, 1, [&](int c, int k) { return h.W2[(size_t)k * E2 + c]; }), 0));
+  op.push_back(hi_lo(frag25(4, 2, [&](int c, int k) { return h.W3[(size_t)k * M + c]; }), 0));
+  op.push_back(hi_lo(frag25(2, 4, [&](int c, int k) { return h.W3[(size_t)c * M + k]; }), 0));
+  op.push_back(hi_lo(frag25(1, 2, [&](int c, int k) { return h.W2[(size_t)c * E2 + k]; }), 0));
   for (int a = 0; a < NATTN; ++a) {
-    const std::vector<double> &qk = QK[a], &vo = VO[a];
-    auto at = [](const std::vector<double> &v, int r, int c) { return (r < M && c < M) ? v[(size_t)r * M + c] : 0.0; };
-    // the attention products read these from global memory, in MFMA fragment order: per 16-column tile, three 32-k fragments of 64 lanes x 8 values (lane l:
-    // row l % 16, k = 32 s + 8 (l / 16) ..), then the k = 96..111 tail as 64 lanes x 4
-    auto frag112 = [](const std::vector<float> &v) {
-      std::vector<float> o(v.size());
-      for (int t = 0; t < 7; ++t)
-        for (int l = 0; l < 64; ++l) {
-          const size_t row = (size_t)(16 * t + l % 16) * 112;
-          for (int st = 0; st < 3; ++st)
-            for (int e = 0; e < 8; ++e) o[t * 1792 + st * 512 + l * 8 + e] = v[row + 32 * st + 8 * (l / 16) + e];
-          for (int e = 0; e < 4; ++e) o[t * 1792 + 1536 + l * 4 + e] = v[row + 96 + 4 * (l / 16) + e];
-        }
-      return o;
-    };
-    op.push_back(hi_lo(frag112(mat(112, 112, [&](int c, int k) { return at(qk, k, c); })), 0));
-    op.push_back(hi_lo(frag112(mat(112, 112, [&](int c, int k) { return at(qk, c, k); })), 0));
-    op.push_back(hi_lo(frag112(mat(112, 112, [&](int c, int k) { return at(vo, k, c); })), 0));
-    op.push_back(hi_lo(frag112(mat(112, 112, [&](int c, int k) { return at(vo, c, k); })), 0));
+    op.push_back(hi_lo(frag100([&](int c, int k) { return QK[a][(size_t)k * M + c]; }), 0));
+    op.push_back(hi_lo(frag100([&](int c, int k) { return QK[a][(size_t)c * M + k]; }), 0));
+    op.push_back(hi_lo(frag100([&](int c, int k) { return VO[a][(size_t)k * M + c]; }), 0));
+    op.push_back(hi_lo(frag100([&](int c, int k) { return VO[a][(size_t)c * M + k]; }), 0));
   }
   auto F = [&](const std::vector<double> &v, int ld, int r, int c) { return v[(size_t)r * ld + c]; };
   // the fitting operands in MFMA fragment order: the 16 x 32 fragment (column tile t,

@@ -31,49 +31,17 @@
 // stride for which both the 16-byte row reads and the reads along tokens spread over all
 // banks.  Weights come from L2 in fragment order, one output tile ahead.
 //
-// Two instances: atoms with up to 6 blocks (96 neighbours, nine in ten in water) run
-// with 6 waves, 77 KB of LDS and at most 168 registers, so that two atoms share a CU and
-// every SIMD has three waves; the others run with 8 waves on a second stream.
-#include <algorithm>
-
-#include "dp_env.h"
+// Instances (dp_desc.h): two atoms of up to 6 blocks (96 neighbours, nine in ten in water) to a
+// workgroup of 12 waves with at most 168 registers, so that every SIMD has three; an atom of
+// more to one of 8 waves, on a second stream.
+#include "dp_desc.h"
 
 namespace dp {
 namespace {
 
-constexpr int LDG = M;    // row stride (floats) of G in LDS: 100
 constexpr int LDX = 68;   // row stride of a wave's transposition scratch [16 tokens][64]
 constexpr int LDW = 20;   // ... of a 16 x 16 tile in it
-constexpr int NB_SMALL = 6;  // blocks up to which an atom runs on the first instance
 static_assert(M == 100 && E1 == 25 && E2 == 50, "the fragment layouts below are written for these widths");
-
-// A vector over the 100 features of a lane's token: x[t][i] = feature 16 t + 4 q + i for
-// t < 6, x[6][0] = feature 96 + q (x[6][1..3] are never read as features).
-typedef f4 F100[7];
-
-__device__ __forceinline__ f4 mfma(float a, float b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-__device__ __forceinline__ f4 ldf4(const float *p) { return *reinterpret_cast<const f4 *>(p); }
-// The lane index through an empty asm statement: the compiler then forms lane-derived
-// addresses where they are used instead of keeping them all (and spilling) for the whole
-// kernel.
-__device__ __forceinline__ int lane() {
-  int l = lane_id();
-  asm volatile("" : "+v"(l));
-  return l;
-}
-// Keeps a tile's loads from being scheduled across other tiles' products.
-__device__ __forceinline__ void tile_barrier() { __builtin_amdgcn_sched_barrier(0); }
-__device__ __forceinline__ float sumq(float v) {  // over the four lane groups
-  v += __shfl_xor(v, 16);
-  v += __shfl_xor(v, 32);
-  return v;
-}
-// Orders a wave's own LDS traffic between its lanes.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // acc += W x for a 100 x 100 matrix W[out][k] in fragment order: tile t (outputs
 // 16 t + row for t < 6; 96 + row / 4 for t = 6) at 1600 t, its k = 16 kb + 4 q + s at
@@ -158,103 +126,6 @@ __device__ __forceinline__ void keys_sum(F100 &acc, const float *G, const Y &y, 
     }
 }
 
-// A token's features from / to a row of G.
-__device__ __forceinline__ void get_row(F100 &x, const float *row) {
-  const int q = lane() >> 4;
-#pragma unroll
-  for (int t = 0; t < 6; ++t) x[t] = ldf4(row + 16 * t + 4 * q);
-  x[6] = f4{row[96 + q], 0.f, 0.f, 0.f};
-}
-__device__ __forceinline__ void put_row(float *row, const F100 &x) {
-  const int q = lane() >> 4;
-#pragma unroll
-  for (int t = 0; t < 6; ++t) *reinterpret_cast<f4 *>(row + 16 * t + 4 * q) = x[t];
-  row[96 + q] = x[6][0];
-}
-// A per-feature table (bias, gain) in the same arrangement.
-__device__ __forceinline__ void get_table(F100 &x, const float *__restrict__ p) { get_row(x, p); }
-
-// A block's features in global memory: 1600 floats, every access one contiguous piece.
-__device__ __forceinline__ void save_block(float *__restrict__ p, const F100 &x) {
-  const int l = lane();
-#pragma unroll
-  for (int t = 0; t < 6; ++t) *reinterpret_cast<f4 *>(p + 256 * t + 4 * l) = x[t];
-  p[1536 + l] = x[6][0];
-}
-__device__ __forceinline__ void load_block(F100 &x, const float *__restrict__ p) {
-  const int l = lane();
-#pragma unroll
-  for (int t = 0; t < 6; ++t) x[t] = ldf4(p + 256 * t + 4 * l);
-  x[6] = f4{p[1536 + l], 0.f, 0.f, 0.f};
-}
-
-// Sum over a token's 100 features of f(t, i) (t = 6: i = 0 only).
-template <class Fn> __device__ __forceinline__ float sum100(const Fn &f) {
-  float v = f(6, 0);
-#pragma unroll
-  for (int t = 0; t < 6; ++t)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) v += f(t, i);
-  return sumq(v);
-}
-
-// 1 / sigma of a centred row d, and xh = d / sigma in place.
-__device__ __forceinline__ float normalise(F100 &d, float eps) {
-  const float var = sum100([&](int t, int i) { return d[t][i] * d[t][i]; }) * (1.f / M);
-  const float is = 1.f / sqrtf(var + eps);
-#pragma unroll
-  for (int t = 0; t < 7; ++t) d[t] *= is;
-  return is;
-}
-
-// The environment of one atom, padded to whole blocks; padded tokens (j >= n) have
-// s = sw = dsw = 0, r = 1, rhat = 0.
-template <int NB> struct EnvF {
-  float s[16 * NB], sw[16 * NB] __attribute__((aligned(16)));
-  float r[16 * NB];
-  float rh[3][16 * NB] __attribute__((aligned(16)));
-  int tj[16 * NB];
-};
-
-template <int NB>
-__device__ void build_envf(EnvF<NB> &e, int tid, const double *__restrict__ X, const int *__restrict__ types,
-                           const int *__restrict__ nlist, int i, int n, int natoms, const Grid &g, float rc, float rcs) {
-  for (int j = tid; j < 16 * NB; j += 64 * NB) {
-    float s = 0.f, sw = 0.f, r = 1.f, hx = 0.f, hy = 0.f, hz = 0.f;
-    int tj = 0;
-    if (j < n) {
-      int nj = nlist[(size_t)i * SEL + j];
-      if (nj < 0 || nj >= natoms) nj = i;  // never read outside the coordinate array
-      tj = clamp_type(types[nj]);
-      double d[3];
-      for (int a = 0; a < 3; ++a) {
-        double v = X[3 * nj + a] - X[3 * i + a];
-        if (g.periodic) v -= g.L[a] * rint(v * g.invL[a]);
-        d[a] = v;
-      }
-      const float dx = (float)d[0], dy = (float)d[1], dz = (float)d[2];
-      r = sqrtf(dx * dx + dy * dy + dz * dz);
-      const float u = (r - rcs) / (rc - rcs);
-      if (r < rcs) sw = 1.f;
-      else if (r < rc) sw = u * u * u * (-6.f * u * u + 15.f * u - 10.f) + 1.f;
-      s = sw / r;
-      hx = dx / r; hy = dy / r; hz = dz / r;
-    }
-    e.s[j] = s; e.sw[j] = sw; e.r[j] = r; e.tj[j] = tj;
-    e.rh[0][j] = hx; e.rh[1][j] = hy; e.rh[2][j] = hz;
-  }
-}
-
-// ------------------------------------------------------------ embedding net
-// Its widths 25, 50 = 2 x 25, 100 = 4 x 25 are kept as groups of 25 features, slot r of
-// lane group q holding feature 4 r + q of the group (r < 7; r = 6 only for q = 0, zero
-// elsewhere), so that the residuals [h, h] add registers of the same lane.  h1[r];
-// h2[g][r] with feature 25 g + 4 r + q; G[g][r] likewise for g < 4.  Weights in fragment
-// order: an output group's slots 0-3 and 4-7 are two tiles (row 4 q + i of tile u is slot
-// 4 u + i); a contraction group's 8 slots are two pieces of 4 k steps.
-typedef float S7[7];
-__device__ __forceinline__ bool slot_ok(int r) { return r < 6 || lane() < 16; }
-
 // out[og] += W in over NI input groups: W at ((og * 2 + u) * NI * 2 + 2 ig + piece) * 256.
 template <int NI, int NO>
 __device__ __forceinline__ void emul(S7 (&out)[NO], const float *__restrict__ w, const S7 (&in)[NI]) {
@@ -310,55 +181,6 @@ __device__ __forceinline__ void embed(const Weights<float> &w, float s, int ti, 
     }
 }
 
-// The embedding's G into the token's row.
-__device__ __forceinline__ void put_embedding(float *row, const S7 (&h1)[1], const S7 (&t2)[2], const S7 (&t3)[4]) {
-  const int q = lane() >> 4;
-#pragma unroll
-  for (int g = 0; g < 4; ++g)
-#pragma unroll
-    for (int r = 0; r < 7; ++r)
-      if (slot_ok(r)) row[25 * g + 4 * r + q] = t3[g][r] + (t2[g & 1][r] + h1[0][r]);
-}
-
-// E = exp(S - max) / Z over the keys in place of the scores (0 past the list), with
-// Z = sum_k sw_k exp(S_k - max).
-template <int NB>
-__device__ __forceinline__ void softmax_keys(f4 (&s)[NB], const EnvF<NB> &e, int n, int nb) {
-  const int q = lane() >> 4;
-  float m = -INFINITY;
-#pragma unroll
-  for (int kt = 0; kt < NB; ++kt)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if (16 * kt + 4 * q + i >= n) s[kt][i] = -INFINITY;
-      m = fmaxf(m, s[kt][i]);
-    }
-  m = fmaxf(m, __shfl_xor(m, 16));
-  m = fmaxf(m, __shfl_xor(m, 32));
-  if (m == -INFINITY) m = 0.f;
-  float z = 0.f;
-#pragma unroll
-  for (int kt = 0; kt < NB; ++kt) {
-    const f4 sw = ldf4(e.sw + 16 * kt + 4 * q);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      s[kt][i] = expf(s[kt][i] - m);
-      z += sw[i] * s[kt][i];
-    }
-  }
-  z = sumq(z);
-  const float iz = z > 0.f ? 1.f / z : 0.f;
-#pragma unroll
-  for (int kt = 0; kt < NB; ++kt) s[kt] *= iz;
-}
-
-// rhat_k . h for the four keys of tile kt the lane holds.
-template <int NB>
-__device__ __forceinline__ f4 gate4(const EnvF<NB> &e, int kt, const float (&h)[3]) {
-  const int k = 16 * kt + 4 * (lane() >> 4);
-  return ldf4(e.rh[0] + k) * h[0] + ldf4(e.rh[1] + k) * h[1] + ldf4(e.rh[2] + k) * h[2];
-}
-
 // ======================================================================== forward
 template <int NB> struct SmemFwd {
   float G[16 * NB * LDG] __attribute__((aligned(16)));
@@ -366,38 +188,12 @@ template <int NB> struct SmemFwd {
   EnvF<NB> e;
 };
 
-// The part of a workgroup's work a wave takes: NA atoms (entries blk NA .. of the
-// instance's list), NB waves each.  Past the end of the list nb = 0; steps is the largest
-// nb, so that the waves of both atoms pass the same barriers.
-template <int NB, int NA> struct Part {
-  int half, jb, tid, i, n, nb, steps;
-  __device__ __forceinline__ Part(int blk, const int *__restrict__ idx, int count, const int *__restrict__ nnei) {
-    const int wv = __builtin_amdgcn_readfirstlane(wave_id());
-    half = NA == 1 ? 0 : wv / NB;
-    jb = wv - half * NB;
-    tid = threadIdx.x - half * 64 * NB;
-    steps = 0;
-#pragma unroll
-    for (int a = 0; a < NA; ++a) {
-      const int k = idx[min(blk * NA + a, count - 1)];
-      const int nk = min(max(nnei[k], 0), SEL);
-      const int b = blk * NA + a < count ? min(nk > 0 ? (nk + 15) / 16 : 1, NB) : 0;
-      steps = max(steps, b);
-      if (a == half) {
-        i = k;
-        n = nk;
-        nb = b;
-      }
-    }
-  }
-};
-
 template <int NB, int NA>
-__device__ __forceinline__ void desc_fwd(int blk, int count, SmemFwd<NB> *smem, Weights<float> w, const double *__restrict__ X, const int *__restrict__ types, int natoms, const int *__restrict__ idx,
+__device__ __forceinline__ void desc_fwd(int blk, int count, SmemFwd<NB> *smem, Weights<float> w, const double *__restrict__ X, const int *__restrict__ types, int natoms, const int *__restrict__ idx, int c0,
            const int *__restrict__ nlist, const int *__restrict__ nnei, const Grid *__restrict__ grids,
            const int *__restrict__ sys_of, float rc, float rcs, float ln_eps, float *__restrict__ Gsave,
            float *__restrict__ Tsave) {
-  const Part<NB, NA> pt(blk, idx, count, nnei);
+  const Part<NB, NA> pt(blk, idx, c0, count, nnei);
   SmemFwd<NB> &sm = smem[pt.half];
   const int i = pt.i, n = pt.n, nb = pt.nb, jb = pt.jb, tid = pt.tid;
   const Grid g = grids[sys_of[i]];
@@ -424,7 +220,7 @@ __device__ __forceinline__ void desc_fwd(int blk, int count, SmemFwd<NB> *smem, 
       wmul(u, w.WqkT[layer], x);  // U
       f4 s[NB];
       keys_dot<NB>(s, sm.G, u, nb);  // S = U G^T
-      softmax_keys<NB>(s, sm.e, n, nb);
+      softmax_keys<NB>(s, sm.e, n, [](float v) { return expf(v); });
       // H = A G with A = sw E gate
       keys_sum<NB>(x, sm.G, [&](int kt) { return s[kt] * gate4(sm.e, kt, hj) * ldf4(sm.e.sw + 16 * kt + 4 * q); }, nb);
       wmul(y, w.WvoT[layer], x);     // Y, summed by itself and then added: starting from G would round at G's size
@@ -480,18 +276,18 @@ __device__ __forceinline__ void desc_fwd(int blk, int count, SmemFwd<NB> *smem, 
 template <int NB, int NA>
 __global__ void __launch_bounds__(64 * NB * NA) __attribute__((amdgpu_waves_per_eu(NB == NB_SMALL ? 3 : 2)))
 k_desc_fwd(Weights<float> w, const double *__restrict__ X, const int *__restrict__ types, int natoms,
-           const int *__restrict__ idx, const int *__restrict__ cnt, const int *__restrict__ nlist,
+           const int *__restrict__ idx, const int *__restrict__ cnt, int c0, int ncen, const int *__restrict__ nlist,
            const int *__restrict__ nnei, const Grid *__restrict__ grids, const int *__restrict__ sys_of, float rc, float rcs,
            float ln_eps, float *__restrict__ Gsave, float *__restrict__ Tsave) {
   __shared__ SmemFwd<NB> smem[NA];
-  const int count = *cnt;
+  const int count = idx ? *cnt : ncen;
   if constexpr (NB == NB_SMALL) {  // without the loop, which would keep its invariants in registers
     const int b = blockIdx.x;
     if (b * NA < count)
-      desc_fwd<NB, NA>(b, count, smem, w, X, types, natoms, idx, nlist, nnei, grids, sys_of, rc, rcs, ln_eps, Gsave, Tsave);
+      desc_fwd<NB, NA>(b, count, smem, w, X, types, natoms, idx, c0, nlist, nnei, grids, sys_of, rc, rcs, ln_eps, Gsave, Tsave);
   } else {
     for (int b = blockIdx.x; b * NA < count; b += gridDim.x) {
-      desc_fwd<NB, NA>(b, count, smem, w, X, types, natoms, idx, nlist, nnei, grids, sys_of, rc, rcs, ln_eps, Gsave, Tsave);
+      desc_fwd<NB, NA>(b, count, smem, w, X, types, natoms, idx, c0, nlist, nnei, grids, sys_of, rc, rcs, ln_eps, Gsave, Tsave);
       __syncthreads();
     }
   }
@@ -572,7 +368,7 @@ __device__ __forceinline__ void layer_bwd(const Weights<float> &w, int layer, Sm
       wmul(u, w.WqkT[layer], x);
     }
     keys_dot<NB>(E, sm.G, u, nb);
-    softmax_keys<NB>(E, sm.e, n, nb);
+    softmax_keys<NB>(E, sm.e, n, [](float v) { return expf(v); });
     {  // LayerNorm backward: dX = (dxh - mean(dxh) - xh mean(dxh xh)) / sigma, dxh = gamma dG_out
       F100 xh, ga;
       load_block(xh, saved + 1600 * jb);
@@ -700,11 +496,11 @@ __device__ __forceinline__ void layer_bwd(const Weights<float> &w, int layer, Sm
 }
 
 template <int NB, int NA>
-__device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB> *smem, Weights<float> w, const double *__restrict__ X, const int *__restrict__ types, int natoms, const int *__restrict__ idx,
+__device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB> *smem, Weights<float> w, const double *__restrict__ X, const int *__restrict__ types, int natoms, const int *__restrict__ idx, int c0,
            const int *__restrict__ nlist, const int *__restrict__ nnei, const Grid *__restrict__ grids,
            const int *__restrict__ sys_of, float rc, float rcs, float ln_eps, const float *__restrict__ Gsave,
            const float *__restrict__ fit, float4 *__restrict__ gout) {
-  const Part<NB, NA> pt(blk, idx, count, nnei);
+  const Part<NB, NA> pt(blk, idx, c0, count, nnei);
   SmemBwd<NB> &sm = smem[pt.half];
   const int i = pt.i, n = pt.n, nb = pt.nb, jb = pt.jb, tid = pt.tid;
   const Grid g = grids[sys_of[i]];
@@ -818,18 +614,18 @@ __device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB> *smem, 
 template <int NB, int NA>
 __global__ void __launch_bounds__(64 * NB * NA) __attribute__((amdgpu_waves_per_eu(NB == NB_SMALL ? 3 : 2)))
 k_desc_bwd(Weights<float> w, const double *__restrict__ X, const int *__restrict__ types, int natoms,
-           const int *__restrict__ idx, const int *__restrict__ cnt, const int *__restrict__ nlist,
+           const int *__restrict__ idx, const int *__restrict__ cnt, int c0, int ncen, const int *__restrict__ nlist,
            const int *__restrict__ nnei, const Grid *__restrict__ grids, const int *__restrict__ sys_of, float rc, float rcs,
            float ln_eps, const float *__restrict__ Gsave, const float *__restrict__ fit, float4 *__restrict__ gout) {
   __shared__ SmemBwd<NB> smem[NA];
-  const int count = *cnt;
+  const int count = idx ? *cnt : ncen;
   if constexpr (NB == NB_SMALL) {  // without the loop, which would keep its invariants in registers
     const int b = blockIdx.x;
     if (b * NA < count)
-      desc_bwd<NB, NA>(b, count, smem, w, X, types, natoms, idx, nlist, nnei, grids, sys_of, rc, rcs, ln_eps, Gsave, fit, gout);
+      desc_bwd<NB, NA>(b, count, smem, w, X, types, natoms, idx, c0, nlist, nnei, grids, sys_of, rc, rcs, ln_eps, Gsave, fit, gout);
   } else {
     for (int b = blockIdx.x; b * NA < count; b += gridDim.x) {
-      desc_bwd<NB, NA>(b, count, smem, w, X, types, natoms, idx, nlist, nnei, grids, sys_of, rc, rcs, ln_eps, Gsave, fit, gout);
+      desc_bwd<NB, NA>(b, count, smem, w, X, types, natoms, idx, c0, nlist, nnei, grids, sys_of, rc, rcs, ln_eps, Gsave, fit, gout);
       __syncthreads();
     }
   }
@@ -837,64 +633,22 @@ k_desc_bwd(Weights<float> w, const double *__restrict__ X, const int *__restrict
 
 }  // namespace
 
-// Two atoms share a workgroup where there is more than one atom per CU (256): the waves of
-// a workgroup go to the SIMDs in turn, so that 12 waves put three on each, while a second
-// workgroup of 6 waves does not fit beside a first (two SIMDs would hold four waves of 168
-// registers; 9,999 atoms that way: forward 2.73 ms, backward 6.9 ms, against 2.10 and
-// 4.85 ms in pairs).  Fewer atoms run one to a CU.
-constexpr int PAIR_FROM = 257;
-constexpr int NCU = 256;
-
-// Lists the centres c0 .. c1-1 for the two instances, one addition per wave and instance
-// (one per atom, in the neighbour search, cost 30 us at 3,000 atoms).  The order only
-// changes scheduling.
-__global__ void __launch_bounds__(256) k_class_lists(const int *__restrict__ nnei, int c0, int c1, int *__restrict__ idx,
-                                                     int *__restrict__ cnt, int cap) {
-  const int i = c0 + blockIdx.x * 256 + threadIdx.x;
-  const int l = lane_id();
-  const bool small = i < c1 && nnei[i] <= 16 * NB_SMALL;
-  for (int cls = 0; cls < 2; ++cls) {
-    const unsigned long long mask = __ballot(i < c1 && small == (cls == 0));
-    if (!mask) continue;
-    const int first = __ffsll(mask) - 1;
-    int base = 0;
-    if (l == first) base = atomicAdd(cnt + cls, __popcll(mask));
-    base = __shfl(base, first);
-    const int pos = base + __popcll(mask & ((1ull << l) - 1ull));
-    if ((mask >> l & 1ull) && pos < cap) idx[(size_t)cls * cap + pos] = i;
-  }
-}
-
-// launch(kernel, workgroups, threads, list, stream) for the instances that may have atoms.
-template <class Small, class Pair, class Large, class Launch>
-void launch_instances(const Workspace &ws, int ncen, Small small, Pair pair, Large large, hipStream_t st,
-                      const Launch &launch) {
-  (void)hipEventRecord(ws.fork_ev, st);
-  (void)hipStreamWaitEvent(ws.side, ws.fork_ev, 0);
-  launch(large, std::min(ncen, NCU), 64 * 8, 1, ws.side);
-  if (ncen >= PAIR_FROM) launch(pair, (ncen + 1) / 2, 64 * 2 * NB_SMALL, 0, st);
-  else launch(small, ncen, 64 * NB_SMALL, 0, st);
-  (void)hipEventRecord(ws.join_ev, ws.side);
-  (void)hipStreamWaitEvent(st, ws.join_ev, 0);
-}
-
 void launch_descriptor_fwd(const Weights<float> &w, const Workspace &ws, const double *coords, const int *types, int n,
                            int c0, int c1, float rc, float rcs, float ln_eps, hipStream_t st) {
-  hipLaunchKernelGGL(k_class_lists, dim3((c1 - c0 + 255) / 256), dim3(256), 0, st, ws.nnei, c0, c1, ws.bidx, ws.bcnt,
-                     (int)ws.cap);
-  launch_instances(ws, c1 - c0, k_desc_fwd<NB_SMALL, 1>, k_desc_fwd<NB_SMALL, 2>, k_desc_fwd<8, 1>, st,
-                   [&](auto kernel, int groups, int threads, int list, hipStream_t s) {
-    hipLaunchKernelGGL(kernel, dim3(groups), dim3(threads), 0, s, w, coords, types, n, ws.bidx + list * ws.cap,
-                       ws.bcnt + list, ws.nlist, ws.nnei, ws.grids, ws.sys_of, rc, rcs, ln_eps, ws.Gsave, ws.Tsave);
+  launch_class_lists(ws, n, c0, c1, st);
+  launch_instances(ws, n, c1 - c0, k_desc_fwd<NB_SMALL, 2>, k_desc_fwd<8, 1>, st,
+                   [&](auto kernel, int groups, int threads, const int *idx, const int *cnt, hipStream_t s) {
+    hipLaunchKernelGGL(kernel, dim3(groups), dim3(threads), 0, s, w, coords, types, n, idx, cnt, c0, c1 - c0, ws.nlist,
+                       ws.nnei, ws.grids, ws.sys_of, rc, rcs, ln_eps, ws.Gsave, ws.Tsave);
   });
 }
 
 void launch_descriptor_bwd(const Weights<float> &w, const Workspace &ws, const double *coords, const int *types, int n,
                            int c0, int c1, float rc, float rcs, float ln_eps, hipStream_t st) {
-  launch_instances(ws, c1 - c0, k_desc_bwd<NB_SMALL, 1>, k_desc_bwd<NB_SMALL, 2>, k_desc_bwd<8, 1>, st,
-                   [&](auto kernel, int groups, int threads, int list, hipStream_t s) {
-    hipLaunchKernelGGL(kernel, dim3(groups), dim3(threads), 0, s, w, coords, types, n, ws.bidx + list * ws.cap,
-                       ws.bcnt + list, ws.nlist, ws.nnei, ws.grids, ws.sys_of, rc, rcs, ln_eps, ws.Gsave, ws.fit, ws.g);
+  launch_instances(ws, n, c1 - c0, k_desc_bwd<NB_SMALL, 2>, k_desc_bwd<8, 1>, st,
+                   [&](auto kernel, int groups, int threads, const int *idx, const int *cnt, hipStream_t s) {
+    hipLaunchKernelGGL(kernel, dim3(groups), dim3(threads), 0, s, w, coords, types, n, idx, cnt, c0, c1 - c0, ws.nlist,
+                       ws.nnei, ws.grids, ws.sys_of, rc, rcs, ln_eps, ws.Gsave, ws.fit, ws.g);
   });
 }
 

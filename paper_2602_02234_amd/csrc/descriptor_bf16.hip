@@ -1,101 +1,662 @@
-// Forward descriptor kernel of the bfloat16 path: one workgroup (8 waves) per atom.
-// Environment, type-embedded embedding net (its weights staged in LDS), two attention
-// layers (their weights read from L2 in MFMA fragment order), T = G^T Rt / sel; the input rows of each attention layer are saved for the backward.
-#include "descriptor_bf16.h"
+// Per-atom descriptor kernels of the bfloat16 path on gfx950, forward and backward: the model
+// and the split over waves of the float32 kernels (descriptor.hip, dp_desc.h), with the
+// products on 16x16x32 bfloat16 MFMA.  Rounded to bfloat16 are the operands of the products
+// only: G, U, the attention weights, H, dY, dH, dS, dU and the embedding's h1, h2 and
+// pre-activation gradients; accumulators, residuals, softmax, LayerNorm, the sums of the
+// softmax and gate gradients and T = G^T Rt / sel are float32.
+//
+// A wave carries the 16 tokens of its block in registers, transposed: lane (q = lane / 16,
+// c = lane % 16) holds features (or keys) 16 t + 4 q + i of token c.  Two tiles t = 2 p, 2 p + 1
+// of that form are the eight k of the lane in step p of the next product (k = 32 p + 8 q + e
+// stands for feature 32 p + 4 q + e, or 32 p + 16 + 4 q + e - 4 from e = 4), so an accumulator is
+// rounded and used without a trip through LDS; features 96 + q take the first k of step 3.
+// Rows that other waves read are kept in LDS in that order, 128 values in sixteen 16-byte
+// pieces (piece 4 p + q; 12 + q: feature 96 + q and zeros), the pieces of row r exchanged by
+// r's low bits so that 16 rows' reads of one piece and 4 rows' transposed reads of four
+// (ds_read_tr: four rows of 16 columns, a column to a lane) both spread over all banks.  One
+// copy serves contractions over features and over tokens.
+//
+// In the backward a key's sums over the queries, A^T dH + dS^T U, are formed by the key's wave
+// from the waves' rows of E gate and dH, then W and U, left in LDS between barriers; the factor
+// sw_k multiplies the float32 sum.
+//
+// Bound: vector instructions (softmax, LayerNorm, tanh, conversions), then the latency of the
+// stages between barriers; the matrix cores' share is about a fifth (101 MFMAs of 16 cycles per
+// block and layer forward, 232 backward, at 96 neighbours).
+#include "dp_desc.h"
 
 namespace dp {
 namespace {
 
-struct __align__(16) SmemF16 {
-  bf16_t Gb[NPMAX * LDK];
-  bf16_t GbT[KM * LDT];
-  bf16_t stg[NWF][16 * LDT];
-  bf16_t Wemb[64 * LD2 + KM * LD3];  // the embedding's W2^T and W3^T
-  EnvB e;
+constexpr int RW = 128;   // values in a bfloat16 row in LDS
+constexpr int LDE = 104;  // stride of the rows the embedding is rearranged in (16 fit a block's rows)
+typedef short s4 __attribute__((ext_vector_type(4)));
+static_assert(M == 100 && E1 == 25 && E2 == 50, "the fragment layouts below are written for these widths");
+
+__device__ __forceinline__ f4 mma(bf8 a, bf8 b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
+__device__ __forceinline__ bf8 ld8(const bf16_t *p) { return *reinterpret_cast<const bf8 *>(p); }
+
+// tanh from the hardware exponential and reciprocal: relative error a few 1e-7, far below the
+// bfloat16 rounding of the products it feeds.
+__device__ __forceinline__ float ftanh(float x) {
+  const float t = __expf(-2.f * fabsf(x));
+  return copysignf((1.f - t) * __builtin_amdgcn_rcpf(1.f + t), x);
+}
+
+__device__ __forceinline__ bf8 pack(f4 a, f4 b) {
+  bf8 v;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    v[e] = (__bf16)a[e];
+    v[4 + e] = (__bf16)b[e];
+  }
+  return v;
+}
+// A token's features as a B operand.
+struct XB {
+  bf8 v[4];
+  __device__ __forceinline__ XB() {}
+  __device__ __forceinline__ explicit XB(const F100 &x) {
+#pragma unroll
+    for (int p = 0; p < 3; ++p) v[p] = pack(x[2 * p], x[2 * p + 1]);
+    v[3] = pack(f4{x[6][0], 0.f, 0.f, 0.f}, f4{0.f, 0.f, 0.f, 0.f});
+  }
+};
+// Piece 4 p + q of row 16 b + c, b the base: where the lane's eight values of step p are.
+__device__ __forceinline__ int piece(int p) {
+  const int q = lane() >> 4, c = lane() & 15;
+  return c * RW + 8 * (4 * (p ^ (c & 3)) + (q ^ (c >> 2)));
+}
+__device__ __forceinline__ void put_block(bf16_t *block, const XB &x) {
+#pragma unroll
+  for (int p = 0; p < 4; ++p) *reinterpret_cast<bf8 *>(block + piece(p)) = x.v[p];
+}
+// Values of column 16 t + c in rows 4 q .. 4 q + 3 of a block (t = 6: feature 96 + c / 4 for c a
+// multiple of 4).
+__device__ __forceinline__ s4 column4(const bf16_t *block, int t) {
+  const int q = lane() >> 4, c = lane() & 15, r = c >> 2;
+  const bf16_t *p = block + (4 * q + r) * RW + 8 * (4 * ((t >> 1) ^ r) + ((c & 3) ^ q)) + 4 * (t & 1);
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s4 *)p);
+}
+// ... of two consecutive blocks: the eight k of a contraction over 32 rows.
+__device__ __forceinline__ bf8 column8(const bf16_t *block, int t) {
+  const s4 a = column4(block, t), b = column4(block + 16 * RW, t);
+  typedef short s8 __attribute__((ext_vector_type(8)));
+  const s8 v = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+  return __builtin_bit_cast(bf8, v);
+}
+
+// acc += W x for a 100 x 100 matrix in fragment order: step p < 3 of tile t at (7 p + t) 512 + 8 lane,
+// the seven tiles' k = 96 + q at 10752 + 8 lane + t.  A step's seven tiles are independent
+// products, and the next step's operands are loaded while they run.
+__device__ __forceinline__ void wmul(F100 &acc, const bf16_t *__restrict__ w, const XB &x) {
+  const bf16_t *p = w + 8 * lane();
+  bf8 a[7];
+#pragma unroll
+  for (int t = 0; t < 7; ++t) a[t] = ld8(p + 512 * t);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    bf8 b[7];
+    if (k < 2) {
+#pragma unroll
+      for (int t = 0; t < 7; ++t) b[t] = ld8(p + 512 * (7 * (k + 1) + t));
+    } else if (k == 2) {
+      const bf8 tail = ld8(p + 10752);
+#pragma unroll
+      for (int t = 0; t < 7; ++t) {
+        b[t] = bf8{};
+        b[t][0] = tail[t];
+      }
+    }
+    tile_barrier();
+#pragma unroll
+    for (int t = 0; t < 7; ++t) acc[t] = mma(a[t], x.v[k], acc[t]);
+    if (k < 3)
+#pragma unroll
+      for (int t = 0; t < 7; ++t) a[t] = b[t];
+  }
+}
+
+// s[kt] = G x over the keys of tile kt < nb: rows key 16 kt + 4 q + i, columns tokens.
+template <int NB>
+__device__ __forceinline__ void keys_dot(f4 (&s)[NB], const bf16_t *G, const XB &x, int nb) {
+#pragma unroll
+  for (int kt = 0; kt < NB; ++kt) s[kt] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    tile_barrier();
+    const bf16_t *g = G + piece(p);
+#pragma unroll
+    for (int kt = 0; kt < NB; ++kt)
+      if (kt < NB_SMALL - 2 || kt < nb) s[kt] = mma(ld8(g + 16 * kt * RW), x.v[p], s[kt]);
+  }
+}
+
+// acc += R^T y over rows 32 p .. 32 p + 31 of R, y(p) the lane's eight values of them, for
+// 2 p < nb.  Rows of a block past nb are zero.
+template <int NB, class Y>
+__device__ __forceinline__ void rows_sum(F100 &acc, const bf16_t *R, const Y &y, int nb) {
+#pragma unroll
+  for (int p = 0; p < NB / 2; ++p)
+    if (2 * p < nb) {
+      const bf8 v = y(p);
+      bf8 a[7];
+#pragma unroll
+      for (int t = 0; t < 7; ++t) a[t] = column8(R + 32 * p * RW, t);
+#pragma unroll
+      for (int t = 0; t < 7; ++t) acc[t] = mma(a[t], v, acc[t]);
+      tile_barrier();
+    }
+}
+
+// ------------------------------------------------------------ embedding net
+// Feature groups as in the float32 kernels; a group's seven slots are the lane's k of one step.
+// Weights in fragment order: tile u of output group og, input group ig at ((og 2 + u) NI + ig) 512.
+template <int NI, int NO>
+__device__ __forceinline__ void emul(S7 (&out)[NO], const bf16_t *__restrict__ w, const S7 (&in)[NI]) {
+  bf8 x[NI];
+#pragma unroll
+  for (int ig = 0; ig < NI; ++ig)
+    x[ig] = pack(f4{in[ig][0], in[ig][1], in[ig][2], in[ig][3]}, f4{in[ig][4], in[ig][5], in[ig][6], 0.f});
+#pragma unroll
+  for (int og = 0; og < NO; ++og)
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      f4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ig = 0; ig < NI; ++ig) acc = mma(ld8(w + ((og * 2 + u) * NI + ig) * 512 + 8 * lane()), x[ig], acc);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (4 * u + i < 7) out[og][4 * u + i] = acc[i];
+    }
+}
+
+// h1, t2 = h2 - [h1, h1] and t3 = G - [h2, h2] of the lane's token.
+__device__ __forceinline__ void embed(const Tables &w, const WeightsB16 &wp, float s, int ti, int tj, S7 (&h1)[1],
+                                      S7 (&t2)[2], S7 (&t3)[4]) {
+  const int q = lane() >> 4;
+  const float *bt = w.Bt + (ti * NTYPES + tj) * E1;
+#pragma unroll
+  for (int r = 0; r < 7; ++r) {
+    const int f = slot_ok(r) ? 4 * r + q : 0;
+    const float v = ftanh(s * w.w1s[f] + bt[f]);
+    h1[0][r] = slot_ok(r) ? v : 0.f;
+  }
+  emul<1, 2>(t2, wp.W2T, h1);
+  S7 h2[2];
+#pragma unroll
+  for (int g = 0; g < 2; ++g)
+#pragma unroll
+    for (int r = 0; r < 7; ++r) {
+      const int f = slot_ok(r) ? 25 * g + 4 * r + q : 0;
+      const float v = ftanh(t2[g][r] + w.b2[f]);
+      t2[g][r] = slot_ok(r) ? v : 0.f;
+      h2[g][r] = t2[g][r] + h1[0][r];
+    }
+  emul<2, 4>(t3, wp.W3T, h2);
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+#pragma unroll
+    for (int r = 0; r < 7; ++r) {
+      const int f = slot_ok(r) ? 25 * g + 4 * r + q : 0;
+      const float v = ftanh(t3[g][r] + w.b3[f]);
+      t3[g][r] = slot_ok(r) ? v : 0.f;
+    }
+}
+
+// ======================================================================== forward
+template <int NB> struct SmemFwd {
+  bf16_t G[16 * NB * RW] __attribute__((aligned(16)));    // the layer's input, every token
+  float row[16 * NB * LDG] __attribute__((aligned(16)));  // ... in float32, each wave its own
+  float part[NB][M * 4] __attribute__((aligned(16)));
+  EnvF<NB> e;
 };
 
-__global__ void __launch_bounds__(NWF * 64)
-k_desc_fwd_b16(Tables w, WeightsB16 wp, const double *__restrict__ X, const int *__restrict__ types, int natoms, int c0,
-               const int *__restrict__ nlist, const int *__restrict__ nnei, const Grid *__restrict__ grids, const int *__restrict__ sys_of,
-               float rc, float rcs, float ln_eps, float *__restrict__ Gsave, float *__restrict__ Tsave,
-               int *__restrict__ bidx, int *__restrict__ bcnt, int cap) {
-  __shared__ SmemF16 sm;
-  const int i = c0 + blockIdx.x;
+__device__ __forceinline__ void zero_block(bf16_t *block) {
+#pragma unroll
+  for (int p = 0; p < 4; ++p) *reinterpret_cast<bf8 *>(block + piece(p)) = bf8{};
+}
+
+template <int NB, int NA>
+__device__ __forceinline__ void desc_fwd(int blk, int count, SmemFwd<NB> *smem, const Tables &w, const WeightsB16 &wp,
+                                         const double *__restrict__ X, const int *__restrict__ types, int natoms,
+                                         const int *__restrict__ idx, int c0, const int *__restrict__ nlist,
+                                         const int *__restrict__ nnei, const Grid *__restrict__ grids,
+                                         const int *__restrict__ sys_of, float rc, float rcs, float ln_eps,
+                                         float *__restrict__ Gsave, float *__restrict__ Tsave) {
+  const Part<NB, NA> pt(blk, idx, c0, count, nnei);
+  SmemFwd<NB> &sm = smem[pt.half];
+  const int i = pt.i, n = pt.n, nb = pt.nb, jb = pt.jb, tid = pt.tid;
   const Grid g = grids[sys_of[i]];
-  const int n = min(max(nnei[i], 0), SEL);
-  const int NP = n > 0 ? ((n + 15) / 16) * 16 : 16;
-  const int nb = NP / 16;
-  if (threadIdx.x == 0) {  // list the atom for the backward instance that fits its block count
-    const int cls = nb <= SPLIT_NB ? 0 : 1;
-    bidx[cls * cap + atomicAdd(&bcnt[cls], 1)] = i;
-  }
   const int ti = clamp_type(types[i]);
-  const int wv = wave_id(), l = lane(), q = l >> 4, cl = l & 15;
-  build_envb(sm.e, X, types, nlist, i, n, natoms, g, rc, rcs);
-  bf16_t *w2s = sm.Wemb, *w3s = sm.Wemb + 64 * LD2;
-  stage_weights2<64, 32, KM, 64, NWF * 64>(w2s, LD2, wp.W2T, 32, w3s, LD3, wp.W3T, 64);
+  const int l = lane(), q = l >> 4, c = l & 15;
+  const bool act = jb < nb;
+  build_envf(sm.e, tid, X, types, nlist, i, n, natoms, g, rc, rcs);
   __syncthreads();
-  const bool act = wv < nb;
-  const int jb = wv;
-  bf16_t *stg = sm.stg[wv];
-  f4 gv[7];
+  const int j = 16 * jb + c;  // the lane's token
+  float *row = sm.row + j * LDG;
+  bf16_t *block = sm.G + 16 * jb * RW;
+  XB xb;
   if (act) {
-    // h1 scratch in this wave's own (not yet written) rows of Gb, h2 in its staging buffer
-    embed_rows(w, w2s, LD2, w3s, LD3, sm.e, ti, jb, (float *)(sm.Gb + jb * 16 * LDK), (float *)stg, gv);
-    put_rows(sm.Gb, sm.GbT, gv, jb);
+    S7 h1[1], t2[2], t3[4];
+    embed(w, wp, sm.e.s[j], ti, sm.e.tj[j], h1, t2, t3);
+    put_embedding(row, h1, t2, t3);
+    wave_sync();
+    F100 x;
+    get_row(x, row);
+    xb = XB(x);
+    put_block(block, xb);
+  } else {
+    zero_block(block);
   }
+  __syncthreads();
+  const float hj[3] = {sm.e.rh[0][j], sm.e.rh[1][j], sm.e.rh[2][j]};
+#pragma unroll 1
   for (int layer = 0; layer < NATTN; ++layer) {
-    __syncthreads();  // Gb and GbT hold the layer input
-    f4 sv[8], xh[7];
-    float isig[4];
     if (act) {
-      save_rows(Gsave + ((size_t)i * NATTN + layer) * GSAVE_LAYER, gv, jb);
-      layer_rows(w, wp.WqkT[layer], wp.WvoT[layer], layer, sm.e, sm.Gb, sm.GbT, stg, nullptr, jb, n, nb, NP, ln_eps, gv,
-                 sv, xh, isig, nullptr, nullptr);
+      f4 s[NB];
+      {
+        F100 u = {};
+        wmul(u, wp.WqkT[layer], xb);  // U
+        keys_dot<NB>(s, sm.G, XB(u), nb);  // S = U G^T
+      }
+      softmax_keys<NB>(s, sm.e, n, [](float v) { return __expf(v); });
+      F100 h = {}, y = {}, x;
+      // H = A G with A = sw E gate
+      rows_sum<NB>(h, sm.G, [&](int p) {
+        const int k = 32 * p + 4 * q;
+        return pack(s[2 * p] * gate4(sm.e, 2 * p, hj) * ldf4(sm.e.sw + k),
+                    s[2 * p + 1] * gate4(sm.e, 2 * p + 1, hj) * ldf4(sm.e.sw + k + 16));
+      }, nb);
+      wmul(y, wp.WvoT[layer], XB(h));
+      get_row(x, row);
+#pragma unroll
+      for (int t = 0; t < 7; ++t) y[t] += x[t];
+      // LayerNorm; the centred rows are what the backward reads
+      const float mu = sum100([&](int t, int k) { return y[t][k]; }) * (1.f / M);
+#pragma unroll
+      for (int t = 0; t < 7; ++t) y[t] -= mu;
+      save_block(Gsave + ((size_t)i * NATTN + layer) * GSAVE_LAYER + 1600 * jb, y);
+      normalise(y, ln_eps);
+      F100 ga, be;
+      get_table(ga, w.gamma[layer]);
+      get_table(be, w.beta[layer]);
+#pragma unroll
+      for (int t = 0; t < 7; ++t) y[t] = ga[t] * y[t] + be[t];
+      put_row(row, y);
+      xb = XB(y);
     }
-    __syncthreads();  // every wave is done reading them
-    if (act) put_rows(sm.Gb, sm.GbT, gv, jb);
+    if (layer == NATTN - 1) break;
+    __syncthreads();  // every wave is done with the layer's input
+    if (act) put_block(block, xb);
+    __syncthreads();
+  }
+  // T = G^T Rt / sel: each wave's 16 tokens on float32 MFMA (T^T = Rt^T G, rows c < 4 of the 16
+  // used, step s taking token 4 s + q), then the waves' parts in order
+  if (act) {
+    wave_sync();
+    f4 acc[7];
+#pragma unroll
+    for (int t = 0; t < 7; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int k = 16 * jb + 4 * s + q;
+      const float sk = sm.e.s[k];
+      const float rt = c == 0 ? sk : (c < 4 ? sk * sm.e.rh[c - 1][k] : 0.f);
+      const float *gk = sm.row + k * LDG;
+#pragma unroll
+      for (int t = 0; t < 7; ++t) acc[t] = mfma(rt, gk[t < 6 ? 16 * t + c : 96 + (c & 3)], acc[t]);
+    }
+    if (q == 0)
+#pragma unroll
+      for (int t = 0; t < 7; ++t)
+        if (t < 6 || c < 4) stf4(sm.part[jb] + 4 * (16 * t + c), acc[t]);
   }
   __syncthreads();
-  // T = G^T Rt / sel: per-wave partial over its rows, then a fixed-order sum over waves.
-  // The partial is four fp32 MFMAs per feature tile: A = the wave's G rows 4q + ii
-  // straight from the accumulator registers (lane (q, c) holds G[4q + ii][16t + c], i.e.
-  // A[c][q]), B[q][c] = Rt[4q + ii][c] for c < 4; lane (q, c) ends with T[16t + 4q + r][c].
-  float *tp = (float *)sm.stg[wv];
+  for (int k = tid; k < (nb ? M * 4 : 0); k += 64 * NB) {
+    float acc = 0.f;
+    for (int v = 0; v < nb; ++v) acc += sm.part[v][k];
+    Tsave[(size_t)i * M * 4 + k] = acc * (1.f / (float)SEL);
+  }
+}
+
+// One workgroup per NA atoms of its list; the 8-wave instance loops over its atoms with at most
+// one workgroup per CU (or as many as there are atoms, without a list).
+template <int NB, int NA>
+__global__ void __launch_bounds__(64 * NB * NA) __attribute__((amdgpu_waves_per_eu(NB == NB_SMALL ? 3 : 2)))
+k_desc_fwd_b16(Tables w, WeightsB16 wp, const double *__restrict__ X, const int *__restrict__ types, int natoms,
+               const int *__restrict__ idx, const int *__restrict__ cnt, int c0, int ncen, const int *__restrict__ nlist,
+               const int *__restrict__ nnei, const Grid *__restrict__ grids, const int *__restrict__ sys_of, float rc, float rcs,
+               float ln_eps, float *__restrict__ Gsave, float *__restrict__ Tsave) {
+  __shared__ SmemFwd<NB> smem[NA];
+  const int count = idx ? *cnt : ncen;
+  for (int b = blockIdx.x; b * NA < count; b += gridDim.x) {
+    desc_fwd<NB, NA>(b, count, smem, w, wp, X, types, natoms, idx, c0, nlist, nnei, grids, sys_of, rc, rcs, ln_eps, Gsave, Tsave);
+    if (NB == NB_SMALL) break;  // as many workgroups as atoms
+    __syncthreads();
+  }
+}
+
+// ======================================================================== backward
+template <int NB> struct SmemBwd {
+  bf16_t G[16 * NB * RW] __attribute__((aligned(16)));     // a layer's input, then dH, then U
+  bf16_t K[16 * NB * RW] __attribute__((aligned(16)));     // the queries' rows of E gate, then of W
+  float tile[NB][256] __attribute__((aligned(16)));        // per-wave scratch
+  float drhw[NB][16 * NB * 3];                             // each wave's column sums of dC rhat
+  float wsum[NB][16 * NB] __attribute__((aligned(16)));    // ... of W
+  float dT[M * 4] __attribute__((aligned(16)));
+  EnvF<NB> e;
+};
+static_assert(sizeof(SmemBwd<8>::G) * 2 >= sizeof(float) * 16 * 8 * LDG, "float32 rows of every token fit over G and K");
+
+// Backward of one layer, its input rows in sm.G.  go: in, the gradient of the layer's output
+// for the wave's tokens, out, of its input; d: the layer's saved centred rows.  drh and dsw, the
+// gradients of the token's rhat and sw, are added to.  Ends after a barrier; the block's rows
+// in sm.G are then free.
+//   Row part (per token j): U, S, E recomputed; dX through the LayerNorm, dH = Wvo dX,
+//   dA = G dH, then per key P = sw E, dP = dA gate, rho = sum P dP, W = E (dP - rho),
+//   dS = sw W, dU = G^T dS, and dG_j = dX + Wqk dU.
+//   Column part (per key k): dG_k += sw_k sum_j (E gate)_jk dH_j + W_jk U_j, dsw_k += sum_j W_jk.
+template <int NB>
+__device__ __forceinline__ void layer_bwd(const Tables &w, const WeightsB16 &wp, int layer, SmemBwd<NB> &sm, F100 &go,
+                                          const float *__restrict__ saved, int jb, int n, int nb, float ln_eps,
+                                          float (&drh)[3], float &dsw) {
+  const int l = lane(), q = l >> 4, c = l & 15;
+  const int j = 16 * jb + c;
+  bf16_t *block = sm.G + 16 * jb * RW, *kblock = sm.K + 16 * jb * RW;
+  const bool act = jb < nb;
+  XB ub, hb;
+  bf8 wb[NB / 2];
+  const float hj[3] = {sm.e.rh[0][j], sm.e.rh[1][j], sm.e.rh[2][j]};
   if (act) {
-    f4 tacc[7];
-    zero(tacc);
+    f4 E[NB], W[NB];
+    {
+      F100 u = {};
 #pragma unroll
-    for (int ii = 0; ii < 4; ++ii) {
-      const int j = jb * 16 + 4 * q + ii;
-      const float sj = (j < n) ? sm.e.s[j] : 0.f;
-      const float rt = cl == 0 ? sj : (cl < 4 ? sj * sm.e.rh[3 * j + cl - 1] : 0.f);
-#pragma unroll
-      for (int t = 0; t < 7; ++t) tacc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(gv[t][ii], rt, tacc[t], 0, 0, 0);
+      for (int p = 0; p < 4; ++p) ub.v[p] = ld8(block + piece(p));
+      wmul(u, wp.WqkT[layer], ub);
+      ub = XB(u);
     }
+    keys_dot<NB>(E, sm.G, ub, nb);
+    softmax_keys<NB>(E, sm.e, n, [](float v) { return __expf(v); });
+    {  // LayerNorm backward: dX = (dxh - mean(dxh) - xh mean(dxh xh)) / sigma, dxh = gamma dG_out
+      F100 xh, ga;
+      load_block(xh, saved + 1600 * jb);
+      const float is = normalise(xh, ln_eps);
+      get_table(ga, w.gamma[layer]);
+#pragma unroll
+      for (int t = 0; t < 7; ++t) go[t] = ga[t] * go[t];
+      const float s0 = sum100([&](int t, int k) { return go[t][k]; }) * (1.f / M);
+      const float s1 = sum100([&](int t, int k) { return go[t][k] * xh[t][k]; }) * (1.f / M);
+#pragma unroll
+      for (int t = 0; t < 7; ++t) go[t] = (go[t] - s0 - xh[t] * s1) * is;
+    }
+    {
+      F100 dh = {};
+      wmul(dh, wp.Wvo[layer], XB(go));
+      hb = XB(dh);
+    }
+    keys_dot<NB>(W, sm.G, hb, nb);  // dA
+    float rho = 0.f, hx = 0.f, hy = 0.f, hz = 0.f;
+    // columns of dC rhat: sum_j rhat_j (dA E)_jk, A operand rhat of token 4 q + s in rows a < 3
+    float rj[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) rj[s] = c < 3 ? sm.e.rh[c][16 * jb + 4 * q + s] : 0.f;
+    float *tile = sm.tile[jb];
+#pragma unroll
+    for (int p = 0; p < NB / 2; ++p)
+      if (2 * p < nb) {
+        f4 ea[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          tile_barrier();
+          const int kt = 2 * p + h, k = 16 * kt + 4 * q;
+          const f4 sw = ldf4(sm.e.sw + k), rx = ldf4(sm.e.rh[0] + k), ry = ldf4(sm.e.rh[1] + k), rz = ldf4(sm.e.rh[2] + k);
+          const f4 gt = rx * hj[0] + ry * hj[1] + rz * hj[2];
+          const f4 cc = W[kt] * E[kt];
+          const f4 dC = sw * cc, dP = W[kt] * gt, pr = sw * E[kt] * dP;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            rho += pr[i];
+            hx += dC[i] * rx[i];
+            hy += dC[i] * ry[i];
+            hz += dC[i] * rz[i];
+          }
+          W[kt] = dP;
+          ea[h] = E[kt] * gt;
+          wave_sync();
+          put_tile(tile, cc);
+          wave_sync();
+          const f4 ct = get_tile(tile);
+          f4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int s = 0; s < 4; ++s) acc = mfma(rj[s], ct[s], acc);
+          if (q == 0) {
+            const float swk = sm.e.sw[16 * kt + c];
+            float *o = sm.drhw[jb] + 3 * (16 * kt + c);
+            o[0] = swk * acc[0]; o[1] = swk * acc[1]; o[2] = swk * acc[2];
+          }
+        }
+        *reinterpret_cast<bf8 *>(kblock + piece(p)) = pack(ea[0], ea[1]);
+      }
+    rho = sumq(rho);
+    drh[0] += sumq(hx);
+    drh[1] += sumq(hy);
+    drh[2] += sumq(hz);
+    F100 du = {};
+    rows_sum<NB>(du, sm.G, [&](int p) {
+      f4 d[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int kt = 2 * p + h;
+        W[kt] = E[kt] * (W[kt] - rho);
+        d[h] = ldf4(sm.e.sw + 16 * kt + 4 * q) * W[kt];  // dS
+        const f4 s = sum16(W[kt]);
+        if (c == 0) stf4(sm.wsum[jb] + 16 * kt + 4 * q, s);
+      }
+      wb[p] = pack(W[2 * p], W[2 * p + 1]);
+      return pack(d[0], d[1]);
+    }, nb);
+    F100 r = {};
+    wmul(r, wp.Wqk[layer], XB(du));
+#pragma unroll
+    for (int t = 0; t < 7; ++t) go[t] += r[t];
+  }
+  __syncthreads();  // the layer's input is no longer needed
+  if (act) put_block(block, hb);
+  __syncthreads();
+  F100 acc = {};
+  const auto column = [&](int p) { return column8(sm.K + 32 * p * RW, jb); };
+  if (act) rows_sum<NB>(acc, sm.G, column, nb);
+  __syncthreads();
+  if (act) {
+    put_block(block, ub);
+#pragma unroll
+    for (int p = 0; p < NB / 2; ++p)
+      if (2 * p < nb) *reinterpret_cast<bf8 *>(kblock + piece(p)) = wb[p];
+  }
+  __syncthreads();
+  if (act) {
+    rows_sum<NB>(acc, sm.G, column, nb);
+    const float swj = sm.e.sw[j];
+#pragma unroll
+    for (int t = 0; t < 7; ++t) go[t] += swj * acc[t];
+    for (int u = 0; u < nb; ++u) {
+      dsw += sm.wsum[u][j];
+#pragma unroll
+      for (int a = 0; a < 3; ++a) drh[a] += sm.drhw[u][3 * j + a];
+    }
+  }
+  __syncthreads();
+}
+
+template <int NB, int NA>
+__device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB> *smem, const Tables &w, const WeightsB16 &wp,
+                                         const double *__restrict__ X, const int *__restrict__ types, int natoms,
+                                         const int *__restrict__ idx, int c0, const int *__restrict__ nlist,
+                                         const int *__restrict__ nnei, const Grid *__restrict__ grids,
+                                         const int *__restrict__ sys_of, float rc, float rcs, float ln_eps,
+                                         const float *__restrict__ Gsave, const float *__restrict__ fit,
+                                         float4 *__restrict__ gout) {
+  const Part<NB, NA> pt(blk, idx, c0, count, nnei);
+  SmemBwd<NB> &sm = smem[pt.half];
+  const int i = pt.i, n = pt.n, nb = pt.nb, jb = pt.jb, tid = pt.tid;
+  const Grid g = grids[sys_of[i]];
+  const int ti = clamp_type(types[i]);
+  const int l = lane(), q = l >> 4, c = l & 15;
+  const bool act = jb < nb;
+  const float *gs = Gsave + (size_t)i * NATTN * GSAVE_LAYER;
+  build_envf(sm.e, tid, X, types, nlist, i, n, natoms, g, rc, rcs);
+  const float *dTi = fit + (size_t)i * ND;
+  for (int k = tid; k < M * 4; k += 64 * NB) {
+    float v = dTi[FIT_DT + k];
+    if (k < 4 * M2)
+      for (int p = 0; p < FIT_NPART; ++p) v += dTi[FIT_PART + 4 * M2 * p + k];
+    sm.dT[k] = v;
+  }
+  bf16_t *block = sm.G + 16 * jb * RW, *kblock = sm.K + 16 * jb * RW;
+  if (!act) {
+    zero_block(block);
+    zero_block(kblock);
+  }
+  __syncthreads();
+  const int j = 16 * jb + c;
+  F100 go = {};
+  float drh[3] = {0.f, 0.f, 0.f}, dsw = 0.f, dRt[4] = {0.f, 0.f, 0.f, 0.f};
+  if (act) {
+    F100 x, ga, be;
+    // the top layer's input: layer 0's output
+    load_block(x, gs + 1600 * jb);
+    normalise(x, ln_eps);
+    get_table(ga, w.gamma[0]);
+    get_table(be, w.beta[0]);
+#pragma unroll
+    for (int t = 0; t < 7; ++t) x[t] = ga[t] * x[t] + be[t];
+    put_block(block, XB(x));
+    // dG = Rt dT^T / sel for its output, and dRt = G dT / sel
+    load_block(x, gs + GSAVE_LAYER + 1600 * jb);
+    normalise(x, ln_eps);
+    get_table(ga, w.gamma[1]);
+    get_table(be, w.beta[1]);
+    const float inv_sel = 1.f / (float)SEL;
+    const float sj = sm.e.s[j];
+    const float rt1 = sj * sm.e.rh[0][j], rt2 = sj * sm.e.rh[1][j], rt3 = sj * sm.e.rh[2][j];
+    f4 p = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int t = 0; t < 7; ++t)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = 16 * t + 4 * q + r;
-        if (cl < 4 && m < M) tp[m * 4 + cl] = tacc[t][r];
+      for (int k = 0; k < (t < 6 ? 4 : 1); ++k) {
+        const f4 d = ldf4(sm.dT + 4 * (t < 6 ? 16 * t + 4 * q + k : 96 + q));
+        go[t][k] = (sj * d[0] + rt1 * d[1] + rt2 * d[2] + rt3 * d[3]) * inv_sel;
+        p += (ga[t][k] * x[t][k] + be[t][k]) * d;
       }
+#pragma unroll
+    for (int a = 0; a < 4; ++a) dRt[a] = sumq(p[a]) * inv_sel;
   }
   __syncthreads();
-  for (int x = threadIdx.x; x < M * 4; x += NWF * 64) {
-    float acc = 0.f;
-    for (int v = 0; v < nb; ++v) acc += ((float *)sm.stg[v])[x];
-    Tsave[(size_t)i * M * 4 + x] = acc * (1.f / (float)SEL);
+  layer_bwd<NB>(w, wp, 1, sm, go, gs + GSAVE_LAYER, jb, n, nb, ln_eps, drh, dsw);
+  if (act) {
+    S7 h1[1], t2[2], t3[4];
+    embed(w, wp, sm.e.s[j], ti, sm.e.tj[j], h1, t2, t3);
+    // the block's rows of K, free between the layers: features in order, then the row's pieces
+    bf16_t *e = kblock + c * LDE;
+#pragma unroll
+    for (int g4 = 0; g4 < 4; ++g4)
+#pragma unroll
+      for (int r = 0; r < 7; ++r)
+        if (slot_ok(r)) e[25 * g4 + 4 * r + q] = (__bf16)(t3[g4][r] + (t2[g4 & 1][r] + h1[0][r]));
+    wave_sync();
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
+      const bf4 a = *reinterpret_cast<const bf4 *>(e + 32 * p + 4 * q), b = *reinterpret_cast<const bf4 *>(e + 32 * p + 16 + 4 * q);
+      *reinterpret_cast<bf8 *>(block + piece(p)) = bf8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+    }
+    bf8 tail = {};
+    tail[0] = e[96 + q];
+    *reinterpret_cast<bf8 *>(block + piece(3)) = tail;
+  }
+  __syncthreads();
+  layer_bwd<NB>(w, wp, 0, sm, go, gs, jb, n, nb, ln_eps, drh, dsw);
+  // embedding backward and the pair gradients of the wave's tokens
+  if (act) {
+    float *row = reinterpret_cast<float *>(sm.G) + j * LDG;  // over G and K
+    put_row(row, go);
+    S7 h1[1], t2[2], t3[4];
+    embed(w, wp, sm.e.s[j], ti, sm.e.tj[j], h1, t2, t3);
+    wave_sync();
+    S7 dh2[2], d[4];
+#pragma unroll
+    for (int g4 = 0; g4 < 4; ++g4)
+#pragma unroll
+      for (int r = 0; r < 7; ++r) {
+        const float v = slot_ok(r) ? row[25 * g4 + 4 * r + q] : 0.f;
+        d[g4][r] = v;
+        t3[g4][r] = v * (1.f - t3[g4][r] * t3[g4][r]);  // dpre3
+      }
+    emul<4, 2>(dh2, wp.W3, t3);
+#pragma unroll
+    for (int g2 = 0; g2 < 2; ++g2)
+#pragma unroll
+      for (int r = 0; r < 7; ++r) {
+        dh2[g2][r] += d[g2][r] + d[g2 + 2][r];
+        t2[g2][r] = dh2[g2][r] * (1.f - t2[g2][r] * t2[g2][r]);  // dpre2
+      }
+    S7 dh1[1];
+    emul<2, 1>(dh1, wp.W2, t2);
+    float ds = 0.f;
+#pragma unroll
+    for (int r = 0; r < 7; ++r) {
+      const float v = dh1[0][r] + dh2[0][r] + dh2[1][r];
+      if (slot_ok(r)) ds += v * (1.f - h1[0][r] * h1[0][r]) * w.w1s[4 * r + q];
+    }
+    ds = sumq(ds);
+    if (q == 0 && j < SEL) {
+      float4 out = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (j < n) {
+        const float h[3] = {sm.e.rh[0][j], sm.e.rh[1][j], sm.e.rh[2][j]};
+        out = pair_gradient(sm.e.s[j], sm.e.sw[j], sm.e.r[j], h, ds, dRt, drh, dsw, rc, rcs);
+      }
+      gout[(size_t)i * SEL + j] = out;
+    }
+  }
+  for (int k = nb ? 16 * nb + tid : SEL; k < SEL; k += 64 * NB) gout[(size_t)i * SEL + k] = make_float4(0.f, 0.f, 0.f, 0.f);
+}
+
+template <int NB, int NA>
+__global__ void __launch_bounds__(64 * NB * NA) __attribute__((amdgpu_waves_per_eu(NB == NB_SMALL ? 3 : 2)))
+k_desc_bwd_b16(Tables w, WeightsB16 wp, const double *__restrict__ X, const int *__restrict__ types, int natoms,
+               const int *__restrict__ idx, const int *__restrict__ cnt, int c0, int ncen, const int *__restrict__ nlist,
+               const int *__restrict__ nnei, const Grid *__restrict__ grids, const int *__restrict__ sys_of, float rc, float rcs,
+               float ln_eps, const float *__restrict__ Gsave, const float *__restrict__ fit, float4 *__restrict__ gout) {
+  __shared__ SmemBwd<NB> smem[NA];
+  const int count = idx ? *cnt : ncen;
+  for (int b = blockIdx.x; b * NA < count; b += gridDim.x) {
+    desc_bwd<NB, NA>(b, count, smem, w, wp, X, types, natoms, idx, c0, nlist, nnei, grids, sys_of, rc, rcs, ln_eps, Gsave, fit, gout);
+    if (NB == NB_SMALL) break;
+    __syncthreads();
   }
 }
 
 }  // namespace
 
-void launch_descriptor_fwd_b16(const Tables &w, const WeightsB16 &wp, const Workspace &ws,
-                               const double *coords, const int *types, int n, int c0, int c1,
-                               float rc, float rcs, float ln_eps, hipStream_t st) {
-  hipLaunchKernelGGL(k_desc_fwd_b16, dim3(c1 - c0), dim3(NWF * 64), 0, st, w, wp, coords, types, n, c0, ws.nlist, ws.nnei, ws.grids,
-                     ws.sys_of, rc, rcs, ln_eps, ws.Gsave, ws.Tsave, ws.bidx, ws.bcnt, (int)ws.cap);
+void launch_descriptor_fwd_b16(const Tables &w, const WeightsB16 &wp, const Workspace &ws, const double *coords,
+                               const int *types, int n, int c0, int c1, float rc, float rcs, float ln_eps, hipStream_t st) {
+  launch_class_lists(ws, n, c0, c1, st);
+  launch_instances(ws, n, c1 - c0, k_desc_fwd_b16<NB_SMALL, 2>, k_desc_fwd_b16<8, 1>, st,
+                   [&](auto kernel, int groups, int threads, const int *idx, const int *cnt, hipStream_t s) {
+    hipLaunchKernelGGL(kernel, dim3(groups), dim3(threads), 0, s, w, wp, coords, types, n, idx, cnt, c0, c1 - c0, ws.nlist,
+                       ws.nnei, ws.grids, ws.sys_of, rc, rcs, ln_eps, ws.Gsave, ws.Tsave);
+  });
+}
+
+void launch_descriptor_bwd_b16(const Tables &w, const WeightsB16 &wp, const Workspace &ws, const double *coords,
+                               const int *types, int n, int c0, int c1, float rc, float rcs, float ln_eps, hipStream_t st) {
+  launch_instances(ws, n, c1 - c0, k_desc_bwd_b16<NB_SMALL, 2>, k_desc_bwd_b16<8, 1>, st,
+                   [&](auto kernel, int groups, int threads, const int *idx, const int *cnt, hipStream_t s) {
+    hipLaunchKernelGGL(kernel, dim3(groups), dim3(threads), 0, s, w, wp, coords, types, n, idx, cnt, c0, c1 - c0, ws.nlist,
+                       ws.nnei, ws.grids, ws.sys_of, rc, rcs, ln_eps, ws.Gsave, ws.fit, ws.g);
+  });
 }
 
 }  // namespace dp

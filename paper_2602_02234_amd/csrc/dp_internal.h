@@ -82,18 +82,15 @@ template <typename T> struct Weights : Tables {
   const T *F3[MAXH];
 };
 
-// Extra device weights of the bfloat16 path: GEMM operands zero-padded to MFMA
-// tile multiples and stored [output column][k] (k contiguous, 16-byte rows), so
-// every MFMA fragment is one 16-byte load.  Feature width 100 is padded to 112,
-// embedding widths 25/50 to 32/64, the fitting width 240 to 256 along k.  The
-// fitting operands come as a two-term split w = hi + lo (both bf16).
+// Extra device weights of the bfloat16 path: the products' operands in MFMA fragment order,
+// named by the matrix whose rows are the outputs (the orders: descriptor_bf16.hip, fitting.hip),
+// the fitting width 240 padded to 256 along k.
 struct WeightsB16 {
-  const bf16_t *W2T;           // [64][32]    W2T[c][k] = W2[k][c]
-  const bf16_t *W3T;           // [112][64]   W3T[m][k] = W3[k][m]
-  const bf16_t *W3;            // [64][112]   W3[c][m]
-  const bf16_t *W2;            // [32][64]    W2[e1][e2]
-  // attention weights, [112][112] each, in MFMA fragment order (see mm_g)
-  const bf16_t *WqkT[NATTN];   // WqkT[c][k] = Wqk[k][c]
+  const bf16_t *W2T;           // [E2][E1], groups of 25
+  const bf16_t *W3T;           // [M][E2]
+  const bf16_t *W3;            // [E2][M]
+  const bf16_t *W2;            // [E1][E2]
+  const bf16_t *WqkT[NATTN];   // [M][M]
   const bf16_t *Wqk[NATTN];
   const bf16_t *WvoT[NATTN];
   const bf16_t *Wvo[NATTN];

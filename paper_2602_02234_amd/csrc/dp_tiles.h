@@ -110,6 +110,20 @@ __device__ __forceinline__ void tiles(const T *__restrict__ p, const f4 (&x)[NK]
   }
 }
 
+// 16 x 16 tile in LDS, element (token, key) swizzled so that neither access has a bank conflict:
+// put writes a lane's four keys of its token, get reads token 4 q + s of key c.
+__device__ __forceinline__ void put_tile(float *tile, f4 y) {
+  const int q = lane() >> 4, c = lane() & 15, h = c >> 2;
+  stf4(tile + 16 * (4 * h + ((c & 3) ^ h)) + 4 * (q ^ h), y);
+}
+__device__ __forceinline__ f4 get_tile(const float *tile) {
+  const int q = lane() >> 4, c = lane() & 15;
+  f4 o;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) o[s] = tile[16 * (4 * q + (s ^ q)) + (c ^ (4 * q))];
+  return o;
+}
+
 // tanh of the layers' hot loops, from the hardware exponential and reciprocal:
 // tanh x = 1 - 2 / (1 + exp(2 x)); absolute error about 1e-7, the float32 rounding of the
 // sums it enters.

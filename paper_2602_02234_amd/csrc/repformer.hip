@@ -249,20 +249,6 @@ __device__ __forceinline__ void transpose_block(f4 (&o)[2], const f4 (&x)[2], fl
     for (int s = 0; s < 4; ++s) o[t][s] = scr[(4 * q + s) * LK + 16 * t + c];
   wave_sync();
 }
-// 16 x 16 tile in LDS, element (token, key) swizzled so that neither access has a bank conflict:
-// put writes a lane's four keys of its token, get reads token 4 q + s of key c.
-__device__ __forceinline__ void put_tile(float *tile, f4 y) {
-  const int q = lane() >> 4, c = lane() & 15, h = c >> 2;
-  stf4(tile + 16 * (4 * h + ((c & 3) ^ h)) + 4 * (q ^ h), y);
-}
-__device__ __forceinline__ f4 get_tile(const float *tile) {
-  const int q = lane() >> 4, c = lane() & 15;
-  f4 o;
-#pragma unroll
-  for (int s = 0; s < 4; ++s) o[s] = tile[16 * (4 * q + (s ^ q)) + (c ^ (4 * q))];
-  return o;
-}
-
 // The node update's W1 (224 x 64) in the registers of a workgroup of NW waves, a quarter-wave to a
 // row: row 4 (wave + NW r) + q, columns 4 c ..  One load serves every atom of the workgroup,
 // and W1 x and W1^T dz alike.
