@@ -62,28 +62,33 @@ struct XB {
     v[3] = pack(f4{x[6][0], 0.f, 0.f, 0.f}, f4{0.f, 0.f, 0.f, 0.f});
   }
 };
-// Piece 4 p + q of row 16 b + c, b the base: where the lane's eight values of step p are.
-__device__ __forceinline__ int piece(int p) {
-  const int q = lane() >> 4, c = lane() & 15;
-  return c * RW + 8 * (4 * (p ^ (c & 3)) + (q ^ (c >> 2)));
+// Offset in a block (16 rows) of piece 4 p + q of row c: the lane's eight values of step p.  The row's
+// low bits are exchanged in, so step p differs from step 0 in the bits of 32 p alone.
+__device__ __forceinline__ int piece0() {
+  const int l = lane(), q = l >> 4, c = l & 15;
+  return c * RW + 8 * (4 * (c & 3) + (q ^ (c >> 2)));
 }
+__device__ __forceinline__ int piece(int p0, int p) { return p0 ^ (32 * p); }
 __device__ __forceinline__ void put_block(bf16_t *block, const XB &x) {
+  const int p0 = piece0();
 #pragma unroll
-  for (int p = 0; p < 4; ++p) *reinterpret_cast<bf8 *>(block + piece(p)) = x.v[p];
+  for (int p = 0; p < 4; ++p) *reinterpret_cast<bf8 *>(block + piece(p0, p)) = x.v[p];
 }
-// Values of column 16 t + c in rows 4 q .. 4 q + 3 of a block (t = 6: feature 96 + c / 4 for c a
-// multiple of 4).
-__device__ __forceinline__ s4 column4(const bf16_t *block, int t) {
-  const int q = lane() >> 4, c = lane() & 15, r = c >> 2;
-  const bf16_t *p = block + (4 * q + r) * RW + 8 * (4 * ((t >> 1) ^ r) + ((c & 3) ^ q)) + 4 * (t & 1);
+// Where the lane reads the values of column 16 t + c in rows 4 q .. 4 q + 3 of a block (t = 6: feature
+// 96 + c / 4 for c a multiple of 4): for t = 0 and, by the bits of t / 2, for the others.
+__device__ __forceinline__ int column0() {
+  const int l = lane(), q = l >> 4, c = l & 15, r = c >> 2;
+  return (4 * q + r) * RW + 8 * (4 * r + ((c & 3) ^ q));
+}
+__device__ __forceinline__ s4 read_tr(const bf16_t *p) {
   return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s4 *)p);
 }
-// ... of two consecutive blocks: the eight k of a contraction over 32 rows.
-__device__ __forceinline__ bf8 column8(const bf16_t *block, int t) {
-  const s4 a = column4(block, t), b = column4(block + 16 * RW, t);
+// ... of two consecutive blocks, cu = (column0 ^ 32 (t / 2)) + 4 (t & 1): the eight k of a
+// contraction over 32 rows.
+__device__ __forceinline__ bf8 column8(const bf16_t *block, int cu) {
   typedef short s8 __attribute__((ext_vector_type(8)));
-  const s8 v = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-  return __builtin_bit_cast(bf8, v);
+  const s4 a = read_tr(block + cu), b = read_tr(block + 16 * RW + cu);
+  return __builtin_bit_cast(bf8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
 // acc += W x for a 100 x 100 matrix in fragment order: step p < 3 of tile t at (7 p + t) 512 + 8 lane,
@@ -111,6 +116,7 @@ __device__ __forceinline__ void wmul(F100 &acc, const bf16_t *__restrict__ w, co
     tile_barrier();
 #pragma unroll
     for (int t = 0; t < 7; ++t) acc[t] = mma(a[t], x.v[k], acc[t]);
+    tile_barrier();
     if (k < 3)
 #pragma unroll
       for (int t = 0; t < 7; ++t) a[t] = b[t];
@@ -122,10 +128,11 @@ template <int NB>
 __device__ __forceinline__ void keys_dot(f4 (&s)[NB], const bf16_t *G, const XB &x, int nb) {
 #pragma unroll
   for (int kt = 0; kt < NB; ++kt) s[kt] = f4{0.f, 0.f, 0.f, 0.f};
+  const int p0 = piece0();
 #pragma unroll
   for (int p = 0; p < 4; ++p) {
     tile_barrier();
-    const bf16_t *g = G + piece(p);
+    const bf16_t *g = G + piece(p0, p);
 #pragma unroll
     for (int kt = 0; kt < NB; ++kt)
       if (kt < NB_SMALL - 2 || kt < nb) s[kt] = mma(ld8(g + 16 * kt * RW), x.v[p], s[kt]);
@@ -136,13 +143,14 @@ __device__ __forceinline__ void keys_dot(f4 (&s)[NB], const bf16_t *G, const XB 
 // 2 p < nb.  Rows of a block past nb are zero.
 template <int NB, class Y>
 __device__ __forceinline__ void rows_sum(F100 &acc, const bf16_t *R, const Y &y, int nb) {
+  const int cu = column0();
 #pragma unroll
   for (int p = 0; p < NB / 2; ++p)
     if (2 * p < nb) {
       const bf8 v = y(p);
       bf8 a[7];
 #pragma unroll
-      for (int t = 0; t < 7; ++t) a[t] = column8(R + 32 * p * RW, t);
+      for (int t = 0; t < 7; ++t) a[t] = column8(R + 32 * p * RW, (cu ^ (32 * (t >> 1))) + 4 * (t & 1));
 #pragma unroll
       for (int t = 0; t < 7; ++t) acc[t] = mma(a[t], v, acc[t]);
       tile_barrier();
@@ -155,6 +163,7 @@ __device__ __forceinline__ void rows_sum(F100 &acc, const bf16_t *R, const Y &y,
 template <int NI, int NO>
 __device__ __forceinline__ void emul(S7 (&out)[NO], const bf16_t *__restrict__ w, const S7 (&in)[NI]) {
   bf8 x[NI];
+  const bf16_t *wl = w + 8 * lane();
 #pragma unroll
   for (int ig = 0; ig < NI; ++ig)
     x[ig] = pack(f4{in[ig][0], in[ig][1], in[ig][2], in[ig][3]}, f4{in[ig][4], in[ig][5], in[ig][6], 0.f});
@@ -164,18 +173,45 @@ __device__ __forceinline__ void emul(S7 (&out)[NO], const bf16_t *__restrict__ w
     for (int u = 0; u < 2; ++u) {
       f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int ig = 0; ig < NI; ++ig) acc = mma(ld8(w + ((og * 2 + u) * NI + ig) * 512 + 8 * lane()), x[ig], acc);
+      for (int ig = 0; ig < NI; ++ig) acc = mma(ld8(wl + ((og * 2 + u) * NI + ig) * 512), x[ig], acc);
 #pragma unroll
       for (int i = 0; i < 4; ++i)
         if (4 * u + i < 7) out[og][4 * u + i] = acc[i];
     }
 }
 
-// h1, t2 = h2 - [h1, h1] and t3 = G - [h2, h2] of the lane's token.
-__device__ __forceinline__ void embed(const Tables &w, const WeightsB16 &wp, float s, int ti, int tj, S7 (&h1)[1],
-                                      S7 (&t2)[2], S7 (&t3)[4]) {
+// The small tables of one atom in LDS, where a read is a short wait and needs no address of its own.
+struct Tab {
+  float gamma[NATTN][M] __attribute__((aligned(16)));
+  float beta[NATTN][M] __attribute__((aligned(16)));
+  float b3[M], b2[E2], w1s[E1], Bt[NTYPES * E1];  // Bt: the centre's type
+};
+// Tile t of a per-feature table, in a token's arrangement.
+__device__ __forceinline__ f4 tab4(const float *p, int t) {
   const int q = lane() >> 4;
-  const float *bt = w.Bt + (ti * NTYPES + tj) * E1;
+  return t < 6 ? ldf4(p + 16 * t + 4 * q) : f4{p[96 + q], 0.f, 0.f, 0.f};
+}
+__device__ __forceinline__ void load_tab(Tab &t, const Tables &w, int ti, int tid, int nthr) {
+  for (int k = tid; k < NTYPES * E1; k += nthr) {
+    t.Bt[k] = w.Bt[ti * NTYPES * E1 + k];
+    if (k < M) {
+#pragma unroll
+      for (int a = 0; a < NATTN; ++a) {
+        t.gamma[a][k] = w.gamma[a][k];
+        t.beta[a][k] = w.beta[a][k];
+      }
+      t.b3[k] = w.b3[k];
+    }
+    if (k < E2) t.b2[k] = w.b2[k];
+    if (k < E1) t.w1s[k] = w.w1s[k];
+  }
+}
+
+// h1, t2 = h2 - [h1, h1] and t3 = G - [h2, h2] of the lane's token.
+__device__ __forceinline__ void embed(const Tab &w, const WeightsB16 &wp, float s, int tj, S7 (&h1)[1], S7 (&t2)[2],
+                                      S7 (&t3)[4]) {
+  const int q = lane() >> 4;
+  const float *bt = w.Bt + tj * E1;
 #pragma unroll
   for (int r = 0; r < 7; ++r) {
     const int f = slot_ok(r) ? 4 * r + q : 0;
@@ -210,11 +246,18 @@ template <int NB> struct SmemFwd {
   float row[16 * NB * LDG] __attribute__((aligned(16)));  // ... in float32, each wave its own
   float part[NB][M * 4] __attribute__((aligned(16)));
   EnvF<NB> e;
+  Tab tab;
 };
 
 __device__ __forceinline__ void zero_block(bf16_t *block) {
 #pragma unroll
-  for (int p = 0; p < 4; ++p) *reinterpret_cast<bf8 *>(block + piece(p)) = bf8{};
+  for (int p = 0; p < 4; ++p) *reinterpret_cast<bf8 *>(block + piece(piece0(), p)) = bf8{};
+}
+
+// The barriers of the other waves' work, for a wave without tokens.  Such waves take a path of their
+// own, so that no register of the work is carried past a branch around it.
+__device__ __forceinline__ void pass_barriers(int n) {
+  for (int k = 0; k < n; ++k) __syncthreads();
 }
 
 template <int NB, int NA>
@@ -228,32 +271,33 @@ __device__ __forceinline__ void desc_fwd(int blk, int count, SmemFwd<NB> *smem, 
   SmemFwd<NB> &sm = smem[pt.half];
   const int i = pt.i, n = pt.n, nb = pt.nb, jb = pt.jb, tid = pt.tid;
   const Grid g = grids[sys_of[i]];
-  const int ti = clamp_type(types[i]);
   const int l = lane(), q = l >> 4, c = l & 15;
   const bool act = jb < nb;
+  load_tab(sm.tab, w, clamp_type(types[i]), tid, 64 * NB);
   build_envf(sm.e, tid, X, types, nlist, i, n, natoms, g, rc, rcs);
   __syncthreads();
   const int j = 16 * jb + c;  // the lane's token
   float *row = sm.row + j * LDG;
   bf16_t *block = sm.G + 16 * jb * RW;
-  XB xb;
-  if (act) {
-    S7 h1[1], t2[2], t3[4];
-    embed(w, wp, sm.e.s[j], ti, sm.e.tj[j], h1, t2, t3);
-    put_embedding(row, h1, t2, t3);
-    wave_sync();
-    F100 x;
-    get_row(x, row);
-    xb = XB(x);
-    put_block(block, xb);
-  } else {
+  if (!act) {
     zero_block(block);
-  }
-  __syncthreads();
-  const float hj[3] = {sm.e.rh[0][j], sm.e.rh[1][j], sm.e.rh[2][j]};
+    pass_barriers(3);
+  } else {
+    XB xb;
+    {
+      S7 h1[1], t2[2], t3[4];
+      embed(sm.tab, wp, sm.e.s[j], sm.e.tj[j], h1, t2, t3);
+      put_embedding(row, h1, t2, t3);
+      wave_sync();
+      F100 x;
+      get_row(x, row);
+      xb = XB(x);
+      put_block(block, xb);
+    }
+    __syncthreads();
+    const float hj[3] = {sm.e.rh[0][j], sm.e.rh[1][j], sm.e.rh[2][j]};
 #pragma unroll 1
-  for (int layer = 0; layer < NATTN; ++layer) {
-    if (act) {
+    for (int layer = 0; layer < NATTN; ++layer) {
       f4 s[NB];
       {
         F100 u = {};
@@ -278,39 +322,36 @@ __device__ __forceinline__ void desc_fwd(int blk, int count, SmemFwd<NB> *smem, 
       for (int t = 0; t < 7; ++t) y[t] -= mu;
       save_block(Gsave + ((size_t)i * NATTN + layer) * GSAVE_LAYER + 1600 * jb, y);
       normalise(y, ln_eps);
-      F100 ga, be;
-      get_table(ga, w.gamma[layer]);
-      get_table(be, w.beta[layer]);
 #pragma unroll
-      for (int t = 0; t < 7; ++t) y[t] = ga[t] * y[t] + be[t];
+      for (int t = 0; t < 7; ++t) y[t] = tab4(sm.tab.gamma[layer], t) * y[t] + tab4(sm.tab.beta[layer], t);
       put_row(row, y);
       xb = XB(y);
+      if (layer == NATTN - 1) break;
+      __syncthreads();  // every wave is done with the layer's input
+      put_block(block, xb);
+      __syncthreads();
     }
-    if (layer == NATTN - 1) break;
-    __syncthreads();  // every wave is done with the layer's input
-    if (act) put_block(block, xb);
-    __syncthreads();
-  }
-  // T = G^T Rt / sel: each wave's 16 tokens on float32 MFMA (T^T = Rt^T G, rows c < 4 of the 16
-  // used, step s taking token 4 s + q), then the waves' parts in order
-  if (act) {
-    wave_sync();
-    f4 acc[7];
+    // T = G^T Rt / sel: each wave's 16 tokens on float32 MFMA (T^T = Rt^T G, rows c < 4 of the 16
+    // used, step s taking token 4 s + q), then the waves' parts in order
+    {
+      wave_sync();
+      f4 acc[7];
 #pragma unroll
-    for (int t = 0; t < 7; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
+      for (int t = 0; t < 7; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int k = 16 * jb + 4 * s + q;
-      const float sk = sm.e.s[k];
-      const float rt = c == 0 ? sk : (c < 4 ? sk * sm.e.rh[c - 1][k] : 0.f);
-      const float *gk = sm.row + k * LDG;
+      for (int s = 0; s < 4; ++s) {
+        const int k = 16 * jb + 4 * s + q;
+        const float sk = sm.e.s[k];
+        const float rt = c == 0 ? sk : (c < 4 ? sk * sm.e.rh[c - 1][k] : 0.f);
+        const float *gk = sm.row + k * LDG;
 #pragma unroll
-      for (int t = 0; t < 7; ++t) acc[t] = mfma(rt, gk[t < 6 ? 16 * t + c : 96 + (c & 3)], acc[t]);
+        for (int t = 0; t < 7; ++t) acc[t] = mfma(rt, gk[t < 6 ? 16 * t + c : 96 + (c & 3)], acc[t]);
+      }
+      if (q == 0)
+#pragma unroll
+        for (int t = 0; t < 7; ++t)
+          if (t < 6 || c < 4) stf4(sm.part[jb] + 4 * (16 * t + c), acc[t]);
     }
-    if (q == 0)
-#pragma unroll
-      for (int t = 0; t < 7; ++t)
-        if (t < 6 || c < 4) stf4(sm.part[jb] + 4 * (16 * t + c), acc[t]);
   }
   __syncthreads();
   for (int k = tid; k < (nb ? M * 4 : 0); k += 64 * NB) {
@@ -346,146 +387,138 @@ template <int NB> struct SmemBwd {
   float wsum[NB][16 * NB] __attribute__((aligned(16)));    // ... of W
   float dT[M * 4] __attribute__((aligned(16)));
   EnvF<NB> e;
+  Tab tab;
 };
 static_assert(sizeof(SmemBwd<8>::G) * 2 >= sizeof(float) * 16 * 8 * LDG, "float32 rows of every token fit over G and K");
 
-// Backward of one layer, its input rows in sm.G.  go: in, the gradient of the layer's output
-// for the wave's tokens, out, of its input; d: the layer's saved centred rows.  drh and dsw, the
-// gradients of the token's rhat and sw, are added to.  Ends after a barrier; the block's rows
-// in sm.G are then free.
-//   Row part (per token j): U, S, E recomputed; dX through the LayerNorm, dH = Wvo dX,
-//   dA = G dH, then per key P = sw E, dP = dA gate, rho = sum P dP, W = E (dP - rho),
-//   dS = sw W, dU = G^T dS, and dG_j = dX + Wqk dU.
+// LayerNorm backward in place: dX = (dxh - mean(dxh) - xh mean(dxh xh)) / sigma, dxh = gamma dG_out.
+__device__ __forceinline__ void norm_bwd(F100 &go, const F100 &xh, float is, const float *gamma) {
+#pragma unroll
+  for (int t = 0; t < 7; ++t) go[t] = tab4(gamma, t) * go[t];
+  const float s0 = sum100([&](int t, int k) { return go[t][k]; }) * (1.f / M);
+  const float s1 = sum100([&](int t, int k) { return go[t][k] * xh[t][k]; }) * (1.f / M);
+#pragma unroll
+  for (int t = 0; t < 7; ++t) go[t] = (go[t] - s0 - xh[t] * s1) * is;
+}
+
+// Backward of one layer, its input rows in sm.G.  go: in, the gradient of the LayerNorm's input
+// (dX) for the wave's tokens, out, of the layer's input.  drh and dsw, the gradients of the
+// token's rhat and sw, are added to.  Ends after a barrier; sm.G and sm.K are then free.
+//   Row part (per token j): dH = Wvo dX; U, S, E recomputed; dA = G dH, then per key P = sw E,
+//   dP = dA gate, rho = sum P dP, W = E (dP - rho), dS = sw W, dU = G^T dS, and dG_j = dX + Wqk dU.
+//   (dH comes first: beside E the products' operands would not fit the registers.)
 //   Column part (per key k): dG_k += sw_k sum_j (E gate)_jk dH_j + W_jk U_j, dsw_k += sum_j W_jk.
 template <int NB>
-__device__ __forceinline__ void layer_bwd(const Tables &w, const WeightsB16 &wp, int layer, SmemBwd<NB> &sm, F100 &go,
-                                          const float *__restrict__ saved, int jb, int n, int nb, float ln_eps,
+__device__ __forceinline__ void layer_bwd(const WeightsB16 &wp, int layer, SmemBwd<NB> &sm, F100 &go, int jb, int n, int nb,
                                           float (&drh)[3], float &dsw) {
   const int l = lane(), q = l >> 4, c = l & 15;
   const int j = 16 * jb + c;
   bf16_t *block = sm.G + 16 * jb * RW, *kblock = sm.K + 16 * jb * RW;
-  const bool act = jb < nb;
   XB ub, hb;
+  const int p0 = piece0();
   bf8 wb[NB / 2];
   const float hj[3] = {sm.e.rh[0][j], sm.e.rh[1][j], sm.e.rh[2][j]};
-  if (act) {
-    f4 E[NB], W[NB];
-    {
-      F100 u = {};
+  {
+    F100 dh = {};
+    wmul(dh, wp.Wvo[layer], XB(go));
+    hb = XB(dh);
+  }
+  {
+    F100 u = {};
 #pragma unroll
-      for (int p = 0; p < 4; ++p) ub.v[p] = ld8(block + piece(p));
-      wmul(u, wp.WqkT[layer], ub);
-      ub = XB(u);
-    }
-    keys_dot<NB>(E, sm.G, ub, nb);
-    softmax_keys<NB>(E, sm.e, n, [](float v) { return __expf(v); });
-    {  // LayerNorm backward: dX = (dxh - mean(dxh) - xh mean(dxh xh)) / sigma, dxh = gamma dG_out
-      F100 xh, ga;
-      load_block(xh, saved + 1600 * jb);
-      const float is = normalise(xh, ln_eps);
-      get_table(ga, w.gamma[layer]);
+    for (int p = 0; p < 4; ++p) ub.v[p] = ld8(block + piece(p0, p));
+    wmul(u, wp.WqkT[layer], ub);
+    ub = XB(u);
+  }
+  f4 E[NB], W[NB];
+  keys_dot<NB>(E, sm.G, ub, nb);
+  softmax_keys<NB>(E, sm.e, n, [](float v) { return __expf(v); });
+  keys_dot<NB>(W, sm.G, hb, nb);  // dA
+  float rho = 0.f, hx = 0.f, hy = 0.f, hz = 0.f;
+  // columns of dC rhat: sum_j rhat_j (dA E)_jk, A operand rhat of token 4 q + s in rows a < 3
+  float rj[4];
 #pragma unroll
-      for (int t = 0; t < 7; ++t) go[t] = ga[t] * go[t];
-      const float s0 = sum100([&](int t, int k) { return go[t][k]; }) * (1.f / M);
-      const float s1 = sum100([&](int t, int k) { return go[t][k] * xh[t][k]; }) * (1.f / M);
+  for (int s = 0; s < 4; ++s) rj[s] = c < 3 ? sm.e.rh[c][16 * jb + 4 * q + s] : 0.f;
+  float *tile = sm.tile[jb];
 #pragma unroll
-      for (int t = 0; t < 7; ++t) go[t] = (go[t] - s0 - xh[t] * s1) * is;
-    }
-    {
-      F100 dh = {};
-      wmul(dh, wp.Wvo[layer], XB(go));
-      hb = XB(dh);
-    }
-    keys_dot<NB>(W, sm.G, hb, nb);  // dA
-    float rho = 0.f, hx = 0.f, hy = 0.f, hz = 0.f;
-    // columns of dC rhat: sum_j rhat_j (dA E)_jk, A operand rhat of token 4 q + s in rows a < 3
-    float rj[4];
-#pragma unroll
-    for (int s = 0; s < 4; ++s) rj[s] = c < 3 ? sm.e.rh[c][16 * jb + 4 * q + s] : 0.f;
-    float *tile = sm.tile[jb];
-#pragma unroll
-    for (int p = 0; p < NB / 2; ++p)
-      if (2 * p < nb) {
-        f4 ea[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          tile_barrier();
-          const int kt = 2 * p + h, k = 16 * kt + 4 * q;
-          const f4 sw = ldf4(sm.e.sw + k), rx = ldf4(sm.e.rh[0] + k), ry = ldf4(sm.e.rh[1] + k), rz = ldf4(sm.e.rh[2] + k);
-          const f4 gt = rx * hj[0] + ry * hj[1] + rz * hj[2];
-          const f4 cc = W[kt] * E[kt];
-          const f4 dC = sw * cc, dP = W[kt] * gt, pr = sw * E[kt] * dP;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            rho += pr[i];
-            hx += dC[i] * rx[i];
-            hy += dC[i] * ry[i];
-            hz += dC[i] * rz[i];
-          }
-          W[kt] = dP;
-          ea[h] = E[kt] * gt;
-          wave_sync();
-          put_tile(tile, cc);
-          wave_sync();
-          const f4 ct = get_tile(tile);
-          f4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int s = 0; s < 4; ++s) acc = mfma(rj[s], ct[s], acc);
-          if (q == 0) {
-            const float swk = sm.e.sw[16 * kt + c];
-            float *o = sm.drhw[jb] + 3 * (16 * kt + c);
-            o[0] = swk * acc[0]; o[1] = swk * acc[1]; o[2] = swk * acc[2];
-          }
-        }
-        *reinterpret_cast<bf8 *>(kblock + piece(p)) = pack(ea[0], ea[1]);
-      }
-    rho = sumq(rho);
-    drh[0] += sumq(hx);
-    drh[1] += sumq(hy);
-    drh[2] += sumq(hz);
-    F100 du = {};
-    rows_sum<NB>(du, sm.G, [&](int p) {
-      f4 d[2];
+  for (int p = 0; p < NB / 2; ++p)
+    if (2 * p < nb) {
+      f4 ea[2];
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const int kt = 2 * p + h;
-        W[kt] = E[kt] * (W[kt] - rho);
-        d[h] = ldf4(sm.e.sw + 16 * kt + 4 * q) * W[kt];  // dS
-        const f4 s = sum16(W[kt]);
-        if (c == 0) stf4(sm.wsum[jb] + 16 * kt + 4 * q, s);
-      }
-      wb[p] = pack(W[2 * p], W[2 * p + 1]);
-      return pack(d[0], d[1]);
-    }, nb);
-    F100 r = {};
-    wmul(r, wp.Wqk[layer], XB(du));
+        tile_barrier();
+        const int kt = 2 * p + h, k = 16 * kt + 4 * q;
+        const f4 sw = ldf4(sm.e.sw + k), rx = ldf4(sm.e.rh[0] + k), ry = ldf4(sm.e.rh[1] + k), rz = ldf4(sm.e.rh[2] + k);
+        const f4 gt = rx * hj[0] + ry * hj[1] + rz * hj[2];
+        const f4 cc = W[kt] * E[kt];
+        const f4 dC = sw * cc, dP = W[kt] * gt, pr = sw * E[kt] * dP;
 #pragma unroll
-    for (int t = 0; t < 7; ++t) go[t] += r[t];
+        for (int i = 0; i < 4; ++i) {
+          rho += pr[i];
+          hx += dC[i] * rx[i];
+          hy += dC[i] * ry[i];
+          hz += dC[i] * rz[i];
+        }
+        W[kt] = dP;
+        ea[h] = E[kt] * gt;
+        wave_sync();
+        put_tile(tile, cc);
+        wave_sync();
+        const f4 ct = get_tile(tile);
+        f4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < 4; ++s) acc = mfma(rj[s], ct[s], acc);
+        if (q == 0) {
+          const float swk = sm.e.sw[16 * kt + c];
+          float *o = sm.drhw[jb] + 3 * (16 * kt + c);
+          o[0] = swk * acc[0]; o[1] = swk * acc[1]; o[2] = swk * acc[2];
+        }
+      }
+      *reinterpret_cast<bf8 *>(kblock + piece(p0, p)) = pack(ea[0], ea[1]);
+    }
+  rho = sumq(rho);
+  drh[0] += sumq(hx);
+  drh[1] += sumq(hy);
+  drh[2] += sumq(hz);
+  bf8 ds[NB / 2];  // dS
+#pragma unroll
+  for (int p = 0; p < NB / 2; ++p) {
+    f4 d[2], v[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int kt = 2 * p + h;
+      v[h] = E[kt] * (W[kt] - rho);
+      d[h] = ldf4(sm.e.sw + 16 * kt + 4 * q) * v[h];
+      const f4 s = sum16(v[h]);
+      if (c == 0) stf4(sm.wsum[jb] + 16 * kt + 4 * q, s);
+    }
+    wb[p] = pack(v[0], v[1]);
+    ds[p] = pack(d[0], d[1]);
   }
+  F100 du = {};
+  rows_sum<NB>(du, sm.G, [&](int p) { return ds[p]; }, nb);
+  wmul(go, wp.Wqk[layer], XB(du));
   __syncthreads();  // the layer's input is no longer needed
-  if (act) put_block(block, hb);
+  put_block(block, hb);
   __syncthreads();
   F100 acc = {};
-  const auto column = [&](int p) { return column8(sm.K + 32 * p * RW, jb); };
-  if (act) rows_sum<NB>(acc, sm.G, column, nb);
+  const int cj = (column0() ^ (32 * (jb >> 1))) + 4 * (jb & 1);
+  const auto column = [&](int p) { return column8(sm.K + 32 * p * RW, cj); };
+  rows_sum<NB>(acc, sm.G, column, nb);
   __syncthreads();
-  if (act) {
-    put_block(block, ub);
+  put_block(block, ub);
 #pragma unroll
-    for (int p = 0; p < NB / 2; ++p)
-      if (2 * p < nb) *reinterpret_cast<bf8 *>(kblock + piece(p)) = wb[p];
-  }
+  for (int p = 0; p < NB / 2; ++p)
+    if (2 * p < nb) *reinterpret_cast<bf8 *>(kblock + piece(p0, p)) = wb[p];
   __syncthreads();
-  if (act) {
-    rows_sum<NB>(acc, sm.G, column, nb);
-    const float swj = sm.e.sw[j];
+  rows_sum<NB>(acc, sm.G, column, nb);
+  const float swj = sm.e.sw[j];
 #pragma unroll
-    for (int t = 0; t < 7; ++t) go[t] += swj * acc[t];
-    for (int u = 0; u < nb; ++u) {
-      dsw += sm.wsum[u][j];
+  for (int t = 0; t < 7; ++t) go[t] += swj * acc[t];
+  for (int u = 0; u < nb; ++u) {
+    dsw += sm.wsum[u][j];
 #pragma unroll
-      for (int a = 0; a < 3; ++a) drh[a] += sm.drhw[u][3 * j + a];
-    }
+    for (int a = 0; a < 3; ++a) drh[a] += sm.drhw[u][3 * j + a];
   }
   __syncthreads();
 }
@@ -502,10 +535,11 @@ __device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB> *smem, 
   SmemBwd<NB> &sm = smem[pt.half];
   const int i = pt.i, n = pt.n, nb = pt.nb, jb = pt.jb, tid = pt.tid;
   const Grid g = grids[sys_of[i]];
-  const int ti = clamp_type(types[i]);
   const int l = lane(), q = l >> 4, c = l & 15;
   const bool act = jb < nb;
-  const float *gs = Gsave + (size_t)i * NATTN * GSAVE_LAYER;
+  const float *gs = Gsave + (size_t)i * NATTN * GSAVE_LAYER + 1600 * jb;
+  for (int k = nb ? 16 * nb + tid : SEL; k < SEL; k += 64 * NB) gout[(size_t)i * SEL + k] = make_float4(0.f, 0.f, 0.f, 0.f);
+  load_tab(sm.tab, w, clamp_type(types[i]), tid, 64 * NB);
   build_envf(sm.e, tid, X, types, nlist, i, n, natoms, g, rc, rcs);
   const float *dTi = fit + (size_t)i * ND;
   for (int k = tid; k < M * 4; k += 64 * NB) {
@@ -518,48 +552,56 @@ __device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB> *smem, 
   if (!act) {
     zero_block(block);
     zero_block(kblock);
+    pass_barriers(13);
+    return;
   }
+  F100 x, xh;  // the centred rows of layers 0 and 1
+  load_block(x, gs);
+  load_block(xh, gs + GSAVE_LAYER);
   __syncthreads();
   const int j = 16 * jb + c;
-  F100 go = {};
+  F100 go;
   float drh[3] = {0.f, 0.f, 0.f}, dsw = 0.f, dRt[4] = {0.f, 0.f, 0.f, 0.f};
-  if (act) {
-    F100 x, ga, be;
+  {
     // the top layer's input: layer 0's output
-    load_block(x, gs + 1600 * jb);
     normalise(x, ln_eps);
-    get_table(ga, w.gamma[0]);
-    get_table(be, w.beta[0]);
 #pragma unroll
-    for (int t = 0; t < 7; ++t) x[t] = ga[t] * x[t] + be[t];
+    for (int t = 0; t < 7; ++t) x[t] = tab4(sm.tab.gamma[0], t) * x[t] + tab4(sm.tab.beta[0], t);
     put_block(block, XB(x));
+    tile_barrier();
     // dG = Rt dT^T / sel for its output, and dRt = G dT / sel
-    load_block(x, gs + GSAVE_LAYER + 1600 * jb);
-    normalise(x, ln_eps);
-    get_table(ga, w.gamma[1]);
-    get_table(be, w.beta[1]);
+    const float is = normalise(xh, ln_eps);
     const float inv_sel = 1.f / (float)SEL;
     const float sj = sm.e.s[j];
     const float rt1 = sj * sm.e.rh[0][j], rt2 = sj * sm.e.rh[1][j], rt3 = sj * sm.e.rh[2][j];
     f4 p = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int t = 0; t < 7; ++t)
+    for (int t = 0; t < 7; ++t) {
+      tile_barrier();
+      const f4 gv = tab4(sm.tab.gamma[1], t) * xh[t] + tab4(sm.tab.beta[1], t);
 #pragma unroll
       for (int k = 0; k < (t < 6 ? 4 : 1); ++k) {
         const f4 d = ldf4(sm.dT + 4 * (t < 6 ? 16 * t + 4 * q + k : 96 + q));
         go[t][k] = (sj * d[0] + rt1 * d[1] + rt2 * d[2] + rt3 * d[3]) * inv_sel;
-        p += (ga[t][k] * x[t][k] + be[t][k]) * d;
+        p += gv[k] * d;
       }
+    }
 #pragma unroll
     for (int a = 0; a < 4; ++a) dRt[a] = sumq(p[a]) * inv_sel;
+    tile_barrier();
+    norm_bwd(go, xh, is, sm.tab.gamma[1]);
+    tile_barrier();
   }
   __syncthreads();
-  layer_bwd<NB>(w, wp, 1, sm, go, gs + GSAVE_LAYER, jb, n, nb, ln_eps, drh, dsw);
-  if (act) {
+  layer_bwd<NB>(wp, 1, sm, go, jb, n, nb, drh, dsw);
+  {
+    F100 x0;
+    load_block(x0, gs);
     S7 h1[1], t2[2], t3[4];
-    embed(w, wp, sm.e.s[j], ti, sm.e.tj[j], h1, t2, t3);
+    embed(sm.tab, wp, sm.e.s[j], sm.e.tj[j], h1, t2, t3);
     // the block's rows of K, free between the layers: features in order, then the row's pieces
     bf16_t *e = kblock + c * LDE;
+    const int p0 = piece0();
 #pragma unroll
     for (int g4 = 0; g4 < 4; ++g4)
 #pragma unroll
@@ -570,20 +612,22 @@ __device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB> *smem, 
     for (int p = 0; p < 3; ++p) {
       typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
       const bf4 a = *reinterpret_cast<const bf4 *>(e + 32 * p + 4 * q), b = *reinterpret_cast<const bf4 *>(e + 32 * p + 16 + 4 * q);
-      *reinterpret_cast<bf8 *>(block + piece(p)) = bf8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+      *reinterpret_cast<bf8 *>(block + piece(p0, p)) = bf8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
     }
     bf8 tail = {};
     tail[0] = e[96 + q];
-    *reinterpret_cast<bf8 *>(block + piece(3)) = tail;
+    *reinterpret_cast<bf8 *>(block + piece(p0, 3)) = tail;
+    const float is = normalise(x0, ln_eps);
+    norm_bwd(go, x0, is, sm.tab.gamma[0]);
   }
   __syncthreads();
-  layer_bwd<NB>(w, wp, 0, sm, go, gs, jb, n, nb, ln_eps, drh, dsw);
+  layer_bwd<NB>(wp, 0, sm, go, jb, n, nb, drh, dsw);
   // embedding backward and the pair gradients of the wave's tokens
-  if (act) {
+  {
     float *row = reinterpret_cast<float *>(sm.G) + j * LDG;  // over G and K
     put_row(row, go);
     S7 h1[1], t2[2], t3[4];
-    embed(w, wp, sm.e.s[j], ti, sm.e.tj[j], h1, t2, t3);
+    embed(sm.tab, wp, sm.e.s[j], sm.e.tj[j], h1, t2, t3);
     wave_sync();
     S7 dh2[2], d[4];
 #pragma unroll
@@ -608,7 +652,7 @@ __device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB> *smem, 
 #pragma unroll
     for (int r = 0; r < 7; ++r) {
       const float v = dh1[0][r] + dh2[0][r] + dh2[1][r];
-      if (slot_ok(r)) ds += v * (1.f - h1[0][r] * h1[0][r]) * w.w1s[4 * r + q];
+      if (slot_ok(r)) ds += v * (1.f - h1[0][r] * h1[0][r]) * sm.tab.w1s[4 * r + q];
     }
     ds = sumq(ds);
     if (q == 0 && j < SEL) {
@@ -620,7 +664,6 @@ __device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB> *smem, 
       gout[(size_t)i * SEL + j] = out;
     }
   }
-  for (int k = nb ? 16 * nb + tid : SEL; k < SEL; k += 64 * NB) gout[(size_t)i * SEL + k] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
 template <int NB, int NA>

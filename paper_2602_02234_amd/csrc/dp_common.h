@@ -88,7 +88,7 @@ __device__ __forceinline__ int acc_col() { return lane_id() & 15; }
 // mirror 0x141 (lane ^ 7 within 8), row mirror 0x140 (lane ^ 15 within 16) and row
 // rotation by 8, 0x128 (lane ^ 8 within 16).  Every lane of the wave must be active.
 template <int CTRL> __device__ __forceinline__ float dpp(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
 }
 // Sum over the 16 lanes sharing lane/16 (one tile row group); the same value in all of
 // them (each step adds a partner's value, and a + b == b + a exactly).
