@@ -303,9 +303,35 @@ void pack_weights(const HostModel &h, int pr, Image &im) {
             }
     return v;
   };
+  // W3^T has its outputs in the order of the [M][M] products, W3 its contraction
+  auto out100 = [&](auto W) {
+    std::vector<float> v(7 * 2 * 512, 0.f);
+    for (int t = 0; t < 7; ++t)
+      for (int ig = 0; ig < 2; ++ig)
+        for (int l = 0; l < 64; ++l)
+          for (int e = 0; e < 7; ++e) {
+            const int out = t < 6 ? 16 * t + l % 16 : 96 + l % 16 / 4, fi = 4 * e + l / 16;
+            if (fi < 25) v[(2 * t + ig) * 512 + 8 * l + e] = (float)W(out, 25 * ig + fi);
+          }
+    return v;
+  };
+  auto in100 = [&](auto W) {
+    std::vector<float> v(2 * 2 * 4 * 512, 0.f);
+    for (int og = 0; og < 2; ++og)
+      for (int u = 0; u < 2; ++u)
+        for (int l = 0; l < 64; ++l) {
+          const int ro = 4 * u + l % 4, fo = 4 * ro + l % 16 / 4;
+          if (ro >= 7 || fo >= 25) continue;
+          for (int p = 0; p < 3; ++p)
+            for (int e = 0; e < 8; ++e)
+              v[((og * 2 + u) * 4 + p) * 512 + 8 * l + e] = (float)W(25 * og + fo, 32 * p + 4 * (l / 16) + (e < 4 ? e : e + 12));
+          v[((og * 2 + u) * 4 + 3) * 512 + 8 * l] = (float)W(25 * og + fo, 96 + l / 16);
+        }
+    return v;
+  };
   op.push_back(hi_lo(frag25(2, 1, [&](int c, int k) { return h.W2[(size_t)k * E2 + c]; }), 0));
-  op.push_back(hi_lo(frag25(4, 2, [&](int c, int k) { return h.W3[(size_t)k * M + c]; }), 0));
-  op.push_back(hi_lo(frag25(2, 4, [&](int c, int k) { return h.W3[(size_t)c * M + k]; }), 0));
+  op.push_back(hi_lo(out100([&](int c, int k) { return h.W3[(size_t)k * M + c]; }), 0));
+  op.push_back(hi_lo(in100([&](int c, int k) { return h.W3[(size_t)c * M + k]; }), 0));
   op.push_back(hi_lo(frag25(1, 2, [&](int c, int k) { return h.W2[(size_t)c * E2 + k]; }), 0));
   for (int a = 0; a < NATTN; ++a) {
     op.push_back(hi_lo(frag100([&](int c, int k) { return QK[a][(size_t)k * M + c]; }), 0));

@@ -29,7 +29,9 @@ namespace dp {
 namespace {
 
 constexpr int RW = 128;   // values in a bfloat16 row in LDS
-constexpr int LDE = 104;  // stride of the rows the embedding is rearranged in (16 fit a block's rows)
+constexpr int LDH = 52;   // stride (floats) of the rows a block's features are rearranged in (16 fit its rows)
+constexpr int WMAT = 11264;                        // values of an attention matrix in fragment order
+constexpr int W2T_N = 4 * 512, W3T_N = 14 * 512;   // ... of the embedding's
 typedef short s4 __attribute__((ext_vector_type(4)));
 static_assert(M == 100 && E1 == 25 && E2 == 50, "the fragment layouts below are written for these widths");
 
@@ -91,10 +93,10 @@ __device__ __forceinline__ bf8 column8(const bf16_t *block, int cu) {
   return __builtin_bit_cast(bf8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-// acc += W x for a 100 x 100 matrix in fragment order: step p < 3 of tile t at (7 p + t) 512 + 8 lane,
+// acc += W x for a 100 x 100 matrix in fragment order, in LDS: step p < 3 of tile t at (7 p + t) 512 + 8 lane,
 // the seven tiles' k = 96 + q at 10752 + 8 lane + t.  A step's seven tiles are independent
 // products, and the next step's operands are loaded while they run.
-__device__ __forceinline__ void wmul(F100 &acc, const bf16_t *__restrict__ w, const XB &x) {
+__device__ __forceinline__ void wmul(F100 &acc, const bf16_t *w, const XB &x) {
   const bf16_t *p = w + 8 * lane();
   bf8 a[7];
 #pragma unroll
@@ -161,7 +163,7 @@ __device__ __forceinline__ void rows_sum(F100 &acc, const bf16_t *R, const Y &y,
 // Feature groups as in the float32 kernels; a group's seven slots are the lane's k of one step.
 // Weights in fragment order: tile u of output group og, input group ig at ((og 2 + u) NI + ig) 512.
 template <int NI, int NO>
-__device__ __forceinline__ void emul(S7 (&out)[NO], const bf16_t *__restrict__ w, const S7 (&in)[NI]) {
+__device__ __forceinline__ void emul(S7 (&out)[NO], const bf16_t *w, const S7 (&in)[NI]) {
   bf8 x[NI];
   const bf16_t *wl = w + 8 * lane();
 #pragma unroll
@@ -207,10 +209,11 @@ __device__ __forceinline__ void load_tab(Tab &t, const Tables &w, int ti, int ti
   }
 }
 
-// h1, t2 = h2 - [h1, h1] and t3 = G - [h2, h2] of the lane's token.
-__device__ __forceinline__ void embed(const Tab &w, const WeightsB16 &wp, float s, int tj, S7 (&h1)[1], S7 (&t2)[2],
-                                      S7 (&t3)[4]) {
-  const int q = lane() >> 4;
+// h1 and t2 = h2 - [h1, h1] by groups and t3 = G - [h2, h2] of the lane's token; w2T, w3T: the
+// weights, in LDS.  h2 is left in scr (float32, [16][LDH]), from where residual() adds it.
+__device__ __forceinline__ void embed(const Tab &w, const bf16_t *w2T, const bf16_t *w3T, float s, int tj, float *scr,
+                                      S7 (&h1)[1], S7 (&t2)[2], F100 &t3) {
+  const int l = lane(), q = l >> 4, c = l & 15;
   const float *bt = w.Bt + tj * E1;
 #pragma unroll
   for (int r = 0; r < 7; ++r) {
@@ -218,35 +221,85 @@ __device__ __forceinline__ void embed(const Tab &w, const WeightsB16 &wp, float 
     const float v = ftanh(s * w.w1s[f] + bt[f]);
     h1[0][r] = slot_ok(r) ? v : 0.f;
   }
-  emul<1, 2>(t2, wp.W2T, h1);
-  S7 h2[2];
+  emul<1, 2>(t2, w2T, h1);
+  bf8 x[2];
 #pragma unroll
-  for (int g = 0; g < 2; ++g)
+  for (int g = 0; g < 2; ++g) {
+    float h[8] = {};
 #pragma unroll
     for (int r = 0; r < 7; ++r) {
       const int f = slot_ok(r) ? 25 * g + 4 * r + q : 0;
       const float v = ftanh(t2[g][r] + w.b2[f]);
       t2[g][r] = slot_ok(r) ? v : 0.f;
-      h2[g][r] = t2[g][r] + h1[0][r];
+      h[r] = t2[g][r] + h1[0][r];
+      if (slot_ok(r)) scr[c * LDH + 25 * g + 4 * r + q] = h[r];
     }
-  emul<2, 4>(t3, wp.W3T, h2);
+    x[g] = pack(f4{h[0], h[1], h[2], h[3]}, f4{h[4], h[5], h[6], h[7]});
+  }
 #pragma unroll
-  for (int g = 0; g < 4; ++g)
+  for (int t = 0; t < 7; ++t) {
+    f4 acc = tab4(w.b3, t);
 #pragma unroll
-    for (int r = 0; r < 7; ++r) {
-      const int f = slot_ok(r) ? 25 * g + 4 * r + q : 0;
-      const float v = ftanh(t3[g][r] + w.b3[f]);
-      t3[g][r] = slot_ok(r) ? v : 0.f;
-    }
+    for (int g = 0; g < 2; ++g) acc = mma(ld8(w3T + (2 * t + g) * 512 + 8 * l), x[g], acc);
+#pragma unroll
+    for (int k = 0; k < (t < 6 ? 4 : 1); ++k) t3[t][k] = ftanh(acc[k]);
+  }
+}
+// [h2, h2] in a token's arrangement: feature f is h2[f % 50].
+__device__ __forceinline__ f4 residual(const float *scr, int t) {
+  const int l = lane(), q = l >> 4;
+  const float *h = scr + (l & 15) * LDH + 4 * q;
+  typedef float f2 __attribute__((ext_vector_type(2)));
+  if (t < 3) return ldf4(h + 16 * t);
+  if (t == 6) return f4{scr[(l & 15) * LDH + 46 + q], 0.f, 0.f, 0.f};
+  // 16 t + 4 q + i - 50, even; at t = 3, q = 0 the first two are still 48, 49
+  const f2 a = *reinterpret_cast<const f2 *>(t == 3 && q == 0 ? h + 48 : h + 16 * t - 50);
+  const f2 b = *reinterpret_cast<const f2 *>(h + 16 * t - 48);
+  return f4{a[0], a[1], b[0], b[1]};
 }
 
+// Copy of N values from global memory to LDS by a workgroup of NT threads: loaded here, stored later.
+template <int N, int NT> struct Fetch {
+  static constexpr int P = N / 8, R = (P + NT - 1) / NT;
+  bf8 v[R];
+  __device__ __forceinline__ explicit Fetch(const bf16_t *__restrict__ w) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int k = threadIdx.x + r * NT;
+      v[r] = ld8(w + 8 * (k < P ? k : 0));
+    }
+  }
+  __device__ __forceinline__ void store(bf16_t *d) const {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int k = threadIdx.x + r * NT;
+      if (k < P) *reinterpret_cast<bf8 *>(d + 8 * k) = v[r];
+    }
+  }
+};
+template <int NT> struct FetchEmb {  // W2^T, then W3^T
+  Fetch<W2T_N, NT> a;
+  Fetch<W3T_N, NT> b;
+  __device__ __forceinline__ explicit FetchEmb(const WeightsB16 &wp) : a(wp.W2T), b(wp.W3T) {}
+  __device__ __forceinline__ void store(bf16_t *d) const {
+    a.store(d);
+    b.store(d + W2T_N);
+  }
+};
+
 // ======================================================================== forward
-template <int NB> struct SmemFwd {
-  bf16_t G[16 * NB * RW] __attribute__((aligned(16)));    // the layer's input, every token
-  float row[16 * NB * LDG] __attribute__((aligned(16)));  // ... in float32, each wave its own
-  float part[NB][M * 4] __attribute__((aligned(16)));
+template <int NB> struct AtomFwd {
+  bf16_t G[16 * NB * RW] __attribute__((aligned(16)));  // the layer's input, every token
   EnvF<NB> e;
   Tab tab;
+};
+template <int NB, int NA> struct SmemFwd {
+  AtomFwd<NB> a[NA];
+  bf16_t E[W2T_N + W3T_N] __attribute__((aligned(16)));
+  union {
+    bf16_t W[2][WMAT] __attribute__((aligned(16)));       // the layer's Wqk^T, Wvo^T
+    float part[NA][NB][M * 4];                            // the waves' parts of T
+  };
 };
 
 __device__ __forceinline__ void zero_block(bf16_t *block) {
@@ -254,43 +307,57 @@ __device__ __forceinline__ void zero_block(bf16_t *block) {
   for (int p = 0; p < 4; ++p) *reinterpret_cast<bf8 *>(block + piece(piece0(), p)) = bf8{};
 }
 
-// The barriers of the other waves' work, for a wave without tokens.  Such waves take a path of their
-// own, so that no register of the work is carried past a branch around it.
-__device__ __forceinline__ void pass_barriers(int n) {
-  for (int k = 0; k < n; ++k) __syncthreads();
-}
-
+// The weights go through LDS: twelve waves reading 22 KB each for a product from the vector cache, at
+// 64 bytes a cycle, took 4,100 cycles where the copy takes 350 and the LDS reads half.  A wave
+// without tokens takes a path of its own, with the same copies and barriers, so that no register
+// of the others' work is carried past a branch around it.
 template <int NB, int NA>
-__device__ __forceinline__ void desc_fwd(int blk, int count, SmemFwd<NB> *smem, const Tables &w, const WeightsB16 &wp,
+__device__ __forceinline__ void desc_fwd(int blk, int count, SmemFwd<NB, NA> &sh, const Tables &w, const WeightsB16 &wp,
                                          const double *__restrict__ X, const int *__restrict__ types, int natoms,
                                          const int *__restrict__ idx, int c0, const int *__restrict__ nlist,
                                          const int *__restrict__ nnei, const Grid *__restrict__ grids,
                                          const int *__restrict__ sys_of, float rc, float rcs, float ln_eps,
                                          float *__restrict__ Gsave, float *__restrict__ Tsave) {
+  constexpr int NT = 64 * NB * NA;
   const Part<NB, NA> pt(blk, idx, c0, count, nnei);
-  SmemFwd<NB> &sm = smem[pt.half];
+  AtomFwd<NB> &sm = sh.a[pt.half];
   const int i = pt.i, n = pt.n, nb = pt.nb, jb = pt.jb, tid = pt.tid;
   const Grid g = grids[sys_of[i]];
   const int l = lane(), q = l >> 4, c = l & 15;
-  const bool act = jb < nb;
-  load_tab(sm.tab, w, clamp_type(types[i]), tid, 64 * NB);
-  build_envf(sm.e, tid, X, types, nlist, i, n, natoms, g, rc, rcs);
+  {
+    const FetchEmb<NT> fe(wp);
+    const Fetch<WMAT, NT> fu(wp.WqkT[0]), fy(wp.WvoT[0]);
+    load_tab(sm.tab, w, clamp_type(types[i]), tid, 64 * NB);
+    build_envf(sm.e, tid, X, types, nlist, i, n, natoms, g, rc, rcs);
+    fe.store(sh.E);
+    fu.store(sh.W[0]);
+    fy.store(sh.W[1]);
+  }
   __syncthreads();
   const int j = 16 * jb + c;  // the lane's token
-  float *row = sm.row + j * LDG;
   bf16_t *block = sm.G + 16 * jb * RW;
-  if (!act) {
+  if (jb >= nb) {
     zero_block(block);
-    pass_barriers(3);
+    __syncthreads();
+    for (int layer = 1; layer < NATTN; ++layer) {
+      const Fetch<WMAT, NT> fu(wp.WqkT[layer]), fy(wp.WvoT[layer]);
+      __syncthreads();
+      fu.store(sh.W[0]);
+      fy.store(sh.W[1]);
+      __syncthreads();
+    }
+    __syncthreads();
   } else {
+    F100 x;  // the token's G
     XB xb;
+    float *scr = reinterpret_cast<float *>(block);
     {
-      S7 h1[1], t2[2], t3[4];
-      embed(sm.tab, wp, sm.e.s[j], sm.e.tj[j], h1, t2, t3);
-      put_embedding(row, h1, t2, t3);
+      S7 h1[1], t2[2];
+      embed(sm.tab, sh.E, sh.E + W2T_N, sm.e.s[j], sm.e.tj[j], scr, h1, t2, x);
       wave_sync();
-      F100 x;
-      get_row(x, row);
+#pragma unroll
+      for (int t = 0; t < 7; ++t) x[t] += residual(scr, t);
+      wave_sync();
       xb = XB(x);
       put_block(block, xb);
     }
@@ -301,62 +368,71 @@ __device__ __forceinline__ void desc_fwd(int blk, int count, SmemFwd<NB> *smem, 
       f4 s[NB];
       {
         F100 u = {};
-        wmul(u, wp.WqkT[layer], xb);  // U
+        wmul(u, sh.W[0], xb);  // U
         keys_dot<NB>(s, sm.G, XB(u), nb);  // S = U G^T
       }
       softmax_keys<NB>(s, sm.e, n, [](float v) { return __expf(v); });
-      F100 h = {}, y = {}, x;
-      // H = A G with A = sw E gate
-      rows_sum<NB>(h, sm.G, [&](int p) {
-        const int k = 32 * p + 4 * q;
-        return pack(s[2 * p] * gate4(sm.e, 2 * p, hj) * ldf4(sm.e.sw + k),
-                    s[2 * p + 1] * gate4(sm.e, 2 * p + 1, hj) * ldf4(sm.e.sw + k + 16));
-      }, nb);
-      wmul(y, wp.WvoT[layer], XB(h));
-      get_row(x, row);
-#pragma unroll
-      for (int t = 0; t < 7; ++t) y[t] += x[t];
+      {
+        F100 h = {};
+        // H = A G with A = sw E gate
+        rows_sum<NB>(h, sm.G, [&](int p) {
+          const int k = 32 * p + 4 * q;
+          return pack(s[2 * p] * gate4(sm.e, 2 * p, hj) * ldf4(sm.e.sw + k),
+                      s[2 * p + 1] * gate4(sm.e, 2 * p + 1, hj) * ldf4(sm.e.sw + k + 16));
+        }, nb);
+        wmul(x, sh.W[1], XB(h));  // G + Y
+      }
+      const int next = layer + 1 < NATTN ? layer + 1 : layer;
+      const Fetch<WMAT, NT> fu(wp.WqkT[next]), fy(wp.WvoT[next]);
       // LayerNorm; the centred rows are what the backward reads
-      const float mu = sum100([&](int t, int k) { return y[t][k]; }) * (1.f / M);
+      const float mu = sum100([&](int t, int k) { return x[t][k]; }) * (1.f / M);
 #pragma unroll
-      for (int t = 0; t < 7; ++t) y[t] -= mu;
-      save_block(Gsave + ((size_t)i * NATTN + layer) * GSAVE_LAYER + 1600 * jb, y);
-      normalise(y, ln_eps);
+      for (int t = 0; t < 7; ++t) x[t] -= mu;
+      save_block(Gsave + ((size_t)i * NATTN + layer) * GSAVE_LAYER + 1600 * jb, x);
+      normalise(x, ln_eps);
 #pragma unroll
-      for (int t = 0; t < 7; ++t) y[t] = tab4(sm.tab.gamma[layer], t) * y[t] + tab4(sm.tab.beta[layer], t);
-      put_row(row, y);
-      xb = XB(y);
+      for (int t = 0; t < 7; ++t) x[t] = tab4(sm.tab.gamma[layer], t) * x[t] + tab4(sm.tab.beta[layer], t);
+      __syncthreads();  // every wave is done with the layer's input and weights
       if (layer == NATTN - 1) break;
-      __syncthreads();  // every wave is done with the layer's input
+      xb = XB(x);
       put_block(block, xb);
+      fu.store(sh.W[0]);
+      fy.store(sh.W[1]);
       __syncthreads();
     }
     // T = G^T Rt / sel: each wave's 16 tokens on float32 MFMA (T^T = Rt^T G, rows c < 4 of the 16
-    // used, step s taking token 4 s + q), then the waves' parts in order
-    {
+    // used, step s taking token 4 s + q), three tiles of G at a time through the block's rows;
+    // then the waves' parts in order
+    float rt[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int k = 16 * jb + 4 * s + q;
+      const float sk = sm.e.s[k];
+      rt[s] = c == 0 ? sk : (c < 4 ? sk * sm.e.rh[c - 1][k] : 0.f);
+    }
+#pragma unroll
+    for (int h = 0; h < 3; ++h) {
       wave_sync();
-      f4 acc[7];
 #pragma unroll
-      for (int t = 0; t < 7; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int k = 16 * jb + 4 * s + q;
-        const float sk = sm.e.s[k];
-        const float rt = c == 0 ? sk : (c < 4 ? sk * sm.e.rh[c - 1][k] : 0.f);
-        const float *gk = sm.row + k * LDG;
-#pragma unroll
-        for (int t = 0; t < 7; ++t) acc[t] = mfma(rt, gk[t < 6 ? 16 * t + c : 96 + (c & 3)], acc[t]);
+      for (int t = 0; t < 3; ++t) {
+        if (3 * h + t < 6) stf4(scr + c * LDH + 16 * t + 4 * q, x[3 * h + t]);
+        if (3 * h + t == 6) scr[c * LDH + q] = x[6][0];
       }
-      if (q == 0)
+      wave_sync();
 #pragma unroll
-        for (int t = 0; t < 7; ++t)
-          if (t < 6 || c < 4) stf4(sm.part[jb] + 4 * (16 * t + c), acc[t]);
+      for (int t = 0; t < 3; ++t) {
+        if (3 * h + t > 6) continue;
+        f4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < 4; ++s) acc = mfma(rt[s], scr[(4 * s + q) * LDH + 16 * t + (h < 2 ? c : c & 3)], acc);
+        if (q == 0 && (h < 2 || c < 4)) stf4(sh.part[pt.half][jb] + 4 * (48 * h + 16 * t + c), acc);
+      }
     }
   }
   __syncthreads();
   for (int k = tid; k < (nb ? M * 4 : 0); k += 64 * NB) {
     float acc = 0.f;
-    for (int v = 0; v < nb; ++v) acc += sm.part[v][k];
+    for (int v = 0; v < nb; ++v) acc += sh.part[pt.half][v][k];
     Tsave[(size_t)i * M * 4 + k] = acc * (1.f / (float)SEL);
   }
 }
@@ -369,7 +445,7 @@ k_desc_fwd_b16(Tables w, WeightsB16 wp, const double *__restrict__ X, const int 
                const int *__restrict__ idx, const int *__restrict__ cnt, int c0, int ncen, const int *__restrict__ nlist,
                const int *__restrict__ nnei, const Grid *__restrict__ grids, const int *__restrict__ sys_of, float rc, float rcs,
                float ln_eps, float *__restrict__ Gsave, float *__restrict__ Tsave) {
-  __shared__ SmemFwd<NB> smem[NA];
+  __shared__ SmemFwd<NB, NA> smem;
   const int count = idx ? *cnt : ncen;
   for (int b = blockIdx.x; b * NA < count; b += gridDim.x) {
     desc_fwd<NB, NA>(b, count, smem, w, wp, X, types, natoms, idx, c0, nlist, nnei, grids, sys_of, rc, rcs, ln_eps, Gsave, Tsave);
@@ -379,17 +455,45 @@ k_desc_fwd_b16(Tables w, WeightsB16 wp, const double *__restrict__ X, const int 
 }
 
 // ======================================================================== backward
-template <int NB> struct SmemBwd {
+template <int NB> struct AtomBwd {
   bf16_t G[16 * NB * RW] __attribute__((aligned(16)));     // a layer's input, then dH, then U
   bf16_t K[16 * NB * RW] __attribute__((aligned(16)));     // the queries' rows of E gate, then of W
-  float tile[NB][256] __attribute__((aligned(16)));        // per-wave scratch
   float drhw[NB][16 * NB * 3];                             // each wave's column sums of dC rhat
   float wsum[NB][16 * NB] __attribute__((aligned(16)));    // ... of W
   float dT[M * 4] __attribute__((aligned(16)));
   EnvF<NB> e;
   Tab tab;
 };
-static_assert(sizeof(SmemBwd<8>::G) * 2 >= sizeof(float) * 16 * 8 * LDG, "float32 rows of every token fit over G and K");
+// Wvo and Wqk^T of a layer are read before the first rows go to K, so they are kept there (in the
+// two atoms' K, or, with one atom, the second beside it); Wqk, and between the layers the
+// embedding's weights, have space of their own.
+template <int NB, int NA> struct SmemBwd {
+  AtomBwd<NB> a[NA];
+  bf16_t W[NA == 2 ? 1 : 2][WMAT] __attribute__((aligned(16)));
+  float tile[NA == 2 ? 1 : NB][NA == 2 ? 4 : 256] __attribute__((aligned(16)));
+  __device__ __forceinline__ bf16_t *wvo() { return a[0].K; }
+  __device__ __forceinline__ bf16_t *wqkT() { return NA == 2 ? a[NA - 1].K : W[NA == 2 ? 0 : 1]; }
+};
+static_assert(sizeof(AtomBwd<NB_SMALL>::K) >= sizeof(bf16_t) * WMAT && WMAT >= W2T_N + W3T_N, "the weights fit");
+static_assert(sizeof(AtomBwd<8>::G) * 2 >= sizeof(float) * 16 * 8 * LDG, "float32 rows of every token fit over G and K");
+
+// Row r of a wave's 16 x 16 float32 tile: in the quarter of the block's rows of K that 96 keys leave
+// free, or in `tile`.  put: the lane's four keys of token c; get: o[s] = token 4 q + (s ^ q), key c
+// (s permuted so that the four lane groups are in different banks).
+template <int NB> __device__ __forceinline__ float *tile_row(bf16_t *kblock, float *tile, int r) {
+  return NB == NB_SMALL ? reinterpret_cast<float *>(kblock + r * RW + 32 * (3 ^ (r & 3))) : tile + 16 * r;
+}
+template <int NB> __device__ __forceinline__ void tile_put(bf16_t *kblock, float *tile, f4 y) {
+  const int l = lane(), q = l >> 4, c = l & 15;
+  stf4(tile_row<NB>(kblock, tile, c) + 4 * (q ^ (c >> 2)), y);
+}
+template <int NB> __device__ __forceinline__ f4 tile_get(bf16_t *kblock, float *tile) {
+  const int l = lane(), q = l >> 4, c = l & 15;
+  f4 o;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) o[s] = tile_row<NB>(kblock, tile, 4 * q + (s ^ q))[c ^ (4 * q)];
+  return o;
+}
 
 // LayerNorm backward in place: dX = (dxh - mean(dxh) - xh mean(dxh xh)) / sigma, dxh = gamma dG_out.
 __device__ __forceinline__ void norm_bwd(F100 &go, const F100 &xh, float is, const float *gamma) {
@@ -408,38 +512,44 @@ __device__ __forceinline__ void norm_bwd(F100 &go, const F100 &xh, float is, con
 //   dP = dA gate, rho = sum P dP, W = E (dP - rho), dS = sw W, dU = G^T dS, and dG_j = dX + Wqk dU.
 //   (dH comes first: beside E the products' operands would not fit the registers.)
 //   Column part (per key k): dG_k += sw_k sum_j (E gate)_jk dH_j + W_jk U_j, dsw_k += sum_j W_jk.
-template <int NB>
-__device__ __forceinline__ void layer_bwd(const WeightsB16 &wp, int layer, SmemBwd<NB> &sm, F100 &go, int jb, int n, int nb,
-                                          float (&drh)[3], float &dsw) {
+template <int NB, int NA>
+__device__ __forceinline__ void layer_bwd(const WeightsB16 &wp, int layer, SmemBwd<NB, NA> &sh, AtomBwd<NB> &sm, F100 &go,
+                                          int jb, int n, int nb, float (&drh)[3], float &dsw) {
+  constexpr int NT = 64 * NB * NA;
   const int l = lane(), q = l >> 4, c = l & 15;
   const int j = 16 * jb + c;
   bf16_t *block = sm.G + 16 * jb * RW, *kblock = sm.K + 16 * jb * RW;
+  float *tile = sh.tile[NA == 2 ? 0 : jb];
   XB ub, hb;
   const int p0 = piece0();
   bf8 wb[NB / 2];
   const float hj[3] = {sm.e.rh[0][j], sm.e.rh[1][j], sm.e.rh[2][j]};
   {
     F100 dh = {};
-    wmul(dh, wp.Wvo[layer], XB(go));
+    wmul(dh, sh.wvo(), XB(go));
     hb = XB(dh);
   }
   {
     F100 u = {};
 #pragma unroll
     for (int p = 0; p < 4; ++p) ub.v[p] = ld8(block + piece(p0, p));
-    wmul(u, wp.WqkT[layer], ub);
+    wmul(u, sh.wqkT(), ub);
     ub = XB(u);
   }
   f4 E[NB], W[NB];
-  keys_dot<NB>(E, sm.G, ub, nb);
+  {
+    const Fetch<WMAT, NT> f(wp.Wqk[layer]);
+    keys_dot<NB>(E, sm.G, ub, nb);
+    f.store(sh.W[0]);
+  }
   softmax_keys<NB>(E, sm.e, n, [](float v) { return __expf(v); });
   keys_dot<NB>(W, sm.G, hb, nb);  // dA
+  __syncthreads();  // K is free, Wqk is there
   float rho = 0.f, hx = 0.f, hy = 0.f, hz = 0.f;
-  // columns of dC rhat: sum_j rhat_j (dA E)_jk, A operand rhat of token 4 q + s in rows a < 3
+  // columns of dC rhat: sum_j rhat_j (dA E)_jk, A operand rhat of the tile's tokens in rows a < 3
   float rj[4];
 #pragma unroll
-  for (int s = 0; s < 4; ++s) rj[s] = c < 3 ? sm.e.rh[c][16 * jb + 4 * q + s] : 0.f;
-  float *tile = sm.tile[jb];
+  for (int s = 0; s < 4; ++s) rj[s] = c < 3 ? sm.e.rh[c][16 * jb + 4 * q + (s ^ q)] : 0.f;
 #pragma unroll
   for (int p = 0; p < NB / 2; ++p)
     if (2 * p < nb) {
@@ -462,9 +572,9 @@ __device__ __forceinline__ void layer_bwd(const WeightsB16 &wp, int layer, SmemB
         W[kt] = dP;
         ea[h] = E[kt] * gt;
         wave_sync();
-        put_tile(tile, cc);
+        tile_put<NB>(kblock, tile, cc);
         wave_sync();
-        const f4 ct = get_tile(tile);
+        const f4 ct = tile_get<NB>(kblock, tile);
         f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int s = 0; s < 4; ++s) acc = mfma(rj[s], ct[s], acc);
@@ -497,8 +607,10 @@ __device__ __forceinline__ void layer_bwd(const WeightsB16 &wp, int layer, SmemB
   }
   F100 du = {};
   rows_sum<NB>(du, sm.G, [&](int p) { return ds[p]; }, nb);
-  wmul(go, wp.Wqk[layer], XB(du));
-  __syncthreads();  // the layer's input is no longer needed
+  wmul(go, sh.W[0], XB(du));
+  const FetchEmb<NT> fe(wp);
+  __syncthreads();  // the layer's input and weights are no longer needed
+  fe.store(sh.W[0]);
   put_block(block, hb);
   __syncthreads();
   F100 acc = {};
@@ -523,36 +635,65 @@ __device__ __forceinline__ void layer_bwd(const WeightsB16 &wp, int layer, SmemB
   __syncthreads();
 }
 
+// The same copies and barriers for a wave without tokens.
 template <int NB, int NA>
-__device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB> *smem, const Tables &w, const WeightsB16 &wp,
+__device__ __forceinline__ void layer_bwd_idle(const WeightsB16 &wp, int layer, SmemBwd<NB, NA> &sh, bf16_t *kblock) {
+  constexpr int NT = 64 * NB * NA;
+  {
+    const Fetch<WMAT, NT> f(wp.Wqk[layer]);
+    f.store(sh.W[0]);
+  }
+  __syncthreads();
+  const FetchEmb<NT> fe(wp);
+  zero_block(kblock);
+  __syncthreads();
+  fe.store(sh.W[0]);
+  for (int k = 0; k < 4; ++k) __syncthreads();
+}
+
+template <int NB, int NA>
+__device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB, NA> &sh, const Tables &w, const WeightsB16 &wp,
                                          const double *__restrict__ X, const int *__restrict__ types, int natoms,
                                          const int *__restrict__ idx, int c0, const int *__restrict__ nlist,
                                          const int *__restrict__ nnei, const Grid *__restrict__ grids,
                                          const int *__restrict__ sys_of, float rc, float rcs, float ln_eps,
                                          const float *__restrict__ Gsave, const float *__restrict__ fit,
                                          float4 *__restrict__ gout) {
+  constexpr int NT = 64 * NB * NA;
   const Part<NB, NA> pt(blk, idx, c0, count, nnei);
-  SmemBwd<NB> &sm = smem[pt.half];
+  AtomBwd<NB> &sm = sh.a[pt.half];
   const int i = pt.i, n = pt.n, nb = pt.nb, jb = pt.jb, tid = pt.tid;
   const Grid g = grids[sys_of[i]];
   const int l = lane(), q = l >> 4, c = l & 15;
-  const bool act = jb < nb;
   const float *gs = Gsave + (size_t)i * NATTN * GSAVE_LAYER + 1600 * jb;
-  for (int k = nb ? 16 * nb + tid : SEL; k < SEL; k += 64 * NB) gout[(size_t)i * SEL + k] = make_float4(0.f, 0.f, 0.f, 0.f);
-  load_tab(sm.tab, w, clamp_type(types[i]), tid, 64 * NB);
-  build_envf(sm.e, tid, X, types, nlist, i, n, natoms, g, rc, rcs);
-  const float *dTi = fit + (size_t)i * ND;
-  for (int k = tid; k < M * 4; k += 64 * NB) {
-    float v = dTi[FIT_DT + k];
-    if (k < 4 * M2)
-      for (int p = 0; p < FIT_NPART; ++p) v += dTi[FIT_PART + 4 * M2 * p + k];
-    sm.dT[k] = v;
-  }
   bf16_t *block = sm.G + 16 * jb * RW, *kblock = sm.K + 16 * jb * RW;
-  if (!act) {
+  {
+    const Fetch<WMAT, NT> fv(wp.Wvo[NATTN - 1]), fq(wp.WqkT[NATTN - 1]);
+    for (int k = nb ? 16 * nb + tid : SEL; k < SEL; k += 64 * NB) gout[(size_t)i * SEL + k] = make_float4(0.f, 0.f, 0.f, 0.f);
+    load_tab(sm.tab, w, clamp_type(types[i]), tid, 64 * NB);
+    build_envf(sm.e, tid, X, types, nlist, i, n, natoms, g, rc, rcs);
+    const float *dTi = fit + (size_t)i * ND;
+    for (int k = tid; k < M * 4; k += 64 * NB) {
+      float v = dTi[FIT_DT + k];
+      if (k < 4 * M2)
+        for (int p = 0; p < FIT_NPART; ++p) v += dTi[FIT_PART + 4 * M2 * p + k];
+      sm.dT[k] = v;
+    }
+    fv.store(sh.wvo());
+    fq.store(sh.wqkT());
+  }
+  if (jb >= nb) {
     zero_block(block);
-    zero_block(kblock);
-    pass_barriers(13);
+    __syncthreads();
+    __syncthreads();
+    layer_bwd_idle<NB, NA>(wp, 1, sh, kblock);
+    {
+      const Fetch<WMAT, NT> fv(wp.Wvo[0]), fq(wp.WqkT[0]);
+      fv.store(sh.wvo());
+      fq.store(sh.wqkT());
+    }
+    __syncthreads();
+    layer_bwd_idle<NB, NA>(wp, 0, sh, kblock);
     return;
   }
   F100 x, xh;  // the centred rows of layers 0 and 1
@@ -593,76 +734,75 @@ __device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB> *smem, 
     tile_barrier();
   }
   __syncthreads();
-  layer_bwd<NB>(wp, 1, sm, go, jb, n, nb, drh, dsw);
+  layer_bwd<NB, NA>(wp, 1, sh, sm, go, jb, n, nb, drh, dsw);
   {
-    F100 x0;
+    F100 x0, t3;
+    const Fetch<WMAT, NT> fv(wp.Wvo[0]), fq(wp.WqkT[0]);
     load_block(x0, gs);
-    S7 h1[1], t2[2], t3[4];
-    embed(sm.tab, wp, sm.e.s[j], sm.e.tj[j], h1, t2, t3);
-    // the block's rows of K, free between the layers: features in order, then the row's pieces
-    bf16_t *e = kblock + c * LDE;
-    const int p0 = piece0();
-#pragma unroll
-    for (int g4 = 0; g4 < 4; ++g4)
-#pragma unroll
-      for (int r = 0; r < 7; ++r)
-        if (slot_ok(r)) e[25 * g4 + 4 * r + q] = (__bf16)(t3[g4][r] + (t2[g4 & 1][r] + h1[0][r]));
+    S7 h1[1], t2[2];
+    float *scr = reinterpret_cast<float *>(block);
+    embed(sm.tab, sh.W[0], sh.W[0] + W2T_N, sm.e.s[j], sm.e.tj[j], scr, h1, t2, t3);
     wave_sync();
 #pragma unroll
-    for (int p = 0; p < 3; ++p) {
-      typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
-      const bf4 a = *reinterpret_cast<const bf4 *>(e + 32 * p + 4 * q), b = *reinterpret_cast<const bf4 *>(e + 32 * p + 16 + 4 * q);
-      *reinterpret_cast<bf8 *>(block + piece(p0, p)) = bf8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-    }
-    bf8 tail = {};
-    tail[0] = e[96 + q];
-    *reinterpret_cast<bf8 *>(block + piece(p0, 3)) = tail;
+    for (int t = 0; t < 7; ++t) t3[t] += residual(scr, t);
+    wave_sync();
+    put_block(block, XB(t3));
+    fv.store(sh.wvo());
+    fq.store(sh.wqkT());
     const float is = normalise(x0, ln_eps);
     norm_bwd(go, x0, is, sm.tab.gamma[0]);
   }
   __syncthreads();
-  layer_bwd<NB>(wp, 0, sm, go, jb, n, nb, drh, dsw);
+  layer_bwd<NB, NA>(wp, 0, sh, sm, go, jb, n, nb, drh, dsw);
   // embedding backward and the pair gradients of the wave's tokens
+  float *row = reinterpret_cast<float *>(sm.G) + j * LDG;  // over G and K
+  S7 h1[1], t2[2], dh2[2];
   {
-    float *row = reinterpret_cast<float *>(sm.G) + j * LDG;  // over G and K
-    put_row(row, go);
-    S7 h1[1], t2[2], t3[4];
-    embed(sm.tab, wp, sm.e.s[j], sm.e.tj[j], h1, t2, t3);
+    F100 t3;
+    float *scr = reinterpret_cast<float *>(sm.G) + 16 * jb * LDG;  // the block's rows, before dG is put there
+    embed(sm.tab, sh.W[0], sh.W[0] + W2T_N, sm.e.s[j], sm.e.tj[j], scr, h1, t2, t3);
     wave_sync();
-    S7 dh2[2], d[4];
+    put_row(row, go);
 #pragma unroll
-    for (int g4 = 0; g4 < 4; ++g4)
-#pragma unroll
-      for (int r = 0; r < 7; ++r) {
-        const float v = slot_ok(r) ? row[25 * g4 + 4 * r + q] : 0.f;
-        d[g4][r] = v;
-        t3[g4][r] = v * (1.f - t3[g4][r] * t3[g4][r]);  // dpre3
-      }
-    emul<4, 2>(dh2, wp.W3, t3);
+    for (int t = 0; t < 7; ++t) t3[t] = go[t] * (1.f - t3[t] * t3[t]);  // dpre3
+    const XB d(t3);
 #pragma unroll
     for (int g2 = 0; g2 < 2; ++g2)
 #pragma unroll
-      for (int r = 0; r < 7; ++r) {
-        dh2[g2][r] += d[g2][r] + d[g2 + 2][r];
-        t2[g2][r] = dh2[g2][r] * (1.f - t2[g2][r] * t2[g2][r]);  // dpre2
+      for (int u = 0; u < 2; ++u) {
+        f4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int p = 0; p < 4; ++p) acc = mma(ld8(wp.W3 + ((2 * g2 + u) * 4 + p) * 512 + 8 * l), d.v[p], acc);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (4 * u + k < 7) dh2[g2][4 * u + k] = acc[k];
       }
-    S7 dh1[1];
-    emul<2, 1>(dh1, wp.W2, t2);
-    float ds = 0.f;
+  }
+  wave_sync();
+#pragma unroll
+  for (int g2 = 0; g2 < 2; ++g2)
 #pragma unroll
     for (int r = 0; r < 7; ++r) {
-      const float v = dh1[0][r] + dh2[0][r] + dh2[1][r];
-      if (slot_ok(r)) ds += v * (1.f - h1[0][r] * h1[0][r]) * sm.tab.w1s[4 * r + q];
+      const float v = slot_ok(r) ? row[25 * g2 + 4 * r + q] + row[E2 + 25 * g2 + 4 * r + q] : 0.f;
+      dh2[g2][r] += v;
+      t2[g2][r] = dh2[g2][r] * (1.f - t2[g2][r] * t2[g2][r]);  // dpre2
     }
-    ds = sumq(ds);
-    if (q == 0 && j < SEL) {
-      float4 out = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (j < n) {
-        const float h[3] = {sm.e.rh[0][j], sm.e.rh[1][j], sm.e.rh[2][j]};
-        out = pair_gradient(sm.e.s[j], sm.e.sw[j], sm.e.r[j], h, ds, dRt, drh, dsw, rc, rcs);
-      }
-      gout[(size_t)i * SEL + j] = out;
+  S7 dh1[1];
+  emul<2, 1>(dh1, wp.W2, t2);
+  float ds = 0.f;
+#pragma unroll
+  for (int r = 0; r < 7; ++r) {
+    const float v = dh1[0][r] + dh2[0][r] + dh2[1][r];
+    if (slot_ok(r)) ds += v * (1.f - h1[0][r] * h1[0][r]) * sm.tab.w1s[4 * r + q];
+  }
+  ds = sumq(ds);
+  if (q == 0 && j < SEL) {
+    float4 out = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (j < n) {
+      const float h[3] = {sm.e.rh[0][j], sm.e.rh[1][j], sm.e.rh[2][j]};
+      out = pair_gradient(sm.e.s[j], sm.e.sw[j], sm.e.r[j], h, ds, dRt, drh, dsw, rc, rcs);
     }
+    gout[(size_t)i * SEL + j] = out;
   }
 }
 
@@ -672,7 +812,7 @@ k_desc_bwd_b16(Tables w, WeightsB16 wp, const double *__restrict__ X, const int 
                const int *__restrict__ idx, const int *__restrict__ cnt, int c0, int ncen, const int *__restrict__ nlist,
                const int *__restrict__ nnei, const Grid *__restrict__ grids, const int *__restrict__ sys_of, float rc, float rcs,
                float ln_eps, const float *__restrict__ Gsave, const float *__restrict__ fit, float4 *__restrict__ gout) {
-  __shared__ SmemBwd<NB> smem[NA];
+  __shared__ SmemBwd<NB, NA> smem;
   const int count = idx ? *cnt : ncen;
   for (int b = blockIdx.x; b * NA < count; b += gridDim.x) {
     desc_bwd<NB, NA>(b, count, smem, w, wp, X, types, natoms, idx, c0, nlist, nnei, grids, sys_of, rc, rcs, ln_eps, Gsave, fit, gout);
