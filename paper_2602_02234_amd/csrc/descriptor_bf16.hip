@@ -193,20 +193,23 @@ __device__ __forceinline__ f4 tab4(const float *p, int t) {
   const int q = lane() >> 4;
   return t < 6 ? ldf4(p + 16 * t + 4 * q) : f4{p[96 + q], 0.f, 0.f, 0.f};
 }
-__device__ __forceinline__ void load_tab(Tab &t, const Tables &w, int ti, int tid, int nthr) {
-  for (int k = tid; k < NTYPES * E1; k += nthr) {
-    t.Bt[k] = w.Bt[ti * NTYPES * E1 + k];
-    if (k < M) {
-#pragma unroll
-      for (int a = 0; a < NATTN; ++a) {
-        t.gamma[a][k] = w.gamma[a][k];
-        t.beta[a][k] = w.beta[a][k];
-      }
-      t.b3[k] = w.b3[k];
-    }
-    if (k < E2) t.b2[k] = w.b2[k];
-    if (k < E1) t.w1s[k] = w.w1s[k];
+// By 128 threads (k from 0); every load is issued before the first is waited for.
+__device__ __forceinline__ void load_tab(Tab &t, const Tables &w, int ti, int k) {
+  static_assert(NTYPES * E1 <= 128 && NATTN == 2, "one entry of each table per thread");
+  const int km = min(k, M - 1), k2 = min(k, E2 - 1), k1 = min(k, E1 - 1);
+  const float bt = w.Bt[ti * NTYPES * E1 + min(k, NTYPES * E1 - 1)];
+  const float g0 = w.gamma[0][km], g1 = w.gamma[1][km], b0 = w.beta[0][km], b1 = w.beta[1][km];
+  const float b3 = w.b3[km], b2 = w.b2[k2], w1 = w.w1s[k1];
+  if (k < NTYPES * E1) t.Bt[k] = bt;
+  if (k < M) {
+    t.gamma[0][k] = g0;
+    t.gamma[1][k] = g1;
+    t.beta[0][k] = b0;
+    t.beta[1][k] = b1;
+    t.b3[k] = b3;
   }
+  if (k < E2) t.b2[k] = b2;
+  if (k < E1) t.w1s[k] = w1;
 }
 
 // h1 and t2 = h2 - [h1, h1] by groups and t3 = G - [h2, h2] of the lane's token; w2T, w3T: the
@@ -262,17 +265,26 @@ __device__ __forceinline__ f4 residual(const float *scr, int t) {
 template <int N, int NT> struct Fetch {
   static constexpr int P = N / 8, R = (P + NT - 1) / NT;
   bf8 v[R];
-  __device__ __forceinline__ explicit Fetch(const bf16_t *__restrict__ w) {
+  __device__ __forceinline__ Fetch() {}
+  __device__ __forceinline__ explicit Fetch(const bf16_t *__restrict__ w) { load(w); }
+  static __device__ __forceinline__ int thread() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));  // as lane()
+    return t;
+  }
+  __device__ __forceinline__ void load(const bf16_t *__restrict__ w) {
+    const int t = thread();
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const int k = threadIdx.x + r * NT;
+      const int k = t + r * NT;
       v[r] = ld8(w + 8 * (k < P ? k : 0));
     }
   }
   __device__ __forceinline__ void store(bf16_t *d) const {
+    const int t = thread();
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const int k = threadIdx.x + r * NT;
+      const int k = t + r * NT;
       if (k < P) *reinterpret_cast<bf8 *>(d + 8 * k) = v[r];
     }
   }
@@ -327,8 +339,8 @@ __device__ __forceinline__ void desc_fwd(int blk, int count, SmemFwd<NB, NA> &sh
   {
     const FetchEmb<NT> fe(wp);
     const Fetch<WMAT, NT> fu(wp.WqkT[0]), fy(wp.WvoT[0]);
-    load_tab(sm.tab, w, clamp_type(types[i]), tid, 64 * NB);
-    build_envf(sm.e, tid, X, types, nlist, i, n, natoms, g, rc, rcs);
+    if (tid < 128) build_envf(sm.e, tid, X, types, nlist, i, n, natoms, g, rc, rcs);
+    else if (tid < 256) load_tab(sm.tab, w, clamp_type(types[i]), tid - 128);
     fe.store(sh.E);
     fu.store(sh.W[0]);
     fy.store(sh.W[1]);
@@ -372,6 +384,9 @@ __device__ __forceinline__ void desc_fwd(int blk, int count, SmemFwd<NB, NA> &sh
         keys_dot<NB>(s, sm.G, XB(u), nb);  // S = U G^T
       }
       softmax_keys<NB>(s, sm.e, n, [](float v) { return __expf(v); });
+      // the next layer's weights, on their way during the rest of this one
+      const int next = layer + 1 < NATTN ? layer + 1 : layer;
+      const Fetch<WMAT, NT> fu(wp.WqkT[next]), fy(wp.WvoT[next]);
       {
         F100 h = {};
         // H = A G with A = sw E gate
@@ -382,8 +397,6 @@ __device__ __forceinline__ void desc_fwd(int blk, int count, SmemFwd<NB, NA> &sh
         }, nb);
         wmul(x, sh.W[1], XB(h));  // G + Y
       }
-      const int next = layer + 1 < NATTN ? layer + 1 : layer;
-      const Fetch<WMAT, NT> fu(wp.WqkT[next]), fy(wp.WvoT[next]);
       // LayerNorm; the centred rows are what the backward reads
       const float mu = sum100([&](int t, int k) { return x[t][k]; }) * (1.f / M);
 #pragma unroll
@@ -512,17 +525,23 @@ __device__ __forceinline__ void norm_bwd(F100 &go, const F100 &xh, float is, con
 //   dP = dA gate, rho = sum P dP, W = E (dP - rho), dS = sw W, dU = G^T dS, and dG_j = dX + Wqk dU.
 //   (dH comes first: beside E the products' operands would not fit the registers.)
 //   Column part (per key k): dG_k += sw_k sum_j (E gate)_jk dH_j + W_jk U_j, dsw_k += sum_j W_jk.
+// What the column part needs of the row part: U, and W of the token's keys.
+template <int NB> struct Column {
+  XB ub;
+  bf8 w[NB / 2];
+};
+
 template <int NB, int NA>
-__device__ __forceinline__ void layer_bwd(const WeightsB16 &wp, int layer, SmemBwd<NB, NA> &sh, AtomBwd<NB> &sm, F100 &go,
-                                          int jb, int n, int nb, float (&drh)[3], float &dsw) {
+__device__ __forceinline__ void layer_bwd_rows(const WeightsB16 &wp, int layer, SmemBwd<NB, NA> &sh, AtomBwd<NB> &sm,
+                                               F100 &go, Column<NB> &col, int jb, int n, int nb, float (&drh)[3]) {
   constexpr int NT = 64 * NB * NA;
   const int l = lane(), q = l >> 4, c = l & 15;
   const int j = 16 * jb + c;
   bf16_t *block = sm.G + 16 * jb * RW, *kblock = sm.K + 16 * jb * RW;
   float *tile = sh.tile[NA == 2 ? 0 : jb];
-  XB ub, hb;
+  XB &ub = col.ub, hb;
   const int p0 = piece0();
-  bf8 wb[NB / 2];
+  const Fetch<WMAT, NT> f(wp.Wqk[layer]);
   const float hj[3] = {sm.e.rh[0][j], sm.e.rh[1][j], sm.e.rh[2][j]};
   {
     F100 dh = {};
@@ -537,11 +556,8 @@ __device__ __forceinline__ void layer_bwd(const WeightsB16 &wp, int layer, SmemB
     ub = XB(u);
   }
   f4 E[NB], W[NB];
-  {
-    const Fetch<WMAT, NT> f(wp.Wqk[layer]);
-    keys_dot<NB>(E, sm.G, ub, nb);
-    f.store(sh.W[0]);
-  }
+  keys_dot<NB>(E, sm.G, ub, nb);
+  f.store(sh.W[0]);
   softmax_keys<NB>(E, sm.e, n, [](float v) { return __expf(v); });
   keys_dot<NB>(W, sm.G, hb, nb);  // dA
   __syncthreads();  // K is free, Wqk is there
@@ -550,6 +566,18 @@ __device__ __forceinline__ void layer_bwd(const WeightsB16 &wp, int layer, SmemB
   float rj[4];
 #pragma unroll
   for (int s = 0; s < 4; ++s) rj[s] = c < 3 ? sm.e.rh[c][16 * jb + 4 * q + (s ^ q)] : 0.f;
+  // a tile is read back while the next one's terms are formed
+  const auto column_sums = [&](int kt) {
+    const f4 ct = tile_get<NB>(kblock, tile);
+    f4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < 4; ++s) acc = mfma(rj[s], ct[s], acc);
+    if (q == 0) {
+      const float swk = sm.e.sw[16 * kt + c];
+      float *o = sm.drhw[jb] + 3 * (16 * kt + c);
+      o[0] = swk * acc[0]; o[1] = swk * acc[1]; o[2] = swk * acc[2];
+    }
+  };
 #pragma unroll
   for (int p = 0; p < NB / 2; ++p)
     if (2 * p < nb) {
@@ -562,6 +590,7 @@ __device__ __forceinline__ void layer_bwd(const WeightsB16 &wp, int layer, SmemB
         const f4 gt = rx * hj[0] + ry * hj[1] + rz * hj[2];
         const f4 cc = W[kt] * E[kt];
         const f4 dC = sw * cc, dP = W[kt] * gt, pr = sw * E[kt] * dP;
+        if (kt > 0) column_sums(kt - 1);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           rho += pr[i];
@@ -574,18 +603,10 @@ __device__ __forceinline__ void layer_bwd(const WeightsB16 &wp, int layer, SmemB
         wave_sync();
         tile_put<NB>(kblock, tile, cc);
         wave_sync();
-        const f4 ct = tile_get<NB>(kblock, tile);
-        f4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s = 0; s < 4; ++s) acc = mfma(rj[s], ct[s], acc);
-        if (q == 0) {
-          const float swk = sm.e.sw[16 * kt + c];
-          float *o = sm.drhw[jb] + 3 * (16 * kt + c);
-          o[0] = swk * acc[0]; o[1] = swk * acc[1]; o[2] = swk * acc[2];
-        }
       }
       *reinterpret_cast<bf8 *>(kblock + piece(p0, p)) = pack(ea[0], ea[1]);
     }
+  column_sums(2 * ((nb + 1) / 2) - 1);
   rho = sumq(rho);
   drh[0] += sumq(hx);
   drh[1] += sumq(hy);
@@ -602,7 +623,7 @@ __device__ __forceinline__ void layer_bwd(const WeightsB16 &wp, int layer, SmemB
       const f4 s = sum16(v[h]);
       if (c == 0) stf4(sm.wsum[jb] + 16 * kt + 4 * q, s);
     }
-    wb[p] = pack(v[0], v[1]);
+    col.w[p] = pack(v[0], v[1]);
     ds[p] = pack(d[0], d[1]);
   }
   F100 du = {};
@@ -613,24 +634,40 @@ __device__ __forceinline__ void layer_bwd(const WeightsB16 &wp, int layer, SmemB
   fe.store(sh.W[0]);
   put_block(block, hb);
   __syncthreads();
+}
+
+// The rest, in two steps around the sums over dH: `between` may issue loads there.
+template <int NB, int NA, class Fn>
+__device__ __forceinline__ void layer_bwd_columns(AtomBwd<NB> &sm, F100 &go, const Column<NB> &col, int jb, int nb,
+                                                  float (&drh)[3], float &dsw, const Fn &between) {
+  const int l = lane(), c = l & 15;
+  const int j = 16 * jb + c;
+  bf16_t *block = sm.G + 16 * jb * RW, *kblock = sm.K + 16 * jb * RW;
+  const int p0 = piece0();
   F100 acc = {};
   const int cj = (column0() ^ (32 * (jb >> 1))) + 4 * (jb & 1);
   const auto column = [&](int p) { return column8(sm.K + 32 * p * RW, cj); };
   rows_sum<NB>(acc, sm.G, column, nb);
   __syncthreads();
-  put_block(block, ub);
+  between();
+  put_block(block, col.ub);
 #pragma unroll
   for (int p = 0; p < NB / 2; ++p)
-    if (2 * p < nb) *reinterpret_cast<bf8 *>(kblock + piece(p0, p)) = wb[p];
+    if (2 * p < nb) *reinterpret_cast<bf8 *>(kblock + piece(p0, p)) = col.w[p];
   __syncthreads();
   rows_sum<NB>(acc, sm.G, column, nb);
   const float swj = sm.e.sw[j];
 #pragma unroll
   for (int t = 0; t < 7; ++t) go[t] += swj * acc[t];
-  for (int u = 0; u < nb; ++u) {
-    dsw += sm.wsum[u][j];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) drh[a] += sm.drhw[u][3 * j + a];
+  for (int u = 0; u < NB; ++u) {
+    const float ws = sm.wsum[u][j], d0 = sm.drhw[u][3 * j], d1 = sm.drhw[u][3 * j + 1], d2 = sm.drhw[u][3 * j + 2];
+    if (u < nb) {
+      dsw += ws;
+      drh[0] += d0;
+      drh[1] += d1;
+      drh[2] += d2;
+    }
   }
   __syncthreads();
 }
@@ -667,20 +704,33 @@ __device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB, NA> &sh
   const int l = lane(), q = l >> 4, c = l & 15;
   const float *gs = Gsave + (size_t)i * NATTN * GSAVE_LAYER + 1600 * jb;
   bf16_t *block = sm.G + 16 * jb * RW, *kblock = sm.K + 16 * jb * RW;
+  F100 x, xh;  // the centred rows of layers 0 and 1
   {
+    const int nj = tid < 128 ? env_neighbour(nlist, i, tid, n) : 0;
+    load_block(x, gs);
+    load_block(xh, gs + GSAVE_LAYER);
     const Fetch<WMAT, NT> fv(wp.Wvo[NATTN - 1]), fq(wp.WqkT[NATTN - 1]);
-    for (int k = nb ? 16 * nb + tid : SEL; k < SEL; k += 64 * NB) gout[(size_t)i * SEL + k] = make_float4(0.f, 0.f, 0.f, 0.f);
-    load_tab(sm.tab, w, clamp_type(types[i]), tid, 64 * NB);
-    build_envf(sm.e, tid, X, types, nlist, i, n, natoms, g, rc, rcs);
-    const float *dTi = fit + (size_t)i * ND;
-    for (int k = tid; k < M * 4; k += 64 * NB) {
-      float v = dTi[FIT_DT + k];
-      if (k < 4 * M2)
-        for (int p = 0; p < FIT_NPART; ++p) v += dTi[FIT_PART + 4 * M2 * p + k];
-      sm.dT[k] = v;
+    if (tid < 128) {
+      env_entry(sm.e, tid, nj, X, types, i, n, natoms, g, rc, rcs);
+    } else if (tid < 256) {
+      load_tab(sm.tab, w, clamp_type(types[i]), tid - 128);
+    } else {
+      const float *dTi = fit + (size_t)i * ND;
+#pragma unroll
+      for (int u = 0; u < (M * 4 + 64 * NB - 257) / (64 * NB - 256); ++u) {
+        const int k = tid - 256 + u * (64 * NB - 256);
+        if (k < M * 4) {
+          float v = dTi[FIT_DT + k];
+          if (k < 4 * M2)
+#pragma unroll
+            for (int p = 0; p < FIT_NPART; ++p) v += dTi[FIT_PART + 4 * M2 * p + k];
+          sm.dT[k] = v;
+        }
+      }
     }
     fv.store(sh.wvo());
     fq.store(sh.wqkT());
+    for (int k = nb ? 16 * nb + tid : SEL; k < SEL; k += 64 * NB) gout[(size_t)i * SEL + k] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
   if (jb >= nb) {
     zero_block(block);
@@ -696,9 +746,6 @@ __device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB, NA> &sh
     layer_bwd_idle<NB, NA>(wp, 0, sh, kblock);
     return;
   }
-  F100 x, xh;  // the centred rows of layers 0 and 1
-  load_block(x, gs);
-  load_block(xh, gs + GSAVE_LAYER);
   __syncthreads();
   const int j = 16 * jb + c;
   F100 go;
@@ -734,11 +781,16 @@ __device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB, NA> &sh
     tile_barrier();
   }
   __syncthreads();
-  layer_bwd<NB, NA>(wp, 1, sh, sm, go, jb, n, nb, drh, dsw);
+  Column<NB> col;
+  layer_bwd_rows<NB, NA>(wp, 1, sh, sm, go, col, jb, n, nb, drh);
   {
     F100 x0, t3;
-    const Fetch<WMAT, NT> fv(wp.Wvo[0]), fq(wp.WqkT[0]);
-    load_block(x0, gs);
+    Fetch<WMAT, NT> fv, fq;
+    layer_bwd_columns<NB, NA>(sm, go, col, jb, nb, drh, dsw, [&] {  // layer 0's weights and rows, on their way from here
+      fv.load(wp.Wvo[0]);
+      fq.load(wp.WqkT[0]);
+      load_block(x0, gs);
+    });
     S7 h1[1], t2[2];
     float *scr = reinterpret_cast<float *>(block);
     embed(sm.tab, sh.W[0], sh.W[0] + W2T_N, sm.e.s[j], sm.e.tj[j], scr, h1, t2, t3);
@@ -753,7 +805,8 @@ __device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB, NA> &sh
     norm_bwd(go, x0, is, sm.tab.gamma[0]);
   }
   __syncthreads();
-  layer_bwd<NB, NA>(wp, 0, sh, sm, go, jb, n, nb, drh, dsw);
+  layer_bwd_rows<NB, NA>(wp, 0, sh, sm, go, col, jb, n, nb, drh);
+  layer_bwd_columns<NB, NA>(sm, go, col, jb, nb, drh, dsw, [] {});
   // embedding backward and the pair gradients of the wave's tokens
   float *row = reinterpret_cast<float *>(sm.G) + j * LDG;  // over G and K
   S7 h1[1], t2[2], dh2[2];

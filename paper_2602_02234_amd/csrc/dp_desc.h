@@ -76,33 +76,43 @@ template <int NB> struct EnvF {
   int tj[16 * NB];
 };
 
+// The neighbour of token j as listed (its load can be issued ahead of others), and the entry made from it.
+__device__ __forceinline__ int env_neighbour(const int *__restrict__ nlist, int i, int j, int n) {
+  return j < n ? nlist[(size_t)i * SEL + j] : i;
+}
 template <int NB>
-__device__ void build_envf(EnvF<NB> &e, int tid, const double *__restrict__ X, const int *__restrict__ types,
-                           const int *__restrict__ nlist, int i, int n, int natoms, const Grid &g, float rc, float rcs) {
-  for (int j = tid; j < 16 * NB; j += 64 * NB) {
-    float s = 0.f, sw = 0.f, r = 1.f, hx = 0.f, hy = 0.f, hz = 0.f;
-    int tj = 0;
-    if (j < n) {
-      int nj = nlist[(size_t)i * SEL + j];
-      if (nj < 0 || nj >= natoms) nj = i;  // never read outside the coordinate array
-      tj = clamp_type(types[nj]);
-      double d[3];
-      for (int a = 0; a < 3; ++a) {
-        double v = X[3 * nj + a] - X[3 * i + a];
-        if (g.periodic) v -= g.L[a] * rint(v * g.invL[a]);
-        d[a] = v;
-      }
-      const float dx = (float)d[0], dy = (float)d[1], dz = (float)d[2];
-      r = sqrtf(dx * dx + dy * dy + dz * dz);
-      const float u = (r - rcs) / (rc - rcs);
-      if (r < rcs) sw = 1.f;
-      else if (r < rc) sw = u * u * u * (-6.f * u * u + 15.f * u - 10.f) + 1.f;
-      s = sw / r;
-      hx = dx / r; hy = dy / r; hz = dz / r;
+__device__ __forceinline__ void env_entry(EnvF<NB> &e, int j, int nj, const double *__restrict__ X,
+                                          const int *__restrict__ types, int i, int n, int natoms, const Grid &g, float rc,
+                                          float rcs) {
+  if (j >= 16 * NB) return;
+  float s = 0.f, sw = 0.f, r = 1.f, hx = 0.f, hy = 0.f, hz = 0.f;
+  int tj = 0;
+  if (j < n) {
+    if (nj < 0 || nj >= natoms) nj = i;  // never read outside the coordinate array
+    tj = clamp_type(types[nj]);
+    double d[3];
+    for (int a = 0; a < 3; ++a) {
+      double v = X[3 * nj + a] - X[3 * i + a];
+      if (g.periodic) v -= g.L[a] * rint(v * g.invL[a]);
+      d[a] = v;
     }
-    e.s[j] = s; e.sw[j] = sw; e.r[j] = r; e.tj[j] = tj;
-    e.rh[0][j] = hx; e.rh[1][j] = hy; e.rh[2][j] = hz;
+    const float dx = (float)d[0], dy = (float)d[1], dz = (float)d[2];
+    r = sqrtf(dx * dx + dy * dy + dz * dz);
+    const float u = (r - rcs) / (rc - rcs);
+    if (r < rcs) sw = 1.f;
+    else if (r < rc) sw = u * u * u * (-6.f * u * u + 15.f * u - 10.f) + 1.f;
+    s = sw / r;
+    hx = dx / r; hy = dy / r; hz = dz / r;
   }
+  e.s[j] = s; e.sw[j] = sw; e.r[j] = r; e.tj[j] = tj;
+  e.rh[0][j] = hx; e.rh[1][j] = hy; e.rh[2][j] = hz;
+}
+
+template <int NB>
+__device__ __forceinline__ void build_envf(EnvF<NB> &e, int tid, const double *__restrict__ X, const int *__restrict__ types,
+                                           const int *__restrict__ nlist, int i, int n, int natoms, const Grid &g, float rc,
+                                           float rcs) {
+  env_entry(e, tid, env_neighbour(nlist, i, tid, n), X, types, i, n, natoms, g, rc, rcs);
 }
 
 // ------------------------------------------------------------ embedding net
@@ -170,10 +180,12 @@ __device__ __forceinline__ f4 gate4(const EnvF<NB> &e, int kt, const float (&h)[
 template <int NB, int NA> struct Part {
   int half, jb, tid, i, n, nb, steps;
   __device__ __forceinline__ Part(int blk, const int *__restrict__ idx, int c0, int count, const int *__restrict__ nnei) {
-    const int wv = __builtin_amdgcn_readfirstlane(wave_id());
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));  // as lane()
+    const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
     half = NA == 1 ? 0 : wv / NB;
     jb = wv - half * NB;
-    tid = threadIdx.x - half * 64 * NB;
+    tid = t - half * 64 * NB;
     steps = 0;
 #pragma unroll
     for (int a = 0; a < NA; ++a) {
