@@ -43,11 +43,12 @@ constexpr int LDX = 68;   // row stride of a wave's transposition scratch [16 to
 constexpr int LDW = 20;   // ... of a 16 x 16 tile in it
 static_assert(M == 100 && E1 == 25 && E2 == 50, "the fragment layouts below are written for these widths");
 
-// acc += W x for a 100 x 100 matrix W[out][k] in fragment order: tile t (outputs
+// out = W x (ADD: out += W x, summed by itself first) for a 100 x 100 matrix W[out][k] in fragment order: tile t (outputs
 // 16 t + row for t < 6; 96 + row / 4 for t = 6) at 1600 t, its k = 16 kb + 4 q + s at
 // + 256 kb + 4 lane + s, its k = 96 + q at + 1536 + lane.  The next tile's operands are
 // loaded while the current one's 25 products run.
-__device__ __forceinline__ void wmul(F100 &acc, const float *__restrict__ w, const F100 &x) {
+template <bool ADD = false>
+__device__ __forceinline__ void wmul(F100 &out, const float *__restrict__ w, const F100 &x) {
   const int l = lane();
   f4 a[6];
   float at;
@@ -65,11 +66,14 @@ __device__ __forceinline__ void wmul(F100 &acc, const float *__restrict__ w, con
       bt = w[1600 * (t + 1) + 1536 + l];
     }
     tile_barrier();
+    f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int kb = 0; kb < 6; ++kb)
 #pragma unroll
-      for (int s = 0; s < 4; ++s) acc[t] = mfma(a[kb][s], x[kb][s], acc[t]);
-    acc[t] = mfma(at, x[6][0], acc[t]);
+      for (int s = 0; s < 4; ++s) acc = mfma(a[kb][s], x[kb][s], acc);
+    acc = mfma(at, x[6][0], acc);
+    if (ADD) out[t] += acc;
+    else out[t] = acc;
     if (t < 6) {
 #pragma unroll
       for (int kb = 0; kb < 6; ++kb) a[kb] = b[kb];
@@ -126,57 +130,93 @@ __device__ __forceinline__ void keys_sum(F100 &acc, const float *G, const Y &y, 
     }
 }
 
-// out[og] += W in over NI input groups: W at ((og * 2 + u) * NI * 2 + 2 ig + piece) * 256.
-template <int NI, int NO>
-__device__ __forceinline__ void emul(S7 (&out)[NO], const float *__restrict__ w, const S7 (&in)[NI]) {
-  const int l = lane();
+// out[og] = W in over NI input groups: tile it = 2 og + u at it NI 512, piece p at + 256 p.  With AHEAD
+// the tiles' weights are loaded two tiles ahead, the first two by the constructor, which a caller
+// runs early (32 NI registers).
+template <int NI, int NO, bool AHEAD> struct Emul {
+  f4 a[2][2 * NI];
+  const float *w;
+  __device__ __forceinline__ void fetch(f4 (&x)[2 * NI], int it) const {
 #pragma unroll
-  for (int og = 0; og < NO; ++og)
+    for (int p = 0; p < 2 * NI; ++p) x[p] = ldf4(w + (it * 2 * NI + p) * 256);
+  }
+  __device__ __forceinline__ explicit Emul(const float *__restrict__ wm) : w(wm + 4 * lane()) {
+    if (AHEAD) {
+      fetch(a[0], 0);
+      fetch(a[1], 1);
+    }
+  }
+  __device__ __forceinline__ void operator()(S7 (&out)[NO], const S7 (&in)[NI]) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      f4 acc = {0.f, 0.f, 0.f, 0.f};
-      f4 a[2 * NI];
-#pragma unroll
-      for (int p = 0; p < 2 * NI; ++p) a[p] = ldf4(w + ((og * 2 + u) * NI * 2 + p) * 256 + 4 * l);
+    for (int it = 0; it < 2 * NO; ++it) {
+      f4 n[2 * NI];
+      if (!AHEAD) fetch(a[it & 1], it);
+      else if (it + 2 < 2 * NO) fetch(n, it + 2);
       tile_barrier();
+      f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int ig = 0; ig < NI; ++ig)
 #pragma unroll
-        for (int r = 0; r < 7; ++r) acc = mfma(a[2 * ig + r / 4][r % 4], in[ig][r], acc);
+        for (int r = 0; r < 7; ++r) acc = mfma(a[it & 1][2 * ig + r / 4][r % 4], in[ig][r], acc);
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        if (4 * u + i < 7) out[og][4 * u + i] = acc[i];
+        if (4 * (it & 1) + i < 7) out[it / 2][4 * (it & 1) + i] = acc[i];
+      if (AHEAD && it + 2 < 2 * NO)
+#pragma unroll
+        for (int p = 0; p < 2 * NI; ++p) a[it & 1][p] = n[p];
     }
+  }
+};
+
+// tanh without branches: Taylor's series up to 0.45 (its remainder there is below 1e-8), beyond it
+// 1 - 2 t / (1 + t) with t = exp(-2 |x|) from the hardware exponential and reciprocal, the rounding
+// of the exponent, of 1 + t and of the quotient put back.  Within 3 units in the last place in a simulation
+// with the hardware functions off by one, 0.3 in the mean; tanhf's branches took a third of the
+// embedding's time.
+__device__ __forceinline__ float tanh_fast(float x) {
+  constexpr float C = 2.885390043258667f, CL = 3.851926e-8f;  // 2 / ln 2
+  const float ax = fabsf(x), y = -C * ax, yl = fmaf(-C, ax, -y) - CL * ax;
+  float t = __builtin_amdgcn_exp2f(y);
+  t = fmaf(t, yl * 0.6931471805599453f, t);
+  const float d = 1.f + t, dl = t - (d - 1.f), r = __builtin_amdgcn_rcpf(d), q = 2.f * t * r;
+  const float big = 1.f - fmaf(fmaf(-dl, q, fmaf(-d, q, 2.f * t)), r, q);
+  const float z = x * x;
+  float p = fmaf(fmaf(21844.f / 6081075.f, z, -1382.f / 155925.f), z, 62.f / 2835.f);
+  p = fmaf(fmaf(fmaf(p, z, -17.f / 315.f), z, 2.f / 15.f), z, -1.f / 3.f);
+  return ax < 0.45f ? fmaf(p * z, x, x) : copysignf(big, x);
 }
 
 // h1, t2 = h2 - [h1, h1] and t3 = G - [h2, h2] of the lane's token.
+template <bool AHEAD>
 __device__ __forceinline__ void embed(const Weights<float> &w, float s, int ti, int tj, S7 (&h1)[1], S7 (&t2)[2], S7 (&t3)[4]) {
   const int q = lane() >> 4;
+  Emul<1, 2, AHEAD> e2(w.W2T);
+  Emul<2, 4, AHEAD> e3(w.W3T);
   const float *bt = w.Bt + (ti * NTYPES + tj) * E1;
 #pragma unroll
   for (int r = 0; r < 7; ++r) {
     const int f = slot_ok(r) ? 4 * r + q : 0;
-    const float v = tanhf(s * w.w1s[f] + bt[f]);
+    const float v = tanh_fast(s * w.w1s[f] + bt[f]);
     h1[0][r] = slot_ok(r) ? v : 0.f;
   }
-  emul<1, 2>(t2, w.W2T, h1);
+  e2(t2, h1);
   S7 h2[2];
 #pragma unroll
   for (int g = 0; g < 2; ++g)
 #pragma unroll
     for (int r = 0; r < 7; ++r) {
       const int f = slot_ok(r) ? 25 * g + 4 * r + q : 0;
-      const float v = tanhf(t2[g][r] + w.b2[f]);
+      const float v = tanh_fast(t2[g][r] + w.b2[f]);
       t2[g][r] = slot_ok(r) ? v : 0.f;
       h2[g][r] = t2[g][r] + h1[0][r];
     }
-  emul<2, 4>(t3, w.W3T, h2);
+  e3(t3, h2);
 #pragma unroll
   for (int g = 0; g < 4; ++g)
 #pragma unroll
     for (int r = 0; r < 7; ++r) {
       const int f = slot_ok(r) ? 25 * g + 4 * r + q : 0;
-      const float v = tanhf(t3[g][r] + w.b3[f]);
+      const float v = tanh_fast(t3[g][r] + w.b3[f]);
       t3[g][r] = slot_ok(r) ? v : 0.f;
     }
 }
@@ -206,7 +246,7 @@ __device__ __forceinline__ void desc_fwd(int blk, int count, SmemFwd<NB> *smem, 
   float *row = sm.G + j * LDG;
   if (act) {
     S7 h1[1], t2[2], t3[4];
-    embed(w, sm.e.s[j], ti, sm.e.tj[j], h1, t2, t3);
+    embed<true>(w, sm.e.s[j], ti, sm.e.tj[j], h1, t2, t3);
     put_embedding(row, h1, t2, t3);
   }
   __syncthreads();
@@ -215,7 +255,7 @@ __device__ __forceinline__ void desc_fwd(int blk, int count, SmemFwd<NB> *smem, 
   for (int layer = 0; layer < NATTN; ++layer) {
     F100 y = {};
     if (act) {
-      F100 x, u = {};
+      F100 x, u;
       get_row(x, row);
       wmul(u, w.WqkT[layer], x);  // U
       f4 s[NB];
@@ -340,10 +380,16 @@ __device__ __forceinline__ f4 transpose_tile(const f4 &y, float *scr) {
   return o;
 }
 
+// Tile t of a per-feature table, in a token's arrangement.
+__device__ __forceinline__ f4 tab4(const float *__restrict__ p, int t) {
+  const int q = lane() >> 4;
+  return t < 6 ? ldf4(p + 16 * t + 4 * q) : f4{p[96 + q], 0.f, 0.f, 0.f};
+}
+
 // Backward of one layer, its input rows in sm.G.  go: the gradient of the layer's output
-// for the wave's tokens; d: the layer's saved centred rows.  On return sm.G holds the
+// for the wave's tokens; saved: the layer's centred rows.  On return sm.G holds the
 // gradient of the layer's input and every thread has passed a barrier.
-//   Row part (per token j): U, S, E recomputed; dX through the LayerNorm, dH = Wvo dX,
+//   Row part (per token j): dX through the LayerNorm, dH = Wvo dX; U, S, E recomputed;
 //   dA = G dH, then per key P = sw E, dP = dA gate, rho = sum P dP, W = E (dP - rho),
 //   dS = sw W, dU = G^T dS, and dG_j = dX + Wqk dU.
 //   Column part (per key k): dG_k += sw_k sum_j (E gate)_jk dH_j + W_jk U_j and
@@ -351,17 +397,28 @@ __device__ __forceinline__ f4 transpose_tile(const f4 &y, float *scr) {
 //   (j + p) mod nb; a barrier ends each step, so each sum has a fixed order.
 template <int NB>
 __device__ __forceinline__ void layer_bwd(const Weights<float> &w, int layer, SmemBwd<NB> &sm, F100 &go,
-                                          const float *__restrict__ saved, int jb, int tid, int n, int nb, int steps,
+                                          const float *__restrict__ saved, int jb, int n, int nb, int steps,
                                           float ln_eps) {
   const int l = lane(), q = l >> 4, c = l & 15;
   const int j = 16 * jb + c;
   float *row = sm.G + j * LDG;
   float *scr = sm.scr[jb];
-  const bool act = jb < nb;
-  F100 u = {}, dh = {}, dx;
+  F100 u, dh, dx;
   f4 E[NB], W[NB];
   const float hj[3] = {sm.e.rh[0][j], sm.e.rh[1][j], sm.e.rh[2][j]};
-  if (act) {
+  {
+    {  // LayerNorm backward: dX = (dxh - mean(dxh) - xh mean(dxh xh)) / sigma, dxh = gamma dG_out
+      F100 xh;
+      load_block(xh, saved + 1600 * jb);
+      const float is = normalise(xh, ln_eps);
+#pragma unroll
+      for (int t = 0; t < 7; ++t) dx[t] = tab4(w.gamma[layer], t) * go[t];
+      const float s0 = sum100([&](int t, int k) { return dx[t][k]; }) * (1.f / M);
+      const float s1 = sum100([&](int t, int k) { return dx[t][k] * xh[t][k]; }) * (1.f / M);
+#pragma unroll
+      for (int t = 0; t < 7; ++t) dx[t] = (dx[t] - s0 - xh[t] * s1) * is;
+    }
+    wmul(dh, w.Wvo[layer], dx);
     {
       F100 x;
       get_row(x, row);
@@ -369,19 +426,6 @@ __device__ __forceinline__ void layer_bwd(const Weights<float> &w, int layer, Sm
     }
     keys_dot<NB>(E, sm.G, u, nb);
     softmax_keys<NB>(E, sm.e, n, [](float v) { return expf(v); });
-    {  // LayerNorm backward: dX = (dxh - mean(dxh) - xh mean(dxh xh)) / sigma, dxh = gamma dG_out
-      F100 xh, ga;
-      load_block(xh, saved + 1600 * jb);
-      const float is = normalise(xh, ln_eps);
-      get_table(ga, w.gamma[layer]);
-#pragma unroll
-      for (int t = 0; t < 7; ++t) dx[t] = ga[t] * go[t];
-      const float s0 = sum100([&](int t, int k) { return dx[t][k]; }) * (1.f / M);
-      const float s1 = sum100([&](int t, int k) { return dx[t][k] * xh[t][k]; }) * (1.f / M);
-#pragma unroll
-      for (int t = 0; t < 7; ++t) dx[t] = (dx[t] - s0 - xh[t] * s1) * is;
-    }
-    wmul(dh, w.Wvo[layer], dx);
     keys_dot<NB>(W, sm.G, dh, nb);  // dA
     float rho = 0.f, hx = 0.f, hy = 0.f, hz = 0.f;
     // columns of dC rhat: sum_j rhat_j (dA E)_jk, A operand rhat of token 4 q + s in rows a < 3
@@ -426,14 +470,11 @@ __device__ __forceinline__ void layer_bwd(const Weights<float> &w, int layer, Sm
       W[kt] = E[kt] * (W[kt] - rho);
       return ldf4(sm.e.sw + 16 * kt + 4 * q) * W[kt];  // dS
     }, nb);
-    F100 r = {};
-    wmul(r, w.Wqk[layer], du);
-#pragma unroll
-    for (int t = 0; t < 7; ++t) dx[t] += r[t];
+    wmul<true>(dx, w.Wqk[layer], du);
   }
   __syncthreads();  // the layer's input is no longer needed
   f4 ut[7], ht[7];
-  if (act) {
+  {
     put_row(row, dx);
     transpose_block(ut, u, scr);
     transpose_block(ht, dh, scr);
@@ -449,7 +490,7 @@ __device__ __forceinline__ void layer_bwd(const Weights<float> &w, int layer, Sm
 #pragma unroll 1
   for (int p = 0; p < steps; ++p) {
     __syncthreads();
-    if (act && p < nb) {
+    if (p < nb) {
       int kb = jb + p;
       if (kb >= nb) kb -= nb;
       wave_sync();
@@ -488,10 +529,10 @@ __device__ __forceinline__ void layer_bwd(const Weights<float> &w, int layer, Sm
     }
   }
   __syncthreads();
-  for (int k = tid; k < 16 * nb * 3; k += 64 * NB) {
-    float v = sm.drh[k];
-    for (int u2 = 0; u2 < nb; ++u2) v += sm.drhw[u2][k];
-    sm.drh[k] = v;
+  if (q < 3) {  // the wave's keys: component q of their gate gradients
+    float v = sm.drh[3 * j + q];
+    for (int u2 = 0; u2 < nb; ++u2) v += sm.drhw[u2][3 * j + q];
+    sm.drh[3 * j + q] = v;
   }
 }
 
@@ -506,7 +547,6 @@ __device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB> *smem, 
   const Grid g = grids[sys_of[i]];
   const int ti = clamp_type(types[i]);
   const int l = lane(), q = l >> 4, c = l & 15;
-  const bool act = jb < nb;
   const float *gs = Gsave + (size_t)i * NATTN * GSAVE_LAYER;
   build_envf(sm.e, tid, X, types, nlist, i, n, natoms, g, rc, rcs);
   for (int k = tid; k < 16 * NB; k += 64 * NB) {
@@ -520,57 +560,65 @@ __device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB> *smem, 
       for (int p = 0; p < FIT_NPART; ++p) v += dTi[FIT_PART + 4 * M2 * p + k];
     sm.dT[k] = v;
   }
+  for (int k = nb ? 16 * nb + tid : SEL; k < SEL; k += 64 * NB) gout[(size_t)i * SEL + k] = make_float4(0.f, 0.f, 0.f, 0.f);
   __syncthreads();
+  // A wave without tokens only passes the others' barriers, on a path of its own, so that no register
+  // of their work is carried past a branch around it.
+  if (jb >= nb) {
+    for (int k = 0; k < 2 * (pt.steps + 2) + 4; ++k) __syncthreads();
+    return;
+  }
   const int j = 16 * jb + c;
   float *row = sm.G + j * LDG;
-  F100 go = {};
-  if (act) {
-    F100 x, ga, be;
+  F100 go;
+  {
+    F100 x;
     // the top layer's input: layer 0's output
     load_block(x, gs + 1600 * jb);
     normalise(x, ln_eps);
-    get_table(ga, w.gamma[0]);
-    get_table(be, w.beta[0]);
 #pragma unroll
-    for (int t = 0; t < 7; ++t) x[t] = ga[t] * x[t] + be[t];
+    for (int t = 0; t < 7; ++t) x[t] = tab4(w.gamma[0], t) * x[t] + tab4(w.beta[0], t);
     put_row(row, x);
     // dG = Rt dT^T / sel for its output, and dRt = G dT / sel
     load_block(x, gs + GSAVE_LAYER + 1600 * jb);
     normalise(x, ln_eps);
-    get_table(ga, w.gamma[1]);
-    get_table(be, w.beta[1]);
     const float inv_sel = 1.f / (float)SEL;
     const float sj = sm.e.s[j];
     const float rt1 = sj * sm.e.rh[0][j], rt2 = sj * sm.e.rh[1][j], rt3 = sj * sm.e.rh[2][j];
     f4 p = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int t = 0; t < 7; ++t)
+    for (int t = 0; t < 7; ++t) {
+      tile_barrier();
+      const f4 gv = tab4(w.gamma[1], t) * x[t] + tab4(w.beta[1], t);
 #pragma unroll
       for (int k = 0; k < (t < 6 ? 4 : 1); ++k) {
         const f4 d = ldf4(sm.dT + 4 * (t < 6 ? 16 * t + 4 * q + k : 96 + q));
         go[t][k] = (sj * d[0] + rt1 * d[1] + rt2 * d[2] + rt3 * d[3]) * inv_sel;
-        p += (ga[t][k] * x[t][k] + be[t][k]) * d;
+        p += gv[k] * d;
       }
+    }
 #pragma unroll
     for (int a = 0; a < 4; ++a) p[a] = sumq(p[a]) * inv_sel;
     if (q == 0) *reinterpret_cast<f4 *>(sm.dRt + 4 * j) = p;
   }
   __syncthreads();
-  layer_bwd<NB>(w, 1, sm, go, gs + GSAVE_LAYER, jb, tid, n, nb, pt.steps, ln_eps);
-  if (act) get_row(go, row);
+  layer_bwd<NB>(w, 1, sm, go, gs + GSAVE_LAYER, jb, n, nb, pt.steps, ln_eps);
+  get_row(go, row);
   __syncthreads();
-  if (act) {
+  {
     S7 h1[1], t2[2], t3[4];
-    embed(w, sm.e.s[j], ti, sm.e.tj[j], h1, t2, t3);
+    embed<(NB > NB_SMALL)>(w, sm.e.s[j], ti, sm.e.tj[j], h1, t2, t3);
     put_embedding(row, h1, t2, t3);
   }
   __syncthreads();
-  layer_bwd<NB>(w, 0, sm, go, gs, jb, tid, n, nb, pt.steps, ln_eps);
+  layer_bwd<NB>(w, 0, sm, go, gs, jb, n, nb, pt.steps, ln_eps);
   __syncthreads();
   // embedding backward and the pair gradients of the wave's tokens
-  if (act) {
+  {
     S7 h1[1], t2[2], t3[4];
-    embed(w, sm.e.s[j], ti, sm.e.tj[j], h1, t2, t3);
+    embed<(NB > NB_SMALL)>(w, sm.e.s[j], ti, sm.e.tj[j], h1, t2, t3);
+    tile_barrier();
+    Emul<4, 2, (NB > NB_SMALL)> e3(w.W3);
     S7 dh2[2], d[4];
 #pragma unroll
     for (int g4 = 0; g4 < 4; ++g4)
@@ -580,7 +628,9 @@ __device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB> *smem, 
         d[g4][r] = v;
         t3[g4][r] = v * (1.f - t3[g4][r] * t3[g4][r]);  // dpre3
       }
-    emul<4, 2>(dh2, w.W3, t3);
+    e3(dh2, t3);
+    tile_barrier();
+    Emul<2, 1, true> e2(w.W2);
 #pragma unroll
     for (int g2 = 0; g2 < 2; ++g2)
 #pragma unroll
@@ -589,7 +639,7 @@ __device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB> *smem, 
         t2[g2][r] = dh2[g2][r] * (1.f - t2[g2][r] * t2[g2][r]);  // dpre2
       }
     S7 dh1[1];
-    emul<2, 1>(dh1, w.W2, t2);
+    e2(dh1, t2);
     float ds = 0.f;
 #pragma unroll
     for (int r = 0; r < 7; ++r) {
@@ -606,7 +656,6 @@ __device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB> *smem, 
       gout[(size_t)i * SEL + j] = out;
     }
   }
-  for (int k = nb ? 16 * nb + tid : SEL; k < SEL; k += 64 * NB) gout[(size_t)i * SEL + k] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
 // One workgroup per NA atoms of its instance's list; the 8-wave instance loops over its list
