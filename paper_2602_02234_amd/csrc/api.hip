@@ -752,8 +752,8 @@ void collect(dp_model *m, int last) {
 
 // Enqueues one step (no host synchronisation; nothing here allocates).  The per-system
 // grids and atom offsets must already be in ws.grids_host / ws.off_host; they are
-// copied to the device first unless `open_single` (one open system, grid built on the
-// device).  Outputs are written only if the step raised no error flag.
+// copied to the device first (one system's travel with the first kernel; with
+// `open_single` its grid is built on the device).  Outputs are written only if the step raised no error flag.
 int enqueue_step(dp_model *m, Workspace &ws, const StepArgs &a, hipStream_t st, bool profile) {
   dp_model *pm = profile ? m : nullptr;
   const int n = (int)a.n;
@@ -763,15 +763,15 @@ int enqueue_step(dp_model *m, Workspace &ws, const StepArgs &a, hipStream_t st, 
   const int cb = a.nsys == 1 ? (int)a.c0 : 0;
   const int ce = (a.nsys == 1 && a.c1 >= 0) ? (int)a.c1 : nc;
   if (a.first_chunk) {
-    if (!a.open_single)
+    const int ncz = a.lists == LISTS_SKIN_REUSE ? 0 : a.ncells + 1;
+    if (a.nsys == 1) {
+      const OneSystem one{ws.grids_host[0], a.open_single ? 0 : 1, {0, n, 0, nc}};
+      launch_prologue(ws, 1, n, ncz, true, st, &one);
+    } else {
       HIP_TRY(hipMemcpyAsync(ws.grids, ws.grids_host, a.nsys * sizeof(Grid), hipMemcpyHostToDevice, st));
-    if (nc < n) {  // off_host[2..3]: the centre range, reduced for the energy
-      ws.off_host[2] = 0;
-      ws.off_host[3] = nc;
+      HIP_TRY(hipMemcpyAsync(ws.sys_off, ws.off_host, (a.nsys + 1) * sizeof(int), hipMemcpyHostToDevice, st));
+      launch_prologue(ws, a.nsys, n, ncz, true, st);
     }
-    HIP_TRY(hipMemcpyAsync(ws.sys_off, ws.off_host, (nc < n ? 4 : a.nsys + 1) * sizeof(int), hipMemcpyHostToDevice,
-                           st));
-    launch_prologue(ws, a.nsys, n, a.lists == LISTS_SKIN_REUSE ? 0 : a.ncells + 1, true, st);
   } else {
     launch_prologue(ws, a.nsys, 0, 0, false, st);  // a later chunk: only the descriptor's atom lists restart
   }
@@ -833,7 +833,7 @@ int enqueue_step(dp_model *m, Workspace &ws, const StepArgs &a, hipStream_t st, 
   return DP_OK;
 }
 
-// Status of a finished step from the flag words copied to ws.flags_host.
+// Status of a finished step from the flag words its last kernel left in ws.flags_host.
 int step_status(const Workspace &ws) {
   const unsigned f = ws.flags_host[0];
   const int s = flags_status(f);
@@ -857,6 +857,7 @@ int launch_graph(dp_model *m, const StepArgs &a, hipStream_t st) {
   k.stream = st;
   k.open_single = a.open_single;
   if (!a.open_single) std::memcpy(k.box, m->ws.grids_host[0].L, 3 * sizeof(double));
+  k.skin = m->skin;  // the cutoffs and, with the box, the grid are arguments of the captured kernels
   k.ws_gen = m->ws.gen;
   // graphs captured on an earlier workspace point at freed buffers: drop them
   for (auto &e : m->graphs)
@@ -866,9 +867,6 @@ int launch_graph(dp_model *m, const StepArgs &a, hipStream_t st) {
     }
   for (auto &e : m->graphs)
     if (e.exec && std::memcmp(&e.key, &k, sizeof(k)) == 0) {
-      // the host-side grid table is uploaded outside the graph (same values as at capture)
-      if (!a.open_single)
-        HIP_TRY(hipMemcpyAsync(m->ws.grids, m->ws.grids_host, sizeof(Grid), hipMemcpyHostToDevice, st));
       HIP_TRY(hipGraphLaunch(e.exec, st));
       return DP_OK;
     }
@@ -943,7 +941,6 @@ int run_single(dp_model *m, StepArgs a, const double *box, hipStream_t st) {
       s = enqueue_step(m, ws, a, st, m->prof);
     }
     if (s != DP_OK) return s;
-    HIP_TRY(hipMemcpyAsync(ws.flags_host, ws.flags, 4 * sizeof(unsigned), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     s = step_status(ws);
     if (s == DP_RETRY) {
@@ -1203,7 +1200,6 @@ int dp_compute_owned_device(dp_model *m, int64_t natoms, int64_t n_owned, const 
   hipStream_t st = (hipStream_t)hip_stream;
   s = enqueue_step(m, ws, a, st, false);
   if (s != DP_OK) return s;
-  HIP_TRY(hipMemcpyAsync(ws.flags_host, ws.flags, 4 * sizeof(unsigned), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
   m->fwd_valid = false;
   s = step_status(ws);
@@ -1252,7 +1248,6 @@ int dp_compute_device_noalloc(dp_model *m, int64_t natoms, const double *d_coord
   hipStream_t st = (hipStream_t)hip_stream;
   s = enqueue_step(m, ws, a, st, false);
   if (s != DP_OK) return s;
-  HIP_TRY(hipMemcpyAsync(ws.flags_host, ws.flags, 4 * sizeof(unsigned), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
   m->fwd_valid = false;
   return step_status(ws);
@@ -1310,7 +1305,6 @@ int dp_compute_batch_device(dp_model *m, int nsys, const int64_t *natoms, const 
   hipStream_t st = (hipStream_t)hip_stream;
   s = enqueue_step(m, ws, a, st, false);
   if (s != DP_OK) return s;
-  HIP_TRY(hipMemcpyAsync(ws.flags_host, ws.flags, 4 * sizeof(unsigned), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
   m->fwd_valid = false;
   return step_status(ws);
@@ -1418,8 +1412,10 @@ int dp_backward_device(dp_model *m, const double *d_grad_energy, double *d_grad_
   const int n = (int)m->fwd_natoms;
   const float rc = (float)m->rc, rcs = (float)m->rcs, eps = (float)m->ln_eps;
   Workspace &ws = m->ws;
-  // the energy-only pass left D, the lists and the grid in place; rerun the fitting
-  // net with its backward
+  // the energy-only pass left T, the lists and the grid in place; rerun the fitting net with its
+  // backward.  The descriptor's atom lists are remade: a pass in chunks left its last chunk's
+  launch_prologue(ws, 1, 0, 0, false, st);
+  launch_descriptor_lists(ws, n, 0, n, st);
   if (m->prec == DP_FP32) {
     launch_fitting(m->wf, ws, m->fwd_types, 0, n, true, st);
     launch_descriptor_bwd(m->wf, ws, m->fwd_coords, m->fwd_types, n, 0, n, rc, rcs, eps, st);

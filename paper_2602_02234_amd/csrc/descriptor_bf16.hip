@@ -878,7 +878,7 @@ k_desc_bwd_b16(Tables w, WeightsB16 wp, const double *__restrict__ X, const int 
 
 void launch_descriptor_fwd_b16(const Tables &w, const WeightsB16 &wp, const Workspace &ws, const double *coords,
                                const int *types, int n, int c0, int c1, float rc, float rcs, float ln_eps, hipStream_t st) {
-  launch_class_lists(ws, n, c0, c1, st);
+  launch_descriptor_lists(ws, n, c0, c1, st);
   launch_instances(ws, n, c1 - c0, k_desc_fwd_b16<NB_SMALL, 2>, k_desc_fwd_b16<8, 1>, st,
                    [&](auto kernel, int groups, int threads, const int *idx, const int *cnt, hipStream_t s) {
     hipLaunchKernelGGL(kernel, dim3(groups), dim3(threads), 0, s, w, wp, coords, types, n, idx, cnt, c0, c1 - c0, ws.nlist,

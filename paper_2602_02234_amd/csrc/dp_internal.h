@@ -35,7 +35,8 @@ enum : unsigned {
   FLAG_OVERLAP = 1u, FLAG_TYPE = 2u, FLAG_NONFINITE = 4u, FLAG_TOO_DENSE = 8u, FLAG_STALE = 16u,
   FLAG_SKIN_FULL = 32u,
   FLAG_INCOMPLETE = 64u,  // a list was truncated to sel and the model needs complete lists
-  FLAG_ERRORS = 127u,     // any of the above: outputs are not written
+  FLAG_ANGLES = 128u,     // more angles than the GNN's buffers hold: the host enlarges them and redoes the step
+  FLAG_ERRORS = 255u,     // any of the above: outputs are not written
 };
 
 constexpr int MAXH = 4;  // fitting heads one model may carry
@@ -177,7 +178,7 @@ struct GraphKey {
   int open_single;
   int64_t n;
   const void *X, *types, *energy, *forces, *virial, *atom_energy, *stream;
-  double box[3];
+  double box[3], skin;
   uint64_t ws_gen;  // workspace generation the graph's buffers belong to
 };
 struct GraphEntry {
@@ -232,7 +233,14 @@ void set_error(const std::string &s);
 // Launchers (defined in the kernel translation units); all enqueue on `st` and read the
 // per-system grids (ws.grids), atom ranges (ws.sys_off) and atom -> system map (ws.sys_of).
 // Clears the step's counters and flags (and ncells_zero cell counts) and maps atoms to systems.
-void launch_prologue(const Workspace &ws, int nsys, int n, int ncells_zero, bool clear_flags, hipStream_t st);
+// With `one` (a single system) it also writes that system's grid (unless the grid is built on the
+// device) and atom ranges, which then need no copy from the host.
+struct OneSystem {
+  Grid grid;
+  int set_grid, off[4];  // atoms 0 .. off[1]-1, centres off[2] .. off[3]-1
+};
+void launch_prologue(const Workspace &ws, int nsys, int n, int ncells_zero, bool clear_flags, hipStream_t st,
+                     const OneSystem *one = nullptr);
 void launch_cells(const Workspace &ws, const double *coords, const int *types, int n, int ntypes, bool open_single,
                   int ncells_total, double cell_cutoff, hipStream_t st);
 // Lists for the atoms i0 .. i1-1 with candidates among all n; those at or beyond ncen get
@@ -240,9 +248,6 @@ void launch_cells(const Workspace &ws, const double *coords, const int *types, i
 void launch_nlist(const Workspace &ws, const double *coords, int n, int i0, int i1, int ncen, double cutoff,
                   bool skin, hipStream_t st);
 void launch_filter(const Workspace &ws, const double *coords, int n, double rc, hipStream_t st);
-// For models that need complete lists: turns a truncation (overflow count > 0) into the
-// FLAG_INCOMPLETE error, so that the step's later kernels write nothing.
-void launch_require_complete(const Workspace &ws, hipStream_t st);
 // slot[i][j] (n x SEL) = the position of i in the list of its j-th neighbour, or -1 (also
 // for j past the end of i's list); the lists are sorted, so each is a binary search.
 void launch_rev_slots(const Workspace &ws, int n, int *slot, hipStream_t st);
@@ -256,6 +261,9 @@ void launch_descriptor_fwd(const Weights<float> &w, const Workspace &ws, const d
 // The fitting net over the atoms c0 .. c1-1 from ws.Tsave (E_i, and dE/dT into ws.fit when backward).
 void launch_fitting(const Weights<float> &w, const Workspace &ws, const int *types, int c0, int c1, bool backward,
                     hipStream_t st);
+// The centres c0 .. c1-1 of n atoms into the descriptor kernels' atom lists (ws.bidx; their counts
+// restart with the prologue); the forward launchers do this themselves.
+void launch_descriptor_lists(const Workspace &ws, int n, int c0, int c1, hipStream_t st);
 void launch_descriptor_fwd_b16(const Tables &w, const WeightsB16 &wp, const Workspace &ws,
                                const double *coords, const int *types, int n, int c0, int c1, float rc,
                                float rcs, float ln_eps, hipStream_t st);

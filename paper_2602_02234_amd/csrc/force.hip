@@ -135,14 +135,16 @@ __global__ void __launch_bounds__(256) k_forces(
 // component 0 the energy (E_i over the energy ranges eoff[s] .. eoff[s+1]-1, copied to
 // atom_energy when given), components 1..nv the virial (vpart over off[s] .. off[s+1]-1,
 // nv = 9 or 0), then one per fitting head when there are several (Eh into Ehsys).
-// A system's sums do not depend on which other systems share the step.
+// A system's sums do not depend on which other systems share the step.  As the last kernel of a
+// step it leaves the step's status words in pinned host memory, which saves a copy.
 __global__ void __launch_bounds__(1024) k_reduce(const double *__restrict__ Ei, const double *__restrict__ vpart,
                                                  const double *__restrict__ Eh, const int *__restrict__ eoff,
                                                  const int *__restrict__ off, int ncomp, int nv,
                                                  double *__restrict__ energy, double *__restrict__ atom_energy,
                                                  double *__restrict__ virial, double *__restrict__ Ehsys,
-                                                 const unsigned *__restrict__ flags) {
+                                                 const unsigned *__restrict__ flags, unsigned *__restrict__ host_flags) {
   __shared__ double ss[1024], sc[1024];
+  if (blockIdx.x == 0 && threadIdx.x < 4) host_flags[threadIdx.x] = flags[threadIdx.x];
   if (step_failed(flags)) return;
   const int comp = blockIdx.x % ncomp, s = blockIdx.x / ncomp;
   if (comp > nv) {
@@ -182,7 +184,7 @@ void launch_reduce(const Workspace &ws, const int *eoff, int nsys, double *energ
   const int nv = virial ? 9 : 0;
   const int ncomp = 1 + nv + (nheads > 1 ? nheads : 0);
   hipLaunchKernelGGL(k_reduce, dim3(nsys * ncomp), dim3(1024), 0, st, ws.Ei, ws.vpart, ws.Eh, eoff, ws.sys_off, ncomp,
-                     nv, energy, atom_energy, virial, ws.Ehsys, ws.flags);
+                     nv, energy, atom_energy, virial, ws.Ehsys, ws.flags, ws.flags_host);
 }
 
 void launch_sum(const Workspace &ws, const double *src, double *out, hipStream_t st) {

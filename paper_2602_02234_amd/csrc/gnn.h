@@ -60,7 +60,7 @@ struct Weights {
 // i start at aoff[i] (p-major: angle (p, q) at aoff[i] + p (nc_i - 1) + q - (q > p)).
 struct Buffers {
   int64_t cap = 0, acap = 0;  // atoms, angles
-  int64_t *aoff = nullptr;    // [cap + 3]: angle offsets, then the step's edge and angle-list edge counts
+  int64_t *aoff = nullptr;    // [cap + 1]: angle offsets
   float *nf = nullptr;        // [2][cap][64]       n after layers 1, 2
   float *ef = nullptr;        // [3][cap][SEL][64]  e after layers 1, 2, 3
   float *af = nullptr;        // [3][acap][32]      a after layers 1, 2, 3
@@ -77,11 +77,12 @@ struct Geo {
   int asel;
 };
 
-// aoff[1 .. n]: angle counts of every atom, then their inclusive prefix (aoff[0] = 0);
-// aoff[cap + 1]: the number of edges (sum of the list lengths); aoff[cap + 2]: the
-// number of angle-list edges of the atoms with angles.
+// aoff[1 .. n]: angle counts of every atom, then their inclusive prefix (aoff[0] = 0).
+// host_tot (pinned host memory): the step's angles, edges (sum of the list lengths) and
+// angle-list edges.  Sets FLAG_INCOMPLETE if a list was truncated, and FLAG_ANGLES if the
+// angle buffers are too small: the step's later kernels then write nothing.
 void launch_angle_offsets(const Buffers &b, const Workspace &ws, const double *coords, int n, const Geo &geo,
-                          hipStream_t st);
+                          int64_t *host_tot, hipStream_t st);
 // Layer `layer` (0 .. 2) forward over all n atoms; the last layer also evaluates the
 // fitting net (E_i into Ei) and its gradient dE/dn (into dnl).
 template <typename T>

@@ -159,11 +159,12 @@ __global__ void __launch_bounds__(256) k_angle_count(const double *__restrict__ 
 
 // Inclusive prefix of aoff[1 .. n] in one workgroup: each thread sums a contiguous run,
 // the 1024 run totals are scanned, then each run is rewritten.
-// The same workgroup also writes the total edge count (sum of nnei) to etot[0] and the
-// number of angle-list edges of the atoms that have angles (sum of nc, from nc (nc - 1))
-// to etot[1].
+// The same workgroup also writes to host_tot the angles, the edges (sum of nnei) and the
+// angle-list edges of the atoms that have angles (sum of nc, from nc (nc - 1)), and sets the
+// step's error bits: a truncated list, or more than acap angles.
 __global__ void __launch_bounds__(1024) k_angle_scan(int64_t *__restrict__ aoff, const int *__restrict__ nnei, int n,
-                                                     int64_t *__restrict__ etot) {
+                                                     int64_t acap, int64_t *__restrict__ host_tot,
+                                                     unsigned *__restrict__ flags) {
   __shared__ int64_t part[1024];
   __shared__ int64_t epart[1024], cpart[1024];
   const int t = threadIdx.x;
@@ -189,14 +190,20 @@ __global__ void __launch_bounds__(1024) k_angle_scan(int64_t *__restrict__ aoff,
     __syncthreads();
   }
   if (t == 0) {
-    etot[0] = epart[0];
-    etot[1] = cpart[0];
+    host_tot[1] = epart[0];
+    host_tot[2] = cpart[0];
   }
   for (int off = 1; off < 1024; off <<= 1) {
     const int64_t v = t >= off ? part[t - off] : 0;
     __syncthreads();
     part[t] += v;
     __syncthreads();
+  }
+  if (t == 1023) {
+    host_tot[0] = part[t];
+    unsigned f = flags[1] != 0u ? FLAG_INCOMPLETE : 0u;  // a truncated list: the model needs complete ones
+    if (part[t] > acap) f |= FLAG_ANGLES;
+    if (f) atomicOr(flags, f);
   }
   int64_t run = t > 0 ? part[t - 1] : 0;
   for (int k = b0; k < b1; ++k) {
@@ -809,10 +816,10 @@ constexpr int WIDE_UP_TO = 512;
 }  // namespace
 
 void launch_angle_offsets(const Buffers &b, const Workspace &ws, const double *coords, int n, const Geo &geo,
-                          hipStream_t st) {
+                          int64_t *host_tot, hipStream_t st) {
   hipLaunchKernelGGL(k_angle_count, dim3((n + 3) / 4), dim3(256), 0, st, coords, ws.nlist, ws.nnei, ws.grids, n, geo,
                      b.aoff);
-  hipLaunchKernelGGL(k_angle_scan, dim3(1), dim3(1024), 0, st, b.aoff, ws.nnei, n, b.aoff + b.cap + 1);
+  hipLaunchKernelGGL(k_angle_scan, dim3(1), dim3(1024), 0, st, b.aoff, ws.nnei, n, b.acap, host_tot, ws.flags);
 }
 
 template <typename T>

@@ -26,6 +26,7 @@ struct dp_gnn {
   double *fpark = nullptr;  // forces when only the virial is asked for
   int64_t fpark_cap = 0;
   int64_t *tot_host = nullptr;  // pinned: angles, edges, angle-list edges
+  int64_t angles_for = 0;       // atoms up to which steps use the angle buffers as they are
   int64_t last_angles = 0, last_edges = 0, last_aedges = 0;
   // per-phase device time (dp_gnn_profile_enable): lists, forward layers, backward
   // layers, forces and reductions
@@ -249,7 +250,7 @@ int ensure_atoms(gnn::Buffers &b, int64_t n) {
   b.slot = nullptr;
   b.cap = 0;
   const size_t c = (size_t)cap, e = c * SEL * EDIM;
-  G_TRY(hipMalloc(&b.aoff, (c + 3) * sizeof(int64_t)));
+  G_TRY(hipMalloc(&b.aoff, (c + 1) * sizeof(int64_t)));
   G_TRY(hipMalloc(&b.nf, 2 * c * NDIM * sizeof(float)));
   G_TRY(hipMalloc(&b.ef, 3 * e * sizeof(float)));
   G_TRY(hipMalloc(&b.de, e * sizeof(float)));
@@ -283,6 +284,11 @@ int gnn_status(const Workspace &ws) {
   return s;
 }
 
+// One step.  The angle buffers are sized by the number of angles, which the device counts:
+// the host waits for it where the buffers are new for this many atoms (or phases are
+// timed); otherwise the whole step is enqueued with the buffers there are, and if they turn
+// out too small (FLAG_ANGLES, DP_RETRY) the caller enlarges them and repeats it.  The wait cost 45 us of
+// a 192-atom step of 560.
 int gnn_step(dp_gnn *m, int64_t natoms, const double *X, const int32_t *types, const double *box, double *energy,
              double *forces, double *virial, double *atom_energy, hipStream_t st) {
   Workspace &ws = m->ws;
@@ -296,37 +302,31 @@ int gnn_step(dp_gnn *m, int64_t natoms, const double *X, const int32_t *types, c
   if (s != DP_OK) return s;
   const bool open = box == nullptr;
   const int ncells = open ? MAX_CELLS : g.ncells;
-  ws.grids_host[0] = g;
-  ws.off_host[0] = 0;
-  ws.off_host[1] = n;
-  if (!open) G_TRY(hipMemcpyAsync(ws.grids, ws.grids_host, sizeof(Grid), hipMemcpyHostToDevice, st));
-  G_TRY(hipMemcpyAsync(ws.sys_off, ws.off_host, 2 * sizeof(int), hipMemcpyHostToDevice, st));
+  const OneSystem one{g, open ? 0 : 1, {0, n, 0, n}};
   if (m->prof) G_TRY(hipEventRecord(m->ev[0], st));
-  launch_prologue(ws, 1, n, ncells + 1, true, st);
+  launch_prologue(ws, 1, n, ncells + 1, true, st, &one);
   launch_cells(ws, X, types, n, m->ntypes, open, ncells, m->rc, st);
   launch_nlist(ws, X, n, 0, n, n, m->rc, false, st);
-  launch_require_complete(ws, st);
   gnn::Geo geo{(float)m->rc, (float)m->rcs, (float)m->rca, 1.f / (float)m->sel, 1.f / (float)m->asel, m->asel};
-  gnn::launch_angle_offsets(m->b, ws, X, n, geo, st);
+  const bool wait = m->prof || n > m->angles_for;
+  gnn::Buffers b = m->b;
+  if (wait) b.acap = INT64_MAX;  // made to fit below
+  gnn::launch_angle_offsets(b, ws, X, n, geo, m->tot_host, st);
   G_TRY(hipGetLastError());
   if (m->prof) G_TRY(hipEventRecord(m->ev[1], st));
-  // the angle count sizes the angle buffers: one host round trip per step
-  G_TRY(hipMemcpyAsync(m->tot_host, m->b.aoff + n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-  G_TRY(hipMemcpyAsync(m->tot_host + 1, m->b.aoff + m->b.cap + 1, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, st));
-  G_TRY(hipMemcpyAsync(ws.flags_host, ws.flags, 4 * sizeof(unsigned), hipMemcpyDeviceToHost, st));
-  G_TRY(hipStreamSynchronize(st));
-  if (m->prof) {
-    float ms = 0.f;
-    m->lists_ms = hipEventElapsedTime(&ms, m->ev[0], m->ev[1]) == hipSuccess ? ms : 0.0;
+  if (wait) {
+    G_TRY(hipMemcpyAsync(ws.flags_host, ws.flags, 4 * sizeof(unsigned), hipMemcpyDeviceToHost, st));
+    G_TRY(hipStreamSynchronize(st));
+    if (m->prof) {
+      float ms = 0.f;
+      m->lists_ms = hipEventElapsedTime(&ms, m->ev[0], m->ev[1]) == hipSuccess ? ms : 0.0;
+    }
+    s = gnn_status(ws);
+    if (s != DP_OK) return s;
+    s = ensure_angles(m->b, std::max<int64_t>(m->tot_host[0], 1));
+    if (s != DP_OK) return s;
+    m->angles_for = std::max<int64_t>(m->angles_for, n);
   }
-  s = gnn_status(ws);
-  if (s != DP_OK) return s;
-  const int64_t na = m->tot_host[0];
-  m->last_angles = na;
-  m->last_edges = m->tot_host[1];
-  m->last_aedges = m->tot_host[2];
-  s = ensure_angles(m->b, std::max<int64_t>(na, 1));
-  if (s != DP_OK) return s;
   const bool bwd = forces || virial;
   if (m->prof) G_TRY(hipEventRecord(m->ev[2], st));
   for (int l = 0; l < NLAYER; ++l) {
@@ -363,9 +363,17 @@ int gnn_step(dp_gnn *m, int64_t natoms, const double *X, const int32_t *types, c
   launch_reduce(ws, ws.sys_off, 1, energy, atom_energy, virial, 1, st);
   G_TRY(hipGetLastError());
   if (m->prof) G_TRY(hipEventRecord(m->ev[0], st));  // end of the last phase (ev[0] is free again)
-  G_TRY(hipMemcpyAsync(ws.flags_host, ws.flags, 4 * sizeof(unsigned), hipMemcpyDeviceToHost, st));
   G_TRY(hipStreamSynchronize(st));
   s = gnn_status(ws);
+  if (s == DP_OK && (ws.flags_host[0] & FLAG_ANGLES)) {
+    s = ensure_angles(m->b, m->tot_host[0]);
+    return s == DP_OK ? DP_RETRY : s;
+  }
+  if (s >= 0) {
+    m->last_angles = m->tot_host[0];
+    m->last_edges = m->tot_host[1];
+    m->last_aedges = m->tot_host[2];
+  }
   if (s >= 0 && m->prof) {
     // phases: lists ev1 - (start), fwd ev3 - ev2, bwd ev4 - ev3, forces/reductions end - ev4
     float ms = 0.f;
@@ -453,8 +461,12 @@ int dp_gnn_compute_device(dp_gnn *m, int64_t natoms, const double *d_coords, con
     return DP_ERR_TOO_LARGE;
   }
   G_TRY(hipSetDevice(m->device));
-  return gnn_step(m, natoms, d_coords, d_types, box_host, d_energy, d_forces, d_virial, d_atom_energy,
+  int s = gnn_step(m, natoms, d_coords, d_types, box_host, d_energy, d_forces, d_virial, d_atom_energy,
                   (hipStream_t)hip_stream);
+  if (s == DP_RETRY)
+    s = gnn_step(m, natoms, d_coords, d_types, box_host, d_energy, d_forces, d_virial, d_atom_energy,
+                  (hipStream_t)hip_stream);
+  return s;
 }
 
 int dp_gnn_graph_size(const dp_gnn *m, int64_t *edges, int64_t *angle_edges, int64_t *angles) {

@@ -72,11 +72,16 @@ __global__ void __launch_bounds__(1024) k_grid_open(const double *__restrict__ X
 
 // Start of a step: clears the status words (nflags of them), the completion counters
 // (ndone) and the backward instances' atom counts, clears the cell counts (ncz entries),
-// and writes sys_of[a] = s for off[s] <= a < off[s + 1], a < n.  Grid-stride; no
-// workgroup depends on another.
+// and writes sys_of[a] = s for off[s] <= a < off[s + 1], a < n; a single system's grid and
+// atom ranges travel as arguments.  Grid-stride; no workgroup depends on another.
 __global__ void k_prologue(const int *__restrict__ off, int nsys, int n, int *__restrict__ sys_of,
                            int *__restrict__ cell_count, int ncz, unsigned *__restrict__ flags, int nflags,
-                           int *__restrict__ done, int ndone, int *__restrict__ bcnt) {
+                           int *__restrict__ done, int ndone, int *__restrict__ bcnt, OneSystem one, int use_one,
+                           Grid *__restrict__ grids, int *__restrict__ sys_off) {
+  if (use_one && blockIdx.x == 0) {
+    if (threadIdx.x < 4) sys_off[threadIdx.x] = one.off[threadIdx.x];
+    if (threadIdx.x == 0 && one.set_grid) grids[0] = one.grid;
+  }
   const int stride = gridDim.x * blockDim.x;
   for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < max(max(n, ncz), max(ndone, 2)); t += stride) {
     if (t < nflags) flags[t] = 0u;
@@ -84,7 +89,7 @@ __global__ void k_prologue(const int *__restrict__ off, int nsys, int n, int *__
     if (t < ndone) done[t] = 0;
     if (t < ncz) cell_count[t] = 0;
     if (t < n) {
-      int lo = 0, hi = nsys - 1;
+      int lo = 0, hi = nsys - 1;  // (one system: nothing is read)
       while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
         if (off[mid] <= t) lo = mid; else hi = mid - 1;
@@ -101,10 +106,11 @@ __global__ void __launch_bounds__(1024) k_cell_assign(
     const double *__restrict__ X, const int *__restrict__ types, int n, int ntypes, const Grid *__restrict__ grids,
     const int *__restrict__ sys_of, int *__restrict__ cell_of, int *__restrict__ cell_count,
     int *__restrict__ start, int *__restrict__ cursor, int ncells_host, const Grid *__restrict__ open_grid,
-    int *__restrict__ blocks_done, unsigned *__restrict__ flags) {
+    int *__restrict__ blocks_done, int *__restrict__ atoms, unsigned *__restrict__ flags) {
   __shared__ int part[1024];
   __shared__ bool is_last;
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  int cell = 0;
   if (i < n) {
     const Grid g = grids[sys_of[i]];
     const int t = types[i];
@@ -120,7 +126,7 @@ __global__ void __launch_bounds__(1024) k_cell_assign(
       c[a] = clampi((int)floor(w * g.icw[a]), 0, g.nc[a] - 1);
     }
     if (!ok) atomicOr(flags, FLAG_NONFINITE);
-    const int cell = g.cell_base + (c[0] * g.nc[1] + c[1]) * g.nc[2] + c[2];
+    cell = g.cell_base + (c[0] * g.nc[1] + c[1]) * g.nc[2] + c[2];
     cell_of[i] = cell;
     atomicAdd(&cell_count[cell], 1);
   }
@@ -153,6 +159,11 @@ __global__ void __launch_bounds__(1024) k_cell_assign(
     run += cell_count[k];
   }
   if (threadIdx.x == 1023) start[nc] = part[1023];
+  if (gridDim.x == 1) {
+    __threadfence();
+    __syncthreads();  // the cursors are set
+    if (i < n) atoms[atomicAdd(&cursor[cell], 1)] = i;
+  }
 }
 
 __global__ void k_cell_fill(const int *__restrict__ cell_of, int *__restrict__ cursor, int *__restrict__ atoms, int n) {
@@ -362,22 +373,13 @@ __global__ void k_copy_f64(const double *__restrict__ src, double *__restrict__ 
 
 }  // namespace
 
-void launch_prologue(const Workspace &ws, int nsys, int n, int ncells_zero, bool clear_flags, hipStream_t st) {
+void launch_prologue(const Workspace &ws, int nsys, int n, int ncells_zero, bool clear_flags, hipStream_t st,
+                     const OneSystem *one) {
   const int work = std::max(n, ncells_zero);
   const int blocks = std::max(1, std::min((work + 255) / 256, 4096));
   hipLaunchKernelGGL(k_prologue, dim3(blocks), dim3(256), 0, st, ws.sys_off, nsys, n, ws.sys_of, ws.cell_count,
                      ncells_zero, ws.flags, clear_flags ? 4 : 0, ws.done, clear_flags ? 2 * ws.cap_sys + 1 : 0,
-                     ws.bcnt);
-}
-
-namespace {
-__global__ void k_require_complete(unsigned *__restrict__ flags) {
-  if (threadIdx.x == 0 && flags[1] != 0u) flags[0] |= FLAG_INCOMPLETE;
-}
-}  // namespace
-
-void launch_require_complete(const Workspace &ws, hipStream_t st) {
-  hipLaunchKernelGGL(k_require_complete, dim3(1), dim3(64), 0, st, ws.flags);
+                     ws.bcnt, one ? *one : OneSystem{}, one ? 1 : 0, ws.grids, ws.sys_off);
 }
 
 namespace {
@@ -418,9 +420,10 @@ void launch_cells(const Workspace &ws, const double *coords, const int *types, i
   // the block counter of the assign pass is the last completion counter (cleared by the prologue)
   hipLaunchKernelGGL(k_cell_assign, dim3((n + 1023) / 1024), dim3(1024), 0, st, coords, types, n, ntypes, ws.grids,
                      ws.sys_of, ws.cell_of, ws.cell_count, ws.cell_start, ws.cell_cursor, ncells_total,
-                     open_single ? ws.grids : (const Grid *)nullptr, ws.done + 2 * ws.cap_sys, ws.flags);
-  hipLaunchKernelGGL(k_cell_fill, dim3((n + 255) / 256), dim3(256), 0, st, ws.cell_of, ws.cell_cursor,
-                     ws.cell_atoms, n);
+                     open_single ? ws.grids : (const Grid *)nullptr, ws.done + 2 * ws.cap_sys, ws.cell_atoms, ws.flags);
+  if (n > 1024)
+    hipLaunchKernelGGL(k_cell_fill, dim3((n + 255) / 256), dim3(256), 0, st, ws.cell_of, ws.cell_cursor,
+                       ws.cell_atoms, n);
 }
 
 void launch_nlist(const Workspace &ws, const double *coords, int n, int i0, int i1, int ncen, double cutoff, bool skin,

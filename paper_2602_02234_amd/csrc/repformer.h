@@ -55,15 +55,15 @@ struct Buffers {
   float *gs = nullptr;   // [cap][SEL][GSN]    dE/ds, dE/dsw, dE/drhat per edge over the layers
   int *slot = nullptr;   // [cap][SEL]         position of i in the list of its j-th neighbour, or -1
   int *idx = nullptr;    // [2][cap]           atoms of each kernel instance (counts: Workspace::bcnt)
-  int64_t *etot = nullptr;  // [1] edges of the step
 };
 
 struct Geo {
   float rc, rcs, inv_sel;
 };
 
-// *b.etot = sum of the list lengths of the n atoms; also lists the atoms of the kernels' instances.
-void launch_edge_count(const Buffers &b, const Workspace &ws, int n, hipStream_t st);
+// *host_etot (pinned host memory) = sum of the list lengths of the n atoms; lists the atoms of the
+// kernels' instances; sets FLAG_INCOMPLETE if a list was truncated.
+void launch_edge_count(const Buffers &b, const Workspace &ws, int n, int64_t *host_etot, hipStream_t st);
 // Layer `layer` (0 .. 2) forward over all n atoms; the last layer also evaluates the
 // fitting net (E_i into Ei) and its gradient dE/dg1 (into dnl).  Layer `layer` backward
 // (called for 2, 1, 0); layer 0 writes g_ij = dE/dDelta_ij into ws.g.

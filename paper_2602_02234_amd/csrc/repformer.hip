@@ -772,9 +772,10 @@ k_rep_bwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__rest
 }
 
 // The edge count, and the atoms of the two instances (up to 96 neighbours, or more; the order
-// only changes scheduling).
-__global__ void __launch_bounds__(1024) k_edge_count(const int *__restrict__ nnei, int n, int64_t *__restrict__ etot,
-                                                     int *__restrict__ idx, int *__restrict__ cnt, int cap) {
+// only changes scheduling).  A truncated list is an error: the model needs complete ones.
+__global__ void __launch_bounds__(1024) k_edge_count(const int *__restrict__ nnei, int n, int64_t *__restrict__ host_etot,
+                                                     int *__restrict__ idx, int *__restrict__ cnt, int cap,
+                                                     unsigned *__restrict__ flags) {
   __shared__ int64_t part[1024];
   const int l = lane();
   int64_t s = 0;
@@ -798,13 +799,16 @@ __global__ void __launch_bounds__(1024) k_edge_count(const int *__restrict__ nne
     if ((int)threadIdx.x < off) part[threadIdx.x] += part[threadIdx.x + off];
     __syncthreads();
   }
-  if (threadIdx.x == 0) *etot = part[0];
+  if (threadIdx.x == 0) {
+    *host_etot = part[0];
+    if (flags[1] != 0u) atomicOr(flags, (unsigned)FLAG_INCOMPLETE);
+  }
 }
 
 }  // namespace
 
-void launch_edge_count(const Buffers &b, const Workspace &ws, int n, hipStream_t st) {
-  hipLaunchKernelGGL(k_edge_count, dim3(1), dim3(1024), 0, st, ws.nnei, n, b.etot, b.idx, ws.bcnt, (int)b.cap);
+void launch_edge_count(const Buffers &b, const Workspace &ws, int n, int64_t *host_etot, hipStream_t st) {
+  hipLaunchKernelGGL(k_edge_count, dim3(1), dim3(1024), 0, st, ws.nnei, n, host_etot, b.idx, ws.bcnt, (int)b.cap, ws.flags);
 }
 
 void launch_layer_fwd(const Weights &w, const Buffers &b, const Workspace &ws, const double *coords,

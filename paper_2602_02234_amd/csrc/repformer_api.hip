@@ -193,14 +193,13 @@ int load_weights(dp_rep *m, const char *path) {
 }
 
 void free_buffers(rep::Buffers &b) {
-  void *ps[] = {b.g1f, b.g2f, b.dg2, b.dnj, b.dnl, b.gs, b.slot, b.idx, b.tn, b.Tn, b.etot};
+  void *ps[] = {b.g1f, b.g2f, b.dg2, b.dnj, b.dnl, b.gs, b.slot, b.idx, b.tn, b.Tn};
   for (void *p : ps)
     if (p) (void)hipFree(p);
   b = rep::Buffers{};
 }
 
 int ensure_buffers(rep::Buffers &b, int64_t n) {
-  if (!b.etot) R_TRY(hipMalloc(&b.etot, sizeof(int64_t)));
   if (n <= b.cap) return DP_OK;
   const int64_t cap = std::max<int64_t>(n, b.cap + b.cap / 4);
   void *ps[] = {b.g1f, b.g2f, b.dg2, b.dnj, b.dnl, b.gs, b.slot, b.idx, b.tn, b.Tn};
@@ -250,17 +249,12 @@ int rep_step(dp_rep *m, int64_t natoms, const double *X, const int32_t *types, c
   if (s != DP_OK) return s;
   const bool open = box == nullptr;
   const int ncells = open ? MAX_CELLS : g.ncells;
-  ws.grids_host[0] = g;
-  ws.off_host[0] = 0;
-  ws.off_host[1] = n;
-  if (!open) R_TRY(hipMemcpyAsync(ws.grids, ws.grids_host, sizeof(Grid), hipMemcpyHostToDevice, st));
-  R_TRY(hipMemcpyAsync(ws.sys_off, ws.off_host, 2 * sizeof(int), hipMemcpyHostToDevice, st));
+  const OneSystem one{g, open ? 0 : 1, {0, n, 0, n}};
   record(m, 0, st);
-  launch_prologue(ws, 1, n, ncells + 1, true, st);
+  launch_prologue(ws, 1, n, ncells + 1, true, st, &one);
   launch_cells(ws, X, types, n, m->ntypes, open, ncells, m->rc, st);
   launch_nlist(ws, X, n, 0, n, n, m->rc, false, st);
-  launch_require_complete(ws, st);
-  rep::launch_edge_count(m->b, ws, n, st);
+  rep::launch_edge_count(m->b, ws, n, m->etot_host, st);
   record(m, 1, st);
   rep::Geo geo{(float)m->rc, (float)m->rcs, 1.f / (float)m->sel};
   for (int l = 0; l < NLAYER; ++l) rep::launch_layer_fwd(m->w, m->b, ws, X, types, n, l, geo, ws.Ei, st);
@@ -288,8 +282,6 @@ int rep_step(dp_rep *m, int64_t natoms, const double *X, const int32_t *types, c
   launch_reduce(ws, ws.sys_off, 1, energy, atom_energy, virial, 1, st);
   record(m, 4, st);
   R_TRY(hipGetLastError());
-  R_TRY(hipMemcpyAsync(m->etot_host, m->b.etot, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-  R_TRY(hipMemcpyAsync(ws.flags_host, ws.flags, 4 * sizeof(unsigned), hipMemcpyDeviceToHost, st));
   R_TRY(hipStreamSynchronize(st));
   s = rep_status(ws);
   if (s < 0) return s;
