@@ -38,13 +38,6 @@ static_assert(M == 100 && E1 == 25 && E2 == 50, "the fragment layouts below are 
 __device__ __forceinline__ f4 mma(bf8 a, bf8 b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
 __device__ __forceinline__ bf8 ld8(const bf16_t *p) { return *reinterpret_cast<const bf8 *>(p); }
 
-// tanh from the hardware exponential and reciprocal: relative error a few 1e-7, far below the
-// bfloat16 rounding of the products it feeds.
-__device__ __forceinline__ float ftanh(float x) {
-  const float t = __expf(-2.f * fabsf(x));
-  return copysignf((1.f - t) * __builtin_amdgcn_rcpf(1.f + t), x);
-}
-
 __device__ __forceinline__ bf8 pack(f4 a, f4 b) {
   bf8 v;
 #pragma unroll
@@ -221,7 +214,7 @@ __device__ __forceinline__ void embed(const Tab &w, const bf16_t *w2T, const bf1
 #pragma unroll
   for (int r = 0; r < 7; ++r) {
     const int f = slot_ok(r) ? 4 * r + q : 0;
-    const float v = ftanh(s * w.w1s[f] + bt[f]);
+    const float v = act(s * w.w1s[f] + bt[f]);
     h1[0][r] = slot_ok(r) ? v : 0.f;
   }
   emul<1, 2>(t2, w2T, h1);
@@ -232,7 +225,7 @@ __device__ __forceinline__ void embed(const Tab &w, const bf16_t *w2T, const bf1
 #pragma unroll
     for (int r = 0; r < 7; ++r) {
       const int f = slot_ok(r) ? 25 * g + 4 * r + q : 0;
-      const float v = ftanh(t2[g][r] + w.b2[f]);
+      const float v = act(t2[g][r] + w.b2[f]);
       t2[g][r] = slot_ok(r) ? v : 0.f;
       h[r] = t2[g][r] + h1[0][r];
       if (slot_ok(r)) scr[c * LDH + 25 * g + 4 * r + q] = h[r];
@@ -245,7 +238,7 @@ __device__ __forceinline__ void embed(const Tab &w, const bf16_t *w2T, const bf1
 #pragma unroll
     for (int g = 0; g < 2; ++g) acc = mma(ld8(w3T + (2 * t + g) * 512 + 8 * l), x[g], acc);
 #pragma unroll
-    for (int k = 0; k < (t < 6 ? 4 : 1); ++k) t3[t][k] = ftanh(acc[k]);
+    for (int k = 0; k < (t < 6 ? 4 : 1); ++k) t3[t][k] = act(acc[k]);
   }
 }
 // [h2, h2] in a token's arrangement: feature f is h2[f % 50].
@@ -589,11 +582,11 @@ __device__ __forceinline__ void layer_bwd_rows(const WeightsB16 &wp, int layer, 
         const f4 sw = ldf4(sm.e.sw + k), rx = ldf4(sm.e.rh[0] + k), ry = ldf4(sm.e.rh[1] + k), rz = ldf4(sm.e.rh[2] + k);
         const f4 gt = rx * hj[0] + ry * hj[1] + rz * hj[2];
         const f4 cc = W[kt] * E[kt];
-        const f4 dC = sw * cc, dP = W[kt] * gt, pr = sw * E[kt] * dP;
+        const f4 dC = sw * cc, dP = W[kt] * gt;  // P dP = dC gate
         if (kt > 0) column_sums(kt - 1);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          rho += pr[i];
+          rho = fmaf(dC[i], gt[i], rho);
           hx += dC[i] * rx[i];
           hy += dC[i] * ry[i];
           hz += dC[i] * rz[i];
@@ -760,7 +753,7 @@ __device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB, NA> &sh
     // dG = Rt dT^T / sel for its output, and dRt = G dT / sel
     const float is = normalise(xh, ln_eps);
     const float inv_sel = 1.f / (float)SEL;
-    const float sj = sm.e.s[j];
+    const float sj = sm.e.s[j] * inv_sel;
     const float rt1 = sj * sm.e.rh[0][j], rt2 = sj * sm.e.rh[1][j], rt3 = sj * sm.e.rh[2][j];
     f4 p = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -770,7 +763,7 @@ __device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB, NA> &sh
 #pragma unroll
       for (int k = 0; k < (t < 6 ? 4 : 1); ++k) {
         const f4 d = ldf4(sm.dT + 4 * (t < 6 ? 16 * t + 4 * q + k : 96 + q));
-        go[t][k] = (sj * d[0] + rt1 * d[1] + rt2 * d[2] + rt3 * d[3]) * inv_sel;
+        go[t][k] = sj * d[0] + rt1 * d[1] + rt2 * d[2] + rt3 * d[3];
         p += gv[k] * d;
       }
     }
