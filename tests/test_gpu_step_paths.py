@@ -5,7 +5,8 @@
 * Energy-only passes in chunks, then the backward: the gradient of the unchunked pass.
 * Step graphs under a changed skin: the cutoffs of the earlier skin are not replayed.
 * Neighbour lists of 1,023 to 1,025 atoms, where one workgroup or a kernel of its own
-  enters the atoms into the cells, against all pairs."""
+  enters the atoms into the cells, and of few atoms in more cells than fit the workgroup's
+  LDS, against all pairs."""
 import numpy as np
 import pytest
 
@@ -88,11 +89,14 @@ def test_graphs_of_another_skin(gpu_models):
         m.set_graph(False)
 
 
-@pytest.mark.parametrize("n", [1, 2, 1023, 1024, 1025])
-def test_cells_of_one_workgroup(gpu_models, n):
+@pytest.mark.parametrize("n,a", [(1, 2.6), (2, 2.6), (1023, 2.6), (1024, 2.6), (1025, 2.6), (1000, 20.0)])
+def test_cells_of_one_workgroup(gpu_models, n, a):
+    """n atoms of a cubic lattice of edge a (20 A: 210 A across, 35 cells a side), jittered."""
     rng = np.random.default_rng(n)
     k = np.stack(np.meshgrid(*[np.arange(11)] * 3, indexing="ij"), -1).reshape(-1, 3)
-    X = 2.6 * k[rng.permutation(len(k))[:n]] + rng.uniform(-0.6, 0.6, size=(n, 3))
+    X = a * k[rng.permutation(len(k))[:n]] + rng.uniform(-0.6, 0.6, size=(n, 3))
+    if a > 6.0:  # pairs, so that there are lists
+        X[1::2] = X[:-1:2] + rng.uniform(1.0, 2.0, size=(n // 2, 3))
     nl, nn, _ = gpu_models["fp32"].neighbors(X, None)
     d = np.linalg.norm(X[:, None] - X[None], axis=2)
     for i in range(n):
