@@ -83,8 +83,13 @@ struct Geo {
 // angle buffers are too small: the step's later kernels then write nothing.
 void launch_angle_offsets(const Buffers &b, const Workspace &ws, const double *coords, int n, const Geo &geo,
                           int64_t *host_tot, hipStream_t st);
-// Layer `layer` (0 .. 2) forward over all n atoms; the last layer also evaluates the
-// fitting net (E_i into Ei) and its gradient dE/dn (into dnl).
+// Up to this many atoms every CU holds at most one workgroup of four waves on each SIMD
+// pair; eight waves per atom then shorten the step, and take the fitting net along.
+constexpr int WIDE_UP_TO = 512;
+inline bool separate_fit(int n) { return n > WIDE_UP_TO; }
+// Layer `layer` (0 .. 2) forward over all n atoms.  After the last one the fitting net gives E_i (Ei)
+// and dE/dn (dnl): within the layer's kernel, or (separate_fit) by launch_node_fit from the rows n
+// that the layer leaves in dnl.
 template <typename T>
 void launch_layer_fwd(const Weights &w, const Buffers &b, const Workspace &ws, const double *coords,
                       const int *types, int n, int layer, const Geo &geo, double *Ei, hipStream_t st);

@@ -384,10 +384,13 @@ k_layer_fwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__re
   if (tid < NDIM) {
     n1 = sm.ni[tid] + tanhf(z + w.bnn[l][tid]);
     if (l < NLAYER - 1) b.nf[((size_t)l * b.cap + i) * NDIM + tid] = n1;
+    else if (NW == 4) b.dnl[(size_t)i * NDIM + tid] = n1;  // for launch_node_fit
   }
+  if (NW == 4) return;
   if (l < NLAYER - 1) return;
 
-  // ---------------- fitting net, E_i and dE/dn_i
+  // ---------------- fitting net, E_i and dE/dn_i (up to WIDE_UP_TO atoms: 4 us at 192 atoms, where a
+  // kernel over tiles of 16 atoms takes 9; from 2,931 atoms on that kernel takes the net, 30 us here)
   if (tid < NDIM) sm.xs[tid] = n1;
   const float z1 = matvec<NW * 64, NDIM, FWID>(w.G1, sm.xs, sm.part, threadIdx.x);
   if (tid < FWID) sm.y1[tid] = tanhf(z1 + w.d1[tid]);
@@ -808,10 +811,6 @@ k_layer_bwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__re
                                             (gz - proj * hz) / rr + dr * hz, 0.f);
   }
 }
-
-// Up to this many atoms every CU holds at most one workgroup of four waves on each SIMD
-// pair; eight waves per atom then shorten the step.
-constexpr int WIDE_UP_TO = 512;
 
 }  // namespace
 

@@ -11,6 +11,7 @@
 
 #include "../../include/dp.h"
 #include "gnn.h"
+#include "node_fit.h"
 
 using namespace dp;
 
@@ -20,6 +21,7 @@ struct dp_gnn {
   double rc = 0, rcs = 0, rca = 0;
   int sel = 0, asel = 0, ntypes = 0;
   void *wbuf = nullptr;
+  NodeFit fit{};
   gnn::Weights w{};
   Workspace ws;
   gnn::Buffers b;
@@ -158,12 +160,7 @@ int load_weights(dp_gnn *m, const char *path) {
     put(t.data(), 4 * t.size());
   };
   auto frag32 = [&](int outs, int K, auto W) {
-    std::vector<float> v((size_t)outs * K);
-    for (int t = 0; t < outs / 16; ++t)
-      for (int k = 0; k < K / 16; ++k)
-        for (int ln = 0; ln < 64; ++ln)
-          for (int s = 0; s < 4; ++s)
-            v[((size_t)(t * (K / 16) + k) * 64 + ln) * 4 + s] = (float)W(16 * t + ln % 16, 16 * k + 4 * (ln / 16) + s);
+    const std::vector<float> v = node_fragments(outs, K, W);
     put(v.data(), 4 * v.size());
   };
   auto frag16 = [&](int outs, int K, auto W) {
@@ -185,6 +182,11 @@ int load_weights(dp_gnn *m, const char *path) {
   };
   transposed(src["G1"], NDIM, FWID);
   transposed(src["G2"], FWID, FWID);
+  const std::vector<double> &g1 = src["G1"], &g2 = src["G2"];
+  frag32(FWID, NDIM, [&](int o, int k) { return g1[k * FWID + o]; });
+  frag32(FWID, FWID, [&](int o, int k) { return g2[k * FWID + o]; });
+  frag32(FWID, FWID, [&](int o, int k) { return g2[o * FWID + k]; });
+  frag32(NDIM, FWID, [&](int o, int k) { return g1[o * FWID + k]; });
   for (int l = 0; l < NLAYER; ++l) {
     const std::string s = std::to_string(l);
     const std::vector<double> &aa = src["Waa" + s], &ea = src["Wea" + s], &ee = src["Wee" + s];
@@ -219,6 +221,9 @@ int load_weights(dp_gnn *m, const char *path) {
   (void)nxt();  // d3 goes by value
   w.G3d = (const double *)(base + og);
   w.G1T = nxt(); w.G2T = nxt();
+  NodeFit &nf = m->fit;
+  nf.d1 = w.d1; nf.d2 = w.d2; nf.G3 = w.G3; nf.G3d = w.G3d;
+  nf.G1 = nxt(); nf.G2 = nxt(); nf.G2T = nxt(); nf.G1T = nxt();
   for (int l = 0; l < NLAYER; ++l) {
     auto fr = [&](gnn::Frag &f) {
       const void *p = base + offs[k++];
@@ -229,7 +234,7 @@ int load_weights(dp_gnn *m, const char *path) {
     fr(w.A[l]); fr(w.Mg[l]); fr(w.Xt[l]); fr(w.Yt[l]); fr(w.E[l]); fr(w.N[l]); fr(w.D[l]);
     w.PQ[l] = nxt(); w.PS[l] = nxt();
   }
-  w.d3 = d3;
+  w.d3 = m->fit.d3 = d3;
   return DP_OK;
 }
 
@@ -335,6 +340,7 @@ int gnn_step(dp_gnn *m, int64_t natoms, const double *X, const int32_t *types, c
     else
       gnn::launch_layer_fwd<float>(m->w, m->b, ws, X, types, n, l, geo, ws.Ei, st);
   }
+  if (gnn::separate_fit(n)) launch_node_fit(m->fit, m->b.dnl, n, ws.Ei, ws.flags, st);
   if (m->prof) G_TRY(hipEventRecord(m->ev[3], st));
   if (bwd) {
     launch_rev_slots(ws, n, m->b.slot, st);

@@ -25,21 +25,16 @@ constexpr int XD = G1D + G2D * NAX + G2D;  // node-update input width, 224
 constexpr int FWID = 128;
 constexpr int GSN = 8;                  // per-edge gradient slots: ds, dsw, drhat (3), pad
 
-// Device weights: float32, row-major [in][out] as in the model file (the T-named copies
-// transposed), and the products' operands in MFMA fragment order (dp_tiles.h).
+// Device weights: float32, row-major [in][out] as in the model file and the products' operands in MFMA fragment order (dp_tiles.h).
 struct Weights {
   const float *TN;                      // [NTYPES][64]
   const float *Wp0, *bp0;               // [32]
   const float *ba[NLAYER];               // [32]
   const float *W1[NLAYER], *b1[NLAYER];  // [224][64], [64]
-  const float *G1T, *G2T;                // [128][64], [128][128]
   const float *Pa[NLAYER];               // [g2, g1_j] -> Wa (32 outputs of 96)
   const float *Pqkv[NLAYER];             // g2a -> [Q, K, V] (96 outputs of 32)
   const float *Pqkvt[NLAYER];            // [dQ, dK, dV] -> dE/dg2a (32 outputs of 96)
   const float *Pat[NLAYER];              // dz -> dE/d[g2, g1_j] (96 outputs of 32)
-  const float *G1, *d1, *G2, *d2, *G3;   // fitting
-  const double *G3d;
-  double d3;
 };
 
 // Per-step device buffers (edge rows at the neighbour-list stride SEL).
@@ -64,11 +59,10 @@ struct Geo {
 // *host_etot (pinned host memory) = sum of the list lengths of the n atoms; lists the atoms of the
 // kernels' instances; sets FLAG_INCOMPLETE if a list was truncated.
 void launch_edge_count(const Buffers &b, const Workspace &ws, int n, int64_t *host_etot, hipStream_t st);
-// Layer `layer` (0 .. 2) forward over all n atoms; the last layer also evaluates the
-// fitting net (E_i into Ei) and its gradient dE/dg1 (into dnl).  Layer `layer` backward
-// (called for 2, 1, 0); layer 0 writes g_ij = dE/dDelta_ij into ws.g.
+// Layer `layer` (0 .. 2) forward over all n atoms; the last layer's g1 goes to dnl, where the
+// fitting net (node_fit.h) replaces it by dE/dg1.  Layer `layer` backward (called for 2, 1, 0); layer 0 writes g_ij = dE/dDelta_ij into ws.g.
 void launch_layer_fwd(const Weights &w, const Buffers &b, const Workspace &ws, const double *coords,
-                      const int *types, int n, int layer, const Geo &geo, double *Ei, hipStream_t st);
+                      const int *types, int n, int layer, const Geo &geo, hipStream_t st);
 void launch_layer_bwd(const Weights &w, const Buffers &b, const Workspace &ws, const double *coords,
                       const int *types, int n, int layer, const Geo &geo, hipStream_t st);
 

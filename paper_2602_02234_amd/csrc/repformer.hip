@@ -9,7 +9,7 @@
 // the gradients that meet at a key.  The products run on MFMA (16x16x4 f32).
 //   forward   g2a = g2 + tanh([g2, g1_j] Wa + ba); Q, K, V; E = exp(S - max) / Z over the keys;
 //             g2 <- g2a + sum_k sw_k E gate V_k; T = sum_j g2_j R_j^T and the convolution sums;
-//             the node update; after the last layer the fitting net, E_i and dE/dg1_i.
+//             the node update (the last layer's into dnl, where the fitting net takes it).
 //   backward  the same recomputed but for the layer's output, which is stored; per token j
 //             dA = V dY, per key P = sw E, dP = dA gate, rho = sum P dP, W = E (dP - rho),
 //             dQ = K^T (sw W) / sqrt 32; per key k dV_k = sw_k sum_j E gate dY_j, dK_k = sw_k sum_j
@@ -347,8 +347,7 @@ template <int NB> struct SmemF {
   float part[NB][5][G2D];
   float T[G2D * 4];
   float zp[2 * NB_SMALL][G1D] __attribute__((aligned(16)));  // the waves' parts of the node update
-  float g1i[G1D], xs[XD], mv[64 * NB];
-  float y1[FWID], t2[FWID], dp[FWID];
+  float g1i[G1D], xs[XD];
 };
 
 template <int NB, int NA>
@@ -356,10 +355,9 @@ __device__ __forceinline__ void layer_fwd(int blk, int count, SmemF<NB> *smem, c
                                           const double *__restrict__ Xc, const int *__restrict__ types,
                                           const int *__restrict__ nlist, const int *__restrict__ nnei,
                                           const Grid *__restrict__ grids, int natoms, int l, const Geo &geo,
-                                          const int *__restrict__ idx, double *__restrict__ Ei) {
+                                          const int *__restrict__ idx) {
   const Part<NB, NA> pt(blk, idx, count, nnei);
   SmemF<NB> &sm = smem[pt.half];
-  constexpr int NT = 64 * NB;
   const int i = pt.i, nn = pt.n, nb = pt.nb, jb = pt.jb, tid = pt.tid;
   const int ln = lane(), q = ln >> 4, c = ln & 15;
   const bool act_ = jb < nb, live = nb > 0;
@@ -399,41 +397,15 @@ __device__ __forceinline__ void layer_fwd(int blk, int count, SmemF<NB> *smem, c
   for (int a = 0; a < NA; ++a) w1.forward(smem[a].xs, smem[a].zp[w1.wave]);
   __syncthreads();
   const size_t li = (size_t)l * b.cap + i;
-  float g1n = 0.f;
   if (tid < G1D) {
     float z = w.b1[l][tid];
 #pragma unroll
     for (int u = 0; u < NA * NB; ++u) z += sm.zp[u][tid];
     const float t = tanhf(z);
-    g1n = sm.g1i[tid] + t;
     if (live) b.tn[li * G1D + tid] = t;
-    if (l < NLAYER - 1 && live) b.g1f[li * G1D + tid] = g1n;
+    if (live) (l < NLAYER - 1 ? b.g1f + li * G1D : b.dnl + (size_t)i * G1D)[tid] = sm.g1i[tid] + t;
   }
   if (live && tid < 4 * G2D) b.Tn[li * (4 * G2D) + tid] = sm.T[tid];
-  if (l < NLAYER - 1) return;
-
-  // fitting net, E_i and dE/dg1_i
-  if (tid < G1D) sm.xs[tid] = g1n;
-  const float z1 = matvec<NT, G1D, FWID>(w.G1, sm.xs, sm.mv, tid);
-  if (tid < FWID) sm.y1[tid] = tanhf(z1 + w.d1[tid]);
-  const float z2 = matvec<NT, FWID, FWID>(w.G2, sm.y1, sm.mv, tid);
-  if (tid < FWID) {
-    const float t2 = tanhf(z2 + w.d2[tid]);
-    sm.t2[tid] = t2;
-    sm.dp[tid] = w.G3[tid] * (1.f - t2 * t2);
-  }
-  const float z3 = matvec<NT, FWID, FWID>(w.G2T, sm.dp, sm.mv, tid);  // its first barrier: t2 is complete
-  if (jb == 0) {
-    double E = (double)(sm.t2[ln] + sm.y1[ln]) * w.G3d[ln] + (double)(sm.t2[ln + 64] + sm.y1[ln + 64]) * w.G3d[ln + 64];
-    for (int off = 32; off > 0; off >>= 1) E += __shfl_xor(E, off);
-    if (ln == 0 && live) Ei[i] = w.d3 + E;
-  }
-  float dp1 = 0.f;
-  if (tid < FWID) dp1 = (z3 + w.G3[tid]) * (1.f - sm.y1[tid] * sm.y1[tid]);
-  __syncthreads();
-  if (tid < FWID) sm.dp[tid] = dp1;
-  const float dn = matvec<NT, FWID, G1D>(w.G1T, sm.dp, sm.mv, tid);
-  if (tid < G1D && live) b.dnl[(size_t)i * G1D + tid] = dn;
 }
 
 // ------------------------------------------------------------------ backward
@@ -721,10 +693,10 @@ __device__ __forceinline__ void layer_bwd(int blk, int count, SmemB<NB> *smem, c
 __global__ void __launch_bounds__(64 * NB_MAX) __attribute__((amdgpu_waves_per_eu(2)))
 k_rep_fwd_one(Weights w, Buffers b, const double *__restrict__ Xc, const int *__restrict__ types,
               const int *__restrict__ nlist, const int *__restrict__ nnei, const Grid *__restrict__ grids, int n, int l,
-              Geo geo, double *__restrict__ Ei, const unsigned *__restrict__ flags) {
+              Geo geo, const unsigned *__restrict__ flags) {
   __shared__ SmemF<NB_MAX> sm;
   if (failed(flags)) return;
-  layer_fwd<NB_MAX, 1>(blockIdx.x, n, &sm, w, b, Xc, types, nlist, nnei, grids, n, l, geo, nullptr, Ei);
+  layer_fwd<NB_MAX, 1>(blockIdx.x, n, &sm, w, b, Xc, types, nlist, nnei, grids, n, l, geo, nullptr);
 }
 __global__ void __launch_bounds__(64 * NB_MAX) __attribute__((amdgpu_waves_per_eu(2)))
 k_rep_bwd_one(Weights w, Buffers b, const double *__restrict__ Xc, const int *__restrict__ types,
@@ -739,17 +711,17 @@ k_rep_bwd_one(Weights w, Buffers b, const double *__restrict__ Xc, const int *__
 __global__ void __launch_bounds__(128 * NB_SMALL) __attribute__((amdgpu_waves_per_eu(3)))
 k_rep_fwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__restrict__ types, const int *__restrict__ nlist,
           const int *__restrict__ nnei, const Grid *__restrict__ grids, int n, int l, Geo geo, const int *__restrict__ cnt,
-          double *__restrict__ Ei, const unsigned *__restrict__ flags) {
+          const unsigned *__restrict__ flags) {
   __shared__ union { SmemF<NB_SMALL> two[2]; SmemF<NB_MAX> one; } sm;
   if (failed(flags)) return;
   const int blk = blockIdx.x - NLONG;
   if (blk >= 0) {
-    if (2 * blk < cnt[0]) layer_fwd<NB_SMALL, 2>(blk, cnt[0], sm.two, w, b, Xc, types, nlist, nnei, grids, n, l, geo, b.idx, Ei);
+    if (2 * blk < cnt[0]) layer_fwd<NB_SMALL, 2>(blk, cnt[0], sm.two, w, b, Xc, types, nlist, nnei, grids, n, l, geo, b.idx);
     return;
   }
   if (threadIdx.x >= 64 * NB_MAX) return;
   for (int k = blockIdx.x; k < cnt[1]; k += NLONG) {
-    layer_fwd<NB_MAX, 1>(k, cnt[1], &sm.one, w, b, Xc, types, nlist, nnei, grids, n, l, geo, b.idx + b.cap, Ei);
+    layer_fwd<NB_MAX, 1>(k, cnt[1], &sm.one, w, b, Xc, types, nlist, nnei, grids, n, l, geo, b.idx + b.cap);
     __syncthreads();
   }
 }
@@ -812,13 +784,13 @@ void launch_edge_count(const Buffers &b, const Workspace &ws, int n, int64_t *ho
 }
 
 void launch_layer_fwd(const Weights &w, const Buffers &b, const Workspace &ws, const double *coords,
-                      const int *types, int n, int layer, const Geo &geo, double *Ei, hipStream_t st) {
+                      const int *types, int n, int layer, const Geo &geo, hipStream_t st) {
   if (n <= ONE_UP_TO)
     hipLaunchKernelGGL(k_rep_fwd_one, dim3(n), dim3(64 * NB_MAX), 0, st, w, b, coords, types, ws.nlist, ws.nnei, ws.grids, n,
-                       layer, geo, Ei, ws.flags);
+                       layer, geo, ws.flags);
   else
     hipLaunchKernelGGL(k_rep_fwd, dim3(NLONG + (n + 1) / 2), dim3(128 * NB_SMALL), 0, st, w, b, coords, types, ws.nlist,
-                       ws.nnei, ws.grids, n, layer, geo, ws.bcnt, Ei, ws.flags);
+                       ws.nnei, ws.grids, n, layer, geo, ws.bcnt, ws.flags);
 }
 
 void launch_layer_bwd(const Weights &w, const Buffers &b, const Workspace &ws, const double *coords,

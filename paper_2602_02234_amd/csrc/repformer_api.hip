@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "../../include/dp.h"
+#include "node_fit.h"
 #include "repformer.h"
 
 using namespace dp;
@@ -19,6 +20,7 @@ struct dp_rep {
   double rc = 0, rcs = 0;
   int sel = 0, ntypes = 0;
   void *wbuf = nullptr;
+  NodeFit fit{};
   rep::Weights w{};
   Workspace ws;
   rep::Buffers b;
@@ -135,30 +137,19 @@ int load_weights(dp_rep *m, const char *path) {
   const size_t og = (img.size() + 255) & ~size_t(255);
   img.resize(og + 8 * FWID);
   std::memcpy(img.data() + og, src["G3"].data(), 8 * FWID);
-  // transposed copies and MFMA fragments (their order: dp_tiles.h, W)
+  // MFMA fragments
   auto put = [&](const std::vector<float> &v) {
     const size_t o = (img.size() + 255) & ~size_t(255);
     img.resize(o + 4 * v.size());
     std::memcpy(img.data() + o, v.data(), 4 * v.size());
     offs.push_back(o);
   };
-  auto transposed = [&](const std::vector<double> &v, int rows, int cols) {
-    std::vector<float> t((size_t)rows * cols);
-    for (int r = 0; r < rows; ++r)
-      for (int c = 0; c < cols; ++c) t[(size_t)c * rows + r] = (float)v[(size_t)r * cols + c];
-    put(t);
-  };
-  auto frag = [&](int outs, int K, auto W) {
-    std::vector<float> v((size_t)outs * K);
-    for (int t = 0; t < outs / 16; ++t)
-      for (int k = 0; k < K / 16; ++k)
-        for (int ln = 0; ln < 64; ++ln)
-          for (int s = 0; s < 4; ++s)
-            v[((size_t)(t * (K / 16) + k) * 64 + ln) * 4 + s] = (float)W(16 * t + ln % 16, 16 * k + 4 * (ln / 16) + s);
-    put(v);
-  };
-  transposed(src["G1"], G1D, FWID);
-  transposed(src["G2"], FWID, FWID);
+  auto frag = [&](int outs, int K, auto W) { put(node_fragments(outs, K, W)); };
+  const std::vector<double> &g1 = src["G1"], &g2 = src["G2"];
+  frag(FWID, G1D, [&](int o, int k) { return g1[k * FWID + o]; });
+  frag(FWID, FWID, [&](int o, int k) { return g2[k * FWID + o]; });
+  frag(FWID, FWID, [&](int o, int k) { return g2[o * FWID + k]; });
+  frag(G1D, FWID, [&](int o, int k) { return g1[o * FWID + k]; });
   for (int l = 0; l < NLAYER; ++l) {
     const std::string s = std::to_string(l);
     const std::vector<double> &wa = src["Wa" + s];
@@ -181,14 +172,18 @@ int load_weights(dp_rep *m, const char *path) {
     k += 3;
     w.W1[l] = nxt(); w.b1[l] = nxt();
   }
-  w.G1 = nxt(); w.d1 = nxt(); w.G2 = nxt(); w.d2 = nxt(); w.G3 = nxt();
+  NodeFit &nf = m->fit;
+  (void)nxt();
+  nf.d1 = nxt();
+  (void)nxt();
+  nf.d2 = nxt(); nf.G3 = nxt();
   (void)nxt();  // d3 goes by value
-  w.G3d = (const double *)(base + og);
-  w.G1T = nxt(); w.G2T = nxt();
+  nf.G3d = (const double *)(base + og);
+  nf.G1 = nxt(); nf.G2 = nxt(); nf.G2T = nxt(); nf.G1T = nxt();
   for (int l = 0; l < NLAYER; ++l) {
     w.Pa[l] = nxt(); w.Pqkv[l] = nxt(); w.Pqkvt[l] = nxt(); w.Pat[l] = nxt();
   }
-  w.d3 = d3;
+  nf.d3 = d3;
   return DP_OK;
 }
 
@@ -257,7 +252,8 @@ int rep_step(dp_rep *m, int64_t natoms, const double *X, const int32_t *types, c
   rep::launch_edge_count(m->b, ws, n, m->etot_host, st);
   record(m, 1, st);
   rep::Geo geo{(float)m->rc, (float)m->rcs, 1.f / (float)m->sel};
-  for (int l = 0; l < NLAYER; ++l) rep::launch_layer_fwd(m->w, m->b, ws, X, types, n, l, geo, ws.Ei, st);
+  for (int l = 0; l < NLAYER; ++l) rep::launch_layer_fwd(m->w, m->b, ws, X, types, n, l, geo, st);
+  launch_node_fit(m->fit, m->b.dnl, n, ws.Ei, ws.flags, st);
   record(m, 2, st);
   const bool bwd = forces || virial;
   if (bwd) {
