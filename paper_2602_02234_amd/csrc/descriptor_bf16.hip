@@ -254,34 +254,7 @@ __device__ __forceinline__ f4 residual(const float *scr, int t) {
   return f4{a[0], a[1], b[0], b[1]};
 }
 
-// Copy of N values from global memory to LDS by a workgroup of NT threads: loaded here, stored later.
-template <int N, int NT> struct Fetch {
-  static constexpr int P = N / 8, R = (P + NT - 1) / NT;
-  bf8 v[R];
-  __device__ __forceinline__ Fetch() {}
-  __device__ __forceinline__ explicit Fetch(const bf16_t *__restrict__ w) { load(w); }
-  static __device__ __forceinline__ int thread() {
-    int t = threadIdx.x;
-    asm volatile("" : "+v"(t));  // as lane()
-    return t;
-  }
-  __device__ __forceinline__ void load(const bf16_t *__restrict__ w) {
-    const int t = thread();
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int k = t + r * NT;
-      v[r] = ld8(w + 8 * (k < P ? k : 0));
-    }
-  }
-  __device__ __forceinline__ void store(bf16_t *d) const {
-    const int t = thread();
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int k = t + r * NT;
-      if (k < P) *reinterpret_cast<bf8 *>(d + 8 * k) = v[r];
-    }
-  }
-};
+template <int N, int NT> using Fetch = Copy16<N / 8, NT>;
 template <int NT> struct FetchEmb {  // W2^T, then W3^T
   Fetch<W2T_N, NT> a;
   Fetch<W3T_N, NT> b;

@@ -124,6 +124,37 @@ __device__ __forceinline__ f4 get_tile(const float *tile) {
   return o;
 }
 
+// Copy of N 16-byte pieces from global memory to LDS by a workgroup of NT threads: loaded first, stored
+// when their place is free.
+template <int N, int NT> struct Copy16 {
+  static constexpr int R = (N + NT - 1) / NT;
+  f4 v[R];
+  static __device__ __forceinline__ int thread() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));  // as lane()
+    return t;
+  }
+  __device__ __forceinline__ Copy16() {}
+  __device__ __forceinline__ explicit Copy16(const void *__restrict__ w) { load(w); }
+  __device__ __forceinline__ void load(const void *__restrict__ w) {
+    const int t = thread();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int k = t + r * NT;
+      v[r] = ldf4(static_cast<const float *>(w) + 4 * (k < N ? k : 0));
+    }
+  }
+  // pieces A .. B - 1 only, to d
+  template <int A = 0, int B = N> __device__ __forceinline__ void store(void *d) const {
+    const int t = thread();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int k = t + r * NT;
+      if (k >= A && k < B) stf4(static_cast<float *>(d) + 4 * (k - A), v[r]);
+    }
+  }
+};
+
 // tanh of the layers' hot loops, from the hardware exponential and reciprocal:
 // tanh x = 1 - 2 / (1 + exp(2 x)); absolute error about 1e-7, the float32 rounding of the
 // sums it enters.

@@ -37,6 +37,7 @@ namespace rep {
 namespace {
 
 constexpr int LK = G2D + 4;   // row stride of the keys' rows in LDS: row reads and reads along keys without conflicts
+constexpr int PMAT = 3072;     // floats of one of the pair matrices Pa, Pqkv, Pqkvt, Pat (which lie in this order)
 constexpr int NB_SMALL = 6;   // blocks up to which two atoms share a workgroup of 12 waves
 constexpr int NB_MAX = 8;     // blocks of the longest list
 constexpr int ONE_UP_TO = 256;  // atoms up to which each has a workgroup (and a CU) of its own
@@ -148,20 +149,20 @@ __device__ __forceinline__ void product(f4 (&out)[NT], const float *__restrict__
 }
 
 // Pair update and projections of the lane's token: ta = tanh([g2, g1_j] Wa + ba), g2a = g2 + ta,
-// q its query; its key and value rows go to LDS.
-__device__ __forceinline__ void pair_and_qkv(const Weights &w, int l, const f4 (&x)[6], f4 (&ta)[2], f4 (&g2a)[2],
-                                             f4 (&qr)[2], float *Krow, float *Vrow) {
+// q its query; its key and value rows go to LDS.  wl: Pa and Pqkv in LDS.
+__device__ __forceinline__ void pair_and_qkv(const Weights &w, const float *wl, int l, const f4 (&x)[6], f4 (&ta)[2],
+                                             f4 (&g2a)[2], f4 (&qr)[2], float *Krow, float *Vrow) {
   const int q = lane() >> 4;
 #pragma unroll
   for (int t = 0; t < 2; ++t) ta[t] = ldf4(w.ba[l] + 16 * t + 4 * q);
-  product<6, 2>(ta, w.Pa[l], x);
+  product<6, 2>(ta, wl, x);
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     ta[t] = act(ta[t]);
     g2a[t] = x[t] + ta[t];
   }
   f4 qkv[6] = {};
-  product<2, 6>(qkv, w.Pqkv[l], g2a);
+  product<2, 6>(qkv, wl + PMAT, g2a);
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     qr[t] = qkv[t];
@@ -351,7 +352,7 @@ template <int NB> struct SmemF {
 };
 
 template <int NB, int NA>
-__device__ __forceinline__ void layer_fwd(int blk, int count, SmemF<NB> *smem, const Weights &w, const Buffers &b,
+__device__ __forceinline__ void layer_fwd(int blk, int count, SmemF<NB> *smem, float *wl, const Weights &w, const Buffers &b,
                                           const double *__restrict__ Xc, const int *__restrict__ types,
                                           const int *__restrict__ nlist, const int *__restrict__ nnei,
                                           const Grid *__restrict__ grids, int natoms, int l, const Geo &geo,
@@ -361,15 +362,17 @@ __device__ __forceinline__ void layer_fwd(int blk, int count, SmemF<NB> *smem, c
   const int i = pt.i, nn = pt.n, nb = pt.nb, jb = pt.jb, tid = pt.tid;
   const int ln = lane(), q = ln >> 4, c = ln & 15;
   const bool act_ = jb < nb, live = nb > 0;
+  const Copy16<PMAT / 2, 64 * NB * NA> cw(w.Pa[l]);
   build_envn<NB>(sm.e, tid, Xc, types, nlist, i, nn, natoms, grids[0], geo);
   if (tid < G1D)
     sm.g1i[tid] = l == 0 ? w.TN[clamp_type(types[i]) * G1D + tid] : b.g1f[((size_t)(l - 1) * b.cap + i) * G1D + tid];
+  cw.store(wl);
   __syncthreads();
   const int j = 16 * jb + c;
   f4 x[6], ta[2], g2a[2], qr[2];
   if (act_) {
     token_in<NB>(w, b, sm.e, l, i, j, nn, x);
-    pair_and_qkv(w, l, x, ta, g2a, qr, sm.K + j * LK, sm.V + j * LK);
+    pair_and_qkv(w, wl, l, x, ta, g2a, qr, sm.K + j * LK, sm.V + j * LK);
   }
   const NodeW<NA * NB> w1(w.W1[l], pt.half * NB + jb);
   tile_barrier();
@@ -437,6 +440,8 @@ __device__ __forceinline__ void layer_bwd(int blk, int count, SmemB<NB> *smem, c
   const bool act_ = jb < nb, live = nb > 0, top = l == NLAYER - 1;
   const f4 zero = {0.f, 0.f, 0.f, 0.f};
   const float isq = 0.17677669529663687f;
+  float *wl = &smem[0].tile[0][0][0];  // the tiles' place, until the scores
+  const Copy16<PMAT / 2, 64 * NB * NA> cw(w.Pa[l]);
   build_envn<NB>(sm.e, tid, Xc, types, nlist, i, nn, natoms, grids[0], geo);
   for (int k = tid; k < 16 * NB; k += NT) sm.slot[k] = !top && k < nn ? b.slot[(size_t)i * SEL + k] : -1;
   const size_t li = (size_t)l * b.cap + i;
@@ -446,6 +451,7 @@ __device__ __forceinline__ void layer_bwd(int blk, int count, SmemB<NB> *smem, c
     dni = b.dnl[(size_t)i * G1D + tid];
   }
   if (tid < 4 * G2D) sm.T[tid] = b.Tn[li * (4 * G2D) + tid];
+  cw.store(wl);
   __syncthreads();
   const int j = 16 * jb + c;
   const bool ok = act_ && j < nn;
@@ -469,7 +475,7 @@ __device__ __forceinline__ void layer_bwd(int blk, int count, SmemB<NB> *smem, c
       dy[t] = ok && !top ? ldf4(b.dg2 + ((size_t)i * SEL + j) * G2D + 16 * t + 4 * q) : zero;
       g1[t] = x[2 + t];
     }
-    pair_and_qkv(w, l, x, ta, g2a, qr, sm.K + j * LK, sm.V + j * LK);
+    pair_and_qkv(w, wl, l, x, ta, g2a, qr, sm.K + j * LK, sm.V + j * LK);
   }
   {
     f4 dn = v[0] + v[1] + v[2] + v[3];
@@ -610,8 +616,11 @@ __device__ __forceinline__ void layer_bwd(int blk, int count, SmemB<NB> *smem, c
       stf4(sm.V + j * LK + 16 * t + 4 * q, dy[t]);
     }
   __syncthreads();
+  const Copy16<PMAT / 2, 64 * NB * NA> ct(w.Pqkvt[l]);
   if (act_) column(sm.V, [](f4) {}, dv);
   __syncthreads();
+  ct.template store<0, PMAT / 4>(smem[0].V);  // the rows of dY are no longer needed
+  if (NA == 2) ct.template store<PMAT / 4, PMAT / 2>(smem[NA - 1].V);
   if (act_)
 #pragma unroll
     for (int kt = 0; kt < NB; ++kt)
@@ -638,14 +647,15 @@ __device__ __forceinline__ void layer_bwd(int blk, int count, SmemB<NB> *smem, c
     dqkv[4 + t] = sm.e.sw[j] * dv[t];
     dg[t] = zero;
   }
-  product<6, 2>(dg, w.Pqkvt[l], dqkv);
+  product<6, 2>(dg, smem[0].V, dqkv);
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     dg[t] += dy[t];  // dE/dg2a
     dz[t] = dg[t] * (1.f - ta[t] * ta[t]);
   }
   f4 dx[6] = {};
-  product<2, 6>(dx, w.Pat[l], dz);
+  if (NA == 2) product<2, 6>(dx, smem[NA - 1].V, dz);
+  else product<2, 6>(dx, w.Pat[l], dz);
 #pragma unroll
   for (int t = 0; t < 2; ++t) dg[t] += dx[t];  // dE/dg2 of the layer's input
   if (l > 0) {
@@ -695,8 +705,9 @@ k_rep_fwd_one(Weights w, Buffers b, const double *__restrict__ Xc, const int *__
               const int *__restrict__ nlist, const int *__restrict__ nnei, const Grid *__restrict__ grids, int n, int l,
               Geo geo, const unsigned *__restrict__ flags) {
   __shared__ SmemF<NB_MAX> sm;
+  __shared__ float wl[2 * PMAT] __attribute__((aligned(16)));
   if (failed(flags)) return;
-  layer_fwd<NB_MAX, 1>(blockIdx.x, n, &sm, w, b, Xc, types, nlist, nnei, grids, n, l, geo, nullptr);
+  layer_fwd<NB_MAX, 1>(blockIdx.x, n, &sm, wl, w, b, Xc, types, nlist, nnei, grids, n, l, geo, nullptr);
 }
 __global__ void __launch_bounds__(64 * NB_MAX) __attribute__((amdgpu_waves_per_eu(2)))
 k_rep_bwd_one(Weights w, Buffers b, const double *__restrict__ Xc, const int *__restrict__ types,
@@ -713,15 +724,16 @@ k_rep_fwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__rest
           const int *__restrict__ nnei, const Grid *__restrict__ grids, int n, int l, Geo geo, const int *__restrict__ cnt,
           const unsigned *__restrict__ flags) {
   __shared__ union { SmemF<NB_SMALL> two[2]; SmemF<NB_MAX> one; } sm;
+  __shared__ float wl[2 * PMAT] __attribute__((aligned(16)));
   if (failed(flags)) return;
   const int blk = blockIdx.x - NLONG;
   if (blk >= 0) {
-    if (2 * blk < cnt[0]) layer_fwd<NB_SMALL, 2>(blk, cnt[0], sm.two, w, b, Xc, types, nlist, nnei, grids, n, l, geo, b.idx);
+    if (2 * blk < cnt[0]) layer_fwd<NB_SMALL, 2>(blk, cnt[0], sm.two, wl, w, b, Xc, types, nlist, nnei, grids, n, l, geo, b.idx);
     return;
   }
   if (threadIdx.x >= 64 * NB_MAX) return;
   for (int k = blockIdx.x; k < cnt[1]; k += NLONG) {
-    layer_fwd<NB_MAX, 1>(k, cnt[1], &sm.one, w, b, Xc, types, nlist, nnei, grids, n, l, geo, b.idx + b.cap);
+    layer_fwd<NB_MAX, 1>(k, cnt[1], &sm.one, wl, w, b, Xc, types, nlist, nnei, grids, n, l, geo, b.idx + b.cap);
     __syncthreads();
   }
 }
