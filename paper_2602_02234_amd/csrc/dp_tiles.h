@@ -167,12 +167,30 @@ __device__ __forceinline__ f4 act(f4 v) {
   for (int i = 0; i < 4; ++i) v[i] = act(v[i]);
   return v;
 }
+// tanh without branches: Taylor's series up to 0.45 (its remainder there is below 1e-8), beyond it
+// 1 - 2 t / (1 + t) with t = exp(-2 |x|) from the hardware exponential and reciprocal, the rounding
+// of the exponent, of 1 + t and of the quotient put back.  Within 3 units in the last place in a simulation
+// with the hardware functions off by one, 0.3 in the mean; tanhf's branches took a third of the
+// descriptor's embedding.
+__device__ __forceinline__ float tanh_fast(float x) {
+  constexpr float C = 2.885390043258667f, CL = 3.851926e-8f;  // 2 / ln 2
+  const float ax = fabsf(x), y = -C * ax, yl = fmaf(-C, ax, -y) - CL * ax;
+  float t = __builtin_amdgcn_exp2f(y);
+  t = fmaf(t, yl * 0.6931471805599453f, t);
+  const float d = 1.f + t, dl = t - (d - 1.f), r = __builtin_amdgcn_rcpf(d), q = 2.f * t * r;
+  const float big = 1.f - fmaf(fmaf(-dl, q, fmaf(-d, q, 2.f * t)), r, q);
+  const float z = x * x;
+  float p = fmaf(fmaf(21844.f / 6081075.f, z, -1382.f / 155925.f), z, 62.f / 2835.f);
+  p = fmaf(fmaf(fmaf(p, z, -17.f / 315.f), z, 2.f / 15.f), z, -1.f / 3.f);
+  return ax < 0.45f ? fmaf(p * z, x, x) : copysignf(big, x);
+}
+
 // Initial features tanh(x w + b) of a lane's four features.
 __device__ __forceinline__ f4 init4(float x, const float *__restrict__ w, const float *__restrict__ b) {
   const f4 wv = ldf4(w), bv = ldf4(b);
   f4 v;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) v[i] = tanhf(x * wv[i] + bv[i]);
+  for (int i = 0; i < 4; ++i) v[i] = tanh_fast(x * wv[i] + bv[i]);
   return v;
 }
 

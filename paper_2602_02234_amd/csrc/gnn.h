@@ -63,7 +63,7 @@ struct Buffers {
   int64_t *aoff = nullptr;    // [cap + 1]: angle offsets
   float *nf = nullptr;        // [2][cap][64]       n after layers 1, 2
   float *ef = nullptr;        // [3][cap][SEL][64]  e after layers 1, 2, 3
-  float *af = nullptr;        // [3][acap][32]      a after layers 1, 2, 3
+  float *af = nullptr;        // [2][acap][32]      a after layers 1, 2 (the backward recomputes layer 3's)
   float *da = nullptr;        // [acap][32]         dE/da, updated in place layer by layer
   float *de = nullptr;        // [cap][SEL][64]     dE/de, likewise
   float *dnj = nullptr;       // [2][cap][SEL][64]  edge (i, j)'s part of dE/dn_j, by layer parity

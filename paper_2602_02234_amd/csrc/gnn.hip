@@ -322,7 +322,7 @@ k_layer_fwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__re
 #pragma unroll
           for (int k = 0; k < 2; ++k) a[k] += act(wa[k](x, bp[k] + ldf4(pq + 32 + 16 * k)));
         }
-        if (ok) {
+        if (ok && l < NLAYER - 1) {
           float *ao = b.af + ((size_t)l * b.acap + abase + (int64_t)p * na + t) * ADIM + 4 * q;
           stf4(ao, a[0]);
           stf4(ao + 16, a[1]);
@@ -608,13 +608,9 @@ k_layer_bwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__re
 #pragma unroll
       for (int k = 0; k < 2; ++k) v[k] = ldf4(src + (size_t)idx * ADIM + 16 * k + 4 * q);
     };
-    const float *a1s = b.af + (size_t)l * b.acap * ADIM, *a0s = b.af + (size_t)max(l - 1, 0) * b.acap * ADIM;
-    f4 a1[2], a0[2];
-    if (wv < nc && na > 0) {
-      const int64_t idx = angle(wv, 0);
-      rows(a1s, idx, a1);
-      if (l > 0) rows(a0s, idx, a0);
-    }
+    const float *a0s = b.af + (size_t)max(l - 1, 0) * b.acap * ADIM;
+    f4 a0[2];
+    if (wv < nc && na > 0 && l > 0) rows(a0s, angle(wv, 0), a0);
     for (int qq = wv; qq < nc; qq += NW) {
       const int jq = e.cl[qq];
       const float swq = e.swa[jq] * geo.inv_asel;
@@ -628,7 +624,7 @@ k_layer_bwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__re
         const int p = ok ? t + (t >= qq) : 0;  // columns past the end read a valid row, unused
         const int jp = e.cl[p];
         const int64_t idx = angle(qq, t0);
-        // the next tile's rows of a' and a are read as soon as this one has used its own
+        // the next tile's rows of a are read as soon as this one has used its own
         const bool same = t0 + 16 < na, more = same || qq + NW < nc;
         const int64_t nidx = more ? angle(same ? qq : qq + NW, same ? t0 + 16 : 0) : abase;
         f4 da[2] = {zero, zero};
@@ -638,6 +634,19 @@ k_layer_bwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__re
 #pragma unroll
           for (int k = 0; k < 2; ++k) a0[k] = init4(cs, w.Wa0 + 16 * k + 4 * q, w.ba0 + 16 * k + 4 * q);
         }
+        // the angle update again: a' = a + tanh(...) (recomputed rather than stored: a quarter of the
+        // angles' traffic)
+        f4 ta[2], a1[2];
+        {
+          const X<T, 2> x(a0);
+#pragma unroll
+          for (int k = 0; k < 2; ++k) {
+            ta[k] = act(wa[k](x, ldf4(row + 16 * k + 4 * q) + ldf4(sm.PP + p * LPP + 16 * k + 4 * q)));
+            a1[k] = a0[k] + ta[k];
+          }
+        }
+        if (l > 0) rows(a0s, nidx, a0);
+        tile_barrier();
         // the message: dE/dw and dz_m = w dE/dm (1 - tanh^2)
         const float wr = ok ? e.swa[jp] * swq : 0.f;
         float d = 0.f;
@@ -654,19 +663,10 @@ k_layer_bwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__re
             zm[k] += dz[k];
           }
         }
-        rows(a1s, nidx, a1);
         tile_barrier();
         d = sumq(d);
         d = ok ? d : 0.f;
-        // the angle update: dE/da' and dz_a
-        f4 ta[2];
-        {
-          const X<T, 2> x(a0);
-#pragma unroll
-          for (int k = 0; k < 2; ++k) ta[k] = act(wa[k](x, ldf4(row + 16 * k + 4 * q) + ldf4(sm.PP + p * LPP + 16 * k + 4 * q)));
-        }
-        if (l > 0) rows(a0s, nidx, a0);
-        tile_barrier();
+        // dE/da' and dz_a
         f4 za1[2];
         {
           const X<T, 4> x(dz);

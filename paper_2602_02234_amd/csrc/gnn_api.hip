@@ -274,7 +274,7 @@ int ensure_angles(gnn::Buffers &b, int64_t na) {
   if (b.da) (void)hipFree(b.da);
   b.af = b.da = nullptr;
   b.acap = 0;
-  G_TRY(hipMalloc(&b.af, 3 * (size_t)cap * ADIM * sizeof(float)));
+  G_TRY(hipMalloc(&b.af, 2 * (size_t)cap * ADIM * sizeof(float)));
   G_TRY(hipMalloc(&b.da, (size_t)cap * ADIM * sizeof(float)));
   b.acap = cap;
   return DP_OK;
