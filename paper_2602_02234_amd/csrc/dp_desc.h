@@ -148,8 +148,7 @@ __device__ __forceinline__ void softmax_keys(f4 (&s)[NB], const EnvF<NB> &e, int
       if (16 * kt + 4 * q + i >= n) s[kt][i] = -INFINITY;
       m = fmaxf(m, s[kt][i]);
     }
-  m = fmaxf(m, __shfl_xor(m, 16));
-  m = fmaxf(m, __shfl_xor(m, 32));
+  m = maxq(m);
   if (m == -INFINITY) m = 0.f;
   float z = 0.f;
 #pragma unroll

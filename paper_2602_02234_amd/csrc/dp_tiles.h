@@ -12,11 +12,20 @@ namespace {
 __device__ __forceinline__ bool failed(const unsigned *flags) { return (flags[0] & FLAG_ERRORS) != 0u; }
 __device__ __forceinline__ f4 ldf4(const float *p) { return *reinterpret_cast<const f4 *>(p); }
 __device__ __forceinline__ void stf4(float *p, f4 v) { *reinterpret_cast<f4 *>(p) = v; }
-// Sum over the four lane groups (the lanes of one column).
+// Sum over the four lane groups (the lanes of one column): a swap of a value's odd rows of 16 lanes with
+// its own even rows leaves one of a pair of rows in both lanes of the pair, and the other in the second
+// result; likewise the halves of the wave.  In registers; __shfl_xor goes through LDS.
 __device__ __forceinline__ float sumq(float v) {
-  v += __shfl_xor(v, 16);
-  v += __shfl_xor(v, 32);
-  return v;
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+__device__ __forceinline__ float maxq(float v) {  // likewise the largest
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 __device__ __forceinline__ f4 sum16(f4 v) {
 #pragma unroll
@@ -185,12 +194,14 @@ __device__ __forceinline__ float tanh_fast(float x) {
   return ax < 0.45f ? fmaf(p * z, x, x) : copysignf(big, x);
 }
 
-// Initial features tanh(x w + b) of a lane's four features.
+// Initial features tanh(x w + b) of a lane's four features, with tanhf or tanh_fast: over 16 systems of
+// 768 atoms tanh_fast moved the repformer's virial by 0.8e-7 of itself, always the same way.
+template <float (*Tanh)(float)>
 __device__ __forceinline__ f4 init4(float x, const float *__restrict__ w, const float *__restrict__ b) {
   const f4 wv = ldf4(w), bv = ldf4(b);
   f4 v;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) v[i] = tanh_fast(x * wv[i] + bv[i]);
+  for (int i = 0; i < 4; ++i) v[i] = Tanh(x * wv[i] + bv[i]);
   return v;
 }
 

@@ -214,7 +214,7 @@ __global__ void __launch_bounds__(1024) k_angle_scan(int64_t *__restrict__ aoff,
 
 // The layer's input features e_ij of edge slot j, features 16 t + 4 q .. + 3.
 __device__ __forceinline__ f4 edge_in(const Weights &w, const Buffers &b, const GEnv &e, int l, int i, int j, int f) {
-  return l == 0 ? init4(e.s[j], w.We0 + f, w.be0 + f) : ldf4(b.ef + erow(b, l - 1, i, j) + f);
+  return l == 0 ? init4<tanh_fast>(e.s[j], w.We0 + f, w.be0 + f) : ldf4(b.ef + erow(b, l - 1, i, j) + f);
 }
 // ... and n of the neighbour of slot j.
 __device__ __forceinline__ f4 node_in(const Weights &w, const Buffers &b, const GEnv &e, int l, int j, int f) {
@@ -314,7 +314,7 @@ k_layer_fwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__re
         } else {
           const float cs = cosang(e, jp, e.cl[qr]);
 #pragma unroll
-          for (int k = 0; k < 2; ++k) a[k] = init4(cs, w.Wa0 + 16 * k + 4 * q, w.ba0 + 16 * k + 4 * q);
+          for (int k = 0; k < 2; ++k) a[k] = init4<tanh_fast>(cs, w.Wa0 + 16 * k + 4 * q, w.ba0 + 16 * k + 4 * q);
         }
         const float *pq = sm.PQ + qr * LPQ + 4 * q;
         {
@@ -632,7 +632,7 @@ k_layer_bwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__re
         if (l == 0) {
           const float cs = cosang(e, jp, jq);
 #pragma unroll
-          for (int k = 0; k < 2; ++k) a0[k] = init4(cs, w.Wa0 + 16 * k + 4 * q, w.ba0 + 16 * k + 4 * q);
+          for (int k = 0; k < 2; ++k) a0[k] = init4<tanh_fast>(cs, w.Wa0 + 16 * k + 4 * q, w.ba0 + 16 * k + 4 * q);
         }
         // the angle update again: a' = a + tanh(...) (recomputed rather than stored: a quarter of the
         // angles' traffic)

@@ -129,7 +129,7 @@ __device__ __forceinline__ void token_in(const Weights &w, const Buffers &b, con
     for (int t = 0; t < 4; ++t) x[2 + t] = ldf4(g1 + 16 * t + 4 * q);
 #pragma unroll
     for (int t = 0; t < 2; ++t)
-      x[t] = l == 0 ? init4(e.s[j], w.Wp0 + 16 * t + 4 * q, w.bp0 + 16 * t + 4 * q) : ldf4(b.g2f + erow2(b, l - 1, i, j) + 16 * t + 4 * q);
+      x[t] = l == 0 ? init4<tanhf>(e.s[j], w.Wp0 + 16 * t + 4 * q, w.bp0 + 16 * t + 4 * q) : ldf4(b.g2f + erow2(b, l - 1, i, j) + 16 * t + 4 * q);
   } else {
 #pragma unroll
     for (int t = 0; t < 6; ++t) x[t] = f4{0.f, 0.f, 0.f, 0.f};
@@ -217,8 +217,7 @@ __device__ __forceinline__ void softmax_keys(f4 (&s)[NB], const EnvN<NB> &e, int
       s[kt][i] = 16 * kt + 4 * q + i < n ? s[kt][i] * isq : -INFINITY;
       m = fmaxf(m, s[kt][i]);
     }
-  m = fmaxf(m, __shfl_xor(m, 16));
-  m = fmaxf(m, __shfl_xor(m, 32));
+  m = maxq(m);
   if (m == -INFINITY) m = 0.f;
   float z = 0.f;
 #pragma unroll
@@ -681,7 +680,7 @@ __device__ __forceinline__ void layer_bwd(int blk, int count, SmemB<NB> *smem, c
   float ds = 0.f;
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
-    const f4 g0 = init4(sm.e.s[j], w.Wp0 + 16 * t + 4 * q, w.bp0 + 16 * t + 4 * q);
+    const f4 g0 = init4<tanhf>(sm.e.s[j], w.Wp0 + 16 * t + 4 * q, w.bp0 + 16 * t + 4 * q);
     const f4 g = dg[t] * (1.f - g0 * g0) * ldf4(w.Wp0 + 16 * t + 4 * q);
     ds += (g[0] + g[1]) + (g[2] + g[3]);
   }
