@@ -205,7 +205,7 @@ template <int NB, int NA> struct Part {
 // a workgroup go to the SIMDs in turn, so that 12 waves put three on each, while a second
 // workgroup of 6 waves does not fit beside a first (two SIMDs would hold four waves of 168
 // registers; 9,999 atoms that way, float32: forward 2.73 ms, backward 6.9 ms, against 2.10 and
-// 4.85 ms in pairs).  Up to 256 atoms run one to a workgroup of eight waves, whatever their
+// 4.85 ms in pairs, when both were measured).  Up to 256 atoms run one to a workgroup of eight waves, whatever their
 // lists, without the lists of atoms and the second stream.
 constexpr int PAIR_FROM = 257;
 constexpr int NCU = 256;

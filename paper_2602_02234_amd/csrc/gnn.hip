@@ -28,9 +28,12 @@
 // wave order, so every sum has a fixed order.  Layer 0 turns the accumulated gradients of
 // s, sw_e, sw_a and rhat into g_ij = dE/dDelta_ij for the shared force gather.
 //
-// Bound: at the 9,999-atom box a forward layer moves 1.7 GB of angle rows (0.33 ms at the
-// copy rate) and has 0.42 ms of float32 MFMA work, a backward layer 3.4 GB (0.66 ms) and
-// 0.8 ms.
+// Bound: the products' and the activations' issue, one after the other in a tile, with two or three
+// waves per SIMD to overlap them, then the angle rows' traffic.  At the 9,999-atom box a forward layer moves
+// up to 1.7 GB of angle rows (0.33 ms at the copy rate) and has 0.46 ms of float32 MFMA work, a
+// backward layer up to 2.6 GB (0.5 ms) and 0.95 ms.  Measured per layer there, float32: forward 3.06 ->
+// 1.0 .. 1.1 ms, backward 6.89 -> 1.9 .. 2.4 ms, against kernels that staged every tile in LDS, one wave
+// to a SIMD; 2,931 atoms in bfloat16, a step 7.3 -> 2.1 ms.
 #include "dp_env.h"
 #include "dp_tiles.h"
 #include "gnn.h"
@@ -390,7 +393,7 @@ k_layer_fwd(Weights w, Buffers b, const double *__restrict__ Xc, const int *__re
   if (l < NLAYER - 1) return;
 
   // ---------------- fitting net, E_i and dE/dn_i (up to WIDE_UP_TO atoms: 4 us at 192 atoms, where a
-  // kernel over tiles of 16 atoms takes 9; from 2,931 atoms on that kernel takes the net, 30 us here)
+  // kernel over tiles of 16 atoms takes 9 and a launch; from 2,931 atoms on that kernel takes 9 .. 17 us, this 30 and more)
   if (tid < NDIM) sm.xs[tid] = n1;
   const float z1 = matvec<NW * 64, NDIM, FWID>(w.G1, sm.xs, sm.part, threadIdx.x);
   if (tid < FWID) sm.y1[tid] = tanhf(z1 + w.d1[tid]);
