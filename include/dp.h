@@ -304,7 +304,7 @@ int dp_nve_run(dp_model *m, int64_t natoms, double *d_coords, double *d_vel, con
  *   rc gives DP_ERR_TOO_LARGE (outputs untouched).  The call sizes its angle buffers
  *   from the step's angle count (one host round trip) and returns after the step
  *   has finished on the stream.  A dp_gnn owns grow-only device buffers of about
- *   190 KB per atom and 512 bytes per angle; it is not thread-safe.
+ *   190 KB per atom and 384 bytes per angle; it is not thread-safe.
  * dp_gnn_info: rc, rca, sel, asel of the model (pointers may be NULL).
  * dp_gnn_graph_size: edges (sum of the list lengths), angle-list edges (sum of nc
  *   over the atoms that have angles) and angles of the last successful step

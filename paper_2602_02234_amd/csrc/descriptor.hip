@@ -1,7 +1,7 @@
 // Per-atom descriptor kernels of the float32 path on gfx950: environment matrix,
 // type-embedded embedding net, two gated self-attention layers over the atom's
 // neighbours and the descriptor contraction (forward), and the hand-written backward
-// that turns dE/dD into g_ij = dE_i/dDelta_ij.
+// that turns dE/dT into g_ij = dE_i/dDelta_ij.
 //
 // Model (paper, Section II: embedding net over an atom and its neighbours,
 // self-attention layers updating that representation residually; sizes of the

@@ -1,8 +1,8 @@
-// Shared parts of the message-passing kernels (gnn.hip, repformer.hip): MFMA products in the
-// transposed form -- weights as A operand, features along the accumulator rows, 16 angles,
-// edges or tokens along the columns -- in which lane (q = lane / 16, c = lane % 16) holds
-// features 16 t + 4 q + i of column c, the layout of float4 rows in memory, of an
-// accumulator and of the next product's B operand alike.
+// Shared parts of the per-atom kernels (gnn.hip, repformer.hip, node_fit.hip; the descriptors through
+// dp_desc.h; fitting.hip): MFMA products in the transposed form -- weights as A operand, features
+// along the accumulator rows, 16 angles, edges, tokens or atoms along the columns -- in which
+// lane (q = lane / 16, c = lane % 16) holds features 16 t + 4 q + i of column c, the layout of
+// float4 rows in memory, of an accumulator and of the next product's B operand alike.
 #pragma once
 #include "dp_internal.h"
 
