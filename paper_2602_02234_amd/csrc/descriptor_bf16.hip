@@ -445,6 +445,8 @@ template <int NB> struct AtomBwd {
   float dT[M * 4] __attribute__((aligned(16)));
   EnvF<NB> e;
   Tab tab;
+  float dRt[16 * NB][4] __attribute__((aligned(16)));      // dE/dRt of the tokens
+  float dge[16 * NB][4] __attribute__((aligned(16)));      // the top layer's part of dE/drhat and dE/dsw
 };
 // Wvo and Wqk^T of a layer are read before the first rows go to K, so they are kept there (in the
 // two atoms' K, or, with one atom, the second beside it); Wqk, and between the layers the
@@ -510,7 +512,6 @@ __device__ __forceinline__ void layer_bwd_rows(const WeightsB16 &wp, int layer, 
   float *tile = sh.tile[NA == 2 ? 0 : jb];
   XB &ub = col.ub, hb;
   const int p0 = piece0();
-  const Fetch<WMAT, NT> f(wp.Wqk[layer]);
   const float hj[3] = {sm.e.rh[0][j], sm.e.rh[1][j], sm.e.rh[2][j]};
   {
     F100 dh = {};
@@ -524,6 +525,7 @@ __device__ __forceinline__ void layer_bwd_rows(const WeightsB16 &wp, int layer, 
     wmul(u, sh.wqkT(), ub);
     ub = XB(u);
   }
+  const Fetch<WMAT, NT> f(wp.Wqk[layer]);  // earlier it would wait in scratch memory
   f4 E[NB], W[NB];
   keys_dot<NB>(E, sm.G, ub, nb);
   f.store(sh.W[0]);
@@ -718,7 +720,7 @@ __device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB, NA> &sh
   __syncthreads();
   const int j = 16 * jb + c;
   F100 go;
-  float drh[3] = {0.f, 0.f, 0.f}, dsw = 0.f, dRt[4] = {0.f, 0.f, 0.f, 0.f};
+  float drh[3] = {0.f, 0.f, 0.f}, dsw = 0.f;
   {
     // the top layer's input: layer 0's output
     normalise(x, ln_eps);
@@ -744,7 +746,8 @@ __device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB, NA> &sh
       }
     }
 #pragma unroll
-    for (int a = 0; a < 4; ++a) dRt[a] = sumq(p[a]) * inv_sel;
+    for (int a = 0; a < 4; ++a) p[a] = sumq(p[a]) * inv_sel;
+    if (q == 0) stf4(sm.dRt[j], p);
     tile_barrier();
     norm_bwd(go, xh, is, sm.tab.gamma[1]);
     tile_barrier();
@@ -772,6 +775,8 @@ __device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB, NA> &sh
     fq.store(sh.wqkT());
     const float is = normalise(x0, ln_eps);
     norm_bwd(go, x0, is, sm.tab.gamma[0]);
+    if (q == 0) stf4(sm.dge[j], f4{drh[0], drh[1], drh[2], dsw});  // registers spill
+    drh[0] = drh[1] = drh[2] = dsw = 0.f;
   }
   __syncthreads();
   layer_bwd_rows<NB, NA>(wp, 0, sh, sm, go, col, jb, n, nb, drh);
@@ -822,7 +827,10 @@ __device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB, NA> &sh
     float4 out = make_float4(0.f, 0.f, 0.f, 0.f);
     if (j < n) {
       const float h[3] = {sm.e.rh[0][j], sm.e.rh[1][j], sm.e.rh[2][j]};
-      out = pair_gradient(sm.e.s[j], sm.e.sw[j], sm.e.r[j], h, ds, dRt, drh, dsw, rc, rcs);
+      const float dRt[4] = {sm.dRt[j][0], sm.dRt[j][1], sm.dRt[j][2], sm.dRt[j][3]};
+      const f4 ge = ldf4(sm.dge[j]);
+      for (int a = 0; a < 3; ++a) drh[a] += ge[a];
+      out = pair_gradient(sm.e.s[j], sm.e.sw[j], sm.e.r[j], h, ds, dRt, drh, dsw + ge[3], rc, rcs);
     }
     gout[(size_t)i * SEL + j] = out;
   }
