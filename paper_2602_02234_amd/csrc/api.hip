@@ -572,8 +572,7 @@ int ensure_ws(Workspace &ws, int prec, int64_t n, int nsys, bool skin, bool list
       HIP_TRY(hipMalloc(&ws.Gsave, cap * (size_t)NATTN * GSAVE_LAYER * sizeof(float)));
       HIP_TRY(hipMalloc(&ws.Tsave, cap * (size_t)M * 4 * sizeof(float)));
       HIP_TRY(hipMalloc(&ws.bidx, 2 * cap * sizeof(int)));
-      HIP_TRY(hipMalloc(&ws.fit, (cap + 16) * (size_t)ND * sizeof(float)));  // 16 spare rows for batched readers
-      HIP_TRY(hipMemset(ws.fit, 0, (cap + 16) * (size_t)ND * sizeof(float)));
+      HIP_TRY(hipMalloc(&ws.fit, cap * (size_t)ND * sizeof(float)));
       HIP_TRY(hipMalloc(&ws.Eh, cap * MAXH * sizeof(double)));
     }
     HIP_TRY(hipMalloc(&ws.Ei, cap * sizeof(double)));
