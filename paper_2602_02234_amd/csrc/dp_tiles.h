@@ -183,7 +183,7 @@ __device__ __forceinline__ f4 act(f4 v) {
 // descriptor's embedding.
 __device__ __forceinline__ float tanh_fast(float x) {
   constexpr float C = 2.885390043258667f, CL = 3.851926e-8f;  // 2 / ln 2
-  const float ax = fabsf(x), y = -C * ax, yl = fmaf(-C, ax, -y) - CL * ax;
+  const float ax = fminf(fabsf(x), 32.f), y = -C * ax, yl = fmaf(-C, ax, -y) - CL * ax;  // finite: 1 from 9.1 on
   float t = __builtin_amdgcn_exp2f(y);
   t = fmaf(t, yl * 0.6931471805599453f, t);
   const float d = 1.f + t, dl = t - (d - 1.f), r = __builtin_amdgcn_rcpf(d), q = 2.f * t * r;
@@ -191,7 +191,7 @@ __device__ __forceinline__ float tanh_fast(float x) {
   const float z = x * x;
   float p = fmaf(fmaf(21844.f / 6081075.f, z, -1382.f / 155925.f), z, 62.f / 2835.f);
   p = fmaf(fmaf(fmaf(p, z, -17.f / 315.f), z, 2.f / 15.f), z, -1.f / 3.f);
-  return ax < 0.45f ? fmaf(p * z, x, x) : copysignf(big, x);
+  return !(fabsf(x) >= 0.45f) ? fmaf(p * z, x, x) : copysignf(big, x);  // NaN by the series
 }
 
 // Initial features tanh(x w + b) of a lane's four features, with tanhf or tanh_fast: over 16 systems of
