@@ -148,17 +148,31 @@ __device__ __forceinline__ void product(f4 (&out)[NT], const float *__restrict__
   }
 }
 
+// W x with x = [g2, g1_j], the 32 features of g2 and the halves of g1_j each summed by themselves: shorter
+// sums round less, and g1_j's rounding, alike in all neighbours of one type (in the first layer
+// its parts take five values), does not average out.  The virial cancels to a twelfth of its terms and shows it: in one
+// sum, started from the bias, its error over 8 boxes of 192 atoms was 4.9e-7 of it in the mean, in parts 0.8e-7 .. 2.6e-7 (with
+// either form of tanh).
+__device__ __forceinline__ f4 sum_of_parts(const W<float, 6> &wt, const f4 (&x)[6]) {
+  f4 p[3] = {};
+#pragma unroll
+  for (int k = 0; k < 6; ++k)
+#pragma unroll
+    for (int s = 0; s < 4; ++s) p[k / 2] = mfma(wt.v[k][s], x[k][s], p[k / 2]);
+  return p[0] + (p[1] + p[2]);
+}
+
 // Pair update and projections of the lane's token: ta = tanh([g2, g1_j] Wa + ba), g2a = g2 + ta,
 // q its query; its key and value rows go to LDS.  wl: Pa and Pqkv in LDS.
 __device__ __forceinline__ void pair_and_qkv(const Weights &w, const float *wl, int l, const f4 (&x)[6], f4 (&ta)[2],
                                              f4 (&g2a)[2], f4 (&qr)[2], float *Krow, float *Vrow) {
   const int q = lane() >> 4;
 #pragma unroll
-  for (int t = 0; t < 2; ++t) ta[t] = ldf4(w.ba[l] + 16 * t + 4 * q);
-  product<6, 2>(ta, wl, x);
-#pragma unroll
   for (int t = 0; t < 2; ++t) {
-    ta[t] = act(ta[t]);
+    W<float, 6> wt;
+    wt.load(wl, t);
+    const f4 z = sum_of_parts(wt, x) + ldf4(w.ba[l] + 16 * t + 4 * q);
+    ta[t] = act(z);
     g2a[t] = x[t] + ta[t];
   }
   f4 qkv[6] = {};
