@@ -165,11 +165,14 @@ template <int N, int NT> struct Copy16 {
 };
 
 // tanh of the layers' hot loops, from the hardware exponential and reciprocal:
-// tanh x = 1 - 2 / (1 + exp(2 x)); absolute error about 1e-7, the float32 rounding of the
-// sums it enters.
+// tanh |x| = (1 - t) / (1 + t), t = exp(-2 |x|).  The difference is exact or rounded with the product, so
+// near zero only t's own rounding is left: absolute error 0.9e-8 in the mean and 2.4e-8 at most below 0.05,
+// 3.8e-8 and 1.3e-7 over |x| < 5.  (1 - 2 / (1 + exp(2 x)) is an instruction less but cancels: 4.6e-8 and
+// 1.2e-7 below 0.05.)
 __device__ __forceinline__ float act(float x) {
-  const float t = __builtin_amdgcn_exp2f(x * 2.885390081777927f);  // exp(2 x)
-  return fmaf(-2.f, __builtin_amdgcn_rcpf(1.f + t), 1.f);
+  const float t = __builtin_amdgcn_exp2f(-2.885390081777927f * fabsf(x));
+  const float r = __builtin_amdgcn_rcpf(1.f + t);
+  return copysignf(fmaf(-t, r, r), x);
 }
 __device__ __forceinline__ f4 act(f4 v) {
 #pragma unroll
