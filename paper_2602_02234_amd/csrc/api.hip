@@ -51,7 +51,7 @@ int read_model(const char *path, HostModel &h) {
     set_error(std::string("cannot open model file ") + path);
     return DP_ERR_MODEL_FILE;
   }
-  std::vector<char> raw((std::istreambuf_iterator<char>(f)), std::istreambuf_iterator<char>());
+  const std::vector<char> raw = read_all(f);
   if (raw.size() < 128 || std::memcmp(raw.data(), "DPAMDv01", 8) != 0) {
     set_error("model file: bad magic or short header");
     return DP_ERR_MODEL_FILE;

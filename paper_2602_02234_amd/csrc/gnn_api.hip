@@ -86,7 +86,7 @@ int load_weights(dp_gnn *m, const char *path) {
     set_error(std::string("cannot open GNN model file ") + path);
     return DP_ERR_MODEL_FILE;
   }
-  std::vector<char> raw((std::istreambuf_iterator<char>(f)), std::istreambuf_iterator<char>());
+  const std::vector<char> raw = read_all(f);
   if (raw.size() < 128 || std::memcmp(raw.data(), "DPGNNv01", 8) != 0) {
     set_error("GNN model file: bad magic or short header");
     return DP_ERR_MODEL_FILE;
@@ -112,6 +112,7 @@ int load_weights(dp_gnn *m, const char *path) {
   }
   // device image: every array as float32 (256-byte aligned), plus G3 in float64
   std::vector<unsigned char> img;
+  img.reserve(2 * raw.size());  // the arrays and their fragment-ordered copies in float32
   std::vector<size_t> offs;
   size_t off = 128;
   double d3 = 0.0;
@@ -130,7 +131,6 @@ int load_weights(dp_gnn *m, const char *path) {
         return DP_ERR_MODEL_FILE;
       }
     if (a.first == "d3") d3 = v[0];
-    src[a.first] = v;
     const size_t o = (img.size() + 255) & ~size_t(255);
     img.resize(o + 4 * v.size());
     for (size_t k = 0; k < v.size(); ++k) {
@@ -138,6 +138,7 @@ int load_weights(dp_gnn *m, const char *path) {
       std::memcpy(img.data() + o + 4 * k, &x, 4);
     }
     offs.push_back(o);
+    src[a.first] = std::move(v);
   }
   if (off != raw.size()) {
     set_error("GNN model file: size does not match its header");
