@@ -38,8 +38,7 @@ struct Weights {
   const float *TN;                // [NTYPES][64]
   const float *We0, *be0;         // [64]
   const float *Wa0, *ba0;         // [32]
-  const float *Waa[NLAYER], *baa[NLAYER];  // [96][32], [32]
-  const float *Wea[NLAYER], *bea[NLAYER];  // [64][64], [64]
+  const float *baa[NLAYER], *bea[NLAYER];  // [32], [64]  (Waa and Wea are read in fragment order only)
   const float *Wee[NLAYER], *bee[NLAYER];  // [192][64], [64]
   const float *Wnn[NLAYER], *bnn[NLAYER];  // [128][64], [64]
   const float *G1, *d1, *G2, *d2, *G3;     // [64][128], [128], [128][128], [128], [128]

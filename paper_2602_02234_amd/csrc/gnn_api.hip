@@ -215,7 +215,10 @@ int load_weights(dp_gnn *m, const char *path) {
   gnn::Weights &w = m->w;
   w.TN = nxt(); w.We0 = nxt(); w.be0 = nxt(); w.Wa0 = nxt(); w.ba0 = nxt();
   for (int l = 0; l < NLAYER; ++l) {
-    w.Waa[l] = nxt(); w.baa[l] = nxt(); w.Wea[l] = nxt(); w.bea[l] = nxt();
+    (void)nxt();  // Waa, and Wea below
+    w.baa[l] = nxt();
+    (void)nxt();
+    w.bea[l] = nxt();
     w.Wee[l] = nxt(); w.bee[l] = nxt(); w.Wnn[l] = nxt(); w.bnn[l] = nxt();
   }
   w.G1 = nxt(); w.d1 = nxt(); w.G2 = nxt(); w.d2 = nxt(); w.G3 = nxt();

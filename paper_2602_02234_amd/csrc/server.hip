@@ -201,8 +201,7 @@ int launch_batch(dp_server *s, Lane &L) {
   SRV_TRY(hipMemcpyAsync(L.hF, L.dF, 3 * tot * sizeof(double), hipMemcpyDeviceToHost, L.st));
   SRV_TRY(hipMemcpyAsync(L.hE, L.dE, nsys * sizeof(double), hipMemcpyDeviceToHost, L.st));
   SRV_TRY(hipMemcpyAsync(L.hV, L.dV, 9 * nsys * sizeof(double), hipMemcpyDeviceToHost, L.st));
-  SRV_TRY(hipMemcpyAsync(L.ws.flags_host, L.ws.flags, 4 * sizeof(unsigned), hipMemcpyDeviceToHost, L.st));
-  SRV_TRY(hipEventRecord(L.done_ev, L.st));
+  SRV_TRY(hipEventRecord(L.done_ev, L.st));  // the status words are in flags_host by then (k_reduce)
   L.atoms = tot;
   return DP_OK;
 }
