@@ -253,7 +253,7 @@ __device__ __forceinline__ void desc_fwd(int blk, int count, SmemFwd<NB> *smem, 
 #pragma unroll
       for (int t = 0; t < 7; ++t) y[t] += x[t];
       // LayerNorm; the centred rows are what the backward reads
-      const float mu = sum100([&](int t, int k) { return y[t][k]; }) * (1.f / M);
+      const float mu = sum100([&](int t, int k) { return y[t][k]; }) / (float)M;
 #pragma unroll
       for (int t = 0; t < 7; ++t) y[t] -= mu;
       save_block(Gsave + ((size_t)i * NATTN + layer) * GSAVE_LAYER + 1600 * jb, y);
@@ -292,7 +292,7 @@ __device__ __forceinline__ void desc_fwd(int blk, int count, SmemFwd<NB> *smem, 
   for (int k = tid; k < (nb ? M * 4 : 0); k += 64 * NB) {
     float acc = 0.f;
     for (int v = 0; v < nb; ++v) acc += sm.part[v][k];
-    Tsave[(size_t)i * M * 4 + k] = acc * (1.f / (float)SEL);
+    Tsave[(size_t)i * M * 4 + k] = acc / (float)SEL;
   }
 }
 
@@ -398,8 +398,8 @@ __device__ __forceinline__ void layer_bwd(const Weights<float> &w, int layer, Sm
       const float is = normalise(xh, ln_eps);
 #pragma unroll
       for (int t = 0; t < 7; ++t) dx[t] = tab4(w.gamma[layer], t) * go[t];
-      const float s0 = sum100([&](int t, int k) { return dx[t][k]; }) * (1.f / M);
-      const float s1 = sum100([&](int t, int k) { return dx[t][k] * xh[t][k]; }) * (1.f / M);
+      const float s0 = sum100([&](int t, int k) { return dx[t][k]; }) / (float)M;
+      const float s1 = sum100([&](int t, int k) { return dx[t][k] * xh[t][k]; }) / (float)M;
 #pragma unroll
       for (int t = 0; t < 7; ++t) dx[t] = (dx[t] - s0 - xh[t] * s1) * is;
     }
@@ -567,7 +567,6 @@ __device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB> *smem, 
     // dG = Rt dT^T / sel for its output, and dRt = G dT / sel
     load_block(x, gs + GSAVE_LAYER + 1600 * jb);
     normalise(x, ln_eps);
-    const float inv_sel = 1.f / (float)SEL;
     const float sj = sm.e.s[j];
     const float rt1 = sj * sm.e.rh[0][j], rt2 = sj * sm.e.rh[1][j], rt3 = sj * sm.e.rh[2][j];
     f4 p = {0.f, 0.f, 0.f, 0.f};
@@ -578,12 +577,12 @@ __device__ __forceinline__ void desc_bwd(int blk, int count, SmemBwd<NB> *smem, 
 #pragma unroll
       for (int k = 0; k < (t < 6 ? 4 : 1); ++k) {
         const f4 d = ldf4(sm.dT + 4 * (t < 6 ? 16 * t + 4 * q + k : 96 + q));
-        go[t][k] = (sj * d[0] + rt1 * d[1] + rt2 * d[2] + rt3 * d[3]) * inv_sel;
+        go[t][k] = (sj * d[0] + rt1 * d[1] + rt2 * d[2] + rt3 * d[3]) / (float)SEL;
         p += gv[k] * d;
       }
     }
 #pragma unroll
-    for (int a = 0; a < 4; ++a) p[a] = sumq(p[a]) * inv_sel;
+    for (int a = 0; a < 4; ++a) p[a] = sumq(p[a]) / (float)SEL;
     if (q == 0) *reinterpret_cast<f4 *>(sm.dRt + 4 * j) = p;
   }
   __syncthreads();
