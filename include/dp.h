@@ -301,10 +301,14 @@ int dp_nve_run(dp_model *m, int64_t natoms, double *d_coords, double *d_vel, con
  * dp_gnn_compute_device: arguments, units and outputs as dp_compute_device (device
  *   pointers, box on the host or NULL, energy required, the rest may be NULL).  The
  *   neighbour lists must be complete: an atom with more than sel neighbours within
- *   rc gives DP_ERR_TOO_LARGE (outputs untouched).  The call sizes its angle buffers
- *   from the step's angle count (one host round trip) and returns after the step
- *   has finished on the stream.  A dp_gnn owns grow-only device buffers of about
- *   190 KB per atom and 384 bytes per angle; it is not thread-safe.
+ *   rc gives DP_ERR_TOO_LARGE (outputs untouched).  The call returns after the step
+ *   has finished on the stream.  Its angle buffers are sized from the step's angle
+ *   count, for which the host waits in the middle of the step where there are more
+ *   atoms than in any call before (or phases are timed); other steps run with the
+ *   buffers there are, and one with more angles than they hold writes no outputs, is
+ *   repeated with larger buffers within the call, and takes up to twice as long.  A
+ *   dp_gnn owns grow-only device buffers of about 190 KB per atom and 384 bytes per
+ *   angle; it is not thread-safe.
  * dp_gnn_info: rc, rca, sel, asel of the model (pointers may be NULL).
  * dp_gnn_graph_size: edges (sum of the list lengths), angle-list edges (sum of nc
  *   over the atoms that have angles) and angles of the last successful step

@@ -20,8 +20,8 @@
 // Bound: the float32 MFMA rate (157 TFLOP/s), then the weights' way through L1 in the forward, spills and
 // the stages between barriers in the backward.  Per 16-neighbour block and layer the
 // forward issues 668 and the backward 1,389 MFMAs 16x16x4 of 32 cycles at 96 neighbours.  Measured
-// at 9,999 atoms: forward 1.87 ms (MFMAs alone 1.07), backward 4.40 ms; the step, which took 26.7 ms with
-// kernels that passed every operand through LDS, 6.84 ms; 150 atoms, one to a CU: 66 and 142 us.
+// at 9,999 atoms: forward 1.86 ms (MFMAs alone 1.07), backward 4.42 ms; the step, which took 26.7 ms with
+// kernels that passed every operand through LDS, 6.85 ms; 150 atoms, one to a CU: 66 and 144 us.
 //
 // Layout: one workgroup per atom, one wave per block of 16 neighbours (tokens).  A wave
 // keeps everything that belongs to its tokens in registers, transposed (features or keys

@@ -23,9 +23,9 @@
 // Bound: vector instructions (softmax, LayerNorm, tanh, conversions), then the latency of the
 // stages between barriers; the matrix cores' share is about a fifth (101 MFMAs of 16 cycles per
 // block and layer forward, 232 backward, at 96 neighbours).  In the backward vector instructions and
-// LDS are each busy for two fifths of the time.  Measured at 24,999 atoms: forward 2.72 -> 1.14 ms,
+// LDS are each busy for two fifths of the time.  Measured at 24,999 atoms: forward 2.72 -> 1.18 ms,
 // backward 5.95 -> 2.87 ms, against one atom per CU with G in LDS twice and rows of 16 keys gathered
-// through it; at 192 atoms, one to a CU, 22 and 48 us.  The 12-wave backward spills 39 registers a
+// through it; at 192 atoms, one to a CU, 22 and 49 us.  The 12-wave backward spills 39 registers a
 // wave; with 84 (a matrix loaded two products early, dE/dRt kept to the end) it took 2.94 ms.
 #include "dp_desc.h"
 

@@ -221,7 +221,7 @@ __global__ void __launch_bounds__(NHT * 64) k_fit_mid(Tables w, Heads<P> hd, con
   for (int x = threadIdx.x; x < 2 * 16 * AT * 4; x += NHT * 64) X[x / (64 * AT)].put(x / 4 % (16 * AT), FH + 4 * (x % 4), zero);
   double esum = 0.0;
   // The first half of a matrix is loaded ahead of a barrier, the second while the first is used: both ahead
-  // take half of the registers and spill.
+  // take half of the registers (the bfloat16 instance with 32 atoms spills 16 as it is).
   const auto weights = [&](const typename P::Mat &m, typename P::A (&wf)[H]) {
 #pragma unroll
     for (int s = 0; s < H; ++s) wf[s] = P::load(m, (size_t)t * S + s);

@@ -32,8 +32,8 @@
 // waves per SIMD to overlap them, then the angle rows' traffic.  At the 9,999-atom box a forward layer moves
 // up to 1.7 GB of angle rows (0.33 ms at the copy rate) and has 0.46 ms of float32 MFMA work, a
 // backward layer up to 2.6 GB (0.5 ms) and 0.95 ms.  Measured per layer there, float32: forward 3.06 ->
-// 1.0 .. 1.1 ms, backward 6.89 -> 1.9 .. 2.4 ms, against kernels that staged every tile in LDS, one wave
-// to a SIMD; 2,931 atoms in bfloat16, a step 7.3 -> 2.1 ms.
+// 1.0 .. 1.2 ms, backward 6.89 -> 2.0 .. 2.4 ms, against kernels that staged every tile in LDS, one wave
+// to a SIMD; 2,931 atoms in bfloat16, a step 7.4 -> 2.2 ms.
 #include "dp_env.h"
 #include "dp_tiles.h"
 #include "gnn.h"

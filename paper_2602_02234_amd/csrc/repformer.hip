@@ -24,8 +24,8 @@
 // Bound: matrix cores, then the latency of the stages between barriers.  At 96 neighbours
 // a forward layer has 1,250 MFMAs of 32 cycles per atom (0.16 ms at 9,999 atoms on 256 CUs), a
 // backward layer 2,900 (0.38 ms).  Measured at 9,999 atoms of chain density, per layer: 0.93 ->
-// 0.38 ms forward, 1.97 -> 0.75 .. 0.83 ms backward, against kernels that staged every product's
-// operands in LDS and had one atom per CU; at 768 atoms 76 -> 42 .. 47 and 157 -> 81 .. 87 us.
+// 0.39 .. 0.42 ms forward, 1.97 -> 0.76 .. 0.87 ms backward, against kernels that staged every product's
+// operands in LDS and had one atom per CU; at 768 atoms 76 -> 42 .. 45 and 157 -> 82 .. 88 us.
 #include <algorithm>
 
 #include "dp_env.h"
